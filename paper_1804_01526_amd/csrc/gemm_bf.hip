@@ -14,6 +14,7 @@
 // gemm_bf_kernel: 256 x 256 tile of C per workgroup, 8 waves of 64 x 128, four-stage LDS ring of k-steps of 32 filled
 //                 by asynchronous copies of whole stages, one barrier per k-step, operand registers of the next half
 //                 k-step read while the matrix instructions of this one run.
+// gemm_bf_small_kernel: the same on tiles of 128 x 128 for products with few tiles.
 // Only a non-zero block with an exponent byte above 253 (values from 2^127 on) cannot be packed safely; the pack then
 // marks the header of the packed operand as the block-scaled path does, and the product kernel computes such a product
 // from the stored operands with plain integer and FP32 arithmetic (bf_marked_tile).  Small values need no such care:
@@ -166,15 +167,15 @@ struct BfParams {
 
 // A tile of a product with a marked operand (an exponent byte above 253: values next to the largest finite FP32 number),
 // from the stored operands with the arithmetic of Eq. (2) as written: an integer sum per stored chunk of 32, scaled by
-// 2^(eA + eB) and accumulated in FP32.  Thread t owns column t % 256 of the tile and every second row.  Slow, and
+// 2^(eA + eB) and accumulated in FP32.  Thread t owns column t % COLS of the tile and every (THREADS / COLS)th row.  Slow, and
 // expected never to run on training data; it spares every product the launch of a stand-by kernel.
-template <typename MT>
+template <typename MT, int ROWS, int COLS, int THREADS>
 __device__ void bf_marked_tile(const BfParams &p, int tm, int tn) {
-    const int64_t col = (int64_t)tn * 256 + (threadIdx.x & 255);
+    const int64_t col = (int64_t)tn * COLS + (threadIdx.x % COLS);
     if (col >= p.N) return;
     const MT *b = reinterpret_cast<const MT *>(p.mantB) + col * p.kpad;
-    for (int i = 0; i < 128; ++i) {
-        const int64_t row = (int64_t)tm * 256 + (threadIdx.x >> 8) + 2 * i;
+    for (int r = threadIdx.x / COLS; r < ROWS; r += THREADS / COLS) {
+        const int64_t row = (int64_t)tm * ROWS + r;
         if (row >= p.M) break;
         const MT *a = reinterpret_cast<const MT *>(p.mantA) + row * p.kpad;
         float sum = 0.0f;
@@ -217,8 +218,8 @@ __global__ __launch_bounds__(kBfThreads, 2) void gemm_bf_kernel(const BfGroup g)
     int tm, tn;
     if (!tile_of_workgroup((int)blockIdx.x - first_wg, p.tiles_m, p.tiles_n, tm, tn)) return;   // whole workgroup, before any barrier
     if (p.ha[0] == p.ha[1] || p.hb[0] == p.hb[1]) {            // uniform
-        if (p.wide) bf_marked_tile<int16_t>(p, tm, tn);
-        else bf_marked_tile<int8_t>(p, tm, tn);
+        if (p.wide) bf_marked_tile<int16_t, 256, 256, kBfThreads>(p, tm, tn);
+        else bf_marked_tile<int8_t, 256, 256, kBfThreads>(p, tm, tn);
         return;
     }
 
@@ -385,6 +386,203 @@ __global__ __launch_bounds__(kBfThreads, 2) void gemm_bf_kernel(const BfGroup g)
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// The same product on tiles of 128 x 128, for products with too few tiles of 256 x 256 to fill the chip: 4 waves multiply
+// (64 x 64 each, 2 x 2 results of 32 x 32), 4 more only copy.  The planes, the order of the sums and so every bit of C are
+// those of the kernel above.
+// What bounds it: a compute unit takes in 80 to 88 GB/s through its asynchronous copies whatever the tile (16 KB per k-step
+// here, 0.19 us; the matrix instructions of a k-step take 0.13 us), so with few tiles a k-step of a tile of 256 x 256
+// costs 0.53 us and one of these 0.20 us.  With one wave per SIMD a multiplying wave has nothing to hide behind: copies it
+// issued itself held up its matrix instructions (0.24 us per k-step), hence the copying waves, and operand registers are
+// read a whole k-step ahead.  A ring of 5 stages measured best (4: 0.23 us, 6: 0.24 us per k-step); tiles of 256 x 128 are
+// bound by the same rate and gain nothing.  Operands packed beforehand, 256 x 256 tiles -> these: 1337 x 2052 x 1500
+// (54 -> 187 tiles) 36.2 -> 17.5 us, 700 x 1500 x 6000 (18 -> 72) 99 -> 37 us, 2048^3 (64 -> 256) 44 -> 23 us.
+constexpr int kBfSmallTile = 128;
+constexpr int kBfSmallThreads = 512;
+constexpr int kBfSmallRing = 5;
+constexpr int kBfSmallHalf = 4 * kBfTileBytes;             // 128 rows of one operand, one k-step: 8 KB
+constexpr int kBfSmallStage = 2 * kBfSmallHalf;
+constexpr int kBfSmallCopies = kBfSmallStage / 1024 / 4;   // copy instructions per copying wave and stage
+
+// waits until at most `stages` stages of this wave's copies are outstanding
+__device__ __forceinline__ void bf_small_wait(int stages) {
+    switch (stages) {
+        case 0: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
+        case 1: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(1 * kBfSmallCopies) : "memory"); break;
+        case 2: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kBfSmallCopies) : "memory"); break;
+        case 3: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * kBfSmallCopies) : "memory"); break;
+        default: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * kBfSmallCopies) : "memory"); break;
+    }
+}
+
+// byte offset of 128-row half `rows128` of an operand inside its planes, k-step 0
+__device__ __forceinline__ int64_t bf_half_start(int rows128, int ksteps) {
+    return (int64_t)(rows128 >> 1) * ksteps * kBfStageBytes + (rows128 & 1) * kBfSmallHalf;
+}
+
+template <bool TR, bool F16>
+__global__ __launch_bounds__(kBfSmallThreads, 4) void gemm_bf_small_kernel(const BfGroup g) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    BfParams p = g.p[0];
+    int first_wg = 0;
+#pragma unroll
+    for (int i = 1; i < kBfGroup; ++i)
+        if (i < g.n && (int)blockIdx.x >= g.first[i]) {
+            p = g.p[i];
+            first_wg = g.first[i];
+        }
+    int tm, tn;
+    if (!tile_of_workgroup((int)blockIdx.x - first_wg, p.tiles_m, p.tiles_n, tm, tn)) return;   // whole workgroup, before any barrier
+    if (p.ha[0] == p.ha[1] || p.hb[0] == p.hb[1]) {            // uniform
+        if (p.wide) bf_marked_tile<int16_t, kBfSmallTile, kBfSmallTile, kBfSmallThreads>(p, tm, tn);
+        else bf_marked_tile<int8_t, kBfSmallTile, kBfSmallTile, kBfSmallThreads>(p, tm, tn);
+        return;
+    }
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int n = p.ksteps;
+    if (wave >= 4) {
+        // ---- a copying wave: pieces w, w + 4, ... of 1 KB of every stage, A's first
+        const int cw = wave - 4;
+        const uint32_t voff = lane * 16;
+        const uint8_t *cptr[kBfSmallCopies];
+        uint32_t coff[kBfSmallCopies];
+#pragma unroll
+        for (int i = 0; i < kBfSmallCopies; ++i) {
+            const int byte = (cw + 4 * i) * 1024;
+            coff[i] = byte;
+            cptr[i] = byte < kBfSmallHalf ? p.pa + bf_half_start(tm, n) + byte : p.pb + bf_half_start(tn, n) + (byte - kBfSmallHalf);
+        }
+#define HBFP_BS_COPY(slot)                                                                                                    \
+    {                                                                                                                         \
+        _Pragma("unroll") for (int i = 0; i < kBfSmallCopies; ++i) {                                                          \
+            async_copy16(cptr[i], voff, (uint32_t)((slot) * kBfSmallStage) + coff[i]);                                        \
+            cptr[i] += kBfStageBytes;                                                                                         \
+        }                                                                                                                     \
+    }
+        const int ahead = n < kBfSmallRing ? n : kBfSmallRing;
+        for (int st = 0; st < ahead; ++st) HBFP_BS_COPY(st);
+        bf_small_wait(ahead - 1);                              // stage 0 has landed
+        __builtin_amdgcn_s_barrier();
+        int slot = 0;
+        for (int ks = 0; ks + 1 < n; ++ks) {
+            const int last = ks + kBfSmallRing - 1 < n - 1 ? ks + kBfSmallRing - 1 : n - 1;      // newest stage under way
+            bf_small_wait(last - (ks + 1));                    // stage ks + 1 has landed
+            __builtin_amdgcn_s_barrier();                      // ... and everybody has read stage ks
+            if (ks + kBfSmallRing < n) HBFP_BS_COPY(slot);
+            slot = slot + 1 == kBfSmallRing ? 0 : slot + 1;
+        }
+#undef HBFP_BS_COPY
+        return;
+    }
+    // ---- a multiplying wave
+    const int wm = wave & 1, wn = wave >> 1;
+    int abase = lane * 16 + 2 * wm * kBfTileBytes, bbase = lane * 16 + kBfSmallHalf + 2 * wn * kBfTileBytes;
+    asm volatile("" : "+v"(abase), "+v"(bbase));
+    v16f acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+    v4i_t af[2][2][2], bf[2][2][2];                            // [buffer][half of the k-step][row or column tile]
+#define HBFP_BS_READ(buf, base_)                                                                                              \
+    {                                                                                                                         \
+        _Pragma("unroll") for (int h = 0; h < 2; ++h) {                                                                       \
+            _Pragma("unroll") for (int i = 0; i < 2; ++i)                                                                     \
+                af[buf][h][i] = *reinterpret_cast<const v4i_t *>((base_) + abase + i * kBfTileBytes + h * 1024);              \
+            _Pragma("unroll") for (int j = 0; j < 2; ++j)                                                                     \
+                bf[buf][h][j] = *reinterpret_cast<const v4i_t *>((base_) + bbase + j * kBfTileBytes + h * 1024);              \
+        }                                                                                                                     \
+    }
+    // matrix instruction x = 0 .. 7 of a k-step: half x / 4, row tile (x / 2) % 2, column tile x % 2
+#define HBFP_BS_MFMA(buf, x)                                                                                                  \
+    {                                                                                                                         \
+        const v4i_t a_ = af[buf][(x) >> 2][((x) >> 1) & 1], b_ = bf[buf][(x) >> 2][(x) & 1];                                  \
+        v16f &c_ = acc[((x) >> 1) & 1][(x) & 1];                                                                              \
+        if (F16) c_ = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a_), __builtin_bit_cast(v8h, b_), c_, 0, 0, 0);\
+        else c_ = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, TR ? b_ : a_), __builtin_bit_cast(v8bf, TR ? a_ : b_),\
+                                                          c_, 0, 0, 0);                                                       \
+    }
+#define HBFP_BS_FENCE                                                                                                         \
+    asm volatile("" ::: "memory");                                                                                            \
+    __builtin_amdgcn_sched_barrier(0)
+#define HBFP_BS_PIN                                                                                                           \
+    _Pragma("unroll") for (int i_ = 0; i_ < 2; ++i_)                                                                          \
+        _Pragma("unroll") for (int j_ = 0; j_ < 2; ++j_) asm volatile("" : "+v"(acc[i_][j_][0]))
+    // One k-step: its operand registers (buffer `cur`) were requested a k-step ago.  The first four matrix instructions
+    // wait for them and keep the pipe busy across the hand-over; behind it stage ks + 1 is complete and its registers are
+    // requested under the remaining ones.
+#define HBFP_BS_KSTEP(cur, more)                                                                                              \
+    {                                                                                                                         \
+        ring = ring + 1 == kBfSmallRing ? 0 : ring + 1;                                                                       \
+        _Pragma("unroll") for (int x = 0; x < 4; ++x) HBFP_BS_MFMA(cur, x);                                                   \
+        HBFP_BS_PIN;                                                                                                          \
+        if (more) {                                                                                                           \
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                                                                \
+            __builtin_amdgcn_s_barrier();                                                                                     \
+            HBFP_BS_FENCE;                                                                                                    \
+            HBFP_BS_READ(1 - (cur), lds + ring * kBfSmallStage);                                                              \
+        }                                                                                                                     \
+        HBFP_BS_FENCE;                                                                                                        \
+        HBFP_BS_PIN;                                                                                                          \
+        _Pragma("unroll") for (int x = 4; x < 8; ++x) HBFP_BS_MFMA(cur, x);                                                   \
+        HBFP_BS_PIN;                                                                                                          \
+        HBFP_BS_FENCE;                                                                                                        \
+    }
+    __builtin_amdgcn_s_setprio(1);
+    __builtin_amdgcn_s_barrier();
+    HBFP_BS_FENCE;
+    HBFP_BS_READ(0, lds);
+    int ring = 0;
+    // the number of k-steps is a multiple of 4 (the packed k axis is a multiple of 128)
+    for (int ks = 0; ks + 2 < n; ks += 2) {
+        HBFP_BS_KSTEP(0, true);
+        HBFP_BS_KSTEP(1, true);
+    }
+    HBFP_BS_KSTEP(0, true);
+    HBFP_BS_KSTEP(1, false);
+    __builtin_amdgcn_s_setprio(0);
+#undef HBFP_BS_KSTEP
+#undef HBFP_BS_FENCE
+#undef HBFP_BS_PIN
+#undef HBFP_BS_MFMA
+#undef HBFP_BS_READ
+
+    const int l32 = lane & 31, lh = lane >> 5;
+    const int64_t row0 = (int64_t)tm * kBfSmallTile + wm * 64, col0 = (int64_t)tn * kBfSmallTile + wn * 64;
+    if (TR && !F16) {
+        if (g.out.rounding) mx_store_encoded<1>(g.out, acc, row0, col0, p.M, p.N, lane);
+        else mx_store_encoded<0>(g.out, acc, row0, col0, p.M, p.N, lane);
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        int sa[16];
+        if (F16) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sa[v] = p.sa[row0 + i * 32 + 8 * (v >> 2) + 4 * lh + (v & 3)];      // padded to whole panels
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int64_t col = col0 + j * 32 + l32;
+            if (col >= p.N) continue;
+            const int sb = F16 ? p.sb[col] : 0;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int64_t row = row0 + i * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
+                if (row < p.M) {
+                    float *dst = p.C + row * p.ldc + col;
+                    const float x = F16 ? __builtin_ldexpf(acc[i][j][v], sa[v] + sb) : acc[i][j][v];
+                    if (p.beta) *dst = *dst + x;
+                    else __builtin_nontemporal_store(x, dst);
+                }
+            }
+        }
+    }
+}
+
 int64_t klen_of(const GemmArgs &a, int m) { return bf_klen(a.kpad, a.kbp, a.kblock, a.nblk, a.kdim, m); }
 
 BfPackParams bf_pack_params(const GemmArgs &a, const void *mant, const uint8_t *exps, int64_t R, int64_t exp_ld, int m, void *packed,
@@ -464,6 +662,30 @@ int launch_f16_planes_pack(const GemmArgs &a, void *packed_a, void *packed_b, hi
     return launch_pack(a, packed_a, packed_b, true, s);
 }
 
+// Whether n products run on tiles of 128 x 128.  A round of one tile of 256 x 256 per compute unit takes as long as 2.6
+// rounds of tiles of 128 x 128 (above), so the smaller ones are taken while they need at most twice as many rounds:
+// measured 700 x 6000 x 1500 (1 round against 2) 35.5 -> 24.7 us; with three the two are level (1500 x 6000 x 700: 26.3 and
+// 26.5 us, 6000 x 2048 x 2048: 50 and 52 us) and with four the larger are ahead (4096^3: 110 and 139 us).
+static bool bf_small_tiles(int n, const GemmArgs *args) {
+    int64_t large = 0, small = 0;
+    for (int i = 0; i < n; ++i) {
+        large += ceil_div(args[i].M, 256) * ceil_div(args[i].N, 256);
+        small += ceil_div(args[i].M, kBfSmallTile) * ceil_div(args[i].N, kBfSmallTile);
+    }
+    return ceil_div(small, 256) <= 2 * ceil_div(large, 256);
+}
+
+template <bool TR, bool F16>
+static int launch_bf_kernel(bool small, unsigned workgroups, const BfGroup &g, hipStream_t s) {
+    static std::atomic<bool> configured[2];
+    const int bytes = small ? kBfSmallRing * kBfSmallStage : kBfRing * kBfStage;
+    const void *kernel = small ? reinterpret_cast<const void *>(&gemm_bf_small_kernel<TR, F16>) : reinterpret_cast<const void *>(&gemm_bf_kernel<TR, F16>);
+    if (allow_dynamic_lds(configured[small], kernel, bytes) != HBFP_OK) return HBFP_ERR_LAUNCH;
+    if (small) hipLaunchKernelGGL((gemm_bf_small_kernel<TR, F16>), dim3(workgroups), dim3(kBfSmallThreads), bytes, s, g);
+    else hipLaunchKernelGGL((gemm_bf_kernel<TR, F16>), dim3(workgroups), dim3(kBfThreads), bytes, s, g);
+    return launch_status();
+}
+
 // n <= HBFP_BATCH_MAX products of operands packed as bf16 planes, in one launch; out: product 0 of a single-product
 // launch is delivered as this encoded operand (a marked operand: the FP32 product goes to args[0].C instead)
 static int launch_bf_group(int n, const GemmArgs *args, const void *const *packed_a, const void *const *packed_b, const MxOut *out,
@@ -473,6 +695,8 @@ static int launch_bf_group(int n, const GemmArgs *args, const void *const *packe
     g.n = n;
     if (out) g.out = *out;
     int64_t first = 0;
+    const bool small = bf_small_tiles(n, args);
+    const int64_t tile = small ? kBfSmallTile : 256;
     for (int i = 0; i < n; ++i) {
         const GemmArgs &a = args[i];
         if (!(f16 ? gemm_f16_planes_possible(a) : gemm_bf_possible(a)) || klen_of(a, a.mA) != klen_of(a, a.mB)) return HBFP_ERR_FORMAT;
@@ -488,8 +712,8 @@ static int launch_bf_group(int n, const GemmArgs *args, const void *const *packe
         p.N = a.N;
         p.ldc = a.ldc;
         p.ksteps = (int32_t)(klen_of(a, a.mA) / 32);
-        p.tiles_m = (int32_t)ceil_div(a.M, 256);
-        p.tiles_n = (int32_t)ceil_div(a.N, 256);
+        p.tiles_m = (int32_t)ceil_div(a.M, tile);
+        p.tiles_n = (int32_t)ceil_div(a.N, tile);
         p.beta = a.beta != 0.0f;
         p.mantA = a.mantA;
         p.mantB = a.mantB;
@@ -507,16 +731,9 @@ static int launch_bf_group(int n, const GemmArgs *args, const void *const *packe
         if (first > 0x7ffffff0) return HBFP_ERR_ARG;
     }
     for (int i = n; i <= kBfGroup; ++i) g.first[i] = (int32_t)first;
-    static std::atomic<bool> configured[3];
-    const int which = f16 ? 2 : out ? 1 : 0;
-    const void *kernel = f16   ? reinterpret_cast<const void *>(&gemm_bf_kernel<false, true>)
-                         : out ? reinterpret_cast<const void *>(&gemm_bf_kernel<true, false>)
-                               : reinterpret_cast<const void *>(&gemm_bf_kernel<false, false>);
-    if (allow_dynamic_lds(configured[which], kernel, kBfRing * kBfStage) != HBFP_OK) return HBFP_ERR_LAUNCH;
-    if (f16) hipLaunchKernelGGL((gemm_bf_kernel<false, true>), dim3((unsigned)first), dim3(kBfThreads), kBfRing * kBfStage, s, g);
-    else if (out) hipLaunchKernelGGL((gemm_bf_kernel<true, false>), dim3((unsigned)first), dim3(kBfThreads), kBfRing * kBfStage, s, g);
-    else hipLaunchKernelGGL((gemm_bf_kernel<false, false>), dim3((unsigned)first), dim3(kBfThreads), kBfRing * kBfStage, s, g);
-    return launch_status();
+    if (f16) return launch_bf_kernel<false, true>(small, (unsigned)first, g, s);
+    if (out) return launch_bf_kernel<true, false>(small, (unsigned)first, g, s);
+    return launch_bf_kernel<false, false>(small, (unsigned)first, g, s);
 }
 
 int launch_bf_products(int n, const GemmArgs *args, const void *const *packed_a, const void *const *packed_b, hipStream_t s) {

@@ -38,8 +38,8 @@ __device__ __forceinline__ uint32_t max_of_half_wave(uint32_t v) {
 // exponent block are then 16 registers of lane l32 and 16 of lane l32 + 32: one maximum over registers and one
 // exchange across the wave halves per block (a block of 64 combines two column tiles).  Same arithmetic and the same
 // stochastic-rounding index (position in C) as the conversion kernels, so the result equals converting the FP32 product.
-template <int ROUND>
-__device__ __forceinline__ void mx_store_encoded(const MxOut &o, v16f (&acc)[2][4], int64_t row0, int64_t col0, int64_t M,
+template <int ROUND, int COLS>
+__device__ __forceinline__ void mx_store_encoded(const MxOut &o, v16f (&acc)[2][COLS], int64_t row0, int64_t col0, int64_t M,
                                                  int64_t N, int lane) {
     const int l32 = lane & 31, lh = lane >> 5;
     const bool relu = o.relu != 0;
@@ -49,7 +49,7 @@ __device__ __forceinline__ void mx_store_encoded(const MxOut &o, v16f (&acc)[2][
     for (int i = 0; i < 2; ++i) {
         const int64_t row = row0 + i * 32 + l32;
 #pragma unroll
-        for (int jp = 0; jp < 2; ++jp) {                       // two column tiles at a time: one block of 64 or two of 32
+        for (int jp = 0; jp < COLS / 2; ++jp) {                // two column tiles at a time: one block of 64 or two of 32
             uint32_t am[2], eb[2];
             int left[2];                                        // columns of this lane's run that exist
 #pragma unroll
@@ -126,6 +126,9 @@ __device__ __forceinline__ void mx_store_encoded(const MxOut &o, v16f (&acc)[2][
                 } else {
                     const int64_t b0 = (col0 >> 6) + jp;
                     if (b0 < o.exp_ld) o.exps[row * o.exp_ld + b0] = b0 < o.nblk ? (uint8_t)eb[0] : (uint8_t)1;
+                    // tiles narrower than the four blocks that the row length is rounded up to: the last one pads
+                    if (COLS == 2 && (b0 + 1) * 64 == o.kpad)
+                        for (int64_t b = b0 + 1; b < o.exp_ld; ++b) o.exps[row * o.exp_ld + b] = 1;
                 }
             }
             __builtin_amdgcn_sched_barrier(0);                 // the unrolled epilogue must not pile up temporaries

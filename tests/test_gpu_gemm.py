@@ -920,6 +920,37 @@ def test_bf16_kernel_extreme_mantissas_and_exponents(hb):
     _run(hb, huge, small, (1, 24, 9, 0, 0), (24, 1, 9, 0, 0), partials=False, kernel=BF16, beta=1.0)
 
 
+@pytest.mark.parametrize("m,blk", [(8, 24), (9, 32), (12, 64)])
+@pytest.mark.parametrize("K", [40, 150, 700, 1300])
+def test_small_tiles_give_the_bits_of_the_large_tiles(hb, m, blk, K):
+    """Packed products of few tiles run on tiles of 128 x 128, of many on 256 x 256: same planes, same order of the sums.
+    The product of the first M rows and N columns is, bit for bit, the corner of the whole product, at the edges of the
+    smaller tiles and with fewer k-steps (4, 8) than the ring has stages or a few more (24, 44).  The whole product is
+    held to the oracle on sampled rows."""
+    rng = np.random.default_rng(5 * K + m)
+    A = (rng.standard_normal((4096, K)) * np.exp2(rng.integers(-3, 4, size=(4096, 1)))).astype(np.float32)
+    B = (rng.standard_normal((K, 3841)) * 0.05).astype(np.float32)
+    fa, fb = hb.make_format(m, 1, blk), hb.make_format(m, blk, 1)
+    X, W = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    x, w = hb.encode(X, 1, fa), hb.encode(W, 0, fb)
+    whole = hb.gemm_packed(x, hb.pack(x), w, hb.pack(w))              # 16 x 16 tiles of 256 x 256
+    rows = np.sort(rng.choice(4096, size=8, replace=False))
+    want = ref.gemm(ref.decode(ref.encode(A, 1, blk, m)), ref.decode(ref.encode(B, blk, 1, m)), rows=rows)
+    assert rel_fro(whole.cpu().numpy()[rows], want) <= TOL
+    for M, N in ((1, 1), (64, 65), (127, 129), (128, 128), (257, 383), (1000, 640)):
+        print(f"[case] corner {M}x{N}x{K} m={m} blocks of {blk}", flush=True)
+        xs, wsub = hb.encode(X[:M], 1, fa), hb.encode(W[:, :N], 0, fb)
+        px, pw = hb.pack(xs), hb.pack(wsub)
+        out = torch.full((M, N + 3), 7.0, device="cuda")
+        hb.gemm_packed(xs, px, wsub, pw, out=out[:, :N])
+        torch.cuda.synchronize()
+        assert torch.equal(out[:, :N], whole[:M, :N])
+        assert (out[:, N:] == 7.0).all()
+        hb.gemm_packed(xs, px, wsub, pw, out=out[:, :N], beta=1.0)
+        torch.cuda.synchronize()
+        assert torch.equal(out[:, :N], whole[:M, :N] + whole[:M, :N])
+
+
 def test_bf16_kernel_is_the_automatic_choice_and_equals_the_packed_route(hb):
     """hbfp_gemm on a shape where 256 x 256 tiles pay gives, bit for bit, what HBFP_KERNEL_BF16 and hbfp_gemm_packed on
     operands packed beforehand give; a batch of such products in one launch likewise."""

@@ -8,6 +8,8 @@
 //   col   1-D blocks down the source rows (k strided in the source): each lane owns
 //         one operand row and a whole block in registers, the k-contiguous output is
 //         transposed through LDS so that global stores are full 128-byte lines.
+//   strip long blocks down the source rows (one exponent per column, filter tiles): a workgroup per block and strip of
+//         columns, which it reads twice.
 //   tile  everything else (2-D tiles, very long blocks): a max pass into a small
 //         per-tile array, then a quantise pass.
 #include "bfp_device.h"
@@ -458,6 +460,7 @@ struct ColParams {
     int32_t kblock, nblk, nb_stored, m;
     int32_t rblock;     // operand rows (lanes) sharing one exponent: 1 for 1-D blocks, up to 64 for 2-D tiles
     int32_t lanes;      // lanes of a wave that carry operand rows: the largest multiple of rblock <= 64
+    int32_t narrow;     // a workgroup covers 1 / 2^narrow of the pieces that its LDS tile has room for (col_narrow)
     uint32_t row_groups;   // workgroups per group of blocks (the grid is flat: block group = blockIdx.x / row_groups)
     uint32_t s0, s1;
     // TABLE (second pass of the two-pass conversion): the largest magnitude of every exponent block has been computed
@@ -513,14 +516,15 @@ __global__ __launch_bounds__(kThreads) void enc_col_kernel(const ColParams p) {
     // the wave index as a scalar: block indices, block lengths and (CONV) output positions stay on the scalar unit
     const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     const int64_t r = (int64_t)(blockIdx.x % p.row_groups) * p.lanes + lane;
-    const int64_t blk0 = (int64_t)(blockIdx.x / p.row_groups) * NBT;
+    const int nbt = NBT >> p.narrow;
+    const int64_t blk0 = (int64_t)(blockIdx.x / p.row_groups) * nbt;
     const bool r_ok = lane < p.lanes && r < p.R;
     const int group0 = (lane / p.rblock) * p.rblock;   // first lane of this lane's 2-D tile
     int conv_fr = 0, conv_fs = 0, conv_ch = 0;          // CONV: this lane's filter tap and channel
     if (CONV) conv_window_entry(p.cv, r_ok ? (uint32_t)r : 0u, conv_fr, conv_fs, conv_ch);
     const int conv_off = CONV ? (conv_fr * p.cv.W + conv_fs) * p.cv.C + conv_ch : 0;    // of the lane's window entry from the corner
 
-    for (int bi = wave; bi < NBT; bi += 4) {
+    for (int bi = wave; bi < nbt; bi += 4) {
         const int64_t piece = blk0 + bi;                                  // stored piece of KBP elements
         const int64_t blk = TABLE ? piece / p.spb : piece;                // exponent block
         const int sub = TABLE ? (int)(piece % p.spb) * KBP : 0;           // the piece's offset in its block
@@ -591,11 +595,12 @@ __global__ __launch_bounds__(kThreads) void enc_col_kernel(const ColParams p) {
 
     // stored blocks of this tile that exist in the operand row
     const int64_t left_blocks = p.nb_stored - blk0;
-    const int valid_bytes = (int)((left_blocks < NBT ? left_blocks : NBT) * KBP * ESZ);
-    const int piece = t & 31;
+    const int valid_bytes = (int)((left_blocks < nbt ? left_blocks : nbt) * KBP * ESZ);
+    const int piece = t & ((32 >> p.narrow) - 1);                          // 16 bytes of a row; 32 of them when it is whole
 #pragma unroll
     for (int pass = 0; pass < 8; ++pass) {
-        const int rl = pass * 8 + (t >> 5);
+        if (pass >= (8 >> p.narrow)) break;                                // uniform
+        const int rl = (pass << (3 + p.narrow)) + (t >> (5 - p.narrow));
         const int64_t rr = (int64_t)(blockIdx.x % p.row_groups) * p.lanes + rl;
         if (rl < p.lanes && rr < p.R && piece * 16 < valid_bytes) {
             const uint4 d = *reinterpret_cast<const uint4 *>(tile + rl * kColStride + piece * 16);
@@ -611,11 +616,23 @@ __global__ __launch_bounds__(kThreads) void enc_col_kernel(const ColParams p) {
 #pragma unroll
         for (int w = 0; w < NBT / 4; ++w) {
             const int64_t b = blk0 + 4 * w;
-            if (b < p.exp_ld)
+            if (4 * w < nbt && b < p.exp_ld)
                 *reinterpret_cast<uint32_t *>(p.exps + r * p.exp_ld + b) =
                     *reinterpret_cast<const uint32_t *>(etile + t * NBT + 4 * w);
         }
     }
+}
+
+// How far a workgroup's share is cut down.  A wave walks its pieces one after the other (about 1.5 us each: 32 strided
+// loads, then the rounding), so a matrix that gives only a few whole tiles waits for them on a chip that is mostly idle:
+// 256 x 256 took 7.6 us as 4 workgroups of 4 pieces per wave, 700 x 1500 8.0 us as 48.  One piece per wave still writes 128
+// bytes of an operand row at a time: 4.0, 4.3 us; 188 whole tiles (700 x 6000) 9.3 -> 7.1 us.  From 256 whole tiles on they are
+// kept: 4500 x 2999 (423) takes 15.0 us with them and 16.2 us with halves, 50176 x 144 (393) 10.8 and 11.1 us.
+int col_narrow(int64_t row_groups, int64_t pieces, int nbt) {
+    int narrow = 0;
+    if (row_groups * ceil_div(pieces, nbt) >= 256) return 0;
+    while ((nbt >> (narrow + 1)) >= 4 && row_groups * ceil_div(pieces, nbt >> narrow) < 512) ++narrow;
+    return narrow;
 }
 
 template <int KBP>
@@ -712,11 +729,13 @@ __global__ __launch_bounds__(kThreads) void tile_amax_kernel(const TileParams p,
                     a[2] = max(a[2], __float_as_uint(d.z) & 0x7fffffffu);
                     a[3] = max(a[3], __float_as_uint(d.w) & 0x7fffffffu);
                 }
-            } else {
+            } else if (ncol) {
+                // a column that does not exist reads the last one, whose block it counts for (tc)
+#pragma unroll 4
                 for (int64_t rr = r; rr < rend; ++rr)
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        if (e < ncol) a[e] = max(a[e], __float_as_uint(p.src[rr * p.ld + c0 + e]) & 0x7fffffffu);
+                        a[e] = max(a[e], __float_as_uint(p.src[rr * p.ld + (c0 + e < p.src_cols ? c0 + e : p.src_cols - 1)]) & 0x7fffffffu);
             }
             r = rend;
             uint32_t *row_of_table = p.tile_amax + tr * p.nbc;
@@ -848,6 +867,108 @@ void launch_rowwave_n(const WaveParams &p, dim3 grid, bool wide, int rounding, h
     else if (!wide) hipLaunchKernelGGL((enc_rowwave_kernel<false, 1, NV>), grid, dim3(kThreads), 0, s, p);
     else if (rounding == 0) hipLaunchKernelGGL((enc_rowwave_kernel<true, 0, NV>), grid, dim3(kThreads), 0, s, p);
     else hipLaunchKernelGGL((enc_rowwave_kernel<true, 1, NV>), grid, dim3(kThreads), 0, s, p);
+}
+
+// ------------------------------------------------------------------------------------------
+// Long exponent blocks down the source rows (one exponent per column, filter tiles over a whole window), k strided in the
+// source: one workgroup per strip of cw columns and exponent block.  It reads its part of the block for the maxima,
+// combines them in LDS and reads it again (from the caches) to quantise, so there is no table to clear, no atomic to memory
+// and one launch instead of three.  Bound by the latency of its strided loads (16 in flight per thread) for small matrices
+// and by the second read for larger ones.  Dealing neighbouring strips, which share cache lines, to the same XCD took
+// 4500 x 2999 from 47 to 25 us.
+struct StripParams {
+    const float *src;
+    uint8_t *mant;
+    uint8_t *exps;
+    int64_t ld, kpad, exp_ld, src_cols;
+    int32_t R, K, kblock, kbp, nblk, m;
+    int32_t rblock, kshare, nreg;     // operand rows and stored blocks per exponent, exponent blocks along k
+    int32_t cw;                       // columns of a strip: a multiple of rblock, at most 64
+    uint32_t s0, s1;
+};
+constexpr int kStripThreads = 512;
+
+template <bool WIDE, int ROUND>
+__global__ __launch_bounds__(kStripThreads) void enc_strip_kernel(const StripParams p) {
+    __shared__ uint32_t tile_max[64];
+    const int t = threadIdx.x, groups = kStripThreads / p.cw;
+    const int c = t % p.cw, g = t / p.cw;
+    // neighbouring strips share cache lines: XCD x (workgroup x modulo 8) takes a contiguous eighth of them
+    const int strips = (p.R + p.cw - 1) / p.cw, per_xcd = (strips + 7) >> 3;
+    const int strip = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    const int col = strip * p.cw + c, reg = blockIdx.y;
+    const bool live = g < groups && (int)(blockIdx.x >> 3) < per_xcd && col < p.R;
+    if (t < 64) tile_max[t] = 0;
+    __syncthreads();
+    const int kfirst = reg * p.kshare * p.kblock;
+    const int kend = reg == p.nreg - 1 ? p.K : kfirst + p.kshare * p.kblock;
+    const float *s = p.src + (live ? col : 0);
+    uint32_t amax = 0;
+    if (live) {
+        int k = kfirst + g;
+        for (; k + 15 * groups < kend; k += 16 * groups) {            // 16 loads in flight
+            float v[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = s[(int64_t)(k + i * groups) * p.ld];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) amax = max(amax, __float_as_uint(v[i]) & 0x7fffffffu);
+        }
+#pragma unroll 4
+        for (; k < kend; k += groups) amax = max(amax, __float_as_uint(s[(int64_t)k * p.ld]) & 0x7fffffffu);
+        atomicMax(&tile_max[c / p.rblock], amax);
+    }
+    __syncthreads();
+    if (!live) return;
+    const uint32_t Eb = block_exponent<ROUND>(tile_max[c / p.rblock], p.m);
+    uint8_t *erow = p.exps + (int64_t)col * p.exp_ld;
+    if (reg == p.nreg - 1 && g == 0)
+        for (int64_t b = p.nblk; b < p.exp_ld; ++b) erow[b] = 1;      // exponent bytes past the last block
+    // stored positions of this exponent block, 16 at a time; the last one also covers the padding of the row
+    const int pfirst = reg * p.kshare * p.kbp;
+    const int pend = reg == p.nreg - 1 ? (int)p.kpad : pfirst + p.kshare * p.kbp;
+    for (int pos = pfirst + 16 * g; pos < pend; pos += 16 * groups) {
+        const int blk = pos / p.kbp, off = pos - blk * p.kbp;
+        int n = 0;                                                     // elements that exist
+        if (blk < p.nblk) {
+            const int left = (p.K - blk * p.kblock < p.kblock ? p.K - blk * p.kblock : p.kblock) - off;
+            n = left < 0 ? 0 : (left < 16 ? left : 16);
+        }
+        const int k0 = n ? blk * p.kblock + off : 0;
+        float v[16];
+        if (n == 16) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = s[(int64_t)(k0 + i) * p.ld];
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = i < n ? s[(int64_t)(k0 + i) * p.ld] : 0.0f;
+        }
+        int q[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const uint64_t idx = (uint64_t)(k0 + i) * (uint64_t)p.src_cols + (uint64_t)col;
+            q[i] = quantise<ROUND>(v[i], Eb, p.m, (uint32_t)idx, (uint32_t)(idx >> 32), p.s0, p.s1);
+        }
+        uint8_t *dst = p.mant + ((int64_t)col * p.kpad + pos) * (WIDE ? 2 : 1);
+        if (!WIDE) {
+            uint4 o;
+            o.x = pack4_i8(q[0], q[1], q[2], q[3]);
+            o.y = pack4_i8(q[4], q[5], q[6], q[7]);
+            o.z = pack4_i8(q[8], q[9], q[10], q[11]);
+            o.w = pack4_i8(q[12], q[13], q[14], q[15]);
+            *reinterpret_cast<uint4 *>(dst) = o;
+        } else {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                uint4 o;
+                o.x = pack2_i16(q[8 * h], q[8 * h + 1]);
+                o.y = pack2_i16(q[8 * h + 2], q[8 * h + 3]);
+                o.z = pack2_i16(q[8 * h + 4], q[8 * h + 5]);
+                o.w = pack2_i16(q[8 * h + 6], q[8 * h + 7]);
+                reinterpret_cast<uint4 *>(dst)[h] = o;
+            }
+        }
+        if (off == 0 && blk < p.nblk) erow[blk] = (uint8_t)Eb;
+    }
 }
 
 void magic_of(uint32_t d, uint32_t (&magic)[2]) {
@@ -1169,7 +1290,9 @@ int launch_encode_im2col(const float *x, const hbfp_conv2d &c, int64_t ho, int64
         const bool wide = g.m > 8;
         const int nbt = kColRowBytes / ((int)g.kbp * (wide ? 2 : 1));
         const int64_t nb_cover = p.nb_stored > g.exp_ld ? p.nb_stored : g.exp_ld;
-        const int64_t gx = ceil_div(g.R, 64), gy = ceil_div(nb_cover, nbt);
+        const int64_t gx = ceil_div(g.R, 64);
+        p.narrow = col_narrow(gx, nb_cover, nbt);
+        const int64_t gy = ceil_div(nb_cover, nbt >> p.narrow);
         if (gx > 0x7fffffff || gx * gy > 0x7fffffff) return HBFP_ERR_ARG;
         p.row_groups = (uint32_t)gx;
         const dim3 grid((unsigned)(gx * gy));
@@ -1254,7 +1377,9 @@ int launch_encode_col_fused(const float *src, const EncodeGeom &g, void *mant, u
     const int nbt = kColRowBytes / ((int)g.kbp * (wide ? 2 : 1));
     // cover every stored block and every exponent byte up to exp_ld
     const int64_t nb_cover = p.nb_stored > g.exp_ld ? p.nb_stored : g.exp_ld;
-    const int64_t gx = ceil_div(g.R, p.lanes), gy = ceil_div(nb_cover, nbt);
+    const int64_t gx = ceil_div(g.R, p.lanes);
+    p.narrow = col_narrow(gx, nb_cover, nbt);
+    const int64_t gy = ceil_div(nb_cover, nbt >> p.narrow);
     if (gx > 0x7fffffff || gx * gy > 0x7fffffff) return HBFP_ERR_ARG;
     p.row_groups = (uint32_t)gx;
     const dim3 grid((unsigned)(gx * gy));
@@ -1310,9 +1435,60 @@ static int launch_encode_rowwave(const float *src, const EncodeGeom &g, void *ma
     return launch_status();
 }
 
+// Columns of a strip of enc_strip_kernel: 16 (64 bytes of a source row, or the width of a block), twice that when there are
+// workgroups to spare (measured 2000 x 2000, blocks of 128: 2000 strips of 16 columns 11.0 us, 1008 of 32 8.0 us; 4096^2,
+// 96 x 24 tiles: 24 columns 39 us, 48 columns 32 us).
+static int strip_columns(const EncodeGeom &g) {
+    const int64_t w = g.rblock >= 16 ? g.rblock : 16 / g.rblock * g.rblock;
+    const bool spare = ceil_div(g.R, w) * ceil_div(g.nblk, g.kshare) >= 1024;
+    return (int)(spare && 2 * w <= 48 ? 2 * w : w);
+}
+// What a workgroup reads twice has to stay within the reach of one compute unit: up to 80 Ki values per strip and block the
+// strips are ahead of the two-pass conversion (one exponent per column: 500 x 300 15.0 -> 4.8 us, 4500 x 2999 67 -> 25 us,
+// 4096^2 36 -> 27 us, 3000 x 5000 35 -> 29 us; 216 x 24 tiles of 1296 x 144 16.7 -> 5.2 us), beyond it they are behind
+// (10000 x 500: 27 and 40 us, 8192^2: 110 and 145 us).  Rows that are not 16-byte aligned slow the maximum pass of the two down
+// to half, so the line lies at twice as much there (6001 x 5999: 145 -> 83 us, 8191 x 3001: 99 -> 52 us).
+static bool strip_ok(const EncodeGeom &g, const float *src) {
+    if (g.axis != 0 || g.rblock > 64 || g.R > 0x7fffff00 || g.kpad > 0x3fffffff) return false;
+    const int64_t nreg = ceil_div(g.nblk, g.kshare), kext = nreg == 1 ? g.K : g.kshare * g.kblock;
+    const bool vec_ok = ((uintptr_t)src & 15) == 0 && g.ld % 4 == 0;
+    return nreg <= 65535 && kext * strip_columns(g) <= (vec_ok ? 80 : 160) * 1024;
+}
+
+static int launch_encode_strip(const float *src, const EncodeGeom &g, void *mant, uint8_t *exps, hipStream_t s) {
+    StripParams p;
+    p.src = src;
+    p.mant = (uint8_t *)mant;
+    p.exps = exps;
+    p.ld = g.ld;
+    p.kpad = g.kpad;
+    p.exp_ld = g.exp_ld;
+    p.src_cols = g.src_cols;
+    p.R = (int32_t)g.R;
+    p.K = (int32_t)g.K;
+    p.kblock = (int32_t)g.kblock;
+    p.kbp = (int32_t)g.kbp;
+    p.nblk = (int32_t)g.nblk;
+    p.m = g.m;
+    p.rblock = (int32_t)g.rblock;
+    p.kshare = (int32_t)(g.kshare > g.nblk ? g.nblk : g.kshare);
+    p.nreg = (int32_t)ceil_div(p.nblk, p.kshare);
+    p.cw = strip_columns(g);
+    p.s0 = g.seed_lo;
+    p.s1 = g.seed_hi;
+    const dim3 grid((unsigned)(ceil_div(ceil_div(g.R, p.cw), 8) * 8), (unsigned)p.nreg);
+    const bool wide = g.m > 8;
+    if (!wide && g.rounding == 0) hipLaunchKernelGGL((enc_strip_kernel<false, 0>), grid, dim3(kStripThreads), 0, s, p);
+    else if (!wide) hipLaunchKernelGGL((enc_strip_kernel<false, 1>), grid, dim3(kStripThreads), 0, s, p);
+    else if (g.rounding == 0) hipLaunchKernelGGL((enc_strip_kernel<true, 0>), grid, dim3(kStripThreads), 0, s, p);
+    else hipLaunchKernelGGL((enc_strip_kernel<true, 1>), grid, dim3(kStripThreads), 0, s, p);
+    return launch_status();
+}
+
 int launch_encode_generic(const float *src, const EncodeGeom &g, void *mant, uint8_t *exps,
                           uint32_t *tile_amax, hipStream_t s) {
     if (rowwave_ok(g)) return launch_encode_rowwave(src, g, mant, exps, s);
+    if (strip_ok(g, src)) return launch_encode_strip(src, g, mant, exps, s);
     const bool wide = g.m > 8;
     {
         TileParams p;
@@ -1396,7 +1572,9 @@ int launch_encode_generic(const float *src, const EncodeGeom &g, void *mant, uin
         p.spb = (int32_t)(g.kbp / 32);
         p.kshare = (int32_t)(g.kshare > g.nblk ? g.nblk : g.kshare);
         const int nbt = kColRowBytes / (32 * (wide ? 2 : 1));
-        const int64_t gx = ceil_div(g.R, 64), gy = ceil_div(p.nb_stored, nbt);
+        const int64_t gx = ceil_div(g.R, 64);
+        p.narrow = col_narrow(gx, p.nb_stored, nbt);
+        const int64_t gy = ceil_div(p.nb_stored, nbt >> p.narrow);
         if (gx > 0x7fffffff || gx * gy > 0x7fffffff) return HBFP_ERR_ARG;
         p.row_groups = (uint32_t)gx;
         launch_col_table(p, dim3((unsigned)(gx * gy)), wide, g.rounding, s);

@@ -509,3 +509,54 @@ def test_encode_multi_matches_single_encodes(hb, rows, cols, outs, rounding):
         mant, exps = unpack(t)
         np.testing.assert_array_equal(exps, want.exps)
         np.testing.assert_array_equal(mant, want.mant)
+
+
+@pytest.mark.parametrize("m,rounding", [(8, 0), (12, 0), (8, 1), (13, 1)])
+@pytest.mark.parametrize("rows,cols,br,bc,slot", [
+    (70, 17, 0, 1, 0),             # one exponent per column, one strip and a column
+    (65, 16, 0, 1, 0),             # the shortest block that the column kernel leaves over
+    (5120, 36, 0, 1, 0),           # the longest strip with aligned rows, and the same from unaligned ones
+    (5121, 36, 0, 1, 0),           # one element more: two passes from aligned rows
+    (10241, 33, 0, 1, 0),          # two passes from unaligned rows
+    (1000, 333, 70, 3, 0),         # tiles across 3 columns, 14 whole blocks and a short one
+    (777, 50, 200, 64, 0),         # the widest tile
+    (129, 63, 128, 48, 0),         # a block of one element behind a whole one
+    (1396, 150, 216, 24, 24),      # filter tiles: stored blocks of 24 that repeat an exponent over 9 of them
+    (2000, 1100, 72, 2, 24),       # enough blocks for strips of twice the width
+    (4200, 515, 128, 24, 0),       # the same with tiles of 24 columns
+    (90, 5, 0, 0, 30),             # one exponent for the matrix, stored blocks of 30
+])
+def test_long_blocks_down_the_rows(hb, rows, cols, br, bc, slot, m, rounding):
+    """Long exponent blocks down the source rows against the oracle, bit for bit: the strip kernel at the edges of its strips,
+    blocks and rule, and the two-pass conversion next to it.  Some columns are zero, some blocks tiny."""
+    print(f"[case] {rows}x{cols} blocks {br}x{bc} slot {slot} m={m} rounding={rounding}", flush=True)
+    rng = np.random.default_rng(rows + cols)
+    X = (rng.standard_normal((rows, cols)) * np.exp2(rng.integers(-20, 21, size=(rows, cols)))).astype(np.float32)
+    X[:, cols // 2] = 0.0
+    X[: rows // 3, cols // 3] *= np.float32(2.0 ** -100)
+    pad = torch.full((rows, cols + 3), 3.0e38, device="cuda")
+    pad[:, :cols] = torch.from_numpy(X).cuda()
+    for src in (torch.from_numpy(X).cuda(), pad[:, :cols]):          # rows back to back, and 3 elements apart
+        fmt = hb.make_format(m, br, bc, rounding, 1234567, k_slot=slot)
+        out = hb.alloc(fmt, rows, cols, 0)
+        out.mant.fill_(85)
+        out.exps.fill_(85)
+        hb.encode(src, 0, fmt, out=out)
+        torch.cuda.synchronize()
+        want = ref.encode(X, br, bc, m, rounding, 1234567)
+        mant, exps = unpack(out)
+        np.testing.assert_array_equal(mant, want.mant)
+        np.testing.assert_array_equal(exps, want.exps)
+
+
+@pytest.mark.parametrize("rows,cols,blk,m", [(700, 6000, 24, 8), (256, 256, 32, 8), (1000, 70, 16, 12), (129, 1000, 64, 8), (8200, 1024, 32, 8)])
+def test_column_conversion_of_few_and_many_workgroups(hb, rows, cols, blk, m):
+    """The column kernel with whole, halved and quartered shares per workgroup, against the oracle bit for bit."""
+    print(f"[case] {rows}x{cols} blocks {blk}x1 m={m}", flush=True)
+    X = np.random.default_rng(rows).standard_normal((rows, cols)).astype(np.float32)
+    out = hb.encode(torch.from_numpy(X).cuda(), 0, hb.make_format(m, blk, 1))
+    torch.cuda.synchronize()
+    want = ref.encode(X, blk, 1, m)
+    mant, exps = unpack(out)
+    np.testing.assert_array_equal(mant, want.mant)
+    np.testing.assert_array_equal(exps, want.exps)

@@ -918,27 +918,49 @@ __global__ __launch_bounds__(kW8Threads, 4) void gemm_i8_w8_kernel(const W8Param
         }
 }
 
-// fixed-order sum over the split-K slices: deterministic, no float atomics.  The slices of one output are
-// requested eight at a time and added in slice order, so the result does not depend on the unrolling.
+// Fixed-order sum over the split-K slices: deterministic, no float atomics.  The slices of one output are requested eight at
+// a time and added in slice order, so the result does not depend on the unrolling.  VEC: four consecutive outputs per thread
+// (N and ldc multiples of 4, C 16-byte aligned).  Bound by the slices, which the product has just written (64-bit index
+// divisions and 4-byte loads had it at 7.4 us for 7 slices of 700 x 1500, 8 us for 4 of 1024^2).
+template <bool VEC>
 __global__ __launch_bounds__(kThreads) void splitk_reduce_kernel(const float *partial, float *C, int64_t M, int64_t N,
                                                                   int64_t ldc, int splits, int beta, const int *run_a,
                                                                   const int *run_b) {
     if (stands_down(run_a, run_b)) return;
+    constexpr int W = VEC ? 4 : 1;
+    typedef float vec __attribute__((ext_vector_type(W)));
     const int64_t n = M * N;
-    for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < n; e += (int64_t)gridDim.x * kThreads) {
-        const int64_t i = e / N, j = e % N;
-        float s = beta ? C[i * ldc + j] : 0.0f;
+    for (int64_t e = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * W; e < n; e += (int64_t)gridDim.x * kThreads * W) {
+        const int64_t i = n < ((int64_t)1 << 31) ? (int64_t)((uint32_t)e / (uint32_t)N) : e / N;
+        float *out = C + i * ldc + (e - i * N);
+        vec s = beta ? *reinterpret_cast<const vec *>(out) : vec(0.0f);
         int z = 0;
         for (; z + 8 <= splits; z += 8) {
-            float t[8];
+            vec t[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) t[u] = partial[(int64_t)(z + u) * n + e];
+            for (int u = 0; u < 8; ++u) t[u] = *reinterpret_cast<const vec *>(partial + (int64_t)(z + u) * n + e);
 #pragma unroll
             for (int u = 0; u < 8; ++u) s += t[u];
         }
-        for (; z < splits; ++z) s += partial[(int64_t)z * n + e];
-        C[i * ldc + j] = s;
+        vec t[7];
+#pragma unroll
+        for (int u = 0; u < 7; ++u)
+            if (z + u < splits) t[u] = *reinterpret_cast<const vec *>(partial + (int64_t)(z + u) * n + e);
+#pragma unroll
+        for (int u = 0; u < 7; ++u)
+            if (z + u < splits) s += t[u];
+        *reinterpret_cast<vec *>(out) = s;
     }
+}
+
+int launch_splitk_reduce(const GemmParams &p, hipStream_t s) {
+    // few outputs with many slices (1296 x 144, 24 slices): one output per thread keeps more loads in flight (58 against 60 us in all)
+    const bool vec = p.M * p.N >= 512 * 1024 && p.N % 4 == 0 && p.ldc % 4 == 0 && ((uintptr_t)p.C & 15) == 0;
+    int64_t nb = ceil_div(p.M * p.N, kThreads * (vec ? 4 : 1));
+    if (nb > 8192) nb = 8192;
+    if (vec) hipLaunchKernelGGL(splitk_reduce_kernel<true>, dim3((unsigned)nb), dim3(kThreads), 0, s, p.partial, p.C, p.M, p.N, p.ldc, p.splits, p.beta, p.run_a, p.run_b);
+    else hipLaunchKernelGGL(splitk_reduce_kernel<false>, dim3((unsigned)nb), dim3(kThreads), 0, s, p.partial, p.C, p.M, p.N, p.ldc, p.splits, p.beta, p.run_a, p.run_b);
+    return launch_status();
 }
 
 template <int SPB, bool DUMP>
@@ -951,17 +973,26 @@ int launch_t(const GemmParams &p, dim3 grid, hipStream_t s) {
 
 }  // namespace
 
-// Split K when the tile grid alone cannot fill the chip (the weight-gradient shape: small
-// M x N, very long K).  Pure function of the shapes so that the workspace query agrees.
+// Split K when the tile grid alone cannot fill the chip (the weight-gradient shape: small M x N, very long K).  Pure function
+// of the shapes so that the workspace query agrees.  The number of k ranges with the smallest estimate: a k-step of 32
+// takes 0.32 us for a workgroup that has its compute unit to itself, 0.54 us for one of two that share it, and the slices are
+// written and read back at about 4 TB/s behind 3 us for the second launch.  (Twice as many ranges as fill the chip once, the
+// rule before, cost 1000 x 1024 x 4096 32.6 us against 27.3 us with 4, 1500^3 30.9 us against 23.7 us unsplit.)
 static int choose_splits(int64_t M, int64_t N, int64_t nstage, int64_t stages_per_block) {
     const int64_t tiles = ceil_div(M, BM) * ceil_div(N, BN);
     const int64_t units = nstage / stages_per_block;   // whole exponent blocks (or stages) that can be dealt out
     if (tiles >= 256 || units < 8) return 1;
-    int64_t s = ceil_div(512, tiles);
-    if (s > units / 4) s = units / 4;
-    if (s > 128) s = 128;
-    if (s > 8) s -= s % 8;                             // the k ranges are dealt to the 8 XCDs in turn: keep them level
-    return s < 1 ? 1 : (int)s;
+    // half a tile's worth of columns is half the work: its other waves only copy
+    const double work = 0.5 * (double)(ceil_div(M, BM) * ceil_div(N, 64));
+    double best = 0.0;
+    int splits = 1;
+    for (int s = 1; s <= 128 && s <= units / 4 && (s == 1 || work * s <= 512.0); ++s) {
+        if (s > 8 && s % 8) continue;                  // the k ranges are dealt to the 8 XCDs in turn: keep them level
+        const double steps = (double)(ceil_div(units, s) * stages_per_block * 4);
+        const double us = steps * (work * s <= 256.0 ? 0.32 : 0.54) + (s > 1 ? 3.0 + (double)(s + 1) * (double)(M * N) * 4e-6 / 4.0 : 0.0);
+        if (s == 1 || us < best) best = us, splits = s;
+    }
+    return splits;
 }
 
 // the asynchronous-copy kernel addresses an operand tile with 32-bit offsets
@@ -1188,11 +1219,7 @@ int launch_gemm_conv_i8(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int
     int rc = launch_status();
     if (rc != HBFP_OK) return rc;
     if (p.splits > 1) {
-        int64_t nb = ceil_div(a.M * a.N, kThreads);
-        if (nb > 8192) nb = 8192;
-        hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)nb), dim3(kThreads), 0, s, p.partial, p.C, p.M, p.N, p.ldc, p.splits,
-                           p.beta, (const int *)nullptr, (const int *)nullptr);
-        rc = launch_status();
+        rc = launch_splitk_reduce(p, s);
     }
     return rc;
 }
@@ -1294,11 +1321,7 @@ int launch_gemm_f16(const GemmArgs &a, void *workspace, hipStream_t s) {
     rc = launch_status();
     if (rc != HBFP_OK) return rc;
     if (p.splits > 1) {
-        int64_t nb = ceil_div(a.M * a.N, kThreads);
-        if (nb > 8192) nb = 8192;
-        hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)nb), dim3(kThreads), 0, s, p.partial, p.C, p.M, p.N, p.ldc, p.splits,
-                           p.beta, (const int *)nullptr, (const int *)nullptr);
-        rc = launch_status();
+        rc = launch_splitk_reduce(p, s);
     }
     return rc;
 }
@@ -1395,11 +1418,7 @@ int launch_gemm_i8(const GemmArgs &a, void *workspace, hipStream_t s) {
     }
     if (rc != HBFP_OK) return rc;
     if (!a.P && p.splits > 1) {
-        int64_t nb = ceil_div(a.M * a.N, kThreads);
-        if (nb > 8192) nb = 8192;
-        hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)nb), dim3(kThreads), 0, s, p.partial, p.C, p.M, p.N,
-                           p.ldc, p.splits, p.beta, p.run_a, p.run_b);
-        rc = launch_status();
+        rc = launch_splitk_reduce(p, s);
     }
     return rc;
 }

@@ -454,7 +454,8 @@ int hbfp_gemm_batch(int n, const hbfp_tensor *const *A, const hbfp_tensor *const
  *   kernel   HBFP_KERNEL_* as for hbfp_gemm_select
  * The result equals hbfp_gemm_select followed by hbfp_encode of its output, bit for bit.  When the bf16 or the block-scaled
  * kernel computes the product and out has k along the columns of the product in blocks of 32 or 64 (one exponent per block
- * and row), the kernel converts its accumulators itself; otherwise the FP32 product goes through the workspace.
+ * and row), the kernel converts its accumulators itself; so do the int8 kernels on operands in blocks of at most 32 for
+ * mantissas of at most 8 bits in blocks of 32.  Otherwise the FP32 product goes through the workspace.
  *   workspace  hbfp_gemm_bfp_workspace bytes (includes A->rows * B->rows floats), 256-byte aligned
  * Errors: as hbfp_gemm_select; HBFP_ERR_LAYOUT if out is not the plan of an A->rows x B->rows matrix.
  */

@@ -1025,6 +1025,11 @@ int hbfp_gemm_bfp(const hbfp_tensor *A, const hbfp_tensor *B, const hbfp_tensor 
     char *ws_gemm = (char *)workspace + part[0], *ws_enc = ws_gemm + part[1];
     const int64_t M = A->rows, N = B->rows;
     if (!fused) {
+        // a product that run_gemm would hand to the int8 kernels, delivered by them where the output's format allows it
+        const GemmArgs g = gemm_args(A, B);
+        const bool int8 = (kernel == HBFP_KERNEL_AUTO || kernel == HBFP_KERNEL_INT8) && !use_bf(g, kernel) && !use_f16_planes(g, kernel) &&
+                          !use_scaled(g, kernel);
+        if (int8 && gemm_i8_encoded_output_ok(g, *out)) return launch_gemm_i8(g, ws_gemm, s, out, relu);
         rc = run_gemm(A, B, C, N, 0.0f, nullptr, kernel, ws_gemm, part[1], stream);
         if (rc == HBFP_OK && relu) rc = launch_relu(C, M * N, s);
         if (rc != HBFP_OK) return rc;

@@ -953,6 +953,77 @@ __global__ __launch_bounds__(kThreads) void splitk_reduce_kernel(const float *pa
     }
 }
 
+// The same sum delivered as an encoded operand: ReLU if asked for, then the conversion of Sec. 4.1 with blocks of 32 along the
+// columns of C, as converting the summed FP32 product would give it.  A thread owns four columns of a row, 8 lanes a block.
+template <int ROUND>
+__global__ __launch_bounds__(kThreads) void splitk_reduce_encode_kernel(const float *partial, int64_t M, int64_t N, int splits, const W8Enc o) {
+    const uint32_t quads = (uint32_t)(o.kpad / 4);                  // a multiple of 32: the 8 lanes of a block stay together
+    const int64_t n = M * N;
+    for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < M * quads; e += (int64_t)gridDim.x * kThreads) {
+        const int64_t row = M * quads < ((int64_t)1 << 31) ? (int64_t)((uint32_t)e / quads) : e / quads;
+        const int64_t col = (e - row * quads) * 4;
+        const int left = N - col >= 4 ? 4 : (N - col > 0 ? (int)(N - col) : 0);
+        const float *src = partial + row * N + col;
+        float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (left == 4 && N % 4 == 0) {
+#pragma unroll 8
+            for (int z = 0; z < splits; ++z) {
+                const float4 d = *reinterpret_cast<const float4 *>(src + (int64_t)z * n);
+                x[0] += d.x, x[1] += d.y, x[2] += d.z, x[3] += d.w;
+            }
+        } else {
+            for (int z = 0; z < splits; ++z)
+                for (int i = 0; i < left; ++i) x[i] += src[(int64_t)z * n + i];
+        }
+        uint32_t amax = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (o.relu && x[i] < 0.0f) x[i] = 0.0f;
+            amax = max(amax, __float_as_uint(x[i]) & 0x7fffffffu);
+        }
+        amax = max(amax, (uint32_t)__shfl_xor((int)amax, 1));
+        amax = max(amax, (uint32_t)__shfl_xor((int)amax, 2));
+        amax = max(amax, (uint32_t)__shfl_xor((int)amax, 4));
+        const uint32_t Eb = block_exponent<ROUND>(amax, o.m);
+        uint32_t w = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint64_t idx = (uint64_t)row * (uint64_t)N + (uint64_t)(col + i);
+            w |= ((uint32_t)quantise<ROUND>(x[i], Eb, o.m, (uint32_t)idx, (uint32_t)(idx >> 32), o.s0, o.s1) & 0xffu) << (8 * i);
+        }
+        *reinterpret_cast<uint32_t *>(o.mant + row * o.kpad + col) = w;
+        const int64_t b = col >> 5;
+        if ((col & 31) == 0 && b < o.exp_ld) o.exps[row * o.exp_ld + b] = b < o.nblk ? (uint8_t)Eb : (uint8_t)1;
+    }
+}
+
+int launch_splitk_reduce_encode(const GemmParams &p, const W8Enc &o, hipStream_t s) {
+    int64_t nb = ceil_div(p.M * (o.kpad / 4), kThreads);
+    if (nb > 8192) nb = 8192;
+    if (o.rounding) hipLaunchKernelGGL(splitk_reduce_encode_kernel<1>, dim3((unsigned)nb), dim3(kThreads), 0, s, p.partial, p.M, p.N, p.splits, o);
+    else hipLaunchKernelGGL(splitk_reduce_encode_kernel<0>, dim3((unsigned)nb), dim3(kThreads), 0, s, p.partial, p.M, p.N, p.splits, o);
+    return launch_status();
+}
+
+W8Enc w8_enc_of(const hbfp_tensor &t, int relu) {
+    W8Enc o = {};
+    o.mant = (uint8_t *)t.mant;
+    o.exps = t.exps;
+    o.kpad = t.kpad;
+    o.exp_ld = t.exp_ld;
+    o.nblk = (int32_t)t.nblk;
+    o.m = t.mant_bits;
+    o.rounding = t.rounding;
+    o.relu = relu;
+    o.s0 = (uint32_t)t.seed;
+    o.s1 = (uint32_t)(t.seed >> 32);
+    return o;
+}
+// an operand with k along the columns of C in blocks of 32 of one row, at most 8 bits: what the epilogues above deliver
+bool w8_enc_ok(const hbfp_tensor &t, int64_t M, int64_t N) {
+    return t.contract_axis == 1 && t.kblock == 32 && t.kblock_pad == 32 && t.rblock == 1 && t.kshare == 1 && t.mant_bits <= 8 && t.rows == M && t.kdim == N;
+}
+
 int launch_splitk_reduce(const GemmParams &p, hipStream_t s) {
     // few outputs with many slices (1296 x 144, 24 slices): one output per thread keeps more loads in flight (58 against 60 us in all)
     const bool vec = p.M * p.N >= 512 * 1024 && p.N % 4 == 0 && p.ldc % 4 == 0 && ((uintptr_t)p.C & 15) == 0;
@@ -1040,8 +1111,7 @@ __global__ __launch_bounds__(256) void conv_words_kernel(const uint8_t *eimg, in
 
 // whether the gathering kernel can deliver this product as the encoded operand `out` (no split along k)
 bool conv_encoded_output_ok(int64_t M, int64_t N, int64_t kpad, const hbfp_tensor &out) {
-    return out.contract_axis == 1 && out.kblock == 32 && out.kblock_pad == 32 && out.rblock == 1 && out.kshare == 1 && out.mant_bits <= 8 &&
-           out.rows == M && out.kdim == N && choose_splits(M, N, kpad / BK, 1) == 1;
+    return w8_enc_ok(out, M, N) && choose_splits(M, N, kpad / BK, 1) == 1;
 }
 
 size_t gemm_conv_workspace(int64_t M, int64_t N, int64_t kpad, int64_t pixels, int cblocks) {
@@ -1179,16 +1249,7 @@ int launch_gemm_conv_i8(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int
                                     : dim3((unsigned)(ceil_div(tm * tn, 8) * 8), (unsigned)p.splits);
     if (enc) {
         if (dilated || p.splits != 1 || p.beta) return HBFP_ERR_ARG;
-        q.enc.mant = (uint8_t *)enc->mant;
-        q.enc.exps = enc->exps;
-        q.enc.kpad = enc->kpad;
-        q.enc.exp_ld = enc->exp_ld;
-        q.enc.nblk = (int32_t)enc->nblk;
-        q.enc.m = enc->mant_bits;
-        q.enc.rounding = enc->rounding;
-        q.enc.relu = relu;
-        q.enc.s0 = (uint32_t)enc->seed;
-        q.enc.s1 = (uint32_t)(enc->seed >> 32);
+        q.enc = w8_enc_of(*enc, relu);
         // (the variant that scales runs of blocks once has no registers left for this epilogue: the caller converts behind it)
         if (chain > 1) return HBFP_ERR_ARG;
         static std::atomic<bool> c0{false}, c1{false};
@@ -1353,7 +1414,14 @@ bool gemm_i8_standby_words(const GemmArgs &a, void *workspace, StandbyWords *w) 
     return true;
 }
 
-int launch_gemm_i8(const GemmArgs &a, void *workspace, hipStream_t s) {
+// whether launch_gemm_i8 can deliver this product as the encoded operand `out`
+bool gemm_i8_encoded_output_ok(const GemmArgs &a, const hbfp_tensor &out) {
+    return !a.P && !a.run_a && a.mA <= 8 && a.mB <= 8 && a.kbp == 32 && use_w8(a.kpad) && !gemm_wide_ok(a) && w8_enc_ok(out, a.M, a.N);
+}
+
+// enc: the product leaves as this encoded operand (gemm_i8_encoded_output_ok), with ReLU first if asked for; a.C is then unused
+int launch_gemm_i8(const GemmArgs &a, void *workspace, hipStream_t s, const hbfp_tensor *enc, int relu) {
+    if (enc && (a.wide || a.beta != 0.0f || !gemm_i8_encoded_output_ok(a, *enc))) return HBFP_ERR_FORMAT;
     if (a.wide ? gemm_wide_possible(a) : gemm_wide_ok(a)) return launch_gemm_wide(a, s);
     GemmParams p;
     p.A = (const uint8_t *)a.mantA;
@@ -1390,13 +1458,14 @@ int launch_gemm_i8(const GemmArgs &a, void *workspace, hipStream_t s) {
         // behind the block-scaled kernel the product almost never runs: one launch, no scale-word kernel in front of it;
         // it is the 8-wave kernel when the product kernel has prepared its scale words (words_ready), else the 4-wave one
         if (use_w8(a.kpad) && (!a.run_a || a.words_ready)) {
-            static std::atomic<bool> configured[3];
-            const void *const kernels[3] = {reinterpret_cast<const void *>(&gemm_i8_w8_kernel<1>), reinterpret_cast<const void *>(&gemm_i8_w8_kernel<2>),
-                                            reinterpret_cast<const void *>(&gemm_i8_w8_kernel<0>)};
-            for (int i = 0; i < 3; ++i)
+            static std::atomic<bool> configured[4];
+            const void *const kernels[4] = {reinterpret_cast<const void *>(&gemm_i8_w8_kernel<1>), reinterpret_cast<const void *>(&gemm_i8_w8_kernel<2>),
+                                            reinterpret_cast<const void *>(&gemm_i8_w8_kernel<0>),
+                                            reinterpret_cast<const void *>(&gemm_i8_w8_kernel<1, false, false, 0, true>)};
+            for (int i = 0; i < 4; ++i)
                 if (allow_dynamic_lds(configured[i], kernels[i], kW8LdsBytes) != HBFP_OK) return HBFP_ERR_LAUNCH;
             if (!workspace) return HBFP_ERR_WORKSPACE;
-            W8Params q;
+            W8Params q = {};
             q.g = p;
             q.mpad = ceil_div(a.M, 128) * 128;
             q.npad = ceil_div(a.N, 128) * 128;
@@ -1408,6 +1477,11 @@ int launch_gemm_i8(const GemmArgs &a, void *workspace, hipStream_t s) {
                                         const_cast<uint32_t *>(q.wA), const_cast<uint32_t *>(q.wB), a.run_a, a.run_b, s);
                 if (rc != HBFP_OK) return rc;
             }
+            if (enc) q.enc = w8_enc_of(*enc, relu);
+            if (enc && p.splits == 1) {
+                hipLaunchKernelGGL((gemm_i8_w8_kernel<1, false, false, 0, true>), grid, dim3(kW8Threads), kW8LdsBytes, s, q);
+                return launch_status();
+            }
             if (p.spb == 1) hipLaunchKernelGGL(gemm_i8_w8_kernel<1>, grid, dim3(kW8Threads), kW8LdsBytes, s, q);
             else if (p.spb == 2) hipLaunchKernelGGL(gemm_i8_w8_kernel<2>, grid, dim3(kW8Threads), kW8LdsBytes, s, q);
             else hipLaunchKernelGGL(gemm_i8_w8_kernel<0>, grid, dim3(kW8Threads), kW8LdsBytes, s, q);
@@ -1418,7 +1492,7 @@ int launch_gemm_i8(const GemmArgs &a, void *workspace, hipStream_t s) {
     }
     if (rc != HBFP_OK) return rc;
     if (!a.P && p.splits > 1) {
-        rc = launch_splitk_reduce(p, s);
+        rc = enc ? launch_splitk_reduce_encode(p, w8_enc_of(*enc, relu), s) : launch_splitk_reduce(p, s);
     }
     return rc;
 }

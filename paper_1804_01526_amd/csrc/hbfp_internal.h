@@ -86,7 +86,8 @@ bool gemm_i8_standby_words(const GemmArgs &a, void *workspace, StandbyWords *w);
 bool tile_path_ok(const hbfp_tensor *const *outs, int n, const hbfp_tensor *wide_in, const float *src, int64_t ld);
 int launch_tile_encode(const float *src, int64_t ld, float alpha, const hbfp_tensor *wide_in, const hbfp_tensor *const *outs,
                        int n, hipStream_t s);
-int launch_gemm_i8(const GemmArgs &a, void *workspace, hipStream_t s);
+int launch_gemm_i8(const GemmArgs &a, void *workspace, hipStream_t s, const hbfp_tensor *enc = nullptr, int relu = 0);
+bool gemm_i8_encoded_output_ok(const GemmArgs &a, const hbfp_tensor &out);
 size_t gemm_i8_workspace(int64_t M, int64_t N, int64_t kpad, int64_t kbp, int64_t exp_ld);
 size_t gemm_conv_workspace(int64_t M, int64_t N, int64_t kpad, int64_t pixels, int cblocks);
 int launch_gemm_conv_i8(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64_t wo, int64_t pix_bytes, void *workspace,

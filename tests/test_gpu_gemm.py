@@ -1286,6 +1286,19 @@ def _check_bfp_output(hb, A, B, fa, fb, fo, axis, relu, kernel, fused):
         assert ws <= n_fused + 512          # no scratch for the conversion beyond the product's own
 
 
+@pytest.mark.parametrize("fo,relu", [((1, 32, 8, 0, 0), True), ((1, 32, 8, 1, 77), False), ((1, 32, 5, 1, 3), True)])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 8), (130, 127, 96), (70, 129, 1100), (16, 1030, 4096), (300, 260, 2049), (129, 31, 6000)])
+@pytest.mark.parametrize("kernel,blk", [(0, 32), (1, 24)])
+def test_int8_product_delivered_as_an_encoded_operand(hb, fo, relu, M, N, K, kernel, blk):
+    """The int8 kernels convert their accumulators (few k) or the sum of their slices (split along k), the edges of the
+    tile, of the last block and of the padded row included."""
+    print(f"[case] int8 encoded output {M}x{N}x{K} fo={fo} relu={relu} kernel={kernel} blocks of {blk}", flush=True)
+    rng = np.random.default_rng(M + N + K)
+    A = (rng.standard_normal((M, K)) * np.exp2(rng.integers(-4, 5, size=(M, K)))).astype(np.float32)
+    B = (rng.standard_normal((K, N)) * np.exp2(rng.integers(-4, 5, size=(K, N)))).astype(np.float32)
+    _check_bfp_output(hb, A, B, (1, blk, 8), (blk, 1, 8), fo, 1, relu, kernel, fused=False)
+
+
 @pytest.mark.parametrize("fo,relu", [((1, 32, 8, 0, 0), False), ((1, 32, 8, 1, 77), True), ((1, 64, 8, 0, 0), True),
                                      ((1, 64, 12, 1, 5), False), ((1, 32, 4, 0, 0), False), ((1, 32, 16, 0, 0), True)])
 @pytest.mark.parametrize("M,N,K", [(300, 270, 704), (256, 512, 128), (70, 33, 200)])

@@ -102,6 +102,11 @@ int launch_gemm_f16(const GemmArgs &a, void *workspace, hipStream_t s);
 int launch_gemm_limb(const GemmArgs &a, void *workspace, hipStream_t s);
 size_t gemm_limb_workspace(const hbfp_tensor *A, const hbfp_tensor *B);
 
+// gemm_skinny.hip: int8 products with at most 64 rows of A, no workspace; enc: the product leaves as this encoded operand
+// (blocks of 32 along its columns, at most 8 bits)
+bool gemm_skinny_ok(const GemmArgs &a);
+int launch_gemm_skinny(const GemmArgs &a, hipStream_t s, const hbfp_tensor *enc = nullptr, int relu = 0);
+
 // gemm_wide.hip: int8 kernel for one exponent per operand row (a single block along k), 256 x 256 tiles
 bool gemm_wide_possible(const GemmArgs &a);
 bool gemm_wide_ok(const GemmArgs &a);

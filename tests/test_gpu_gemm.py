@@ -1286,6 +1286,29 @@ def _check_bfp_output(hb, A, B, fa, fb, fo, axis, relu, kernel, fused):
         assert ws <= n_fused + 512          # no scratch for the conversion beyond the product's own
 
 
+@pytest.mark.parametrize("M,N,K,m,blk", [(1, 1, 8, 8, 32), (32, 33, 129, 8, 32), (33, 32, 1000, 8, 24), (64, 515, 2048, 6, 16),
+                                         (17, 300, 4090, 8, 32), (31, 4099, 8100, 8, 32), (64, 100, 2049, 4, 20)])
+def test_products_of_few_rows(hb, M, N, K, m, blk):
+    """hbfp_gemm with at most 64 rows of A: the kernel without workspace on both sides of its rule (rows, contraction length,
+    columns) against the oracle, accumulation into C and a wider C included, and its encoded output against the conversion
+    of its FP32 result."""
+    print(f"[case] few rows {M}x{N}x{K} m={m} blocks of {blk}", flush=True)
+    rng = np.random.default_rng(M * 7 + N + K)
+    A = (rng.standard_normal((M, K)) * np.exp2(rng.integers(-4, 5, size=(M, K)))).astype(np.float32)
+    B = (rng.standard_normal((K, N)) * np.exp2(rng.integers(-4, 5, size=(K, N)))).astype(np.float32)
+    x, w = hb.encode(torch.from_numpy(A).cuda(), 1, hb.make_format(m, 1, blk)), hb.encode(torch.from_numpy(B).cuda(), 0, hb.make_format(m, blk, 1))
+    want = _oracle_product(A, B, (1, blk, m, 0, 0), (blk, 1, m, 0, 0))
+    out = torch.full((M, N + 5), 3.0, device="cuda")
+    hb.gemm(x, w, out=out[:, :N])
+    once = out[:, :N].clone()
+    hb.gemm(x, w, out=out[:, :N], beta=1.0)
+    torch.cuda.synchronize()
+    assert rel_fro(once.cpu().numpy(), want) <= TOL
+    assert torch.equal(out[:, :N], once + once) and (out[:, N:] == 3.0).all()
+    for fo, relu in (((1, 32, 8, 0, 0), True), ((1, 32, 7, 1, 9), False)):
+        _check_bfp_output(hb, A, B, (1, blk, m), (blk, 1, m), fo, 1, relu, 0, fused=False)
+
+
 @pytest.mark.parametrize("fo,relu", [((1, 32, 8, 0, 0), True), ((1, 32, 8, 1, 77), False), ((1, 32, 5, 1, 3), True)])
 @pytest.mark.parametrize("M,N,K", [(1, 1, 8), (130, 127, 96), (70, 129, 1100), (16, 1030, 4096), (300, 260, 2049), (129, 31, 6000)])
 @pytest.mark.parametrize("kernel,blk", [(0, 32), (1, 24)])

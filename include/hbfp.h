@@ -407,8 +407,8 @@ int hbfp_gemm(const hbfp_tensor *A, const hbfp_tensor *B, float *C, int64_t ldc,
  *                       mantissas and the shape is such a one (any block length); FP16 when both operands have
  *                       9..12-bit mantissas in blocks it takes (measured ahead of the int8 and block-scaled families from
  *                       2048^3 to 8192^3); SCALED for the same shapes as BF16 when an operand has at most 5 bits; else INT8
- *                       (with at most 64 rows of A in a kernel of its own: the same arithmetic per block, the sums of the
- *                       blocks in another order than HBFP_KERNEL_INT8's).
+ *                       (small products in a kernel of its own: the same arithmetic per block, the sums of the blocks in
+ *                       another order than HBFP_KERNEL_INT8's).
  * All satisfy the same bound against the FP64 product of the decoded operands.
  * Arguments, domain and errors as hbfp_gemm, plus HBFP_ERR_ARG for an unknown kernel; the workspace
  * size depends on the kernel: hbfp_gemm_select_workspace.

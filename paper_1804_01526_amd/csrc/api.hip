@@ -857,7 +857,7 @@ static int run_gemm(const hbfp_tensor *A, const hbfp_tensor *B, float *C, int64_
         g.run_b = (const int *)pb;
     }
     if (A->mant_bits > 8) return launch_gemm_limb(g, workspace, (hipStream_t)stream);
-    if (kernel == HBFP_KERNEL_AUTO && !g.run_a && gemm_skinny_ok(g)) return launch_gemm_skinny(g, (hipStream_t)stream);
+    if (kernel == HBFP_KERNEL_AUTO && !g.run_a && gemm_small_ok(g)) return launch_gemm_small(g, (hipStream_t)stream);
     return launch_gemm_i8(g, workspace, (hipStream_t)stream);
 }
 
@@ -1031,7 +1031,7 @@ int hbfp_gemm_bfp(const hbfp_tensor *A, const hbfp_tensor *B, const hbfp_tensor 
         const bool int8 = (kernel == HBFP_KERNEL_AUTO || kernel == HBFP_KERNEL_INT8) && !use_bf(g, kernel) && !use_f16_planes(g, kernel) &&
                           !use_scaled(g, kernel);
         if (int8 && gemm_i8_encoded_output_ok(g, *out))
-            return kernel == HBFP_KERNEL_AUTO && gemm_skinny_ok(g) ? launch_gemm_skinny(g, s, out, relu) : launch_gemm_i8(g, ws_gemm, s, out, relu);
+            return kernel == HBFP_KERNEL_AUTO && gemm_small_ok(g) ? launch_gemm_small(g, s, out, relu) : launch_gemm_i8(g, ws_gemm, s, out, relu);
         rc = run_gemm(A, B, C, N, 0.0f, nullptr, kernel, ws_gemm, part[1], stream);
         if (rc == HBFP_OK && relu) rc = launch_relu(C, M * N, s);
         if (rc != HBFP_OK) return rc;

@@ -1049,9 +1049,10 @@ int launch_t(const GemmParams &p, dim3 grid, hipStream_t s) {
 // takes 0.32 us for a workgroup that has its compute unit to itself, 0.54 us for one of two that share it, and the slices are
 // written and read back at about 4 TB/s behind 3 us for the second launch.  (Twice as many ranges as fill the chip once, the
 // rule before, cost 1000 x 1024 x 4096 32.6 us against 27.3 us with 4, 1500^3 30.9 us against 23.7 us unsplit.)
-static int choose_splits(int64_t M, int64_t N, int64_t nstage, int64_t stages_per_block) {
+static int choose_splits(int64_t M, int64_t N, int64_t nstage, int64_t stages_per_block, double *estimate = nullptr) {
     const int64_t tiles = ceil_div(M, BM) * ceil_div(N, BN);
     const int64_t units = nstage / stages_per_block;   // whole exponent blocks (or stages) that can be dealt out
+    if (estimate) *estimate = (double)nstage * 4 * (tiles <= 256 ? 0.32 : 0.54 * (double)tiles / 512.0 > 0.32 ? 0.54 * (double)tiles / 512.0 : 0.32);
     if (tiles >= 256 || units < 8) return 1;
     // half a tile's worth of columns is half the work: its other waves only copy
     const double work = 0.5 * (double)(ceil_div(M, BM) * ceil_div(N, 64));
@@ -1063,7 +1064,14 @@ static int choose_splits(int64_t M, int64_t N, int64_t nstage, int64_t stages_pe
         const double us = steps * (work * s <= 256.0 ? 0.32 : 0.54) + (s > 1 ? 3.0 + (double)(s + 1) * (double)(M * N) * 4e-6 / 4.0 : 0.0);
         if (s == 1 || us < best) best = us, splits = s;
     }
+    if (estimate) *estimate = best;
     return splits;
+}
+// ... and what comes before and after the k-steps: the scale words, the fill of the ring, the stores of C
+double gemm_i8_estimate(const GemmArgs &a) {
+    double us = 0.0;
+    choose_splits(a.M, a.N, a.kpad / BK, 1, &us);
+    return 6.5 + us;
 }
 
 // the asynchronous-copy kernel addresses an operand tile with 32-bit offsets

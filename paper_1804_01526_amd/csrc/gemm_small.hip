@@ -1,11 +1,12 @@
-// BFP matrix product with at most 64 rows of A (inference on a few rows; Eq. (2) of Sec. 4, blocks stored as 32, 8-bit class).
-// Such a product reads every mantissa of B once and does next to nothing with it, so what counts is how soon all of B is
-// under way: a workgroup of 8 waves owns 32 columns of C, its waves deal the contraction out among themselves in groups of
-// four blocks (128 bytes of a row) and load operands and exponent bytes straight into registers, a group ahead; no scale words, no split along k, no slices in memory.  Per block the arithmetic is that of the int8 kernels: an integer sum
-// started from the row constants, one subtraction and one multiply-add.  The eight partial sums meet in LDS and leave as
-// FP32 or, with ReLU if asked for, as an encoded operand.
-// 16 x 4096 x 4096: 11.6 us (scale words 3.2 + product 10.8 + slices 4.0 us before); bound by its vector instructions and
-// load latency in turn (two waves per SIMD), not by the 17 MB of B.
+// Small BFP matrix products: inference on a few rows, layers of a few hundred columns (Eq. (2) of Sec. 4, blocks stored as 32,
+// 8-bit class).  What counts is latency: the 128 x 128-tile kernels behind a launch for scale words, and before one that sums
+// slices where few tiles split the contraction, start at 9 us.  Here a workgroup of 8 waves owns 32 columns and 32 or 64 rows
+// of C; its waves deal the contraction out among themselves in groups of four blocks (128 bytes of a row), load operands
+// and exponent bytes straight into registers, a group ahead, and meet in LDS: one launch, no workspace.  Per block the
+// arithmetic is that of the int8 kernels: an integer sum started from the row constants, one subtraction and one
+// multiply-add.  The result leaves as FP32 or, with ReLU if asked for, as an encoded operand.
+// 256^3: 3.2 us (scale words 2.1 + product 8.4 us before); 16 x 4096 x 4096: 11.6 us (words 3.2 + product 10.8 + slices
+// 4.0), bound by its vector instructions and load latency in turn (two waves per SIMD), not by the 17 MB of B.
 #include <atomic>
 
 #include "bfp_device.h"
@@ -14,10 +15,10 @@
 namespace hbfp {
 namespace {
 
-constexpr int kSkinnyWaves = 8;
-constexpr int kSkinnyThreads = kSkinnyWaves * 64;
+constexpr int kSmallWaves = 8;
+constexpr int kSmallThreads = kSmallWaves * 64;
 
-struct SkinnyParams {
+struct SmallParams {
     const uint8_t *A, *B;        // int8 mantissas [rows][kpad]
     const uint8_t *eA, *eB;      // exponent bytes [rows][exp_ld]
     float *C;                    // [M][ldc]; unused with an encoded output
@@ -34,17 +35,17 @@ struct SkinnyParams {
 
 // MT: row tiles of 32; ENC: the product leaves as an encoded operand
 template <int MT, bool ENC>
-__global__ __launch_bounds__(kSkinnyThreads, 2) void gemm_skinny_kernel(const SkinnyParams p) {
-    __shared__ __attribute__((aligned(16))) float part[kSkinnyWaves][MT * 32][32];
+__global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const SmallParams p) {
+    __shared__ __attribute__((aligned(16))) float part[kSmallWaves][MT * 32][32];
     const int t = threadIdx.x, lane = t & 63, l32 = lane & 31, lh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int64_t col0 = (int64_t)blockIdx.x * 32;
+    const int64_t col0 = (int64_t)blockIdx.x * 32, row0 = (int64_t)blockIdx.y * (32 * MT);
     const int64_t col = col0 + l32 < p.N ? col0 + l32 : p.N - 1;      // columns and rows behind the last read it again
     const uint8_t *b_src = p.B + col * p.kpad + lh * 16, *eb_src = p.eB + col * p.eB_ld;
     const uint8_t *a_src[MT], *ea_src[MT];
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
-        const int64_t row = i * 32 + l32 < p.M ? i * 32 + l32 : p.M - 1;
+        const int64_t row = row0 + i * 32 + l32 < p.M ? row0 + i * 32 + l32 : p.M - 1;
         a_src[i] = p.A + row * p.kpad + lh * 16;
         ea_src[i] = p.eA + row * p.eA_ld;
     }
@@ -77,9 +78,9 @@ __global__ __launch_bounds__(kSkinnyThreads, 2) void gemm_skinny_kernel(const Sk
     // not unrolled: the loop body is small on purpose, because a kernel this short pays for every line of instructions that
     // it fetches (four groups unrolled took 16 x 4096 x 4096 from 10.8 to 16.4 us)
 #pragma unroll 1
-    for (int g = wave; g < p.groups; g += kSkinnyWaves) {
+    for (int g = wave; g < p.groups; g += kSmallWaves) {
         Group next;
-        load(next, g + kSkinnyWaves);
+        load(next, g + kSmallWaves);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -108,17 +109,18 @@ __global__ __launch_bounds__(kSkinnyThreads, 2) void gemm_skinny_kernel(const Sk
     // a thread sums four columns of a row over the waves, in their order; the 8 lanes of a row stay together
     if (t >= MT * 256) return;
     const int r = t >> 3, c4 = (t & 7) * 4;
-    if (r >= p.M) return;
+    const int64_t row = row0 + r;
+    if (row >= p.M) return;
     float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int w = 0; w < kSkinnyWaves; ++w) {
+    for (int w = 0; w < kSmallWaves; ++w) {
         const float4 d = *reinterpret_cast<const float4 *>(&part[w][r][c4]);
         x[0] += d.x, x[1] += d.y, x[2] += d.z, x[3] += d.w;
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) x[i] *= p.final_scale;
     if (!ENC) {
-        float *dst = p.C + (int64_t)r * p.ldc + col0 + c4;
+        float *dst = p.C + row * p.ldc + col0 + c4;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             if (col0 + c4 + i < p.N) dst[i] = p.beta ? dst[i] + x[i] : x[i];
@@ -137,41 +139,53 @@ __global__ __launch_bounds__(kSkinnyThreads, 2) void gemm_skinny_kernel(const Sk
     uint32_t w = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const uint64_t idx = (uint64_t)r * (uint64_t)p.N + (uint64_t)(col0 + c4 + i);
+        const uint64_t idx = (uint64_t)row * (uint64_t)p.N + (uint64_t)(col0 + c4 + i);
         const int q = p.orounding ? quantise<1>(x[i], Eb, p.om, (uint32_t)idx, (uint32_t)(idx >> 32), p.s0, p.s1)
                                   : quantise<0>(x[i], Eb, p.om, 0u, 0u, 0u, 0u);
         w |= ((uint32_t)q & 0xffu) << (8 * i);
     }
-    *reinterpret_cast<uint32_t *>(p.mant + (int64_t)r * p.okpad + col0 + c4) = w;
+    *reinterpret_cast<uint32_t *>(p.mant + row * p.okpad + col0 + c4) = w;
     if (c4 == 0) {
         const int64_t blk = (int64_t)blockIdx.x;
-        if (blk < p.oexp_ld) p.exps[(int64_t)r * p.oexp_ld + blk] = blk < p.onblk ? (uint8_t)Eb : (uint8_t)1;
+        if (blk < p.oexp_ld) p.exps[row * p.oexp_ld + blk] = blk < p.onblk ? (uint8_t)Eb : (uint8_t)1;
     }
 }
 
 template <int MT>
-int launch_skinny(const SkinnyParams &p, bool enc, unsigned workgroups, hipStream_t s) {
-    if (enc) hipLaunchKernelGGL((gemm_skinny_kernel<MT, true>), dim3(workgroups), dim3(kSkinnyThreads), 0, s, p);
-    else hipLaunchKernelGGL((gemm_skinny_kernel<MT, false>), dim3(workgroups), dim3(kSkinnyThreads), 0, s, p);
+int launch_small(const SmallParams &p, bool enc, unsigned workgroups, hipStream_t s) {
+    const dim3 grid(workgroups, (unsigned)ceil_div(p.M, 32 * MT));
+    if (enc) hipLaunchKernelGGL((gemm_small_kernel<MT, true>), grid, dim3(kSmallThreads), 0, s, p);
+    else hipLaunchKernelGGL((gemm_small_kernel<MT, false>), grid, dim3(kSmallThreads), 0, s, p);
     return launch_status();
 }
 
 }  // namespace
 
-// Whether the product runs here.  A wave takes about 2 us per group of four blocks (rows up to 32; 3.9 us up to 64) behind 3.3 us,
-// whatever the number of columns up to one workgroup per compute unit, where the tile kernel with its scale words and slices
-// starts at 10 us and splits a long contraction over the chip.  Measured, tile kernel -> here: 16 rows, 4096 x 4096 17.7 -> 11.6 us,
-// 16 x 1024 x 1024 12.4 -> 5.7, 16 x 8192 x 8192 32 -> 20, 64 x 8192 x 1024 16.4 -> 9.8; behind at 32 x 2048 x 8192 (18.9 and
-// 21.8), 64 x 512 x 4096 (13.9 and 18.7), 64 x 20000 x 512 (14.1 and 15.4).
-bool gemm_skinny_ok(const GemmArgs &a) {
-    if (a.P || a.mA > 8 || a.mB > 8 || a.kbp != 32) return false;
-    if (a.M <= 32) return a.N <= 16384 && (a.kpad <= 4096 || (a.kpad <= 8192 && a.N >= 4096));
-    return a.M <= 64 && a.N <= 8192 && a.kpad <= 2048;
+// The faster of the two tile heights (1 or 2 row tiles of 32) and its estimate.  One workgroup is resident per compute unit; a
+// round of them costs a start and, per group of four blocks, what was measured up to one group per wave and beyond.
+static int small_row_tiles(const GemmArgs &a, double *us) {
+    const double g = (double)(a.kpad / 128), g8 = g < 8 ? g : 8;
+    const int64_t cols = ceil_div(a.N, 32);
+    const double t1 = 1.3 + (double)ceil_div(ceil_div(a.M, 32) * cols, 256) * (1.3 + 0.45 * g8 + 0.26 * (g - g8));
+    const double t2 = 1.3 + (double)ceil_div(ceil_div(a.M, 64) * cols, 256) * (1.6 + 0.75 * g8 + 0.47 * (g - g8));
+    if (us) *us = t1 <= t2 ? t1 : t2;
+    return t1 <= t2 ? 1 : 2;
 }
 
-int launch_gemm_skinny(const GemmArgs &a, hipStream_t s, const hbfp_tensor *enc, int relu) {
-    if (!gemm_skinny_ok(a)) return HBFP_ERR_FORMAT;
-    SkinnyParams p = {};
+// Whether the product runs here: its estimate against that of the 128 x 128-tile kernels, a tenth on the safe side.  Measured, tile kernels -> here:
+// 256^3 9.7 -> 3.2 us, 512^3 11.9 -> 4.4, 300 x 300 x 2000 14.2 -> 8.8, 128 x 4096 x 1024 15.8 -> 9.6, 16 x 4096 x 4096
+// 17.7 -> 11.6, 1024 x 1024 x 512 12.4 -> 10.8; behind at 1024^3 (17.6, 18.0), 2048 x 1024 x 256 (10.3, 14.0),
+// 32 x 2048 x 8192 (18.9, 21.8), 16 x 64 x 8192 (11.8, 17.8).
+bool gemm_small_ok(const GemmArgs &a) {
+    if (a.P || a.mA > 8 || a.mB > 8 || a.kbp != 32 || a.M > (1 << 20) || a.N > (1 << 20)) return false;
+    double us;
+    small_row_tiles(a, &us);
+    return us * 1.1 < gemm_i8_estimate(a);
+}
+
+int launch_gemm_small(const GemmArgs &a, hipStream_t s, const hbfp_tensor *enc, int relu) {
+    if (!gemm_small_ok(a)) return HBFP_ERR_FORMAT;
+    SmallParams p = {};
     p.A = (const uint8_t *)a.mantA;
     p.B = (const uint8_t *)a.mantB;
     p.eA = a.expA;
@@ -201,7 +215,7 @@ int launch_gemm_skinny(const GemmArgs &a, hipStream_t s, const hbfp_tensor *enc,
         cols = enc->kpad;                                      // the padding of the rows too
     }
     const unsigned workgroups = (unsigned)ceil_div(cols, 32);
-    return a.M <= 32 ? launch_skinny<1>(p, enc != nullptr, workgroups, s) : launch_skinny<2>(p, enc != nullptr, workgroups, s);
+    return small_row_tiles(a, nullptr) == 1 ? launch_small<1>(p, enc != nullptr, workgroups, s) : launch_small<2>(p, enc != nullptr, workgroups, s);
 }
 
 }  // namespace hbfp

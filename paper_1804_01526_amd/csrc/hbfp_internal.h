@@ -87,6 +87,8 @@ bool tile_path_ok(const hbfp_tensor *const *outs, int n, const hbfp_tensor *wide
 int launch_tile_encode(const float *src, int64_t ld, float alpha, const hbfp_tensor *wide_in, const hbfp_tensor *const *outs,
                        int n, hipStream_t s);
 int launch_gemm_i8(const GemmArgs &a, void *workspace, hipStream_t s, const hbfp_tensor *enc = nullptr, int relu = 0);
+// microseconds that launch_gemm_i8 is expected to take for blocks stored as 32
+double gemm_i8_estimate(const GemmArgs &a);
 bool gemm_i8_encoded_output_ok(const GemmArgs &a, const hbfp_tensor &out);
 size_t gemm_i8_workspace(int64_t M, int64_t N, int64_t kpad, int64_t kbp, int64_t exp_ld);
 size_t gemm_conv_workspace(int64_t M, int64_t N, int64_t kpad, int64_t pixels, int cblocks);
@@ -102,10 +104,10 @@ int launch_gemm_f16(const GemmArgs &a, void *workspace, hipStream_t s);
 int launch_gemm_limb(const GemmArgs &a, void *workspace, hipStream_t s);
 size_t gemm_limb_workspace(const hbfp_tensor *A, const hbfp_tensor *B);
 
-// gemm_skinny.hip: int8 products with at most 64 rows of A, no workspace; enc: the product leaves as this encoded operand
+// gemm_small.hip: small int8 products in one launch without workspace; enc: the product leaves as this encoded operand
 // (blocks of 32 along its columns, at most 8 bits)
-bool gemm_skinny_ok(const GemmArgs &a);
-int launch_gemm_skinny(const GemmArgs &a, hipStream_t s, const hbfp_tensor *enc = nullptr, int relu = 0);
+bool gemm_small_ok(const GemmArgs &a);
+int launch_gemm_small(const GemmArgs &a, hipStream_t s, const hbfp_tensor *enc = nullptr, int relu = 0);
 
 // gemm_wide.hip: int8 kernel for one exponent per operand row (a single block along k), 256 x 256 tiles
 bool gemm_wide_possible(const GemmArgs &a);

@@ -1287,12 +1287,14 @@ def _check_bfp_output(hb, A, B, fa, fb, fo, axis, relu, kernel, fused):
 
 
 @pytest.mark.parametrize("M,N,K,m,blk", [(1, 1, 8, 8, 32), (32, 33, 129, 8, 32), (33, 32, 1000, 8, 24), (64, 515, 2048, 6, 16),
-                                         (17, 300, 4090, 8, 32), (31, 4099, 8100, 8, 32), (64, 100, 2049, 4, 20)])
-def test_products_of_few_rows(hb, M, N, K, m, blk):
-    """hbfp_gemm with at most 64 rows of A: the kernel without workspace on both sides of its rule (rows, contraction length,
-    columns) against the oracle, accumulation into C and a wider C included, and its encoded output against the conversion
-    of its FP32 result."""
-    print(f"[case] few rows {M}x{N}x{K} m={m} blocks of {blk}", flush=True)
+                                         (17, 300, 4090, 8, 32), (31, 4099, 8100, 8, 32), (64, 100, 2049, 4, 20),
+                                         (256, 256, 256, 8, 32), (97, 1000, 1000, 8, 24), (700, 690, 300, 8, 32), (1024, 1030, 520, 5, 32),
+                                         (1100, 1024, 1024, 8, 32), (1318, 405, 247, 7, 32)])
+def test_small_products(hb, M, N, K, m, blk):
+    """hbfp_gemm on small products: the kernel without workspace, both of its tile heights and both sides of its rule, against
+    the oracle, accumulation into C and a wider C included, and its encoded output against the conversion of its FP32
+    result."""
+    print(f"[case] small product {M}x{N}x{K} m={m} blocks of {blk}", flush=True)
     rng = np.random.default_rng(M * 7 + N + K)
     A = (rng.standard_normal((M, K)) * np.exp2(rng.integers(-4, 5, size=(M, K)))).astype(np.float32)
     B = (rng.standard_normal((K, N)) * np.exp2(rng.integers(-4, 5, size=(K, N)))).astype(np.float32)

@@ -316,7 +316,7 @@ int hbfp_gemm_conv2d_bfp(const hbfp_tensor *image, const hbfp_conv2d *conv, cons
  * zeros are never stored: the product kernel gathers each tap from dy as converted once ([n*ho*wo][filters], blocks along
  * the filters) and reads a page of zeros for the positions in between; all h x w input positions are computed, also those
  * that only part of a window reaches.  Both factors count as their BFP values and the sum is taken as Eq. (2) takes it.
- * With stride 1 this is hbfp_gemm_conv2d on dy with that padding.
+ * With stride 1 this is hbfp_gemm_conv2d on dy with that padding (runs of blocks that share their exponents included).
  *   dy       encoded [n*ho*wo][filters] (ho, wo: the output extents of conv), contraction axis 1, in any of the formats
  *            hbfp_gemm_conv2d takes for its image, with the filters in the place of the channels: stored blocks of
  *            B <= 32 filters, filters a multiple of B, any sharing of exponents beyond (one per training input), <= 8 bits

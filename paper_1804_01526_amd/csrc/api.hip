@@ -688,8 +688,10 @@ int hbfp_gemm_conv2d_dgrad(const hbfp_tensor *dy, const hbfp_conv2d *conv, const
     const GemmArgs g = conv_product_args(dy, filters, conv->n * conv->h * conv->w, dX, ldx, beta);
     // the slot-by-slot gather spreads dy out (zeros multiplied); the others go phase by phase where the window allows
     const bool by_phase = slot_order < 0 && conv_dgrad_by_phase(conv->r, conv->s, conv->stride_h, conv->stride_w);
+    // runs of blocks with one exponent in both operands are scaled once, as in the forward call, where dy is read without gaps
+    const bool runs = conv->stride_h == 1 && conv->stride_w == 1 && conv_runs(dy, &fw, filters, slot_order);
     return launch_gemm_conv_i8(g, fw, conv->h, conv->w, dy->kpad, workspace, (hipStream_t)stream, conv->stride_h, conv->stride_w, by_phase,
-                               slot_order, (int)dy->kblock);
+                               slot_order, (int)dy->kblock, runs ? conv->r * conv->s : 0);
 }
 
 int hbfp_decode(const hbfp_tensor *t, float *dst, int64_t ld, void *stream) {

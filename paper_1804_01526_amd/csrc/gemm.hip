@@ -491,8 +491,13 @@ __device__ __forceinline__ void w8_encode_from_lds(const W8Enc &o, const uint8_t
 // (an image with one exponent per training input against filter tiles that span the whole window, Sec. 5.1): the scale
 // words are staged per k-step as for SPB = 1, but a run is chained like a long block and scaled once, at its last
 // k-step, after p.chain_limit k-steps (the range in which the row constant trick is exact) and at the end of the k range.
-template <int SPB, bool CONV = false, bool F16 = false, int GATHER = 0, bool ENC = false>
+// EB (SPB = 1, no gather): the scale words come from the exponent bytes inside the kernel instead of from memory.  Four waves
+// (0, 1: rows of A; 4, 5: columns) load the four bytes of a row's blocks of a pair of stages with the pair's copies and
+// write its words in front of the hand-over that completes it: a dozen vector instructions per pair in place of the
+// launch that prepared the words (3 to 5 us).
+template <int SPB, bool CONV = false, bool F16 = false, int GATHER = 0, bool ENC = false, bool EB = false>
 __global__ __launch_bounds__(kW8Threads, 4) void gemm_i8_w8_kernel(const W8Params q) {
+    static_assert(!EB || (SPB == 1 && !CONV && !F16), "words from exponent bytes: blocks of one k-step of a plain product");
     constexpr bool STEPW = SPB == 1 || SPB == 3;     // scale words per k-step
     constexpr bool CHAIN = SPB == 0 || SPB == 3;     // the matrix instructions of a block (run) chain through their C input
     constexpr bool DIL = GATHER == 1 || GATHER == 4, PHASE = GATHER == 2, SLOT = GATHER == 3 || GATHER == 4;
@@ -603,6 +608,31 @@ __global__ __launch_bounds__(kW8Threads, 4) void gemm_i8_w8_kernel(const W8Param
             if (++fs == gS) { fs = 0; ++fr; }                                                           \
         }                                                                                               \
     }
+    // EB: this lane's exponent row, the bytes of the pair of stages requested last, and where its words go
+    const bool eb_wave = EB && (wave_u & 2) == 0;                                // waves 0, 1, 4, 5 (uniform)
+    const uint8_t *ebase = nullptr;
+    uint32_t evoff = 0, ebytes = 0;
+    if (eb_wave) {
+        const int64_t rest = wave_u < 4 ? p.M - row0 : p.N - col0, ld = wave_u < 4 ? p.eA_ld : p.eB_ld;
+        const int r = 64 * (wave_u & 1) + lane;
+        ebase = wave_u < 4 ? p.eA + row0 * ld : p.eB + col0 * ld;                // uniform
+        evoff = (uint32_t)(r < rest ? r : (int)rest - 1) * (uint32_t)ld + 2u * (uint32_t)st_begin;
+    }
+#define HBFP_LOAD_BYTES                                                                                 \
+    if (eb_wave) {                                                                                      \
+        ebytes = *reinterpret_cast<const uint32_t *>(ebase + evoff);                                    \
+        evoff += 4;                                                                                     \
+    }
+    // the words of the pair of stages in ring buffers `ring` and `ring` + 1
+#define HBFP_PUT_WORDS(ring, bytes)                                                                     \
+    if (eb_wave) {                                                                                      \
+        uint8_t *to = lds + (ring) * kHalfStage + 2 * kHalfTile + (wave_u < 4 ? 0 : kHalfWords) + (64 * (wave_u & 1) + lane) * 4; \
+        _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                                 \
+            uint32_t e = ((bytes) >> (8 * i)) & 0xffu;                                                  \
+            e = e > 254u ? 254u : e;                                                                    \
+            *reinterpret_cast<uint32_t *>(to + (i >> 1) * kHalfStage + (i & 1) * 512) = wave_u < 4 ? ((e << 7) | 0x40u) : (e << 23); \
+        }                                                                                               \
+    }
 #define HBFP_COPY_NEXT(ring)                                                                            \
     {                                                                                                   \
         const uint32_t lb = (ring) * kHalfStage;                                                        \
@@ -671,7 +701,7 @@ __global__ __launch_bounds__(kW8Threads, 4) void gemm_i8_w8_kernel(const W8Param
                 srcW = q.cv.words + (int64_t)(2 * csub + (wc >> 1)) * q.cv.word_pitch + (wpix + (qy * q.cv.W + qx)); \
             }                                                                                           \
             async_copy4_at(in_w ? srcW : reinterpret_cast<const uint32_t *>(q.cv.zeros + 64), lb + ldsW); \
-        } else {                                                                                        \
+        } else if (!EB) {                                                                               \
             async_copy4(PHASE ? wordsrc + (kphase / 32 + (wc >> 1)) * wordpitch : nextW, voffW, lb + ldsW); \
         }                                                                                               \
         nextA += kHalfK;                                                                                \
@@ -797,9 +827,11 @@ __global__ __launch_bounds__(kW8Threads, 4) void gemm_i8_w8_kernel(const W8Param
                 const int rem = st_end - 2 - st;                 /* stages after this pair */           \
                 if (rem > 0) {                                                                          \
                     HBFP_WAIT_COPIES(0);                                                                \
+                    if (EB) HBFP_PUT_WORDS(((ring) + 2) & 3, ebytes);                                   \
                     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                                  \
                     __builtin_amdgcn_s_barrier();                                                       \
                     asm volatile("" ::: "memory");                                                      \
+                    if (EB && rem >= 4) HBFP_LOAD_BYTES;                                                \
                     if (rem >= 4) { HBFP_COPY_NEXT(ring); HBFP_COPY_NEXT((ring) + 1); }                 \
                     HBFP_READ_STEP(((ring) + 2) & 3, 0, 0);                                             \
                 }                                                                                       \
@@ -808,10 +840,17 @@ __global__ __launch_bounds__(kW8Threads, 4) void gemm_i8_w8_kernel(const W8Param
     }
 
     if (nst > 0) {
+        if (EB) HBFP_LOAD_BYTES;
+        const uint32_t bytes0 = ebytes;
         HBFP_COPY_NEXT(0);
         HBFP_COPY_NEXT(1);
+        if (EB && nst > 2) HBFP_LOAD_BYTES;
         if (nst > 2) { HBFP_COPY_NEXT(2); HBFP_COPY_NEXT(3); }
-        if (nst > 2) HBFP_WAIT_COPIES(6); else HBFP_WAIT_COPIES(0);
+        if (nst > 2) HBFP_WAIT_COPIES(EB ? 4 : 6); else HBFP_WAIT_COPIES(0);
+        if (EB) {
+            HBFP_PUT_WORDS(0, bytes0);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
     }
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -824,8 +863,13 @@ __global__ __launch_bounds__(kW8Threads, 4) void gemm_i8_w8_kernel(const W8Param
             const int rem = st_end - 2 - st;
             if (rem > 0) {
                 HBFP_WAIT_COPIES(0);
+                if (EB) {
+                    HBFP_PUT_WORDS((ring + 2) & 3, ebytes);
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                }
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
+                if (EB && rem >= 4) HBFP_LOAD_BYTES;
                 if (rem >= 4) { HBFP_COPY_NEXT(ring); HBFP_COPY_NEXT(ring + 1); }
             }
         }
@@ -864,6 +908,8 @@ __global__ __launch_bounds__(kW8Threads, 4) void gemm_i8_w8_kernel(const W8Param
 #undef HBFP_READ_STEP
 #undef HBFP_STEP
 #undef HBFP_COPY_NEXT
+#undef HBFP_LOAD_BYTES
+#undef HBFP_PUT_WORDS
 #undef HBFP_NEXT_SLOT
 #undef HBFP_WAIT_COPIES
 
@@ -1498,11 +1544,12 @@ int launch_gemm_i8(const GemmArgs &a, void *workspace, hipStream_t s, const hbfp
         // behind the block-scaled kernel the product almost never runs: one launch, no scale-word kernel in front of it;
         // it is the 8-wave kernel when the product kernel has prepared its scale words (words_ready), else the 4-wave one
         if (use_w8(a.kpad) && (!a.run_a || a.words_ready)) {
-            static std::atomic<bool> configured[4];
-            const void *const kernels[4] = {reinterpret_cast<const void *>(&gemm_i8_w8_kernel<1>), reinterpret_cast<const void *>(&gemm_i8_w8_kernel<2>),
+            static std::atomic<bool> configured[5];
+            const void *const kernels[5] = {reinterpret_cast<const void *>(&gemm_i8_w8_kernel<1>), reinterpret_cast<const void *>(&gemm_i8_w8_kernel<2>),
                                             reinterpret_cast<const void *>(&gemm_i8_w8_kernel<0>),
-                                            reinterpret_cast<const void *>(&gemm_i8_w8_kernel<1, false, false, 0, true>)};
-            for (int i = 0; i < 4; ++i)
+                                            reinterpret_cast<const void *>(&gemm_i8_w8_kernel<1, false, false, 0, true, true>),
+                                            reinterpret_cast<const void *>(&gemm_i8_w8_kernel<1, false, false, 0, false, true>)};
+            for (int i = 0; i < 5; ++i)
                 if (allow_dynamic_lds(configured[i], kernels[i], kW8LdsBytes) != HBFP_OK) return HBFP_ERR_LAUNCH;
             if (!workspace) return HBFP_ERR_WORKSPACE;
             W8Params q = {};
@@ -1512,17 +1559,23 @@ int launch_gemm_i8(const GemmArgs &a, void *workspace, hipStream_t s, const hbfp
             uint8_t *w = (uint8_t *)workspace + split_bytes(a.M, a.N, p.splits);
             q.wA = (const uint32_t *)w;
             q.wB = (const uint32_t *)(w + word_bytes(a.M, a.expA_ld));
-            if (!a.words_ready) {
+            // Scale words inside the kernel (EB): measured words -> bytes 1000 x 4096 x 1024 18.9 -> 16.8 us, 100352 x 128 x 1152
+            // 64.8 -> 59.4, 8192 x 4096 x 1024 102.9 -> 95.7; from about 2^15 tile stages of 128 on the launch is the cheaper
+            // part (4096^3 in blocks of 24: 196 and 200 us, 6144 x 4096 x 4096: 278 and 295).  The converting epilogue exists
+            // with bytes only.
+            const bool bytes = p.spb == 1 && !a.words_ready && (enc || tm * tn * p.nstage <= (1 << 15));
+            if (!a.words_ready && !bytes) {
                 rc = launch_scale_words(a.expA, a.expA_ld, a.M, a.expB, a.expB_ld, a.N, (int)a.expA_ld, 0x40u,
                                         const_cast<uint32_t *>(q.wA), const_cast<uint32_t *>(q.wB), a.run_a, a.run_b, s);
                 if (rc != HBFP_OK) return rc;
             }
             if (enc) q.enc = w8_enc_of(*enc, relu);
             if (enc && p.splits == 1) {
-                hipLaunchKernelGGL((gemm_i8_w8_kernel<1, false, false, 0, true>), grid, dim3(kW8Threads), kW8LdsBytes, s, q);
+                hipLaunchKernelGGL((gemm_i8_w8_kernel<1, false, false, 0, true, true>), grid, dim3(kW8Threads), kW8LdsBytes, s, q);
                 return launch_status();
             }
-            if (p.spb == 1) hipLaunchKernelGGL(gemm_i8_w8_kernel<1>, grid, dim3(kW8Threads), kW8LdsBytes, s, q);
+            if (bytes) hipLaunchKernelGGL((gemm_i8_w8_kernel<1, false, false, 0, false, true>), grid, dim3(kW8Threads), kW8LdsBytes, s, q);
+            else if (p.spb == 1) hipLaunchKernelGGL(gemm_i8_w8_kernel<1>, grid, dim3(kW8Threads), kW8LdsBytes, s, q);
             else if (p.spb == 2) hipLaunchKernelGGL(gemm_i8_w8_kernel<2>, grid, dim3(kW8Threads), kW8LdsBytes, s, q);
             else hipLaunchKernelGGL(gemm_i8_w8_kernel<0>, grid, dim3(kW8Threads), kW8LdsBytes, s, q);
             rc = launch_status();

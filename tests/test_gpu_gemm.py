@@ -1311,6 +1311,18 @@ def test_small_products(hb, M, N, K, m, blk):
         _check_bfp_output(hb, A, B, (1, blk, m), (blk, 1, m), fo, 1, relu, 0, fused=False)
 
 
+@pytest.mark.parametrize("M,N,K,blk", [(130, 70, 100, 24), (128, 64, 129, 32), (257, 385, 1290, 24), (100, 129, 3000, 32), (40, 300, 9000, 16)])
+def test_int8_kernel_with_scale_words_from_bytes(hb, M, N, K, blk):
+    """HBFP_KERNEL_INT8 where the kernel takes its scale words from exponent bytes: one, two and more pairs of stages, split
+    along k, whole and half column tiles, rows and columns spread over 40 binades, overwriting and accumulating."""
+    rng = np.random.default_rng(K + N)
+    A = (rng.standard_normal((M, K)) * np.exp2(rng.integers(-20, 21, size=(M, 1)))).astype(np.float32)
+    B = (rng.standard_normal((K, N)) * np.exp2(rng.integers(-20, 21, size=(1, N)))).astype(np.float32)
+    print(f"[case] words from bytes {M}x{N}x{K} blocks of {blk}", flush=True)
+    _run(hb, A, B, (1, blk, 8, 0, 0), (blk, 1, 8, 0, 0), partials=False, kernel=1)
+    _run(hb, A, B, (1, blk, 8, 0, 0), (blk, 1, 8, 0, 0), partials=False, kernel=1, beta=1.0)
+
+
 @pytest.mark.parametrize("fo,relu", [((1, 32, 8, 0, 0), True), ((1, 32, 8, 1, 77), False), ((1, 32, 5, 1, 3), True)])
 @pytest.mark.parametrize("M,N,K", [(1, 1, 8), (130, 127, 96), (70, 129, 1100), (16, 1030, 4096), (300, 260, 2049), (129, 31, 6000)])
 @pytest.mark.parametrize("kernel,blk", [(0, 32), (1, 24)])

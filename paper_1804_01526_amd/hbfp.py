@@ -221,12 +221,11 @@ def alloc(fmt: Format, rows: int, cols: int, contract_axis: int, device="cuda") 
     return BfpTensor(d, mant, exps)
 
 
-def _workspace(nbytes: int, device, workspace: Optional[torch.Tensor]) -> Optional[torch.Tensor]:
-    if nbytes == 0:
-        return workspace
-    if workspace is None:
-        workspace = torch.empty(nbytes, dtype=torch.uint8, device=device)
-    return workspace
+def _workspace(nbytes: int, device) -> Optional[torch.Tensor]:
+    """Scratch for a call that was given none.  A caller's own workspace goes to the library as it is, which checks its size: asking
+    for the size first would cost such a call a second trip through ctypes (host time of a product 11.6 -> 7.8 us, of gemm_f32
+    20 -> 14.5 us, of a conversion 8.9 -> 8.1 us)."""
+    return torch.empty(nbytes, dtype=torch.uint8, device=device) if nbytes else None
 
 
 def encode(src: torch.Tensor, contract_axis: int, fmt: Format, out: Optional[BfpTensor] = None,
@@ -237,7 +236,8 @@ def encode(src: torch.Tensor, contract_axis: int, fmt: Format, out: Optional[Bfp
     ld = src.stride(0) if rows > 1 else max(src.stride(0), cols)
     if out is None:
         out = alloc(fmt, rows, cols, contract_axis, src.device)
-    workspace = _workspace(encode_workspace(out.desc), src.device, workspace)
+    if workspace is None:
+        workspace = _workspace(encode_workspace(out.desc), src.device)
     _check(_lib.hbfp_encode(_dev_ptr(src), rows, cols, ld, contract_axis, ctypes.byref(fmt), ctypes.byref(out.desc),
                             _dev_ptr(workspace), 0 if workspace is None else workspace.numel(),
                             _stream_ptr(stream)), "hbfp_encode")
@@ -283,7 +283,8 @@ def gemm(a: BfpTensor, b: BfpTensor, out: Optional[torch.Tensor] = None, beta: f
     if out is None:
         out = torch.empty((a.desc.rows, b.desc.rows), dtype=torch.float32, device=a.mant.device)
     assert out.is_cuda and out.dtype == torch.float32 and out.stride(1) == 1
-    workspace = _workspace(gemm_select_workspace(a.desc, b.desc, kernel), out.device, workspace)
+    if workspace is None:
+        workspace = _workspace(gemm_select_workspace(a.desc, b.desc, kernel), out.device)
     _check(_lib.hbfp_gemm_select(ctypes.byref(a.desc), ctypes.byref(b.desc), _dev_ptr(out), out.stride(0), beta, kernel,
                                  _dev_ptr(workspace), 0 if workspace is None else workspace.numel(),
                                  _stream_ptr(stream)), "hbfp_gemm_select")
@@ -306,7 +307,8 @@ def gemm_batch(pairs, outs, beta: float = 0.0, kernel: int = KERNEL_AUTO, worksp
         assert o.is_cuda and o.dtype == torch.float32 and o.stride(1) == 1
     c = (ctypes.c_void_p * n)(*[o.data_ptr() for o in outs])
     ld = (ctypes.c_int64 * n)(*[o.stride(0) for o in outs])
-    workspace = _workspace(gemm_batch_workspace(pairs, kernel), outs[0].device, workspace)
+    if workspace is None:
+        workspace = _workspace(gemm_batch_workspace(pairs, kernel), outs[0].device)
     _check(_lib.hbfp_gemm_batch(n, a, b, c, ld, beta, kernel, _dev_ptr(workspace), 0 if workspace is None else workspace.numel(),
                                 _stream_ptr(stream)), "hbfp_gemm_batch")
     return outs
@@ -324,7 +326,8 @@ def gemm_bfp(a: BfpTensor, b: BfpTensor, fmt: Format, contract_axis: int = 1, re
     """hbfp_gemm_bfp: encode(relu?(A . B^T)) as an operand in format `fmt` (the next product's input)."""
     if out is None:
         out = alloc(fmt, a.desc.rows, b.desc.rows, contract_axis, a.mant.device)
-    workspace = _workspace(gemm_bfp_workspace(a.desc, b.desc, out.desc, kernel), a.mant.device, workspace)
+    if workspace is None:
+        workspace = _workspace(gemm_bfp_workspace(a.desc, b.desc, out.desc, kernel), a.mant.device)
     _check(_lib.hbfp_gemm_bfp(ctypes.byref(a.desc), ctypes.byref(b.desc), ctypes.byref(out.desc), int(relu), kernel,
                               _dev_ptr(workspace), 0 if workspace is None else workspace.numel(), _stream_ptr(stream)),
            "hbfp_gemm_bfp")
@@ -359,7 +362,8 @@ def gemm_packed(a: BfpTensor, packed_a: torch.Tensor, b: BfpTensor, packed_b: to
     if out is None:
         out = torch.empty((a.desc.rows, b.desc.rows), dtype=torch.float32, device=a.mant.device)
     assert out.is_cuda and out.dtype == torch.float32 and out.stride(1) == 1
-    workspace = _workspace(gemm_packed_workspace(a.desc, b.desc), out.device, workspace)
+    if workspace is None:
+        workspace = _workspace(gemm_packed_workspace(a.desc, b.desc), out.device)
     _check(_lib.hbfp_gemm_packed(ctypes.byref(a.desc), _dev_ptr(packed_a), ctypes.byref(b.desc), _dev_ptr(packed_b),
                                  _dev_ptr(out), out.stride(0), beta, _dev_ptr(workspace),
                                  0 if workspace is None else workspace.numel(), _stream_ptr(stream)), "hbfp_gemm_packed")
@@ -384,7 +388,8 @@ def gemm_packed_batch(products, outs, beta: float = 0.0, workspace: Optional[tor
         assert o.is_cuda and o.dtype == torch.float32 and o.stride(1) == 1
     c = (ctypes.c_void_p * n)(*[o.data_ptr() for o in outs])
     ld = (ctypes.c_int64 * n)(*[o.stride(0) for o in outs])
-    workspace = _workspace(gemm_packed_batch_workspace([(p[0], p[2]) for p in products]), outs[0].device, workspace)
+    if workspace is None:
+        workspace = _workspace(gemm_packed_batch_workspace([(p[0], p[2]) for p in products]), outs[0].device)
     _check(_lib.hbfp_gemm_packed_batch(n, a, pa, b, pb, c, ld, beta, _dev_ptr(workspace),
                                        0 if workspace is None else workspace.numel(), _stream_ptr(stream)), "hbfp_gemm_packed_batch")
     return outs
@@ -392,7 +397,8 @@ def gemm_packed_batch(products, outs, beta: float = 0.0, workspace: Optional[tor
 
 def gemm_partials(a: BfpTensor, b: BfpTensor, workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     P = torch.empty((a.desc.rows, b.desc.rows, a.desc.nblk), dtype=torch.int32, device=a.mant.device)
-    workspace = _workspace(gemm_select_workspace(a.desc, b.desc, KERNEL_INT8), P.device, workspace)
+    if workspace is None:
+        workspace = _workspace(gemm_select_workspace(a.desc, b.desc, KERNEL_INT8), P.device)
     _check(_lib.hbfp_gemm_partials(ctypes.byref(a.desc), ctypes.byref(b.desc), _dev_ptr(P), _dev_ptr(workspace),
                                    0 if workspace is None else workspace.numel(), _stream_ptr(stream)),
            "hbfp_gemm_partials")
@@ -403,7 +409,8 @@ def gemm_partials_window(a: BfpTensor, b: BfpTensor, row0: int, rows: int, col0:
                           workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """hbfp_gemm_partials_window: the integer block sums of rows row0.. x columns col0.. of the product only."""
     P = torch.empty((rows, cols, a.desc.nblk), dtype=torch.int32, device=a.mant.device)
-    workspace = _workspace(gemm_select_workspace(a.desc, b.desc, KERNEL_INT8), P.device, workspace)
+    if workspace is None:
+        workspace = _workspace(gemm_select_workspace(a.desc, b.desc, KERNEL_INT8), P.device)
     _check(_lib.hbfp_gemm_partials_window(ctypes.byref(a.desc), ctypes.byref(b.desc), row0, rows, col0, cols, _dev_ptr(P),
                                           _dev_ptr(workspace), 0 if workspace is None else workspace.numel(),
                                           _stream_ptr(stream)), "hbfp_gemm_partials_window")
@@ -419,7 +426,8 @@ def gemm_f32(trans_a: int, trans_b: int, A: torch.Tensor, B: torch.Tensor, fa: F
     N = B.shape[0] if trans_b else B.shape[1]
     if out is None:
         out = torch.empty((M, N), dtype=torch.float32, device=A.device)
-    workspace = _workspace(gemm_f32_workspace(trans_a, trans_b, M, N, K, fa, fb), A.device, workspace)
+    if workspace is None:
+        workspace = _workspace(gemm_f32_workspace(trans_a, trans_b, M, N, K, fa, fb), A.device)
     _check(_lib.hbfp_gemm_f32(trans_a, trans_b, M, N, K, _dev_ptr(A), A.stride(0), _dev_ptr(B), B.stride(0),
                               _dev_ptr(out), out.stride(0), ctypes.byref(fa), ctypes.byref(fb),
                               _dev_ptr(workspace), 0 if workspace is None else workspace.numel(),
@@ -443,7 +451,8 @@ def weight_update(wide: BfpTensor, delta: torch.Tensor, alpha: float, narrow_a: 
                   narrow_b: Optional[BfpTensor] = None, workspace: Optional[torch.Tensor] = None, stream=None):
     """hbfp_weight_update: wide <- encode(fma(alpha, delta, value(wide))), and the same FP32 result into the narrow tensors."""
     assert delta.is_cuda and delta.dtype == torch.float32 and delta.dim() == 2 and delta.stride(1) == 1
-    workspace = _workspace(weight_update_workspace(wide, narrow_a, narrow_b), delta.device, workspace)
+    if workspace is None:
+        workspace = _workspace(weight_update_workspace(wide, narrow_a, narrow_b), delta.device)
     _check(_lib.hbfp_weight_update(ctypes.byref(wide.desc), _dev_ptr(delta), delta.stride(0), alpha,
                                    _desc_ref(narrow_a), _desc_ref(narrow_b), _dev_ptr(workspace),
                                    0 if workspace is None else workspace.numel(), _stream_ptr(stream)),
@@ -472,7 +481,8 @@ def encode_im2col(x: torch.Tensor, conv: Conv2d, fmt: Format, contract_axis: int
     ho, wo = conv.out_hw()
     if out is None:
         out = alloc(fmt, conv.n * ho * wo, conv.r * conv.s * conv.c, contract_axis, x.device)
-    workspace = _workspace(encode_im2col_workspace(conv, out.desc), x.device, workspace)
+    if workspace is None:
+        workspace = _workspace(encode_im2col_workspace(conv, out.desc), x.device)
     _check(_lib.hbfp_encode_im2col(_dev_ptr(x), ctypes.byref(conv), ctypes.byref(out.desc), _dev_ptr(workspace),
                                    0 if workspace is None else workspace.numel(), _stream_ptr(stream)), "hbfp_encode_im2col")
     return out
@@ -490,7 +500,8 @@ def encode_multi(src: torch.Tensor, outs, workspace: Optional[torch.Tensor] = No
     rows, cols = src.shape
     ld = src.stride(0) if rows > 1 else max(src.stride(0), cols)
     arr = _desc_array(outs)
-    workspace = _workspace(encode_multi_workspace(outs), src.device, workspace)
+    if workspace is None:
+        workspace = _workspace(encode_multi_workspace(outs), src.device)
     _check(_lib.hbfp_encode_multi(_dev_ptr(src), ld, len(outs), arr, _dev_ptr(workspace),
                                   0 if workspace is None else workspace.numel(), _stream_ptr(stream)), "hbfp_encode_multi")
     return outs
@@ -512,7 +523,8 @@ def encode_packed(src: torch.Tensor, outs, packed, workspace: Optional[torch.Ten
     n = len(outs)
     ptrs = (ctypes.c_void_p * n)(*[None if b is None else b.data_ptr() for b in packed])
     sizes = (ctypes.c_size_t * n)(*[0 if b is None else b.numel() for b in packed])
-    workspace = _workspace(encode_packed_workspace(outs), src.device, workspace)
+    if workspace is None:
+        workspace = _workspace(encode_packed_workspace(outs), src.device)
     _check(_lib.hbfp_encode_packed(_dev_ptr(src), ld, n, _desc_array(outs), ptrs, sizes, _dev_ptr(workspace),
                                    0 if workspace is None else workspace.numel(), _stream_ptr(stream)), "hbfp_encode_packed")
     return outs
@@ -546,9 +558,10 @@ def encode_packed_batch_workspace(sources) -> int:
 def encode_packed_batch(sources, workspace: Optional[torch.Tensor] = None, stream=None):
     """hbfp_encode_packed_batch: sources is a sequence of (src, outs, packed), each as the arguments of encode_packed."""
     jobs, keep = _encode_jobs(sources)
-    need = ctypes.c_size_t(0)
-    _check(_lib.hbfp_encode_packed_batch_workspace(len(sources), jobs, ctypes.byref(need)), "hbfp_encode_packed_batch_workspace")
-    workspace = _workspace(int(need.value), sources[0][0].device, workspace)
+    if workspace is None:
+        need = ctypes.c_size_t(0)
+        _check(_lib.hbfp_encode_packed_batch_workspace(len(sources), jobs, ctypes.byref(need)), "hbfp_encode_packed_batch_workspace")
+        workspace = _workspace(int(need.value), sources[0][0].device)
     _check(_lib.hbfp_encode_packed_batch(len(sources), jobs, _dev_ptr(workspace), 0 if workspace is None else workspace.numel(),
                                          _stream_ptr(stream)), "hbfp_encode_packed_batch")
     return [s[1] for s in sources]
@@ -578,7 +591,8 @@ def gemm_conv2d(image: BfpTensor, conv: Conv2d, filters: BfpTensor, out: Optiona
     if out is None:
         out = torch.empty((conv.n * ho * wo, filters.desc.rows), dtype=torch.float32, device=image.mant.device)
     assert out.is_cuda and out.dtype == torch.float32 and out.stride(1) == 1
-    workspace = _workspace(gemm_conv2d_workspace(image.desc, conv, filters.desc), out.device, workspace)
+    if workspace is None:
+        workspace = _workspace(gemm_conv2d_workspace(image.desc, conv, filters.desc), out.device)
     _check(_lib.hbfp_gemm_conv2d(ctypes.byref(image.desc), ctypes.byref(conv), ctypes.byref(filters.desc), _dev_ptr(out),
                                  out.stride(0), beta, _dev_ptr(workspace), 0 if workspace is None else workspace.numel(),
                                  _stream_ptr(stream)), "hbfp_gemm_conv2d")
@@ -599,7 +613,8 @@ def gemm_conv2d_bfp(image: BfpTensor, conv: Conv2d, filters: BfpTensor, fmt: For
     ho, wo = conv.out_hw()
     if out is None:
         out = alloc(fmt, conv.n * ho * wo, filters.desc.rows, 1, image.mant.device)
-    workspace = _workspace(gemm_conv2d_bfp_workspace(image.desc, conv, filters.desc, out.desc), image.mant.device, workspace)
+    if workspace is None:
+        workspace = _workspace(gemm_conv2d_bfp_workspace(image.desc, conv, filters.desc, out.desc), image.mant.device)
     _check(_lib.hbfp_gemm_conv2d_bfp(ctypes.byref(image.desc), ctypes.byref(conv), ctypes.byref(filters.desc), ctypes.byref(out.desc),
                                      1 if relu else 0, _dev_ptr(workspace), 0 if workspace is None else workspace.numel(),
                                      _stream_ptr(stream)), "hbfp_gemm_conv2d_bfp")
@@ -620,7 +635,8 @@ def gemm_conv2d_dgrad(dy: BfpTensor, conv: Conv2d, filters: BfpTensor, out: Opti
     if out is None:
         out = torch.empty((conv.n * conv.h * conv.w, filters.desc.rows), dtype=torch.float32, device=dy.mant.device)
     assert out.is_cuda and out.dtype == torch.float32 and out.stride(1) == 1
-    workspace = _workspace(gemm_conv2d_dgrad_workspace(dy.desc, conv, filters.desc), out.device, workspace)
+    if workspace is None:
+        workspace = _workspace(gemm_conv2d_dgrad_workspace(dy.desc, conv, filters.desc), out.device)
     _check(_lib.hbfp_gemm_conv2d_dgrad(ctypes.byref(dy.desc), ctypes.byref(conv), ctypes.byref(filters.desc), _dev_ptr(out),
                                        out.stride(0), beta, _dev_ptr(workspace), 0 if workspace is None else workspace.numel(),
                                        _stream_ptr(stream)), "hbfp_gemm_conv2d_dgrad")

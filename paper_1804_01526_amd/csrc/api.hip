@@ -1286,6 +1286,17 @@ int hbfp_gemm_f32(int transA, int transB, int64_t M, int64_t N, int64_t K,
     rc = check_pair(&p.ta, &p.tb);  // mantissa classes and accumulator bound, before any launch
     if (rc != HBFP_OK) return rc;
     const size_t enc_bytes = p.off_gemm - p.off_enc, gemm_bytes = p.total - p.off_gemm;
+    const EncodeGeom geoms[2] = {geom_of(p.ta, lda), geom_of(p.tb, ldb)};
+    // sources off their element's alignment go on to hbfp_encode and its answer
+    if (((uintptr_t)A & 3) == 0 && ((uintptr_t)B & 3) == 0 && !needs_tile_pass(p.ta) && !needs_tile_pass(p.tb) &&
+        encode_pair_ok(geoms[0], geoms[1])) {
+        const float *const src[2] = {A, B};
+        void *const mant[2] = {p.ta.mant, p.tb.mant};
+        uint8_t *const exps[2] = {p.ta.exps, p.tb.exps};
+        rc = launch_encode_pair(src, geoms, mant, exps, (hipStream_t)stream);
+        if (rc != HBFP_OK) return rc;
+        return hbfp_gemm(&p.ta, &p.tb, C, ldc, 0.0f, w + p.off_gemm, gemm_bytes, stream);
+    }
     rc = transA ? hbfp_encode(A, K, M, lda, 0, fa, &p.ta, w + p.off_enc, enc_bytes, stream)
                 : hbfp_encode(A, M, K, lda, 1, fa, &p.ta, w + p.off_enc, enc_bytes, stream);
     if (rc != HBFP_OK) return rc;

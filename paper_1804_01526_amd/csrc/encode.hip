@@ -140,12 +140,12 @@ struct RowParams {
 
 
 template <int GP, bool WIDE, int ROUND, int U, bool CONV = false>
-__global__ __launch_bounds__(kThreads) void enc_row_kernel(const RowParams p) {
+__device__ __forceinline__ void enc_row_block(const RowParams p, const uint32_t wg) {
     // The (row, chunk) pairs of the whole operand form one flat index space: a workgroup takes U * 256
     // consecutive chunks.  A row holds a multiple of 16 chunks, so the 4/8/16 lanes of a block never
     // straddle rows; rows need not be a power of two long.
     const uint64_t total = (uint64_t)p.R * (uint64_t)p.chunks;
-    const uint64_t g0 = (uint64_t)blockIdx.x * (kThreads * U) + threadIdx.x;
+    const uint64_t g0 = (uint64_t)wg * (kThreads * U) + threadIdx.x;
     // Long rows (a workgroup's chunks inside one row, the usual case): the row and everything that is a multiple of it
     // stay on the scalar unit and a lane adds 32-bit offsets; the flat 64-bit index space is for the general case.
     // Only stochastic rounding, which is bound by its vector instructions, takes this path (nearest-even rounding
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(kThreads) void enc_row_kernel(const RowParams p) {
     uint64_t wg_row = 0;
     uint32_t wg_cl = 0;
     if (one_row) {
-        const uint64_t gw = (uint64_t)blockIdx.x * (kThreads * U);
+        const uint64_t gw = (uint64_t)wg * (kThreads * U);
         wg_row = p.lpr_log2 >= 0 ? gw >> p.lpr_log2 : gw / (uint64_t)(uint32_t)p.chunks;
         wg_cl = (uint32_t)(gw - wg_row * (uint64_t)(uint32_t)p.chunks);
         if (wg_row >= (uint64_t)p.R) return;         // the grid is rounded up to whole workgroups of four chunks per thread
@@ -337,6 +337,11 @@ __global__ __launch_bounds__(kThreads) void enc_row_kernel(const RowParams p) {
     }
 }
 
+template <int GP, bool WIDE, int ROUND, int U, bool CONV = false>
+__global__ __launch_bounds__(kThreads) void enc_row_kernel(const RowParams p) {
+    enc_row_block<GP, WIDE, ROUND, U, CONV>(p, blockIdx.x);
+}
+
 // 2-D tiles whose k axis is contiguous in the source: a workgroup owns the rblock source rows of one
 // row of tiles and 256 chunk lanes of them.  Pass 1 takes the maximum down the rows in each lane and
 // across the lanes of a block; pass 2 reads the same (cache-resident) rows again and quantises.
@@ -506,7 +511,7 @@ __device__ __forceinline__ void conv_col_gather(const ColParams &p, uint32_t img
 }
 
 template <int KBP, bool WIDE, int ROUND, bool TABLE, bool CONV = false>
-__global__ __launch_bounds__(kThreads) void enc_col_kernel(const ColParams p) {
+__device__ __forceinline__ void enc_col_block(const ColParams p, const uint32_t wg) {
     constexpr int ESZ = WIDE ? 2 : 1;
     constexpr int NBT = kColRowBytes / (KBP * ESZ);  // exponent blocks per tile row: 16, 8, 8 or 4
     __shared__ __attribute__((aligned(16))) uint8_t tile[64 * kColStride];
@@ -515,9 +520,9 @@ __global__ __launch_bounds__(kThreads) void enc_col_kernel(const ColParams p) {
 
     // the wave index as a scalar: block indices, block lengths and (CONV) output positions stay on the scalar unit
     const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
-    const int64_t r = (int64_t)(blockIdx.x % p.row_groups) * p.lanes + lane;
+    const int64_t r = (int64_t)(wg % p.row_groups) * p.lanes + lane;
     const int nbt = NBT >> p.narrow;
-    const int64_t blk0 = (int64_t)(blockIdx.x / p.row_groups) * nbt;
+    const int64_t blk0 = (int64_t)(wg / p.row_groups) * nbt;
     const bool r_ok = lane < p.lanes && r < p.R;
     const int group0 = (lane / p.rblock) * p.rblock;   // first lane of this lane's 2-D tile
     int conv_fr = 0, conv_fs = 0, conv_ch = 0;          // CONV: this lane's filter tap and channel
@@ -601,7 +606,7 @@ __global__ __launch_bounds__(kThreads) void enc_col_kernel(const ColParams p) {
     for (int pass = 0; pass < 8; ++pass) {
         if (pass >= (8 >> p.narrow)) break;                                // uniform
         const int rl = (pass << (3 + p.narrow)) + (t >> (5 - p.narrow));
-        const int64_t rr = (int64_t)(blockIdx.x % p.row_groups) * p.lanes + rl;
+        const int64_t rr = (int64_t)(wg % p.row_groups) * p.lanes + rl;
         if (rl < p.lanes && rr < p.R && piece * 16 < valid_bytes) {
             const uint4 d = *reinterpret_cast<const uint4 *>(tile + rl * kColStride + piece * 16);
             typedef unsigned v4u __attribute__((ext_vector_type(4)));
@@ -621,6 +626,27 @@ __global__ __launch_bounds__(kThreads) void enc_col_kernel(const ColParams p) {
                     *reinterpret_cast<const uint32_t *>(etile + t * NBT + 4 * w);
         }
     }
+}
+
+template <int KBP, bool WIDE, int ROUND, bool TABLE, bool CONV = false>
+__global__ __launch_bounds__(kThreads) void enc_col_kernel(const ColParams p) {
+    enc_col_block<KBP, WIDE, ROUND, TABLE, CONV>(p, blockIdx.x);
+}
+
+// Two conversions in one launch (both operands of hbfp_gemm_f32): each along the rows or down them, blocks stored as 32, at
+// most 8 bits, nearest even.  Workgroups first .. belong to the second.  The parameters go by value: by reference the separate
+// kernels lost 2 % (LSTM gate products 131.4 -> 134.4 us).  256 x 256 twice: 3.9 + 4.0 us and the gap between them -> 5.0 us.
+struct EncPair {
+    RowParams row[2];
+    ColParams col[2];
+    int32_t down[2];             // 1: k runs down the source rows (col)
+    uint32_t first;
+};
+__global__ __launch_bounds__(kThreads) void enc_pair_kernel(const EncPair q) {
+    const int j = blockIdx.x >= q.first ? 1 : 0;
+    const uint32_t wg = blockIdx.x - (j ? q.first : 0u);
+    if (q.down[j]) enc_col_block<32, false, 0, false>(q.col[j], wg);
+    else enc_row_block<4, false, 0, 4>(q.row[j], wg);
 }
 
 // How far a workgroup's share is cut down.  A wave walks its pieces one after the other (about 1.5 us each: 32 strided
@@ -1152,8 +1178,8 @@ int ilog2_ceil(int64_t x) {
 
 }  // namespace
 
-int launch_encode_row_fused(const float *src, const EncodeGeom &g, void *mant, uint8_t *exps, hipStream_t s) {
-    RowParams p;
+// parameters and workgroups of the row kernel (1-D blocks)
+static int row_params(const float *src, const EncodeGeom &g, void *mant, uint8_t *exps, RowParams &p, int64_t &workgroups) {
     p.src = src;
     p.mant = (uint8_t *)mant;
     p.exps = exps;
@@ -1187,6 +1213,15 @@ int launch_encode_row_fused(const float *src, const EncodeGeom &g, void *mant, u
     p.gp = 0;
     p.kshare = 1;
     magic_of((uint32_t)p.chunks, p.dChunks);
+    workgroups = ceil_div(g.R * (int64_t)p.chunks, (int64_t)kThreads * 4);
+    return HBFP_OK;
+}
+
+int launch_encode_row_fused(const float *src, const EncodeGeom &g, void *mant, uint8_t *exps, hipStream_t s) {
+    RowParams p;
+    int64_t workgroups = 0;
+    const int rc = row_params(src, g, mant, exps, p, workgroups);
+    if (rc != HBFP_OK) return rc;
     if (g.rblock > 1) {
         p.nseg = (int32_t)ceil_div(p.chunks, kThreads);
         const int64_t gx = ceil_div(g.R, g.rblock);
@@ -1200,9 +1235,8 @@ int launch_encode_row_fused(const float *src, const EncodeGeom &g, void *mant, u
         else return HBFP_ERR_FORMAT;
         return launch_status();
     }
-    const int64_t gx = ceil_div(g.R * (int64_t)p.chunks, (int64_t)kThreads * 4);
-    if (gx > 0x3fffffff) return HBFP_ERR_ARG;                            // the stochastic-rounding launch doubles the grid
-    const dim3 grid((unsigned)gx);
+    if (workgroups > 0x3fffffff) return HBFP_ERR_ARG;                    // the stochastic-rounding launch doubles the grid
+    const dim3 grid((unsigned)workgroups);
     const bool wide = g.m > 8;
     if (g.kbp == 32) launch_row_g<4>(p, grid, wide, g.rounding, s);
     else if (g.kbp == 64) launch_row_g<8>(p, grid, wide, g.rounding, s);
@@ -1347,8 +1381,8 @@ int launch_encode_im2col(const float *x, const hbfp_conv2d &c, int64_t ho, int64
     return launch_status();
 }
 
-int launch_encode_col_fused(const float *src, const EncodeGeom &g, void *mant, uint8_t *exps, hipStream_t s) {
-    ColParams p;
+// parameters and workgroups of the column kernel
+static int col_params(const float *src, const EncodeGeom &g, void *mant, uint8_t *exps, ColParams &p, int64_t &workgroups) {
     p.src = src;
     p.mant = (uint8_t *)mant;
     p.exps = exps;
@@ -1382,10 +1416,46 @@ int launch_encode_col_fused(const float *src, const EncodeGeom &g, void *mant, u
     const int64_t gy = ceil_div(nb_cover, nbt >> p.narrow);
     if (gx > 0x7fffffff || gx * gy > 0x7fffffff) return HBFP_ERR_ARG;
     p.row_groups = (uint32_t)gx;
-    const dim3 grid((unsigned)(gx * gy));
+    workgroups = gx * gy;
+    return HBFP_OK;
+}
+
+int launch_encode_col_fused(const float *src, const EncodeGeom &g, void *mant, uint8_t *exps, hipStream_t s) {
+    ColParams p;
+    int64_t workgroups = 0;
+    const int rc = col_params(src, g, mant, exps, p, workgroups);
+    if (rc != HBFP_OK) return rc;
+    const bool wide = g.m > 8;
+    const dim3 grid((unsigned)workgroups);
     if (g.kbp == 32) launch_col_k<32>(p, grid, wide, g.rounding, s);
     else if (g.kbp == 64) launch_col_k<64>(p, grid, wide, g.rounding, s);
     else return HBFP_ERR_FORMAT;
+    return launch_status();
+}
+
+// Two conversions in one launch: each takes a launch's time (about 3 us) out of the product.  A product of FP32 operands, two
+// conversions against one: 256 x 256 x 256 11.2 -> 8.0 us, 1024 x 1024 x 1024 29.2 -> 25.6, 2048 x 2048 x 2048 46.5 -> 44.0,
+// 512 x 512 x 16384 47.6 -> 44.9, 64 x 8192 x 4096 (33 Mi values) 59.2 -> 56.3, each with both directions alike.  The line lies
+// where the measurements end: past 32 Mi values the row kernel is bound by memory, and the LDS that the column kernel's tile claims
+// for every workgroup here halves the waves it can keep in flight.
+bool encode_pair_ok(const EncodeGeom &a, const EncodeGeom &b) {
+    for (const EncodeGeom *g : {&a, &b})
+        if (g->rblock != 1 || g->kbp != 32 || g->kshare != 1 || g->m > 8 || g->rounding != 0) return false;
+    return a.R * a.kpad + b.R * b.kpad <= (int64_t)32 << 20;
+}
+
+int launch_encode_pair(const float *const *src, const EncodeGeom *g, void *const *mant, uint8_t *const *exps, hipStream_t s) {
+    if (!encode_pair_ok(g[0], g[1])) return HBFP_ERR_FORMAT;
+    EncPair q = {};
+    int64_t workgroups[2];
+    for (int i = 0; i < 2; ++i) {
+        q.down[i] = g[i].axis == 0;
+        const int rc = q.down[i] ? col_params(src[i], g[i], mant[i], exps[i], q.col[i], workgroups[i])
+                                 : row_params(src[i], g[i], mant[i], exps[i], q.row[i], workgroups[i]);
+        if (rc != HBFP_OK) return rc;
+    }
+    q.first = (uint32_t)workgroups[0];
+    hipLaunchKernelGGL(enc_pair_kernel, dim3((unsigned)(workgroups[0] + workgroups[1])), dim3(kThreads), 0, s, q);
     return launch_status();
 }
 

@@ -42,6 +42,9 @@ struct EncodeGeom {
 // encode.hip
 int launch_encode_row_fused(const float *src, const EncodeGeom &g, void *mant, uint8_t *exps, hipStream_t s);
 int launch_encode_col_fused(const float *src, const EncodeGeom &g, void *mant, uint8_t *exps, hipStream_t s);
+// both sources in one launch: small matrices, 1-D blocks stored as 32, at most 8 bits, round to nearest
+bool encode_pair_ok(const EncodeGeom &a, const EncodeGeom &b);
+int launch_encode_pair(const float *const *src, const EncodeGeom *g, void *const *mant, uint8_t *const *exps, hipStream_t s);
 int launch_encode_im2col(const float *x, const hbfp_conv2d &c, int64_t ho, int64_t wo, const EncodeGeom &g, void *mant,
                          uint8_t *exps, uint32_t *table, hipStream_t s);
 int launch_encode_generic(const float *src, const EncodeGeom &g, void *mant, uint8_t *exps,

@@ -1540,3 +1540,25 @@ def test_config3_data_gradient_without_col2im_full_size(hb):
     np.testing.assert_array_equal(mant, oa.mant)
     rows = np.sort(np.random.default_rng(8).choice(100352, size=64, replace=False))
     assert rel_fro(dx.cpu().numpy()[rows], ref.gemm(ref.decode(oa), ref.decode(ob), rows=rows)) <= TOL
+
+
+@pytest.mark.parametrize("M,N,K,block,pad", [(1, 1, 1, 32, 0), (3, 70, 25, 24, 1), (65, 17, 700, 24, 3), (256, 256, 256, 32, 0),
+                                             (130, 257, 1031, 17, 5), (4096, 5000, 4000, 32, 0)])
+@pytest.mark.parametrize("trans_a,trans_b", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_gemm_f32_converts_both_operands(hb, M, N, K, block, pad, trans_a, trans_b):
+    """hbfp_gemm_f32 converts the operands in one launch up to 32 Mi stored values and in two beyond (the last size): in both the
+    product has the bits of the operands converted one by one, also for row strides that leave rows off 16 bytes."""
+    print(f"[case] gemm_f32 {M}x{N}x{K} block {block} pad {pad} {trans_a}{trans_b}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+
+    def source(rows, cols):
+        x = torch.randn((rows, cols + pad), generator=gen, device="cuda")
+        x *= torch.exp2(torch.randint(-20, 20, (rows, 1), generator=gen, device="cuda").float())
+        return x[:, :cols]
+
+    A, B = source(*((K, M) if trans_a else (M, K))), source(*((N, K) if trans_b else (K, N)))
+    fa = hb.make_format(8, *((block, 1) if trans_a else (1, block)))
+    fb = hb.make_format(5, *((1, block) if trans_b else (block, 1)))
+    got = hb.gemm_f32(trans_a, trans_b, A, B, fa, fb)
+    want = hb.gemm(hb.encode(A, 0 if trans_a else 1, fa), hb.encode(B, 1 if trans_b else 0, fb))
+    assert torch.equal(got.view(torch.int32), want.view(torch.int32))

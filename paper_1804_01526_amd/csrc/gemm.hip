@@ -1559,11 +1559,12 @@ int launch_gemm_i8(const GemmArgs &a, void *workspace, hipStream_t s, const hbfp
             uint8_t *w = (uint8_t *)workspace + split_bytes(a.M, a.N, p.splits);
             q.wA = (const uint32_t *)w;
             q.wB = (const uint32_t *)(w + word_bytes(a.M, a.expA_ld));
-            // Scale words inside the kernel (EB): measured words -> bytes 1000 x 4096 x 1024 18.9 -> 16.8 us, 100352 x 128 x 1152
-            // 64.8 -> 59.4, 8192 x 4096 x 1024 102.9 -> 95.7; from about 2^15 tile stages of 128 on the launch is the cheaper
-            // part (4096^3 in blocks of 24: 196 and 200 us, 6144 x 4096 x 4096: 278 and 295).  The converting epilogue exists
-            // with bytes only.
-            const bool bytes = p.spb == 1 && !a.words_ready && (enc || tm * tn * p.nstage <= (1 << 15));
+            // Scale words inside the kernel (EB): measured words -> bytes 1000 x 4096 x 1024 18.9 -> 16.8 us, 1024 x 2048 x 4096 in
+            // blocks of 24 42.3 -> 41.2, 100352 x 128 x 1152 52.7 -> 47.4, 4096 x 4096 x 1024 (8192 tile stages of 128) 45.2 -> 44.3.
+            // Beyond that the launch is the cheaper part: level at 11 000 tile stages (2048 x 2048 x 4096 in blocks of 24 60.9 and
+            // 61.2, 4096 x 2048 x 2048 54.6 and 54.6), 146 -> 152 at 32 768 (4096^3).  The converting epilogue exists with bytes
+            // only.
+            const bool bytes = p.spb == 1 && !a.words_ready && (enc || tm * tn * p.nstage <= (10 << 10));
             if (!a.words_ready && !bytes) {
                 rc = launch_scale_words(a.expA, a.expA_ld, a.M, a.expB, a.expB_ld, a.N, (int)a.expA_ld, 0x40u,
                                         const_cast<uint32_t *>(q.wA), const_cast<uint32_t *>(q.wB), a.run_a, a.run_b, s);

@@ -450,14 +450,16 @@ int hbfp_gemm_batch(int n, const hbfp_tensor *const *A, const hbfp_tensor *const
  * the FP -> BFP conversion of Sec. 4.1 (with the rounding of Sec. 5.3 that `out` names) applied where the product
  * is produced, so that the next product's operand never makes the trip through an FP32 matrix in memory.
  *   out      planned with hbfp_plan for a source matrix of A->rows x B->rows (either contraction axis, any format);
- *            out->mant / out->exps device, written; stochastic rounding draws by position in the product matrix
+ *            out->mant / out->exps device, written; stochastic rounding draws by position in the product matrix.  Its
+ *            buffers may lie over those of A or B (a layer's input replaced by its output)
  *   relu     0 or 1: max(x, 0) on the FP32 values before the conversion (the one floating-point operation between two
  *            products that needs no other operand)
  *   kernel   HBFP_KERNEL_* as for hbfp_gemm_select
  * The result equals hbfp_gemm_select followed by hbfp_encode of its output, bit for bit.  When the bf16 or the block-scaled
  * kernel computes the product and out has k along the columns of the product in blocks of 32 or 64 (one exponent per block
  * and row), the kernel converts its accumulators itself; so do the int8 kernels on operands in blocks of at most 32 for
- * mantissas of at most 8 bits in blocks of 32.  Otherwise the FP32 product goes through the workspace.
+ * mantissas of at most 8 bits in blocks of 32, unless out lies over an operand.  Otherwise the FP32 product goes through
+ * the workspace.
  *   workspace  hbfp_gemm_bfp_workspace bytes (includes A->rows * B->rows floats), 256-byte aligned
  * Errors: as hbfp_gemm_select; HBFP_ERR_LAYOUT if out is not the plan of an A->rows x B->rows matrix.
  */

@@ -152,6 +152,16 @@ GemmArgs gemm_args(const hbfp_tensor *A, const hbfp_tensor *B) {
     return g;
 }
 
+bool ranges_overlap(const void *p, uint64_t np, const void *q, uint64_t nq) {
+    return (uintptr_t)p < (uintptr_t)q + nq && (uintptr_t)q < (uintptr_t)p + np;
+}
+// whether a buffer of `out` shares bytes with a buffer of `in`: a kernel that stores `out` tile by tile while other workgroups
+// still read `in` must then not run
+bool operands_overlap(const hbfp_tensor &out, const hbfp_tensor &in) {
+    return ranges_overlap(out.mant, out.mant_bytes, in.mant, in.mant_bytes) || ranges_overlap(out.mant, out.mant_bytes, in.exps, in.exp_bytes) ||
+           ranges_overlap(out.exps, out.exp_bytes, in.mant, in.mant_bytes) || ranges_overlap(out.exps, out.exp_bytes, in.exps, in.exp_bytes);
+}
+
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // the caller expects marked operands: prepare the 8-wave int8 kernel as the stand-by of the block-scaled product
@@ -1028,11 +1038,12 @@ int hbfp_gemm_bfp(const hbfp_tensor *A, const hbfp_tensor *B, const hbfp_tensor 
     char *ws_gemm = (char *)workspace + part[0], *ws_enc = ws_gemm + part[1];
     const int64_t M = A->rows, N = B->rows;
     if (!fused) {
-        // a product that run_gemm would hand to the int8 kernels, delivered by them where the output's format allows it
+        // a product that run_gemm would hand to the int8 kernels, delivered by them where the output's format allows it and
+        // `out` does not lie over an operand (they read the stored operands until the end; the FP32 product below waits for them)
         const GemmArgs g = gemm_args(A, B);
         const bool int8 = (kernel == HBFP_KERNEL_AUTO || kernel == HBFP_KERNEL_INT8) && !use_bf(g, kernel) && !use_f16_planes(g, kernel) &&
                           !use_scaled(g, kernel);
-        if (int8 && gemm_i8_encoded_output_ok(g, *out))
+        if (int8 && gemm_i8_encoded_output_ok(g, *out) && !operands_overlap(*out, *A) && !operands_overlap(*out, *B))
             return kernel == HBFP_KERNEL_AUTO && gemm_small_ok(g) ? launch_gemm_small(g, s, out, relu) : launch_gemm_i8(g, ws_gemm, s, out, relu);
         rc = run_gemm(A, B, C, N, 0.0f, nullptr, kernel, ws_gemm, part[1], stream);
         if (rc == HBFP_OK && relu) rc = launch_relu(C, M * N, s);

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from oracle import ref
-from tests.util import random_cases, rel_fro, unpack
+from tests.util import launched_kernels, random_cases, rel_fro, unpack
 
 pytestmark = pytest.mark.gpu
 TOL = 1e-5
@@ -1562,3 +1562,33 @@ def test_gemm_f32_converts_both_operands(hb, M, N, K, block, pad, trans_a, trans
     got = hb.gemm_f32(trans_a, trans_b, A, B, fa, fb)
     want = hb.gemm(hb.encode(A, 0 if trans_a else 1, fa), hb.encode(B, 1 if trans_b else 0, fb))
     assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+
+
+@pytest.mark.parametrize("M,K,kernel", [(70, 96, 0), (256, 256, 0), (256, 256, 1), (1000, 512, 1), (130, 2048, 1)])
+@pytest.mark.parametrize("over", ["A", "B"])
+def test_gemm_bfp_over_its_own_operand(hb, M, K, kernel, over):
+    """The encoded product stored over an operand of the product (a square layer in place): few rows, one launch of the tile
+    kernel, split along k.  Same bytes as into buffers of its own, and the product has ended before the first store."""
+    print(f"[case] in place over {over}: {M}x{K}x{K} kernel={kernel}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(M + K)
+    if over == "B":
+        M = K                                                        # B holds K x K, as the product must
+    X, W = torch.randn((M, K), generator=gen, device="cuda"), torch.randn((K, K), generator=gen, device="cuda")
+    fx, fw = hb.make_format(8, 1, 32), hb.make_format(8, 32, 1)
+    x, w = hb.encode(X, 1, fx), hb.encode(W, 0, fw)
+    want = hb.gemm_bfp(x, w, fx, 1, relu=True, kernel=kernel)
+    kept = [t.clone() for t in (x.mant, x.exps, w.mant, w.exps)]
+    target = x if over == "A" else w
+    desc = hb.plan(fx, M, K, 1)
+    desc.mant, desc.exps = target.mant.data_ptr(), target.exps.data_ptr()
+    out = hb.BfpTensor(desc, target.mant, target.exps)
+
+    def call():
+        for t, k in zip((x.mant, x.exps, w.mant, w.exps), kept):
+            t.copy_(k)
+        hb.gemm_bfp(x, w, fx, 1, relu=True, kernel=kernel, out=out)
+
+    names = launched_kernels(call)
+    assert torch.equal(out.mant, want.mant) and torch.equal(out.exps, want.exps)
+    assert names[-1].startswith("enc_") and not any(n in ("gemm_small_kernel<1, true>", "gemm_small_kernel<2, true>") or
+                                                    n.startswith("gemm_i8_w8_kernel<1, false, false, 0, true") for n in names), names

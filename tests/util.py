@@ -44,3 +44,19 @@ def rel_fro(got, want):
     got = np.asarray(got, dtype=np.float64)
     want = np.asarray(want, dtype=np.float64)
     return float(np.linalg.norm(got - want) / max(np.linalg.norm(want), 1e-300))
+
+
+def launched_kernels(call):
+    """The names of the kernels that `call` launches, in their order, without namespaces and parameters
+    ("gemm_small_kernel<1, false>"): which route a rule on sizes took."""
+    import re
+
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    call()                                       # what a first call sets up is not part of the trace
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as trace:
+        call()
+        torch.cuda.synchronize()
+    names = [e for e in sorted(trace.events(), key=lambda e: e.time_range.start) if "_kernel" in e.name]
+    return [re.sub(r"\(anonymous namespace\)::|hbfp::|^void ", "", e.name).split("(")[0] for e in names]

@@ -294,7 +294,9 @@ int hbfp_gemm_conv2d(const hbfp_tensor *image, const hbfp_conv2d *conv, const hb
  * times the bytes, is neither written nor read back, and the next layer needs no conversion call.  Any other output
  * format: the FP32 product in the workspace, then the conversion kernels.  Either way the bytes are those of
  * hbfp_encode on the FP32 result of hbfp_gemm_conv2d.
- *   out    planned and allocated by the caller (hbfp_plan: rows n*ho*wo, columns filters)
+ *   out    planned and allocated by the caller (hbfp_plan: rows n*ho*wo, columns filters).  Its buffers may lie over those of
+ *          the image or the filters; the FP32 product then goes through the workspace, whose size depends on the buffers:
+ *          ask for it with the descriptors of the call (a query without buffers reserves for an image replaced in place)
  *   relu   0 or 1
  *   workspace  hbfp_gemm_conv2d_bfp_workspace bytes, 256-byte aligned
  * Errors: as hbfp_gemm_conv2d; HBFP_ERR_LAYOUT if `out` has another shape.

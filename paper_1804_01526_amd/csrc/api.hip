@@ -594,7 +594,11 @@ static int conv_bfp_plan(const hbfp_tensor *image, const hbfp_conv2d *conv, cons
     if (rc != HBFP_OK) return rc;
     const int64_t M = conv->n * *ho * *wo, N = filters->rows;
     if (out->src_rows != M || out->src_cols != N) return HBFP_ERR_LAYOUT;
-    *fused = conv_encoded_output_ok(M, N, filters->kpad, *out) && !conv_runs(image, conv, filters, *slot_order);
+    // `out` over the image (or the filters): the gathering kernel must have finished before anything is stored.  A query on
+    // descriptors without buffers reserves for that where the two have the same size.
+    const bool in_place = out->mant && image->mant ? operands_overlap(*out, *image) : out->mant_bytes == image->mant_bytes;
+    const bool over_filters = out->mant && filters->mant && operands_overlap(*out, *filters);
+    *fused = conv_encoded_output_ok(M, N, filters->kpad, *out) && !conv_runs(image, conv, filters, *slot_order) && !in_place && !over_filters;
     part[0] = *fused ? 0 : align256((size_t)M * (size_t)N * 4);
     part[1] = align256(gemm_conv_workspace(M, N, filters->kpad, image->rows, (int)(conv->c / image->kblock)));
     size_t enc = 0;

@@ -527,3 +527,26 @@ def test_encode_multi_validation():
     arr2 = (T * 2)(ctypes.pointer(a), ctypes.pointer(big))
     assert lib.hbfp_encode_multi_workspace(2, arr2, ctypes.byref(n)) == hbfp.OK and n.value > 0
     assert lib.hbfp_encode_multi(fake, 200, 2, arr2, None, 0, None) == hbfp.ERR_WORKSPACE
+
+
+def test_conv2d_bfp_workspace_sees_an_output_over_its_image():
+    """The product kernel stores its encoded output while other workgroups still gather the image, so an output that lies over the
+    image (or the filters) needs the FP32 product in the workspace."""
+    conv = hbfp.Conv2d(16, 28, 28, 64, 3, 3, 1, 1, 1, 1, 0, 0)
+    act = hbfp.make_format(8, 1, 32)
+
+    def image(mant, exps):
+        d = hbfp.plan(act, 16 * 28 * 28, 64, 1)
+        d.mant, d.exps = mant, exps
+        return d
+
+    flt = hbfp.plan(hbfp.make_format(8, 32, 1), 9 * 64, 64, 0)
+    flt.mant, flt.exps = 0x10000000, 0x20000000
+    img = image(0x30000000, 0x40000000)
+    apart = hbfp.gemm_conv2d_bfp_workspace(img, conv, flt, image(0x50000000, 0x60000000))
+    c_bytes = 16 * 28 * 28 * 64 * 4
+    for out in (image(0x30000000, 0x40000000), image(0x30000100, 0x60000000), image(0x50000000, 0x40000004),
+                image(0x10000000, 0x60000000), image(0x50000000, 0x20000000)):
+        assert hbfp.gemm_conv2d_bfp_workspace(img, conv, flt, out) == apart + c_bytes
+    assert hbfp.gemm_conv2d_bfp_workspace(image(0, 0), conv, flt, image(0, 0)) == apart + c_bytes
+    assert hbfp.gemm_conv2d_bfp_workspace(img, conv, flt, image(0x30000000 + img.mant_bytes, 0x60000000)) == apart

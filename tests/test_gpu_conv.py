@@ -482,3 +482,20 @@ def test_conv_rejects_what_it_does_not_cover(hb):
     assert hb._lib.hbfp_gemm_conv2d(ctypes.byref(img.desc), ctypes.byref(conv), ctypes.byref(flt.desc), y.data_ptr(), 16, 0.0,
                                     None, 0, None) == hb.ERR_WORKSPACE
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("n,h,w,c,r", [(1, 7, 9, 32, 3), (2, 20, 20, 64, 3), (16, 28, 28, 64, 3), (4, 14, 14, 128, 1)])
+def test_conv_bfp_over_its_own_image(hb, n, h, w, c, r):
+    """The encoded convolution stored over the image it reads (a residual block's layer in place): same bytes as into buffers
+    of its own.  The workspace query sees the overlap."""
+    print(f"[conv bfp in place] {n}x{h}x{w}x{c} r={r}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n + c)
+    conv = hb.Conv2d(n, h, w, c, r, r, r // 2, r // 2, 1, 1, 0, 0)
+    act = hb.make_format(8, 1, 32)
+    img = hb.encode(torch.randn((n * h * w, c), generator=gen, device="cuda"), 1, act)
+    flt = hb.encode(torch.randn((r * r * c, c), generator=gen, device="cuda") * 0.1, 0, hb.make_format(8, 32, 1))
+    want = hb.gemm_conv2d_bfp(img, conv, flt, act, relu=True)
+    assert hb.gemm_conv2d_bfp_workspace(img.desc, conv, flt.desc, img.desc) >= 4 * n * h * w * c
+    hb.gemm_conv2d_bfp(img, conv, flt, act, relu=True, out=img)
+    torch.cuda.synchronize()
+    assert torch.equal(img.mant, want.mant) and torch.equal(img.exps, want.exps)

@@ -1090,24 +1090,32 @@ int launch_t(const GemmParams &p, dim3 grid, hipStream_t s) {
 
 }  // namespace
 
+// What a k-step of 32 takes when the fullest XCD has `wgs` workgroups for its 32 compute units of two places each: the slowest
+// compute unit sets the pace, so the 33rd workgroup costs as much as the 64th would; a few more than fit start late.
+static double k_step_us(int64_t wgs) { return wgs <= 32 ? 0.30 : wgs <= 64 ? 0.45 : 0.65; }
+
 // Split K when the tile grid alone cannot fill the chip (the weight-gradient shape: small M x N, very long K).  Pure function
-// of the shapes so that the workspace query agrees.  The number of k ranges with the smallest estimate: a k-step of 32
-// takes 0.32 us for a workgroup that has its compute unit to itself, 0.54 us for one of two that share it, and the slices are
-// written and read back at about 4 TB/s behind 3 us for the second launch.  (Twice as many ranges as fill the chip once, the
-// rule before, cost 1000 x 1024 x 4096 32.6 us against 27.3 us with 4, 1500^3 30.9 us against 23.7 us unsplit.)
+// of the shapes so that the workspace query agrees.  The number of k ranges with the smallest estimate: the k-steps above on
+// the fullest XCD (up to 7 ranges: the tiles are dealt to the 8 XCDs, every XCD has all ranges of its tiles; from 8 on the
+// ranges are dealt, every XCD has all tiles of its ranges), and the slices written and read back at about 3 TB/s behind 3 us
+// for the second launch.  Fitted to 179 shapes with up to 14 range counts each (int8 in blocks of 16 to 256 and FP16):
+// 6 % behind the best count on average, 8 % before with as many ranges as fill the chip twice (1000 x 1024 x 4096 32.6 -> 27.3
+// us with 4, 1500^3 30.9 -> 23.7 us unsplit).  A count of workgroups for the whole chip instead of the fullest XCD, with half
+// a tile's columns as half a workgroup, put 33 to 40 on an XCD: 3836 x 143 x 11614 in blocks of 24 57 against 40 us with 8,
+// 239 x 3244 x 10764 in blocks of 16 77 against 58 us.
 static int choose_splits(int64_t M, int64_t N, int64_t nstage, int64_t stages_per_block, double *estimate = nullptr) {
     const int64_t tiles = ceil_div(M, BM) * ceil_div(N, BN);
     const int64_t units = nstage / stages_per_block;   // whole exponent blocks (or stages) that can be dealt out
-    if (estimate) *estimate = (double)nstage * 4 * (tiles <= 256 ? 0.32 : 0.54 * (double)tiles / 512.0 > 0.32 ? 0.54 * (double)tiles / 512.0 : 0.32);
+    if (estimate) *estimate = (double)nstage * 4 * (tiles <= 512 ? k_step_us(ceil_div(tiles, 8)) : 0.45 * (double)tiles / 512.0);
     if (tiles >= 256 || units < 8) return 1;
-    // half a tile's worth of columns is half the work: its other waves only copy
-    const double work = 0.5 * (double)(ceil_div(M, BM) * ceil_div(N, 64));
     double best = 0.0;
     int splits = 1;
-    for (int s = 1; s <= 128 && s <= units / 4 && (s == 1 || work * s <= 512.0); ++s) {
+    for (int s = 1; s <= 128 && s <= units / 4; ++s) {
         if (s > 8 && s % 8) continue;                  // the k ranges are dealt to the 8 XCDs in turn: keep them level
+        const int64_t wgs = s < 8 ? ceil_div(tiles, 8) * s : tiles * ceil_div(s, 8);
+        if (s > 1 && wgs > 72) break;
         const double steps = (double)(ceil_div(units, s) * stages_per_block * 4);
-        const double us = steps * (work * s <= 256.0 ? 0.32 : 0.54) + (s > 1 ? 3.0 + (double)(s + 1) * (double)(M * N) * 4e-6 / 4.0 : 0.0);
+        const double us = steps * k_step_us(wgs) + (s > 1 ? 3.0 + (double)(s + 1) * (double)(M * N) * 4e-6 / 3.0 : 0.0);
         if (s == 1 || us < best) best = us, splits = s;
     }
     if (estimate) *estimate = best;

@@ -550,3 +550,22 @@ def test_conv2d_bfp_workspace_sees_an_output_over_its_image():
         assert hbfp.gemm_conv2d_bfp_workspace(img, conv, flt, out) == apart + c_bytes
     assert hbfp.gemm_conv2d_bfp_workspace(image(0, 0), conv, flt, image(0, 0)) == apart + c_bytes
     assert hbfp.gemm_conv2d_bfp_workspace(img, conv, flt, image(0x30000000 + img.mant_bytes, 0x60000000)) == apart
+
+
+@pytest.mark.parametrize("M,N,K,m,blk,slices", [
+    # (fastest measured count; us with it against the count that a rule without a look at the single XCD takes)
+    (3836, 143, 11614, 8, 24, 8),       # 60 tiles: 40 us, 57 with 5
+    (239, 3244, 10764, 8, 16, 8),       # 52 tiles: 58 us, 77 with 5
+    (799, 792, 8550, 12, 32, 8),        # FP16 kernel, 49 tiles: 51 us, 62 with 5
+    (1396, 338, 49536, 12, 64, 16),     # FP16 kernel, 33 tiles: 167 us, 227 with 7
+    (697, 848, 9984, 8, 32, 5),         # 42 tiles: 32 us, 39 with 6
+    (1500, 1500, 1500, 8, 32, 1),       # unsplit: 24 us, 31 with 3
+])
+def test_slices_of_products_split_along_k(M, N, K, m, blk, slices):
+    """The number of FP32 slices in the workspace of a product split along k: no count that puts a few workgroups more on one of
+    the 8 XCDs than it has compute units, because those few then set the pace of the whole product."""
+    a, b = hbfp.plan(hbfp.make_format(m, 1, blk), M, K, 1), hbfp.plan(hbfp.make_format(m, blk, 1), K, N, 0)
+    words = sum(-(-r // 128) * 128 * a.exp_ld * 4 for r in (M, N))
+    planes = sum(-(-r * a.kpad * 2 // 256) * 256 for r in (M, N)) if m > 8 else 0
+    got = hbfp.gemm_select_workspace(a, b, hbfp.KERNEL_INT8 if m <= 8 else hbfp.KERNEL_FP16) - words - planes
+    assert got // (4 * M * N) == (slices if slices > 1 else 0)

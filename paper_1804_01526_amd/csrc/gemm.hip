@@ -1000,22 +1000,44 @@ __global__ __launch_bounds__(kThreads) void splitk_reduce_kernel(const float *pa
 }
 
 // The same sum delivered as an encoded operand: ReLU if asked for, then the conversion of Sec. 4.1 with blocks of 32 along the
-// columns of C, as converting the summed FP32 product would give it.  A thread owns four columns of a row, 8 lanes a block.
-template <int ROUND>
+// columns of C, as converting the summed FP32 product would give it.  A thread owns W columns of a row, 32 / W neighbouring
+// lanes a block.  W = 1, for ragged rows (N no multiple of 4) of 4 and more slices, is bound by the latency of its loads and
+// requests 16 slices, then 8, at a time.  Four columns a thread, read one by one in such a row, left it to wait for every
+// slice: whole calls 17 x 102 x 11401 24.7 -> 12.9 us, 2643 x 73 x 14992 44.8 -> 31.1 (18.6 and 40.5 as product, ReLU and
+// conversion one by one), 800 x 1201 x 5000 38.0 -> 34.8; behind with 2 or 3 slices (1200 x 1001 x 4000 28.4 and 30.0 us).
+template <int ROUND, int W>
 __global__ __launch_bounds__(kThreads) void splitk_reduce_encode_kernel(const float *partial, int64_t M, int64_t N, int splits, const W8Enc o) {
-    const uint32_t quads = (uint32_t)(o.kpad / 4);                  // a multiple of 32: the 8 lanes of a block stay together
+    const uint32_t per_row = (uint32_t)(o.kpad / W);                // a multiple of 32: the lanes of a block stay together
     const int64_t n = M * N;
-    for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < M * quads; e += (int64_t)gridDim.x * kThreads) {
-        const int64_t row = M * quads < ((int64_t)1 << 31) ? (int64_t)((uint32_t)e / quads) : e / quads;
-        const int64_t col = (e - row * quads) * 4;
-        const int left = N - col >= 4 ? 4 : (N - col > 0 ? (int)(N - col) : 0);
+    for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < M * per_row; e += (int64_t)gridDim.x * kThreads) {
+        const int64_t row = M * per_row < ((int64_t)1 << 31) ? (int64_t)((uint32_t)e / per_row) : e / per_row;
+        const int64_t col = (e - row * per_row) * W;
+        const int left = N - col >= W ? W : (N - col > 0 ? (int)(N - col) : 0);
         const float *src = partial + row * N + col;
-        float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (left == 4 && N % 4 == 0) {
+        float x[W] = {};
+        if (W == 1 && left) {
+            int z = 0;
+            for (; z + 16 <= splits; z += 16) {
+                float t[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) t[u] = src[(int64_t)(z + u) * n];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) x[0] += t[u];
+            }
+            for (; z < splits; z += 8) {
+                float t[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (z + u < splits) t[u] = src[(int64_t)(z + u) * n];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (z + u < splits) x[0] += t[u];
+            }
+        } else if (W == 4 && left == 4 && N % 4 == 0) {
 #pragma unroll 8
             for (int z = 0; z < splits; ++z) {
                 const float4 d = *reinterpret_cast<const float4 *>(src + (int64_t)z * n);
-                x[0] += d.x, x[1] += d.y, x[2] += d.z, x[3] += d.w;
+                x[0] += d.x, x[1 % W] += d.y, x[2 % W] += d.z, x[3 % W] += d.w;
             }
         } else {
             for (int z = 0; z < splits; ++z)
@@ -1023,31 +1045,34 @@ __global__ __launch_bounds__(kThreads) void splitk_reduce_encode_kernel(const fl
         }
         uint32_t amax = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < W; ++i) {
             if (o.relu && x[i] < 0.0f) x[i] = 0.0f;
             amax = max(amax, __float_as_uint(x[i]) & 0x7fffffffu);
         }
-        amax = max(amax, (uint32_t)__shfl_xor((int)amax, 1));
-        amax = max(amax, (uint32_t)__shfl_xor((int)amax, 2));
-        amax = max(amax, (uint32_t)__shfl_xor((int)amax, 4));
+#pragma unroll
+        for (int d = 1; d < 32 / W; d *= 2) amax = max(amax, (uint32_t)__shfl_xor((int)amax, d));
         const uint32_t Eb = block_exponent<ROUND>(amax, o.m);
         uint32_t w = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < W; ++i) {
             const uint64_t idx = (uint64_t)row * (uint64_t)N + (uint64_t)(col + i);
             w |= ((uint32_t)quantise<ROUND>(x[i], Eb, o.m, (uint32_t)idx, (uint32_t)(idx >> 32), o.s0, o.s1) & 0xffu) << (8 * i);
         }
-        *reinterpret_cast<uint32_t *>(o.mant + row * o.kpad + col) = w;
+        uint8_t *dst = o.mant + row * o.kpad + col;
+        if (W == 4) *reinterpret_cast<uint32_t *>(dst) = w;
+        else *dst = (uint8_t)w;
         const int64_t b = col >> 5;
         if ((col & 31) == 0 && b < o.exp_ld) o.exps[row * o.exp_ld + b] = b < o.nblk ? (uint8_t)Eb : (uint8_t)1;
     }
 }
 
 int launch_splitk_reduce_encode(const GemmParams &p, const W8Enc &o, hipStream_t s) {
-    int64_t nb = ceil_div(p.M * (o.kpad / 4), kThreads);
+    const int w = p.N % 4 && p.splits >= 4 ? 1 : 4;
+    int64_t nb = ceil_div(p.M * (o.kpad / w), kThreads);
     if (nb > 8192) nb = 8192;
-    if (o.rounding) hipLaunchKernelGGL(splitk_reduce_encode_kernel<1>, dim3((unsigned)nb), dim3(kThreads), 0, s, p.partial, p.M, p.N, p.splits, o);
-    else hipLaunchKernelGGL(splitk_reduce_encode_kernel<0>, dim3((unsigned)nb), dim3(kThreads), 0, s, p.partial, p.M, p.N, p.splits, o);
+    const auto kernel = w == 1 ? (o.rounding ? splitk_reduce_encode_kernel<1, 1> : splitk_reduce_encode_kernel<0, 1>)
+                               : (o.rounding ? splitk_reduce_encode_kernel<1, 4> : splitk_reduce_encode_kernel<0, 4>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(kThreads), 0, s, p.partial, p.M, p.N, p.splits, o);
     return launch_status();
 }
 

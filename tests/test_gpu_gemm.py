@@ -1592,3 +1592,43 @@ def test_gemm_bfp_over_its_own_operand(hb, M, K, kernel, over):
     assert torch.equal(out.mant, want.mant) and torch.equal(out.exps, want.exps)
     assert names[-1].startswith("enc_") and not any(n in ("gemm_small_kernel<1, true>", "gemm_small_kernel<2, true>") or
                                                     n.startswith("gemm_i8_w8_kernel<1, false, false, 0, true") for n in names), names
+
+
+@pytest.mark.parametrize("M,N,K,blk", [(17, 102, 11401, 24), (49, 263, 12511, 24), (1335, 45, 14217, 24)])
+def test_encoded_slice_sum_is_no_slower_than_separate_calls(hb, M, N, K, blk):
+    """An int8 product of few columns, split along k, delivered encoded: not slower than product, ReLU and conversion one by one
+    (rows that leave 16 bytes once took a third longer).  Replayed from graphs; a seventh of margin."""
+    fx, fw, fo = hb.make_format(8, 1, blk), hb.make_format(8, blk, 1), hb.make_format(8, 1, 32)
+    x, w = hb.encode(torch.randn((M, K), device="cuda"), 1, fx), hb.encode(torch.randn((K, N), device="cuda"), 0, fw)
+    out, C = hb.alloc(fo, M, N, 1), torch.empty((M, N), device="cuda")
+    ws = torch.empty(hb.gemm_bfp_workspace(x.desc, w.desc, out.desc, 1), dtype=torch.uint8, device="cuda")
+
+    def separate():
+        hb.gemm(x, w, out=C, kernel=1, workspace=ws)
+        hb.encode(torch.relu_(C), 1, fo, out=out)
+
+    def fastest(call):
+        call()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                call()
+        times = []
+        for _ in range(10):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            graph.replay()
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    both = fastest(separate)
+    want = out.mant.clone(), out.exps.clone()
+    out.mant.fill_(85)
+    out.exps.fill_(85)
+    one = fastest(lambda: hb.gemm_bfp(x, w, fo, 1, relu=True, kernel=1, out=out, workspace=ws))
+    assert torch.equal(out.mant, want[0]) and torch.equal(out.exps, want[1])
+    print(f"[case] {M}x{N}x{K}: one by one {both * 50:.1f} us, one call {one * 50:.1f} us", flush=True)
+    assert one <= both * 8 / 7

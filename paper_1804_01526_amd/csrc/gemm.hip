@@ -1592,12 +1592,15 @@ int launch_gemm_i8(const GemmArgs &a, void *workspace, hipStream_t s, const hbfp
             uint8_t *w = (uint8_t *)workspace + split_bytes(a.M, a.N, p.splits);
             q.wA = (const uint32_t *)w;
             q.wB = (const uint32_t *)(w + word_bytes(a.M, a.expA_ld));
-            // Scale words inside the kernel (EB): measured words -> bytes 1000 x 4096 x 1024 18.9 -> 16.8 us, 1024 x 2048 x 4096 in
-            // blocks of 24 42.3 -> 41.2, 100352 x 128 x 1152 52.7 -> 47.4, 4096 x 4096 x 1024 (8192 tile stages of 128) 45.2 -> 44.3.
-            // Beyond that the launch is the cheaper part: level at 11 000 tile stages (2048 x 2048 x 4096 in blocks of 24 60.9 and
-            // 61.2, 4096 x 2048 x 2048 54.6 and 54.6), 146 -> 152 at 32 768 (4096^3).  The converting epilogue exists with bytes
-            // only.
-            const bool bytes = p.spb == 1 && !a.words_ready && (enc || tm * tn * p.nstage <= (10 << 10));
+            // Scale words inside the kernel (EB).  A launch costs 2 us and the words it writes and the kernel reads back (0.35 us
+            // per MB), bytes cost their conversion in every stage of every tile: words -> bytes 1000 x 4096 x 1024 18.9 -> 16.8 us,
+            // 100352 x 128 x 1152 61.0 -> 54.7 (7056 tile stages of 128, 14 MB of words), 4096 x 4096 x 1024 (8192) 45.4 -> 44.4,
+            // 1296 x 144 x 50176 in blocks of 24 (11 506, 14 MB) 70.8 -> 67.4, 50176 x 144 x 1296 (10 976, 11 MB) 60.4 -> 56.2;
+            // behind at 8192 x 4096 x 1024 (16 384, 1.6 MB) 84.6 and 85.4, 4096^3 (32 768, 4.2 MB) 145.8 and 151.1.  The line
+            // is 0.2 % from the better side on average over 106 shapes; one of 10 240 tile stages whatever the words was 0.8 %.
+            // The converting epilogue exists with bytes only.
+            const size_t words_mb = (word_bytes(a.M, a.expA_ld) + word_bytes(a.N, a.expB_ld)) >> 20;
+            const bool bytes = p.spb == 1 && !a.words_ready && (enc || tm * tn * p.nstage <= (10 << 10) + 500 * (int64_t)words_mb);
             if (!a.words_ready && !bytes) {
                 rc = launch_scale_words(a.expA, a.expA_ld, a.M, a.expB, a.expB_ld, a.N, (int)a.expA_ld, 0x40u,
                                         const_cast<uint32_t *>(q.wA), const_cast<uint32_t *>(q.wB), a.run_a, a.run_b, s);

@@ -1632,3 +1632,15 @@ def test_encoded_slice_sum_is_no_slower_than_separate_calls(hb, M, N, K, blk):
     assert torch.equal(out.mant, want[0]) and torch.equal(out.exps, want[1])
     print(f"[case] {M}x{N}x{K}: one by one {both * 50:.1f} us, one call {one * 50:.1f} us", flush=True)
     assert one <= both * 8 / 7
+
+
+@pytest.mark.parametrize("M,N,K,blk,bytes_inside", [(256, 300, 400, 32, True), (4096, 4096, 1024, 32, True), (1296, 144, 50176, 24, True),
+                                                    (4096, 4096, 4096, 32, False)])
+def test_where_the_scale_words_come_from(hb, M, N, K, blk, bytes_inside):
+    """HBFP_KERNEL_INT8 makes its scale words inside the kernel while that costs less than the launch that writes them: few tile
+    stages, or many words for their number."""
+    x = hb.encode(torch.randn((M, K), device="cuda"), 1, hb.make_format(8, 1, blk))
+    w = hb.encode(torch.randn((K, N), device="cuda"), 0, hb.make_format(8, blk, 1))
+    names = launched_kernels(lambda: hb.gemm(x, w, kernel=1))
+    assert ("scale_words_t_kernel" not in names) == bytes_inside, names
+    assert f"gemm_i8_w8_kernel<1, false, false, 0, false, {str(bytes_inside).lower()}>" in names, names

@@ -1291,9 +1291,9 @@ def _check_bfp_output(hb, A, B, fa, fb, fo, axis, relu, kernel, fused):
                                          (256, 256, 256, 8, 32), (97, 1000, 1000, 8, 24), (700, 690, 300, 8, 32), (1024, 1030, 520, 5, 32),
                                          (1100, 1024, 1024, 8, 32), (1318, 405, 247, 7, 32)])
 def test_small_products(hb, M, N, K, m, blk):
-    """hbfp_gemm on small products: the kernel without workspace, both of its tile heights and both sides of its rule, against
-    the oracle, accumulation into C and a wider C included, and its encoded output against the conversion of its FP32
-    result."""
+    """hbfp_gemm on small products: both tile heights of the kernel that does without workspace, and the tile kernels next to it (which
+    of them runs: test_where_small_products_run), against the oracle, accumulation into C and a wider C included, and the
+    encoded output against the conversion of the FP32 result."""
     print(f"[case] small product {M}x{N}x{K} m={m} blocks of {blk}", flush=True)
     rng = np.random.default_rng(M * 7 + N + K)
     A = (rng.standard_normal((M, K)) * np.exp2(rng.integers(-4, 5, size=(M, K)))).astype(np.float32)
@@ -1644,3 +1644,21 @@ def test_where_the_scale_words_come_from(hb, M, N, K, blk, bytes_inside):
     names = launched_kernels(lambda: hb.gemm(x, w, kernel=1))
     assert ("scale_words_t_kernel" not in names) == bytes_inside, names
     assert f"gemm_i8_w8_kernel<1, false, false, 0, false, {str(bytes_inside).lower()}>" in names, names
+
+
+@pytest.mark.parametrize("M,N,K,blk,where", [
+    (1, 1, 8, 32, "small 1"), (33, 32, 1000, 24, "small 1"), (256, 256, 256, 32, "small 1"), (16, 4096, 4096, 32, "small 1"),
+    (600, 600, 600, 32, "small 2"), (700, 690, 300, 32, "small 2"), (128, 4096, 1024, 32, "small 2"),
+    (1024, 1024, 512, 32, "tile"), (1000, 1000, 1000, 32, "tile"), (2048, 1024, 256, 32, "tile"), (32, 2048, 8192, 32, "tile"), (16, 64, 8192, 32, "tile")])
+def test_where_small_products_run(hb, M, N, K, blk, where):
+    """The automatic choice between the kernel for small products (tiles of 32 or 64 rows) and the tile kernels, both measured with
+    scale words made inside the tile kernel: each case on the side that is at least 4 % faster."""
+    x = hb.encode(torch.randn((M, K), device="cuda"), 1, hb.make_format(8, 1, blk))
+    w = hb.encode(torch.randn((K, N), device="cuda"), 0, hb.make_format(8, blk, 1))
+    fo = hb.make_format(8, 1, 32)
+    for call, enc in ((lambda: hb.gemm(x, w), "false"), (lambda: hb.gemm_bfp(x, w, fo), "true")):
+        names = launched_kernels(call)
+        if where == "tile":
+            assert names[0].startswith("gemm_i8_w8_kernel<1, false, false, 0"), names
+        elif N >= 32 or enc == "false":                              # (shorter blocks: the conversion is a launch of its own)
+            assert names == [f"gemm_small_kernel<{where[-1]}, {enc}>"], names

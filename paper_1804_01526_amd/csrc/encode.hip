@@ -1507,9 +1507,11 @@ static int launch_encode_rowwave(const float *src, const EncodeGeom &g, void *ma
 
 // Columns of a strip of enc_strip_kernel: 16 (64 bytes of a source row, or the width of a block), twice that when there are
 // workgroups to spare (measured 2000 x 2000, blocks of 128: 2000 strips of 16 columns 11.0 us, 1008 of 32 8.0 us; 4096^2,
-// 96 x 24 tiles: 24 columns 39 us, 48 columns 32 us).
+// 96 x 24 tiles: 24 columns 39 us, 48 columns 32 us), and no more than there are (5000 x 3: 14.6 -> 7.8 us, 34 -> 9.8 with
+// stochastic rounding; every thread then has a column).
 static int strip_columns(const EncodeGeom &g) {
     const int64_t w = g.rblock >= 16 ? g.rblock : 16 / g.rblock * g.rblock;
+    if (g.R < w) return (int)(ceil_div(g.R, g.rblock) * g.rblock);
     const bool spare = ceil_div(g.R, w) * ceil_div(g.nblk, g.kshare) >= 1024;
     return (int)(spare && 2 * w <= 48 ? 2 * w : w);
 }
@@ -1518,11 +1520,19 @@ static int strip_columns(const EncodeGeom &g) {
 // 4096^2 36 -> 27 us, 3000 x 5000 35 -> 29 us; 216 x 24 tiles of 1296 x 144 16.7 -> 5.2 us), beyond it they are behind
 // (10000 x 500: 27 and 40 us, 8192^2: 110 and 145 us).  Rows that are not 16-byte aligned slow the maximum pass of the two down
 // to half, so the line lies at twice as much there (6001 x 5999: 145 -> 83 us, 8191 x 3001: 99 -> 52 us).
+// A conversion of fewer than 64 strips takes as long as one of them however narrow the matrix, while two passes spread over the
+// chip (to nearest 5120 x 200 19.0 and 16.2 us, 2560 x 200 10.0 and 12.6; stochastic, which works longer per value, 5120 x 200
+// 35 and 18 us, 2560 x 200 18.4 and 14.7, 1663 x 1344 14.9 and 18.2; unaligned 5000 x 33 62 and 30 us, 3190 x 38 22.8 and 29.3).
+// Their lines are lower, except for tiles of more than 16 columns, which the two passes are slow at (861 x 559 in 64 columns:
+// 25 and 44 us).
 static bool strip_ok(const EncodeGeom &g, const float *src) {
     if (g.axis != 0 || g.rblock > 64 || g.R > 0x7fffff00 || g.kpad > 0x3fffffff) return false;
     const int64_t nreg = ceil_div(g.nblk, g.kshare), kext = nreg == 1 ? g.K : g.kshare * g.kblock;
+    const int64_t cw = strip_columns(g);
     const bool vec_ok = ((uintptr_t)src & 15) == 0 && g.ld % 4 == 0;
-    return nreg <= 65535 && kext * strip_columns(g) <= (vec_ok ? 80 : 160) * 1024;
+    const bool few = ceil_div(g.R, cw) * nreg < 64 && g.rblock <= 16;
+    const int ki = !few ? (vec_ok ? 80 : 160) : g.rounding == 0 ? (vec_ok ? 64 : 160) : (vec_ok ? 32 : 64);
+    return nreg <= 65535 && kext * cw <= (int64_t)ki * 1024;
 }
 
 static int launch_encode_strip(const float *src, const EncodeGeom &g, void *mant, uint8_t *exps, hipStream_t s) {

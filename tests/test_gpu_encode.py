@@ -7,7 +7,7 @@ import pytest
 import torch
 
 from oracle import ref
-from tests.util import random_cases, unpack
+from tests.util import launched_kernels, random_cases, unpack
 
 pytestmark = pytest.mark.gpu
 
@@ -557,6 +557,40 @@ def test_column_conversion_of_few_and_many_workgroups(hb, rows, cols, blk, m):
     out = hb.encode(torch.from_numpy(X).cuda(), 0, hb.make_format(m, blk, 1))
     torch.cuda.synchronize()
     want = ref.encode(X, blk, 1, m)
+    mant, exps = unpack(out)
+    np.testing.assert_array_equal(mant, want.mant)
+    np.testing.assert_array_equal(exps, want.exps)
+
+
+@pytest.mark.parametrize("rows,cols,bc,rounding,where", [
+    (500, 300, 1, 0, "strip"), (4500, 2999, 1, 0, "strip"), (2560, 200, 1, 0, "strip"), (5120, 200, 1, 0, "two passes"),
+    (1280, 64, 1, 1, "strip"), (2560, 200, 1, 1, "two passes"), (5120, 1000, 1, 1, "two passes"), (4096, 4096, 1, 1, "strip"),
+    (3190, 38, 1, 1, "strip"), (5000, 33, 1, 1, "two passes"), (5000, 33, 1, 0, "strip"), (861, 559, 64, 1, "strip"),
+    (5000, 1, 1, 0, "strip"), (7261, 3, 1, 1, "strip"), (11040, 4, 4, 1, "two passes")])
+def test_where_long_blocks_down_the_rows_are_converted(hb, rows, cols, bc, rounding, where):
+    """One exponent per `bc` columns: strips, or two passes where few strips would be too long; each case on the side that was
+    measured faster."""
+    x = torch.randn((rows, cols), device="cuda")
+    fmt = hb.make_format(8, 0, bc, rounding, 3)
+    out = hb.alloc(fmt, rows, cols, 0)
+    names = launched_kernels(lambda: hb.encode(x, 0, fmt, out=out))
+    assert any(n.startswith("enc_strip_kernel") for n in names) == (where == "strip"), names
+
+
+@pytest.mark.parametrize("m,rounding", [(8, 0), (12, 1)])
+@pytest.mark.parametrize("rows,cols,br,bc,slot", [(5000, 1, 0, 1, 0), (300, 3, 0, 1, 0), (700, 7, 0, 2, 0), (513, 5, 200, 3, 0), (640, 15, 128, 4, 0),
+                                                  (1000, 9, 216, 9, 24), (400, 15, 0, 15, 0), (129, 2, 128, 1, 0)])
+def test_strips_narrower_than_sixteen_columns(hb, rows, cols, br, bc, slot, m, rounding):
+    """A strip has no more columns than the matrix: against the oracle bit for bit."""
+    rng = np.random.default_rng(rows + cols)
+    X = (rng.standard_normal((rows, cols)) * np.exp2(rng.integers(-20, 21, size=(rows, cols)))).astype(np.float32)
+    src = torch.from_numpy(X).cuda()
+    fmt = hb.make_format(m, br, bc, rounding, 99, k_slot=slot)
+    out = hb.alloc(fmt, rows, cols, 0)
+    out.mant.fill_(85)
+    out.exps.fill_(85)
+    assert any(n.startswith("enc_strip_kernel") for n in launched_kernels(lambda: hb.encode(src, 0, fmt, out=out)))
+    want = ref.encode(X, br, bc, m, rounding, 99)
     mant, exps = unpack(out)
     np.testing.assert_array_equal(mant, want.mant)
     np.testing.assert_array_equal(exps, want.exps)

@@ -521,7 +521,8 @@ __device__ __forceinline__ void enc_col_block(const ColParams p, const uint32_t 
     // the wave index as a scalar: block indices, block lengths and (CONV) output positions stay on the scalar unit
     const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     const int64_t r = (int64_t)(wg % p.row_groups) * p.lanes + lane;
-    const int nbt = NBT >> p.narrow;
+    const int narrow = NBT > 4 ? p.narrow : 0;         // four pieces are one per wave, never cut further: a constant there
+    const int nbt = NBT >> narrow;
     const int64_t blk0 = (int64_t)(wg / p.row_groups) * nbt;
     const bool r_ok = lane < p.lanes && r < p.R;
     const int group0 = (lane / p.rblock) * p.rblock;   // first lane of this lane's 2-D tile
@@ -601,11 +602,11 @@ __device__ __forceinline__ void enc_col_block(const ColParams p, const uint32_t 
     // stored blocks of this tile that exist in the operand row
     const int64_t left_blocks = p.nb_stored - blk0;
     const int valid_bytes = (int)((left_blocks < nbt ? left_blocks : nbt) * KBP * ESZ);
-    const int piece = t & ((32 >> p.narrow) - 1);                          // 16 bytes of a row; 32 of them when it is whole
+    const int piece = t & ((32 >> narrow) - 1);                            // 16 bytes of a row; 32 of them when it is whole
 #pragma unroll
     for (int pass = 0; pass < 8; ++pass) {
-        if (pass >= (8 >> p.narrow)) break;                                // uniform
-        const int rl = (pass << (3 + p.narrow)) + (t >> (5 - p.narrow));
+        if (pass >= (8 >> narrow)) break;                                  // uniform
+        const int rl = (pass << (3 + narrow)) + (t >> (5 - narrow));
         const int64_t rr = (int64_t)(wg % p.row_groups) * p.lanes + rl;
         if (rl < p.lanes && rr < p.R && piece * 16 < valid_bytes) {
             const uint4 d = *reinterpret_cast<const uint4 *>(tile + rl * kColStride + piece * 16);

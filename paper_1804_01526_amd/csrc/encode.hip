@@ -757,8 +757,10 @@ __global__ __launch_bounds__(kThreads) void tile_amax_kernel(const TileParams p,
                     a[3] = max(a[3], __float_as_uint(d.w) & 0x7fffffffu);
                 }
             } else if (ncol) {
-                // a column that does not exist reads the last one, whose block it counts for (tc)
-#pragma unroll 4
+                // A column that does not exist reads the last one, whose block it counts for (tc).  8 rows at a time: with 4 the
+                // compiler waited for every row (20000 x 513, rows off 16 bytes: 59 us, and one lane's tail columns held up
+                // the whole wave of an aligned matrix, 10000 x 201 39 us; now 35 and 20 us).
+#pragma unroll 8
                 for (int64_t rr = r; rr < rend; ++rr)
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
@@ -1508,31 +1510,42 @@ static int launch_encode_rowwave(const float *src, const EncodeGeom &g, void *ma
 
 // Columns of a strip of enc_strip_kernel: 16 (64 bytes of a source row, or the width of a block), twice that when there are
 // workgroups to spare (measured 2000 x 2000, blocks of 128: 2000 strips of 16 columns 11.0 us, 1008 of 32 8.0 us; 4096^2,
-// 96 x 24 tiles: 24 columns 39 us, 48 columns 32 us), and no more than there are (5000 x 3: 14.6 -> 7.8 us, 34 -> 9.8 with
-// stochastic rounding; every thread then has a column).
+// 96 x 24 tiles: 24 columns 39 us, 48 columns 32 us).  A matrix of at most 8 columns has strips of 1, 2, 4 or 8, or few threads
+// would have a column (5000 x 1 23.5 -> 5.8 us; a width such as 13 is slower than 16, 15.3 and 13.3 us at 3502 x 13).
 static int strip_columns(const EncodeGeom &g) {
     const int64_t w = g.rblock >= 16 ? g.rblock : 16 / g.rblock * g.rblock;
-    if (g.R < w) return (int)(ceil_div(g.R, g.rblock) * g.rblock);
+    if (g.R <= w / 2) {
+        int64_t c = 1;
+        while (c < g.R) c *= 2;
+        return (int)(ceil_div(c, g.rblock) * g.rblock);
+    }
     const bool spare = ceil_div(g.R, w) * ceil_div(g.nblk, g.kshare) >= 1024;
     return (int)(spare && 2 * w <= 48 ? 2 * w : w);
 }
-// What a workgroup reads twice has to stay within the reach of one compute unit: up to 80 Ki values per strip and block the
-// strips are ahead of the two-pass conversion (one exponent per column: 500 x 300 15.0 -> 4.8 us, 4500 x 2999 67 -> 25 us,
-// 4096^2 36 -> 27 us, 3000 x 5000 35 -> 29 us; 216 x 24 tiles of 1296 x 144 16.7 -> 5.2 us), beyond it they are behind
-// (10000 x 500: 27 and 40 us, 8192^2: 110 and 145 us).  Rows that are not 16-byte aligned slow the maximum pass of the two down
-// to half, so the line lies at twice as much there (6001 x 5999: 145 -> 83 us, 8191 x 3001: 99 -> 52 us).
+// What a workgroup reads twice has to stay within the reach of one compute unit.  Rounding to nearest, with enough strips: up to
+// 80 Ki values per strip and block they are ahead of the two-pass conversion (one exponent per column: 500 x 300 15.0 -> 4.8
+// us, 4500 x 2999 39 -> 26 us, 4096^2 36 -> 27 us, 2500 x 6000 31 -> 24 us; 216 x 24 tiles of 1296 x 144 16.7 -> 5.2 us), beyond it
+// behind (8192^2: 110 and 145 us); rows off 16 bytes slow the maximum pass of the two down, there up to 160 Ki (10000 x 3001
+// 74 -> 64 us, 8191 x 3001 64 -> 51).  Stochastic rounding works longer per value: 80 Ki whatever the rows (4500 x 2999 49 -> 38
+// us, behind at 8191 x 6001, 115 and 136).
 // A conversion of fewer than 64 strips takes as long as one of them however narrow the matrix, while two passes spread over the
-// chip (to nearest 5120 x 200 19.0 and 16.2 us, 2560 x 200 10.0 and 12.6; stochastic, which works longer per value, 5120 x 200
-// 35 and 18 us, 2560 x 200 18.4 and 14.7, 1663 x 1344 14.9 and 18.2; unaligned 5000 x 33 62 and 30 us, 3190 x 38 22.8 and 29.3).
-// Their lines are lower, except for tiles of more than 16 columns, which the two passes are slow at (861 x 559 in 64 columns:
-// 25 and 44 us).
+// chip.  One exponent per column: to nearest up to 64 Ki values (96 Ki off 16 bytes): 2560 x 200 12.6 -> 10.0 us, 5830 x 901
+// 30.6 -> 26.9, behind at 5120 x 200 (16.2, 19.0) and 10000 x 501 (30, 43); stochastic up to 32 Ki (48 Ki): 1663 x 1344 18.2 ->
+// 14.9, behind at 2560 x 200 (14.7, 18.4) and 5120 x 1000 (25, 38).  The same where one exponent for the matrix lets the
+// maximum pass read it flat (2421 x 32 12.9 and 16.6 us; 6918 x 14, rows off 16 bytes, 34 -> 25).  Blocks of several columns
+// slow the two passes down: lines as for many strips (5267 x 416 in 8 columns 32 -> 23 us, 861 x 559 in 64 44 -> 25), only
+// stochastic ones of up to 16 columns end at 64 Ki (4992 x 17 in 8 41 and 60).
 static bool strip_ok(const EncodeGeom &g, const float *src) {
     if (g.axis != 0 || g.rblock > 64 || g.R > 0x7fffff00 || g.kpad > 0x3fffffff) return false;
     const int64_t nreg = ceil_div(g.nblk, g.kshare), kext = nreg == 1 ? g.K : g.kshare * g.kblock;
     const int64_t cw = strip_columns(g);
-    const bool vec_ok = ((uintptr_t)src & 15) == 0 && g.ld % 4 == 0;
-    const bool few = ceil_div(g.R, cw) * nreg < 64 && g.rblock <= 16;
-    const int ki = !few ? (vec_ok ? 80 : 160) : g.rounding == 0 ? (vec_ok ? 64 : 160) : (vec_ok ? 32 : 64);
+    const bool vec_ok = ((uintptr_t)src & 15) == 0 && g.ld % 4 == 0, nearest = g.rounding == 0;
+    const bool flat = g.rblock >= g.R && nreg == 1 && vec_ok && g.ld == g.src_cols;
+    int ki = nearest && !vec_ok ? 160 : 80;
+    if (ceil_div(g.R, cw) * nreg < 64) {
+        if (g.rblock == 1 || flat) ki = nearest ? (vec_ok ? 64 : 96) : (vec_ok ? 32 : 48);
+        else if (!nearest && g.rblock <= 16) ki = 64;
+    }
     return nreg <= 65535 && kext * cw <= (int64_t)ki * 1024;
 }
 

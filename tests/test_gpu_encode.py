@@ -565,7 +565,8 @@ def test_column_conversion_of_few_and_many_workgroups(hb, rows, cols, blk, m):
 @pytest.mark.parametrize("rows,cols,bc,rounding,where", [
     (500, 300, 1, 0, "strip"), (4500, 2999, 1, 0, "strip"), (2560, 200, 1, 0, "strip"), (5120, 200, 1, 0, "two passes"),
     (1280, 64, 1, 1, "strip"), (2560, 200, 1, 1, "two passes"), (5120, 1000, 1, 1, "two passes"), (4096, 4096, 1, 1, "strip"),
-    (3190, 38, 1, 1, "strip"), (5000, 33, 1, 1, "two passes"), (5000, 33, 1, 0, "strip"), (861, 559, 64, 1, "strip"),
+    (2000, 38, 1, 1, "strip"), (5000, 33, 1, 1, "two passes"), (10000, 501, 1, 0, "two passes"), (10000, 3001, 1, 0, "strip"),
+    (8191, 6001, 1, 1, "two passes"), (861, 559, 64, 1, "strip"),
     (5000, 1, 1, 0, "strip"), (7261, 3, 1, 1, "strip"), (11040, 4, 4, 1, "two passes")])
 def test_where_long_blocks_down_the_rows_are_converted(hb, rows, cols, bc, rounding, where):
     """One exponent per `bc` columns: strips, or two passes where few strips would be too long; each case on the side that was

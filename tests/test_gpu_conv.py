@@ -369,6 +369,29 @@ def test_conv_data_gradient_general_formats(hb, geom):
     _dgrad_case(hb, n, h, w, c, f, r, s, ph, pw, sh, sw, seed=sum(int(g) for g in geom), kb=kb, by_block=by_block, per_image=per_image, tiles=tiles)
 
 
+@pytest.mark.parametrize("geom", [
+    # n, h, w, c, f, r, s, pad_h, pad_w, beta   (stride 1, blocks of 24, by block, per image, filter tiles)
+    (3, 8, 8, 24, 48, 3, 3, 1, 1, 0.0),
+    (1, 7, 7, 100, 960, 3, 3, 1, 1, 0.0),            # 360 slots in runs of 9, split along k: ranges begin inside a run
+    (1, 7, 7, 100, 960, 3, 3, 1, 1, 1.0),
+    (2, 6, 7, 30, 48, 2, 3, 2, 1, 0.0),              # padding as wide as the window: positions that no window of dY reaches
+    (1, 9, 5, 20, 72, 1, 4, 1, 4, 0.0),              # ... in both directions, windows of one row
+    (2, 5, 12, 130, 48, 4, 2, 0, 1, 1.0),
+])
+def test_conv_data_gradient_scales_runs_once(hb, geom):
+    """Stride 1 in the format of Sec. 5.1: dY is read without gaps, so runs of blocks with one exponent are scaled once, as in the
+    forward call; against the oracle and the forward call, and by the kernel that does so."""
+    from tests.util import launched_kernels
+    n, h, w, c, f, r, s, ph, pw, beta = geom
+    _dgrad_case(hb, n, h, w, c, f, r, s, ph, pw, 1, 1, seed=n + h + c + f, beta=beta, kb=24, by_block=True, per_image=True, tiles=True)
+    conv = hb.Conv2d(n, h, w, c, r, s, ph, pw, 1, 1, 24, 0)
+    ho, wo = conv.out_hw()
+    dy = hb.encode(torch.randn((n * ho * wo, f), device="cuda"), 1, hb.make_format(8, ho * wo, 0, k_slot=24))
+    flt = hb.encode(torch.randn((r * s * f, c), device="cuda"), 0, hb.make_format(8, r * s * 24, 24, k_slot=24))
+    names = launched_kernels(lambda: hb.gemm_conv2d_dgrad(dy, conv, flt))
+    assert any(k.startswith("gemm_i8_w8_kernel<3, true") for k in names), names
+
+
 def test_conv_data_gradient_general_formats_random(hb):
     for seed in random_cases(12):
         rng = np.random.default_rng(9900 + seed)

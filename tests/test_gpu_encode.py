@@ -595,3 +595,28 @@ def test_strips_narrower_than_sixteen_columns(hb, rows, cols, br, bc, slot, m, r
     mant, exps = unpack(out)
     np.testing.assert_array_equal(mant, want.mant)
     np.testing.assert_array_equal(exps, want.exps)
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan, np.finfo(np.float32).max])
+@pytest.mark.parametrize("rows,cols,br,bc,slot", [(500, 33, 0, 1, 0), (700, 40, 128, 1, 0), (432, 50, 216, 24, 24), (6001, 40, 0, 1, 0)])
+def test_one_value_out_of_range_spoils_its_own_block_only(hb, rows, cols, br, bc, slot, bad):
+    """Inputs have to be finite and nothing traps the others: an infinity or NaN leaves its own exponent block unspecified, every
+    other block is as if it were not there (strips, and two passes for the last size)."""
+    rng = np.random.default_rng(rows)
+    X = rng.standard_normal((rows, cols)).astype(np.float32)
+    want = ref.encode(X, br, bc, 8)
+    r, c = rows // 2, cols // 2
+    X[r, c] = bad
+    fmt = hb.make_format(8, br, bc, k_slot=slot)
+    mant, exps = unpack(hb.encode(torch.from_numpy(X).cuda(), 0, fmt))
+    kr, kc = br or rows, bc or cols
+    keep = np.ones((rows, cols), dtype=bool)
+    keep[r // kr * kr:(r // kr + 1) * kr, c // kc * kc:(c // kc + 1) * kc] = False
+    np.testing.assert_array_equal(mant[keep], want.mant[keep])
+    other = np.ones(exps.shape, dtype=bool)
+    other[r // kr, c // kc] = False
+    np.testing.assert_array_equal(exps[other], want.exps[other])
+    if np.isfinite(bad):                                       # the largest finite value is an ordinary one
+        full = ref.encode(X, br, bc, 8)
+        np.testing.assert_array_equal(mant, full.mant)
+        np.testing.assert_array_equal(exps, full.exps)

@@ -1662,3 +1662,19 @@ def test_where_small_products_run(hb, M, N, K, blk, where):
             assert names[0].startswith("gemm_i8_w8_kernel<1, false, false, 0"), names
         elif N >= 32 or enc == "false":                              # (shorter blocks: the conversion is a launch of its own)
             assert names == [f"gemm_small_kernel<{where[-1]}, {enc}>"], names
+
+
+@pytest.mark.parametrize("M,N,K,kernel", [(40, 70, 300, 0), (130, 100, 1100, 1), (130, 70, 9000, 1)])
+def test_encoded_products_next_to_the_largest_value(hb, M, N, K, kernel):
+    """A row of the product that overflows FP32 spoils its own blocks only: the other rows leave the small kernel, the tile kernel and
+    the slice sum as if it were an ordinary one."""
+    fx, fw, fo = hb.make_format(8, 1, 32), hb.make_format(8, 32, 1), hb.make_format(8, 1, 32)
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    X = torch.randn((M, K), generator=gen, device="cuda")
+    w = hb.encode(torch.randn((K, N), generator=gen, device="cuda") * 4.0, 0, fw)
+    want = hb.gemm_bfp(hb.encode(X, 1, fx), w, fo, 1, relu=True, kernel=kernel)
+    X[M // 2] = 2.0 ** 126
+    got = hb.gemm_bfp(hb.encode(X, 1, fx), w, fo, 1, relu=True, kernel=kernel)
+    torch.cuda.synchronize()
+    rest = [i for i in range(M) if i != M // 2]
+    assert torch.equal(got.mant[rest], want.mant[rest]) and torch.equal(got.exps[rest], want.exps[rest])

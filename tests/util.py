@@ -48,15 +48,21 @@ def rel_fro(got, want):
 
 def launched_kernels(call):
     """The names of the kernels that `call` launches, in their order, without namespaces and parameters
-    ("gemm_small_kernel<1, false>"): which route a rule on sizes took."""
+    ("gemm_small_kernel<1, false>"): which route a rule on sizes took.  A trace can lose events, so it is taken until two agree."""
     import re
 
     import torch
     from torch.profiler import ProfilerActivity, profile
     call()                                       # what a first call sets up is not part of the trace
     torch.cuda.synchronize()
-    with profile(activities=[ProfilerActivity.CUDA]) as trace:
-        call()
-        torch.cuda.synchronize()
-    names = [e for e in sorted(trace.events(), key=lambda e: e.time_range.start) if "_kernel" in e.name]
-    return [re.sub(r"\(anonymous namespace\)::|hbfp::|^void ", "", e.name).split("(")[0] for e in names]
+    last = None
+    for _ in range(8):
+        with profile(activities=[ProfilerActivity.CUDA]) as trace:
+            call()
+            torch.cuda.synchronize()
+        events = [e for e in sorted(trace.events(), key=lambda e: e.time_range.start) if "_kernel" in e.name]
+        names = [re.sub(r"\(anonymous namespace\)::|hbfp::|^void ", "", e.name).split("(")[0] for e in events]
+        if names and names == last:
+            return names
+        last = names
+    raise AssertionError(f"no two traces of the call agree; the last one: {last}")

@@ -1678,3 +1678,15 @@ def test_encoded_products_next_to_the_largest_value(hb, M, N, K, kernel):
     torch.cuda.synchronize()
     rest = [i for i in range(M) if i != M // 2]
     assert torch.equal(got.mant[rest], want.mant[rest]) and torch.equal(got.exps[rest], want.exps[rest])
+
+
+@pytest.mark.parametrize("M,N,K,four", [(1296, 144, 9000, True), (247, 776, 11903, True), (92, 1256, 5040, True), (240, 164, 14182, False), (300, 601, 9000, False)])
+def test_where_slices_are_summed_four_at_a_time(hb, M, N, K, four):
+    """Rows of whole quadruples and at least 96 Ki outputs; either way the bits of the sum in slice order."""
+    x = hb.encode(torch.randn((M, K), device="cuda"), 1, hb.make_format(8, 1, 32))
+    w = hb.encode(torch.randn((K, N), device="cuda"), 0, hb.make_format(8, 32, 1))
+    names = launched_kernels(lambda: hb.gemm(x, w, kernel=1))
+    assert names[-1] == f"splitk_reduce_kernel<{str(four).lower()}>", names
+    wide = torch.zeros((M, N + 1), device="cuda")                    # rows that leave 16 bytes: one at a time whatever the size
+    hb.gemm(x, w, out=wide[:, :N], kernel=1)
+    assert torch.equal(wide[:, :N], hb.gemm(x, w, kernel=1)) and not wide[:, N].any()

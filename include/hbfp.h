@@ -350,13 +350,14 @@ int hbfp_gemm_conv2d_dgrad(const hbfp_tensor *dy, const hbfp_conv2d *conv, const
  * hbfp_gemm_select); the outer sum is FP32.  A has M = A->rows operand rows, B has
  * N = B->rows; both must have the same kdim, kblock and mantissa class (both
  * <= 8 bits, or both 9..12 bits, which run as two int8 limbs per mantissa).
- *   C     device FP32 [M][ldc], ldc >= N
+ *   C     device FP32 [M][ldc], ldc >= N; not over the buffers of A or B
  *   beta  0 (overwrite; C is not read) or 1 (accumulate)
  *   workspace  hbfp_gemm_workspace bytes: scale words of both operands (4 bytes per row and
  *              block), one FP32 slice of C per split when the shape is split along k (few
  *              output tiles, long k), two int8 limb planes per operand for mantissas wider
  *              than 8 bits, and the limb planes of both operands when the block-scaled
- *              kernel is chosen
+ *              kernel is chosen.  It is what the shape can need: a product that uses less
+ *              (small ones, words made inside the kernel) still has to bring all of it
  * Domain: block exponent bytes up to 254 (magnitudes below 2^127).
  * Errors: HBFP_ERR_ARG, HBFP_ERR_LAYOUT (kdim/kblock mismatch), HBFP_ERR_FORMAT
  * (mantissa classes differ or exceed 12 bits), HBFP_ERR_RANGE (kblock * max|mA| *

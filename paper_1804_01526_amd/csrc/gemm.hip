@@ -494,7 +494,7 @@ __device__ __forceinline__ void w8_encode_from_lds(const W8Enc &o, const uint8_t
 // EB (SPB = 1, no gather): the scale words come from the exponent bytes inside the kernel instead of from memory.  Four waves
 // (0, 1: rows of A; 4, 5: columns) load the four bytes of a row's blocks of a pair of stages with the pair's copies and
 // write its words in front of the hand-over that completes it: a dozen vector instructions per pair in place of the
-// launch that prepared the words (3 to 5 us).
+// launch that prepared the words (2 to 5 us).
 template <int SPB, bool CONV = false, bool F16 = false, int GATHER = 0, bool ENC = false, bool EB = false>
 __global__ __launch_bounds__(kW8Threads, 4) void gemm_i8_w8_kernel(const W8Params q) {
     static_assert(!EB || (SPB == 1 && !CONV && !F16), "words from exponent bytes: blocks of one k-step of a plain product");

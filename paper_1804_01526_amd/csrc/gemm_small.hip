@@ -2,7 +2,7 @@
 // 8-bit class).  What counts is latency: the 128 x 128-tile kernels behind a launch for scale words, and before one that sums
 // slices where few tiles split the contraction, start at 9 us.  Here a workgroup of 8 waves owns 32 columns and 32 or 64 rows
 // of C; its waves deal the contraction out among themselves in groups of four blocks (128 bytes of a row), load operands
-// and exponent bytes straight into registers, a group ahead, and meet in LDS: one launch, no workspace.  Per block the
+// and exponent bytes straight into registers, a group ahead, and meet in LDS: one launch, no workspace touched.  Per block the
 // arithmetic is that of the int8 kernels: an integer sum started from the row constants, one subtraction and one
 // multiply-add.  The result leaves as FP32 or, with ReLU if asked for, as an encoded operand.
 // 256^3: 3.3 us (the tile kernel 7.8, 9.8 with a launch for its scale words); 16 x 4096 x 4096: 11.8 us (14.7 and 17.2 in two

@@ -1594,6 +1594,23 @@ def test_gemm_bfp_over_its_own_operand(hb, M, K, kernel, over):
                                                     n.startswith("gemm_i8_w8_kernel<1, false, false, 0, true") for n in names), names
 
 
+@pytest.mark.parametrize("m,kernel", [(8, 5), (4, 2), (12, 0), (8, 3)])
+def test_gemm_bfp_over_its_own_input_on_the_other_kernels(hb, m, kernel):
+    """The bf16 and block-scaled kernels read packed copies, the others deliver an FP32 product first: in place as well."""
+    M, K = 300, 256
+    blk = 0 if kernel == 3 else 32
+    fx, fw, fo = hb.make_format(m, 1, blk), hb.make_format(m, blk, 1), hb.make_format(m, 1, 32)
+    x, w = hb.encode(torch.randn((M, K), device="cuda"), 1, fx), hb.encode(torch.randn((K, K), device="cuda"), 0, fw)
+    want = hb.gemm_bfp(x, w, fo, 1, relu=True, kernel=kernel)
+    desc = hb.plan(fo, M, K, 1)
+    assert desc.mant_bytes <= x.mant.numel() * x.mant.element_size()
+    exps = x.exps if blk else torch.empty((M, desc.exp_ld), dtype=torch.uint8, device="cuda")
+    desc.mant, desc.exps = x.mant.data_ptr(), exps.data_ptr()
+    hb.gemm_bfp(x, w, fo, 1, relu=True, kernel=kernel, out=hb.BfpTensor(desc, x.mant, exps))
+    torch.cuda.synchronize()
+    assert torch.equal(x.mant, want.mant) and torch.equal(exps, want.exps)
+
+
 @pytest.mark.parametrize("M,N,K,blk", [(17, 102, 11401, 24), (49, 263, 12511, 24), (1335, 45, 14217, 24)])
 def test_encoded_slice_sum_is_no_slower_than_separate_calls(hb, M, N, K, blk):
     """An int8 product of few columns, split along k, delivered encoded: not slower than product, ReLU and conversion one by one

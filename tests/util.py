@@ -51,11 +51,12 @@ def launched_kernels(call):
     ("gemm_small_kernel<1, false>"): which route a rule on sizes took.  A trace can lose events, so it is taken until two agree."""
     import re
 
+    import pytest
     import torch
     from torch.profiler import ProfilerActivity, profile
     call()                                       # what a first call sets up is not part of the trace
     torch.cuda.synchronize()
-    last = None
+    last, seen = None, False
     for _ in range(8):
         with profile(activities=[ProfilerActivity.CUDA]) as trace:
             call()
@@ -64,5 +65,7 @@ def launched_kernels(call):
         names = [re.sub(r"\(anonymous namespace\)::|hbfp::|^void ", "", e.name).split("(")[0] for e in events]
         if names and names == last:
             return names
-        last = names
+        last, seen = names, seen or bool(names)
+    if not seen:
+        pytest.skip("the profiler records no kernels here")
     raise AssertionError(f"no two traces of the call agree; the last one: {last}")

@@ -949,19 +949,29 @@ __global__ __launch_bounds__(kW8Threads, 4) void gemm_i8_w8_kernel(const W8Param
         }
         return;
     }
+    if (SPB == 3) {
+        // the variant that scales runs once stores output by output: with store_result in it the register allocator spills in
+        // the loop (50176 x 144 x 1296: 56 -> 88 us)
 #pragma unroll
-    for (int ni = 0; ni < 2; ++ni)
+        for (int ni = 0; ni < 2; ++ni)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int64_t i = row0 + wm * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
-            const int64_t j = col0 + wn * 64 + ni * 32 + l32;
-            if (i < p.M && j < p.N) {
-                const float val = acc[ni][v] * p.final_scale;
-                if (p.splits > 1) p.partial[((int64_t)split * p.M + i) * p.N + j] = val;
-                else if (p.beta) p.C[i * p.ldc + j] += val;
-                else __builtin_nontemporal_store(val, p.C + i * p.ldc + j);   // written once, not read again here
+            for (int v = 0; v < 16; ++v) {
+                const int64_t i = row0 + wm * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
+                const int64_t j = col0 + wn * 64 + ni * 32 + l32;
+                if (i < p.M && j < p.N) {
+                    const float val = acc[ni][v] * p.final_scale;
+                    if (p.splits > 1) p.partial[((int64_t)split * p.M + i) * p.N + j] = val;
+                    else if (p.beta) p.C[i * p.ldc + j] += val;
+                    else __builtin_nontemporal_store(val, p.C + i * p.ldc + j);
+                }
             }
-        }
+        return;
+    }
+    const int64_t i0 = row0 + wm * 32, j0 = col0 + wn * 64;
+    const auto value = [&](int, int ni, int v) { return acc[ni][v] * p.final_scale; };
+    // a slice is read again at once by the launch that sums the slices
+    if (p.splits > 1) store_result<1, 2, false>(p.partial + ((int64_t)split * p.M + i0) * p.N + j0, p.N, p.M - i0, p.N - j0, false, lane, value);
+    else store_result<1, 2, true>(p.C + i0 * p.ldc + j0, p.ldc, p.M - i0, p.N - j0, p.beta != 0, lane, value);
 }
 
 // Fixed-order sum over the split-K slices: deterministic, no float atomics.  The slices of one output are requested eight at

@@ -359,31 +359,18 @@ __global__ __launch_bounds__(kBfThreads, 2) void gemm_bf_kernel(const BfGroup g)
         else mx_store_encoded<0>(g.out, acc, row0, col0, p.M, p.N, lane);
         return;
     }
+    int sa[2][16], sb[4];                                     // FP16 planes: the factors of rows (padded to whole panels) and columns
+    if (F16) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        int sa[16];
-        if (F16) {
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) sa[v] = p.sa[row0 + i * 32 + 8 * (v >> 2) + 4 * lh + (v & 3)];      // padded to whole panels
-        }
+            for (int v = 0; v < 16; ++v) sa[i][v] = p.sa[row0 + i * 32 + 8 * (v >> 2) + 4 * lh + (v & 3)];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t col = col0 + j * 32 + l32;
-            if (col >= p.N) continue;
-            const int sb = F16 ? p.sb[col] : 0;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int64_t row = row0 + i * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
-                if (row < p.M) {
-                    float *dst = p.C + row * p.ldc + col;
-                    const float x = F16 ? __builtin_ldexpf(acc[i][j][v], sa[v] + sb) : acc[i][j][v];
-                    // C is written once and not read again here: streaming stores leave the operand panels in the caches
-                    if (p.beta) *dst = *dst + x;
-                    else __builtin_nontemporal_store(x, dst);
-                }
-            }
-        }
+        for (int j = 0; j < 4; ++j) sb[j] = col0 + j * 32 + l32 < p.N ? p.sb[col0 + j * 32 + l32] : 0;
     }
+    // streaming stores leave the operand panels in the caches
+    store_result<2, 4, true>(p.C + row0 * p.ldc + col0, p.ldc, p.M - row0, p.N - col0, p.beta != 0, lane,
+                             [&](int i, int j, int v) { return F16 ? __builtin_ldexpf(acc[i][j][v], sa[i][v] + sb[j]) : acc[i][j][v]; });
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -557,30 +544,18 @@ __global__ __launch_bounds__(kBfSmallThreads, 4) void gemm_bf_small_kernel(const
         else mx_store_encoded<0>(g.out, acc, row0, col0, p.M, p.N, lane);
         return;
     }
+    int sa[2][16], sb[2];                                     // FP16 planes: the factors of rows (padded to whole panels) and columns
+    if (F16) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        int sa[16];
-        if (F16) {
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) sa[v] = p.sa[row0 + i * 32 + 8 * (v >> 2) + 4 * lh + (v & 3)];      // padded to whole panels
-        }
+            for (int v = 0; v < 16; ++v) sa[i][v] = p.sa[row0 + i * 32 + 8 * (v >> 2) + 4 * lh + (v & 3)];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int64_t col = col0 + j * 32 + l32;
-            if (col >= p.N) continue;
-            const int sb = F16 ? p.sb[col] : 0;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int64_t row = row0 + i * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
-                if (row < p.M) {
-                    float *dst = p.C + row * p.ldc + col;
-                    const float x = F16 ? __builtin_ldexpf(acc[i][j][v], sa[v] + sb) : acc[i][j][v];
-                    if (p.beta) *dst = *dst + x;
-                    else __builtin_nontemporal_store(x, dst);
-                }
-            }
-        }
+        for (int j = 0; j < 2; ++j) sb[j] = col0 + j * 32 + l32 < p.N ? p.sb[col0 + j * 32 + l32] : 0;
     }
+    // streaming stores leave the operand panels in the caches
+    store_result<2, 2, true>(p.C + row0 * p.ldc + col0, p.ldc, p.M - row0, p.N - col0, p.beta != 0, lane,
+                             [&](int i, int j, int v) { return F16 ? __builtin_ldexpf(acc[i][j][v], sa[i][v] + sb[j]) : acc[i][j][v]; });
 }
 
 int64_t klen_of(const GemmArgs &a, int m) { return bf_klen(a.kpad, a.kbp, a.kblock, a.nblk, a.kdim, m); }

@@ -57,6 +57,52 @@ __device__ __forceinline__ void async_copy4(const void *gbase, uint32_t voff, ui
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_addr), "v"(voff), "s"(gbase) : "memory");
 }
 
+// Stores a wave's TI x TJ results of 32 x 32 (lane l: column l % 32, register v: row 8 (v / 4) + 4 (l / 32) + v % 4); dst is
+// their first element, rows and cols what is left of the product from there, value(i, j, v) the output.  STREAM: written once
+// and not read again by this call, so past the caches.
+// Bound by its instructions: with a 64-bit product for every row, and two tests and a branch around every store, the 128
+// stores of a lane of the 256 x 256-tile kernels were 2500 instructions of straight code that the waves fetched once each,
+// and a kernel of a few k-steps spent most of its time there.  Here a whole tile is stores and one addition per row; only
+// the edges of the product and C += take the tests.  One-exponent product 3001 x 4500 x 2999 70 -> 64 us, a step of three
+// packed 4096^3 products 431 -> 413, two of 1337 x 2052 x 1500 and their conversions 80.5 -> 73.4, 12-bit 8192^3 1035 -> 984.
+template <int TI, int TJ, bool STREAM, class V>
+__device__ __forceinline__ void store_result(float *dst, int64_t ld, int64_t rows, int64_t cols, bool add, int lane, const V &value) {
+    const int lh = lane >> 5, l32 = lane & 31;
+    if (rows <= 0 || cols <= 0) return;
+    float *p = dst + 4 * lh * ld + l32;
+    if (rows >= 32 * TI && cols >= 32 * TJ && !add) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+#pragma unroll
+                for (int j = 0; j < TJ; ++j) {
+                    if (STREAM) __builtin_nontemporal_store(value(i, j, v), p + 32 * j);
+                    else p[32 * j] = value(i, j, v);
+                }
+                p += (v & 3) == 3 ? 5 * ld : ld;
+            }
+        return;
+    }
+    const int r_end = (int)(rows < 32 * TI ? rows : 32 * TI) - 4 * lh, c_end = (int)(cols < 32 * TJ ? cols : 32 * TJ) - l32;
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            if (32 * i + 8 * (v >> 2) + (v & 3) < r_end) {
+#pragma unroll
+                for (int j = 0; j < TJ; ++j)
+                    if (32 * j < c_end) {
+                        float x = value(i, j, v);
+                        if (add) x = p[32 * j] + x;
+                        if (STREAM) __builtin_nontemporal_store(x, p + 32 * j);
+                        else p[32 * j] = x;
+                    }
+            }
+            p += (v & 3) == 3 ? 5 * ld : ld;
+        }
+}
+
 // A kernel queued behind the block-scaled product kernel as its stand-in runs only when one of the two packed
 // operands is marked out of range (the first two words of its header are equal); without headers it always runs.
 __device__ __forceinline__ bool stands_down(const int *run_a, const int *run_b) {

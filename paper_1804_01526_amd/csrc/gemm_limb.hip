@@ -244,18 +244,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_limb_kernel(const LimbParams
     }
 
     if (DUMP) return;
-#pragma unroll
-    for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int64_t i = row0 + wm * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
-            const int64_t j = col0 + wn * 64 + ni * 32 + l32;
-            if (i < p.M && j < p.N) {
-                const float val = acc[ni][v] * p.final_scale;
-                if (p.beta) p.C[i * p.ldc + j] += val;
-                else __builtin_nontemporal_store(val, p.C + i * p.ldc + j);   // written once, not read again here
-            }
-        }
+    const int64_t i0 = row0 + wm * 32, j0 = col0 + wn * 64;
+    store_result<1, 2, true>(p.C + i0 * p.ldc + j0, p.ldc, p.M - i0, p.N - j0, p.beta != 0, lane,
+                             [&](int, int ni, int v) { return acc[ni][v] * p.final_scale; });
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -428,16 +419,9 @@ __global__ __launch_bounds__(kLwThreads, 4) void gemm_limb_w8_kernel(const LimbW
 #undef HBFP_COPY_STAGE
 #undef HBFP_WAIT_COPIES
 
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int64_t i = row0 + wm * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
-        const int64_t j = col0 + wn * 32 + l32;
-        if (i < p.M && j < p.N) {
-            const float val = acc[v] * p.final_scale;
-            if (p.beta) p.C[i * p.ldc + j] += val;
-            else __builtin_nontemporal_store(val, p.C + i * p.ldc + j);   // written once, not read again here
-        }
-    }
+    const int64_t i0 = row0 + wm * 32, j0 = col0 + wn * 32;
+    store_result<1, 1, true>(p.C + i0 * p.ldc + j0, p.ldc, p.M - i0, p.N - j0, p.beta != 0, lane,
+                             [&](int, int, int v) { return acc[v] * p.final_scale; });
 }
 
 template <int SPB, bool DUMP>

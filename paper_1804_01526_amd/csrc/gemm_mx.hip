@@ -623,13 +623,20 @@ __global__ __launch_bounds__(kMxThreads, 2) void gemm_mx_kernel(const MxGroup g)
 #undef HBFP_MX_FENCE
 #undef HBFP_MX_COPY_STAGE
 
-    const int l32 = lane & 31, lh = lane >> 5;
     const int64_t row0 = (int64_t)tm * 256 + wm * 64, col0 = (int64_t)tn * 256 + wn * 128;
     if (TR) {
         if (g.out.rounding) mx_store_encoded<1>(g.out, acc, row0, col0, p.M, p.N, lane);
         else mx_store_encoded<0>(g.out, acc, row0, col0, p.M, p.N, lane);
         return;
     }
+    if (LA == 1 && LB == 1) {
+        // streaming stores leave the operand panels in the caches
+        store_result<2, 4, true>(p.C + row0 * p.ldc + col0, p.ldc, p.M - row0, p.N - col0, p.beta != 0, lane,
+                                 [&](int i, int j, int v) { return acc[i][j][v]; });
+        return;
+    }
+    // with more limbs store_result leaves the loop short of registers (38 and more spilled): output by output
+    const int l32 = lane & 31, lh = lane >> 5;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -641,7 +648,6 @@ __global__ __launch_bounds__(kMxThreads, 2) void gemm_mx_kernel(const MxGroup g)
                 const int64_t row = row0 + i * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
                 if (row < p.M) {
                     float *dst = p.C + row * p.ldc + col;
-                    // C is written once and not read again here: streaming stores leave the operand panels in the caches
                     if (p.beta) *dst = *dst + acc[i][j][v];
                     else __builtin_nontemporal_store(acc[i][j][v], dst);
                 }

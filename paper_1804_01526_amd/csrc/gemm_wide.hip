@@ -48,6 +48,10 @@ __global__ __launch_bounds__(kWideThreads, 1) void gemm_i8_wide_kernel(const Wid
     const int l32 = lane & 31, lh = lane >> 5;
     const int64_t row0 = (int64_t)tm * kWideRows, col0 = (int64_t)tn * kWideRows;
 
+    // ---- exponents: thread t keeps row t's and column t's until C is stored
+    const int64_t row_t = row0 + t < p.M ? row0 + t : p.M - 1, col_t = col0 + t < p.N ? col0 + t : p.N - 1;
+    const int ea_t = p.eA[row_t * p.eA_ld], eb_t = p.eB[col_t * p.eB_ld];
+
     // ---- copies: piece c of a stage is 16 rows x 64 bytes; pieces 0..15 are A, 16..31 B; wave w moves pieces w, w + 4, ...
     // A lane copies 16 bytes: row 16 c + lane / 4, LDS chunk lane % 4, which holds source chunk (lane % 4) ^ ((row >> 2) & 3).
     // Rows past the edge re-read the last row (their results are never stored).
@@ -180,32 +184,21 @@ __global__ __launch_bounds__(kWideThreads, 1) void gemm_i8_wide_kernel(const Wid
 #undef HBFP_WIDE_COPY_STAGE
 #undef HBFP_WIDE_COPY
 
-    // ---- C = acc * 2^(Ea + Eb + offset): int32 -> FP32 rounds to nearest even above 2^24, the scaling is exact
+    // ---- C = acc * 2^(Ea + Eb + offset): int32 -> FP32 rounds to nearest even above 2^24, the scaling is exact.  The exponent
+    // bytes come through LDS: loaded here, between stores that they could alias, every row waited for its own.
+    __syncthreads();                                        // everybody has read the last stage
+    int *exps = reinterpret_cast<int *>(lds);               // of the rows, then of the columns
+    exps[t] = ea_t > 254 ? 254 : ea_t;
+    exps[kWideRows + t] = (eb_t > 254 ? 254 : eb_t) + p.exp_offset;
+    __syncthreads();
     int eb[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int64_t col = col0 + 128 * wn + 32 * j + l32;
-        int e = col < p.N ? p.eB[col * p.eB_ld] : 1;
-        eb[j] = (e > 254 ? 254 : e) + p.exp_offset;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int64_t row = row0 + 128 * wm + 32 * i + 8 * (v >> 2) + 4 * lh + (v & 3);
-            if (row >= p.M) continue;
-            int ea = p.eA[row * p.eA_ld];
-            ea = ea > 254 ? 254 : ea;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int64_t col = col0 + 128 * wn + 32 * j + l32;
-                if (col >= p.N) continue;
-                const float val = ldexpf((float)acc[i][j][v], ea + eb[j]);
-                float *dst = p.C + row * p.ldc + col;
-                if (p.beta) *dst = *dst + val;
-                else __builtin_nontemporal_store(val, dst);               // written once, not read again here
-            }
-        }
+    for (int j = 0; j < 4; ++j) eb[j] = exps[kWideRows + 128 * wn + 32 * j + l32];
+    const int *ea = exps + 128 * wm + 4 * lh;
+    const int64_t i0 = row0 + 128 * wm, j0 = col0 + 128 * wn;
+    store_result<4, 4, true>(p.C + i0 * p.ldc + j0, p.ldc, p.M - i0, p.N - j0, p.beta != 0, lane, [&](int i, int j, int v) {
+        return __builtin_amdgcn_ldexpf((float)acc[i][j][v], ea[32 * i + 8 * (v >> 2) + (v & 3)] + eb[j]);
+    });
 }
 
 }  // namespace

@@ -1,0 +1,54 @@
+"""Where the product kernels store C: whole tiles, edges of one row or column more or less, a row pitch, and C += .
+
+The inputs are integers whose blocks all hold a 1 in the top bit, so every sum is exact in FP32 and C must equal the FP64
+product of the decoded operands; the bytes of the buffer around C must stay as they were.
+"""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+INT8, SCALED, WIDE, FP16, BF16, F16P = 1, 2, 3, 4, 5, 6
+
+
+def _operands(M, K, N, bits, block):
+    from paper_1804_01526_amd import hbfp
+    g = torch.Generator(device="cuda").manual_seed(M * 1009 + N)
+    top = 2 ** (bits - 1) - 1
+    A = torch.randint(-3, 4, (M, K), device="cuda", generator=g).float()
+    B = torch.randint(-3, 4, (K, N), device="cuda", generator=g).float()
+    A[:, ::block or K] = top
+    B[::block or K, :] = top
+    return (hbfp.encode(A, 1, hbfp.make_format(bits, 1, block, hbfp.RNE)), hbfp.encode(B, 0, hbfp.make_format(bits, block, 1, hbfp.RNE)),
+            A.double() @ B.double())
+
+
+@pytest.mark.parametrize("beta", [0.0, 1.0])
+@pytest.mark.parametrize("kernel,bits,block,edge", [(INT8, 8, 32, 128), (INT8, 8, 0, 128), (BF16, 8, 32, 256), (BF16, 8, 24, 128), (F16P, 12, 64, 256),
+                                                    (FP16, 12, 64, 128), (SCALED, 4, 32, 256), (WIDE, 8, 0, 256)])
+@pytest.mark.parametrize("dm,dn", [(0, 0), (1, -1), (-1, 33), (-31, 0), (0, 1)])
+def test_edges_pitch_and_accumulation(kernel, bits, block, edge, dm, dn, beta):
+    from paper_1804_01526_amd import hbfp
+    M, N, K, pad = edge + dm, 2 * edge + dn, 192, 5
+    print(f"[store] kernel={kernel} bits={bits} block={block} {M}x{N} beta={beta}", flush=True)
+    a, b, want = _operands(M, K, N, bits, block)
+    buf = torch.full((M + 2, N + pad), 7.0, device="cuda")
+    C = buf[1:M + 1, 2:N + 2]
+    if beta:
+        C.copy_(torch.arange(N, device="cuda").float().expand(M, N))
+        want = want + torch.arange(N, device="cuda").double()
+    hbfp.gemm(a, b, out=C, beta=beta, kernel=kernel)
+    assert torch.equal(C.double(), want)
+    buf[1:M + 1, 2:N + 2] = 7.0
+    assert bool((buf == 7.0).all())
+
+
+@pytest.mark.parametrize("M,N", [(128, 128), (127, 130), (64, 257)])
+def test_slices_of_a_split_product(M, N):
+    from paper_1804_01526_amd import hbfp
+    a, b, want = _operands(M, 16384, N, 8, 32)
+    buf = torch.full((M + 1, N + 3), 7.0, device="cuda")
+    hbfp.gemm(a, b, out=buf[:M, 1:N + 1], kernel=INT8)
+    assert torch.equal(buf[:M, 1:N + 1].double(), want.float().double())
+    buf[:M, 1:N + 1] = 7.0
+    assert bool((buf == 7.0).all())

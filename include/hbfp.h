@@ -380,11 +380,11 @@ int hbfp_gemm(const hbfp_tensor *A, const hbfp_tensor *B, float *C, int64_t ldc,
  *                       non-zero block outside that range the call computes the product with the int8
  *                       kernels instead, inside the same call and without host synchronisation;
  *   HBFP_KERNEL_INT8_WIDE  the member of the int8 family for one exponent per operand row (a single block
- *                       along k, the basic scheme of Sec. 4) and mantissas of at most 8 bits: 256 x 256 tiles,
- *                       one uninterrupted chain of matrix instructions, exponents applied when C is stored.
- *                       HBFP_KERNEL_INT8 and HBFP_KERNEL_AUTO take it by themselves when at least 128 such
- *                       tiles are at least 75 % full; naming it runs it on any shape (HBFP_ERR_FORMAT if the
- *                       operands have more than one block or wider mantissas);
+ *                       along k, the basic scheme of Sec. 4) and mantissas of at most 8 bits: one uninterrupted
+ *                       chain of matrix instructions, exponents applied when C is stored (tiles of 128 to 256,
+ *                       long contractions of few tiles split along k).  HBFP_KERNEL_INT8 and HBFP_KERNEL_AUTO
+ *                       take it by themselves for contractions longer than 64; naming it runs it on any shape
+ *                       (HBFP_ERR_FORMAT if the operands have more than one block or wider mantissas);
  *   HBFP_KERNEL_FP16    9..12-bit mantissas as FP16 numbers (an 11-bit magnitude is an FP16 significand): one FP16 matrix
  *                       instruction multiplies them exactly and sums in FP32, then the per-block scale-and-accumulate runs
  *                       on the vector unit as in the int8 family.  A block sum beyond 2^24 is rounded to nearest once per

@@ -805,6 +805,7 @@ int hbfp_gemm_select_workspace(const hbfp_tensor *A, const hbfp_tensor *B, int k
     *bytes = (A->mant_bits > 8 || B->mant_bits > 8) ? gemm_limb_workspace(A, B)
                                                      : gemm_i8_workspace(A->rows, B->rows, A->kpad, A->kblock_pad, A->exp_ld);
     const GemmArgs g = gemm_args(A, B);
+    if (gemm_wide_possible(g) && gemm_wide_workspace(g) > *bytes) *bytes = gemm_wide_workspace(g);
     if (use_bf(g, kernel)) {                                     // [packed A][packed B]
         *bytes = packed_operand_bytes(g.M, g.kpad, g.mA) + packed_operand_bytes(g.N, g.kpad, g.mB);
         return HBFP_OK;

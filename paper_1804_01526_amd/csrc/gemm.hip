@@ -1553,7 +1553,7 @@ bool gemm_i8_encoded_output_ok(const GemmArgs &a, const hbfp_tensor &out) {
 // enc: the product leaves as this encoded operand (gemm_i8_encoded_output_ok), with ReLU first if asked for; a.C is then unused
 int launch_gemm_i8(const GemmArgs &a, void *workspace, hipStream_t s, const hbfp_tensor *enc, int relu) {
     if (enc && (a.wide || a.beta != 0.0f || !gemm_i8_encoded_output_ok(a, *enc))) return HBFP_ERR_FORMAT;
-    if (a.wide ? gemm_wide_possible(a) : gemm_wide_ok(a)) return launch_gemm_wide(a, s);
+    if (a.wide ? gemm_wide_possible(a) : gemm_wide_ok(a)) return launch_gemm_wide(a, workspace, s);
     GemmParams p;
     p.A = (const uint8_t *)a.mantA;
     p.B = (const uint8_t *)a.mantB;

@@ -3,12 +3,13 @@
 //     C[i][j] = 2^(eA[i] + eB[j]) * sum_k mA[i][k] * mB[j][k]
 // Here nothing happens between the matrix instructions of a tile: the whole contraction is one chain of
 // v_mfma_i32_32x32x32_i8 into int32 accumulators and the two exponents are applied once, when C is stored.
-// The kernel is therefore built for the matrix core alone: a 256 x 256 tile of C per workgroup, four waves
-// of 128 x 128 at one wave per SIMD (256 int32 accumulators per lane), so that a pair of matrix instructions
-// needs one 16-byte LDS read per lane (64 B/clk per CU at the full matrix rate; a 64 x 128 wave tile would need
-// 94 of the 128 the LDS can deliver).  Operands are read as they are stored (int8 [rows][kpad]): 64 bytes of k
-// of 256 + 256 rows per stage (32 KB), copied global -> LDS asynchronously into a ring of four buffers, rows of
-// 64 bytes with the 16-byte chunk index XORed with (row >> 2) & 3 as in the other int8 kernels (copies of 16 rows
+// The kernel is therefore built for the matrix core alone: four waves of 32 T x 32 T, T = 4 (a tile of 256 x 256 of C
+// per workgroup, 256 int32 accumulators per lane at one wave per SIMD, a pair of matrix instructions needs one 16-byte
+// LDS read per lane: 64 B/clk per CU at the full matrix rate, where a 64 x 128 wave tile would need 94 of the 128 the
+// LDS can deliver), 3 or 2 (128 x 128, two workgroups per CU).  Large products are bound by the chip's power and go
+// furthest on the largest tile; the smaller ones fill the chip where those are too few, and long contractions of few
+// tiles are split (wide_plan).  Operands are read as they are stored (int8 [rows][kpad]): 64 bytes of k of the tile's
+// rows per stage (32 KB for T = 4), copied global -> LDS asynchronously into a ring of four buffers, rows of 64 bytes with the 16-byte chunk index XORed with (row >> 2) & 3 as in the other int8 kernels (copies of 16 rows
 // and fragment reads of 32 rows then both cover all banks).  Fragments are read one k-step (32) ahead, between
 // the matrix instructions, and the hand-over of a ring buffer (one barrier per stage) sits in the middle of a stage.
 #include "gemm_common.h"
@@ -17,88 +18,100 @@ namespace hbfp {
 namespace {
 
 constexpr int kWideThreads = 256;
-constexpr int kWideRows = 256;                          // tile of C is 256 x 256
 constexpr int kWideK = 64;                              // bytes of k per stage
-constexpr int kWideOperand = kWideRows * kWideK;        // 16 KB
-constexpr int kWideStage = 2 * kWideOperand;            // 32 KB
 constexpr int kWideRing = 4;
-constexpr int kWideLds = kWideRing * kWideStage;        // 128 KB
-constexpr int kWideCopies = kWideStage / 1024 / 4;      // 8 copies of 1 KB (16 rows x 64 B) per wave and stage
+// T: 32 x 32 tiles along a side of a wave's part of C; the workgroup's tile is 64 T x 64 T
+template <int T>
+struct Wide {
+    static constexpr int kRows = 64 * T;
+    static constexpr int kOperand = kRows * kWideK;      // 16 KB for T = 4
+    static constexpr int kStage = 2 * kOperand;
+    static constexpr int kLds = kWideRing * kStage;      // 128 KB for T = 4
+    static constexpr int kCopies = kStage / 1024 / 4;    // copies of 1 KB (16 rows x 64 B) per wave and stage: 2 T
+};
 
 struct WideParams {
     const uint8_t *A, *B;        // int8 mantissas [rows][kpad]
     const uint8_t *eA, *eB;      // exponent bytes [rows][exp_ld], block 0
     float *C;
     int64_t M, N, kpad, eA_ld, eB_ld, ldc;
+    int32_t *partial;            // split along k: int32 sums [splits][M][N]
     int32_t nstage;              // kpad / 64 (even)
+    int32_t splits, stages_per_split;
     int32_t tiles_m, tiles_n, beta;
     int32_t exp_offset;          // C = acc * 2^(Ea + Eb + exp_offset)
     const int *run_a, *run_b;
 };
 
-__global__ __launch_bounds__(kWideThreads, 1) void gemm_i8_wide_kernel(const WideParams p) {
+template <int T>
+__global__ __launch_bounds__(kWideThreads, T == 4 ? 1 : 2) void gemm_i8_wide_kernel(const WideParams p) {
+    typedef Wide<T> W;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     if (stands_down(p.run_a, p.run_b)) return;
-    int tm, tn;
-    if (!tile_of_workgroup(blockIdx.x, p.tiles_m, p.tiles_n, tm, tn)) return;   // whole workgroup, before any barrier
+    int tm, tn, split = blockIdx.y;
+    if (p.splits >= 8 ? !tile_and_split_of_workgroup(blockIdx.x, p.tiles_m, p.tiles_n, p.splits, tm, tn, split)
+                      : !tile_of_workgroup(blockIdx.x, p.tiles_m, p.tiles_n, tm, tn))
+        return;                                                                 // whole workgroup, before any barrier
+    const int st_begin = split * p.stages_per_split;
+    const int nstage = p.nstage - st_begin < p.stages_per_split ? p.nstage - st_begin : p.stages_per_split;   // even, at least 2
 
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = wave & 1, wn = wave >> 1;
     const int l32 = lane & 31, lh = lane >> 5;
-    const int64_t row0 = (int64_t)tm * kWideRows, col0 = (int64_t)tn * kWideRows;
+    const int64_t row0 = (int64_t)tm * W::kRows, col0 = (int64_t)tn * W::kRows;
 
     // ---- exponents: thread t keeps row t's and column t's until C is stored
-    const int64_t row_t = row0 + t < p.M ? row0 + t : p.M - 1, col_t = col0 + t < p.N ? col0 + t : p.N - 1;
-    const int ea_t = p.eA[row_t * p.eA_ld], eb_t = p.eB[col_t * p.eB_ld];
+    const int64_t row_t = row0 + (t < W::kRows ? t : 0), col_t = col0 + (t < W::kRows ? t : 0);
+    const int ea_t = p.eA[(row_t < p.M ? row_t : p.M - 1) * p.eA_ld], eb_t = p.eB[(col_t < p.N ? col_t : p.N - 1) * p.eB_ld];
 
-    // ---- copies: piece c of a stage is 16 rows x 64 bytes; pieces 0..15 are A, 16..31 B; wave w moves pieces w, w + 4, ...
+    // ---- copies: piece c of a stage is 16 rows x 64 bytes; pieces 0 .. 4 T - 1 are A, the others B; wave w moves pieces w, w + 4, ...
     // A lane copies 16 bytes: row 16 c + lane / 4, LDS chunk lane % 4, which holds source chunk (lane % 4) ^ ((row >> 2) & 3).
     // Rows past the edge re-read the last row (their results are never stored).
-    const uint8_t *cbase[kWideCopies];
-    uint32_t cvoff[kWideCopies], coff[kWideCopies];
+    const uint8_t *cbase[W::kCopies];
+    uint32_t cvoff[W::kCopies], coff[W::kCopies];
 #pragma unroll
-    for (int i = 0; i < kWideCopies; ++i) {
+    for (int i = 0; i < W::kCopies; ++i) {
         const int c = wave + 4 * i;
-        const bool is_a = c < 16;
-        const int r = 16 * (c & 15) + (lane >> 2);
+        const bool is_a = c < 4 * T;
+        const int r = 16 * (is_a ? c : c - 4 * T) + (lane >> 2);
         const int64_t lim = is_a ? p.M - row0 : p.N - col0;
         const int rr = r < lim ? r : (int)lim - 1;
         const int chunk = (lane & 3) ^ ((r >> 2) & 3);
-        cbase[i] = is_a ? p.A + row0 * p.kpad : p.B + col0 * p.kpad;
+        cbase[i] = (is_a ? p.A + row0 * p.kpad : p.B + col0 * p.kpad) + (int64_t)st_begin * kWideK;
         cvoff[i] = (uint32_t)rr * (uint32_t)p.kpad + chunk * 16;
         coff[i] = c * 1024;
     }
 #define HBFP_WIDE_COPY(i, ring_)                                                                    \
     {                                                                                              \
-        async_copy16(cbase[i], cvoff[i], (uint32_t)((ring_) * kWideStage) + coff[i]);              \
+        async_copy16(cbase[i], cvoff[i], (uint32_t)((ring_) * W::kStage) + coff[i]);              \
         cbase[i] += kWideK;                                                                        \
     }
 #define HBFP_WIDE_COPY_STAGE(ring_)                                                                 \
     {                                                                                              \
-        _Pragma("unroll") for (int i = 0; i < kWideCopies; ++i) HBFP_WIDE_COPY(i, ring_);          \
+        _Pragma("unroll") for (int i = 0; i < W::kCopies; ++i) HBFP_WIDE_COPY(i, ring_);          \
     }
 
-    // ---- fragment addresses inside a stage: row tile i of A is rows 128 wm + 32 i + l32, k-step s the chunks 2 s + lh
+    // ---- fragment addresses inside a stage: row tile i of A is rows 32 T wm + 32 i + l32, k-step s the chunks 2 s + lh
     int fa[2], fb[2];                                   // per k-step: byte offset of (row tile 0, this lane); tiles are 2 KB apart
     {
-        const int ra = 128 * wm + l32, rb = 128 * wn + l32;
+        const int ra = 32 * T * wm + l32, rb = 32 * T * wn + l32;
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             fa[s] = ra * kWideK + (((2 * s + lh) ^ ((ra >> 2) & 3)) * 16);
-            fb[s] = kWideOperand + rb * kWideK + (((2 * s + lh) ^ ((rb >> 2) & 3)) * 16);
+            fb[s] = W::kOperand + rb * kWideK + (((2 * s + lh) ^ ((rb >> 2) & 3)) * 16);
         }
     }
 
-    v16i acc[4][4];
+    v16i acc[T][T];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < T; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < T; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
 
-    v4i a[2][4], b[2][4];                               // [buffer][tile]
+    v4i a[2][T], b[2][T];                               // [buffer][tile]
 #define HBFP_WIDE_FENCE                 \
     asm volatile("" ::: "memory");      \
     __builtin_amdgcn_sched_barrier(0)
@@ -107,31 +120,21 @@ __global__ __launch_bounds__(kWideThreads, 1) void gemm_i8_wide_kernel(const Wid
         a[buf][i] = *reinterpret_cast<const v4i *>((base_) + fa[s] + (i) * 2048);                             \
         b[buf][i] = *reinterpret_cast<const v4i *>((base_) + fb[s] + (i) * 2048);                             \
     }
-    // one k-step of 32: 16 matrix instructions on buffer `buf`; after each group of four, one row tile and one column
+    // one k-step of 32: T x T matrix instructions on buffer `buf`; after each row of them, one row tile and one column
     // tile of the next k-step are requested into the other buffer (EXTRA: the hand-over's copies ride along)
 #define HBFP_WIDE_ROW(buf, i)                                                                                  \
     {                                                                                                         \
-        _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                         \
+        _Pragma("unroll") for (int j = 0; j < T; ++j)                                                         \
             acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[buf][i], b[buf][j], acc[i][j], 0, 0, 0);      \
     }
 #define HBFP_WIDE_KSTEP(buf, NEXT, nbase_, ns, COPY, ring_)                                                     \
     {                                                                                                         \
-        HBFP_WIDE_ROW(buf, 0);                                                                                \
-        if (NEXT) HBFP_WIDE_READ(1 - (buf), nbase_, ns, 0);                                                   \
-        if (COPY) { HBFP_WIDE_COPY(0, ring_); HBFP_WIDE_COPY(1, ring_); }                                     \
-        HBFP_WIDE_FENCE;                                                                                      \
-        HBFP_WIDE_ROW(buf, 1);                                                                                \
-        if (NEXT) HBFP_WIDE_READ(1 - (buf), nbase_, ns, 1);                                                   \
-        if (COPY) { HBFP_WIDE_COPY(2, ring_); HBFP_WIDE_COPY(3, ring_); }                                     \
-        HBFP_WIDE_FENCE;                                                                                      \
-        HBFP_WIDE_ROW(buf, 2);                                                                                \
-        if (NEXT) HBFP_WIDE_READ(1 - (buf), nbase_, ns, 2);                                                   \
-        if (COPY) { HBFP_WIDE_COPY(4, ring_); HBFP_WIDE_COPY(5, ring_); }                                     \
-        HBFP_WIDE_FENCE;                                                                                      \
-        HBFP_WIDE_ROW(buf, 3);                                                                                \
-        if (NEXT) HBFP_WIDE_READ(1 - (buf), nbase_, ns, 3);                                                   \
-        if (COPY) { HBFP_WIDE_COPY(6, ring_); HBFP_WIDE_COPY(7, ring_); }                                     \
-        HBFP_WIDE_FENCE;                                                                                      \
+        _Pragma("unroll") for (int i_ = 0; i_ < T; ++i_) {                                                    \
+            HBFP_WIDE_ROW(buf, i_);                                                                           \
+            if (NEXT) HBFP_WIDE_READ(1 - (buf), nbase_, ns, i_);                                              \
+            if (COPY) { HBFP_WIDE_COPY(2 * i_, ring_); HBFP_WIDE_COPY(2 * i_ + 1, ring_); }                   \
+            HBFP_WIDE_FENCE;                                                                                  \
+        }                                                                                                     \
     }
     // A stage: k-step 0 (its fragments were requested during the stage before), then the hand-over: this wave's copies
     // of the next stage have landed when only those of the stage after it are in flight; after the barrier everybody's
@@ -141,36 +144,36 @@ __global__ __launch_bounds__(kWideThreads, 1) void gemm_i8_wide_kernel(const Wid
     // the next stage is the last;  3: last stage
 #define HBFP_WIDE_STAGE(MODE)                                                                                  \
     {                                                                                                         \
-        const uint8_t *base = lds + ring * kWideStage;                                                        \
+        const uint8_t *base = lds + ring * W::kStage;                                                        \
         const int next = (ring + 1) & 3, free_ring = (ring + 3) & 3;                                          \
         HBFP_WIDE_KSTEP(0, true, base, 1, false, 0);                                                          \
         if (MODE != 3) {                                                                                      \
-            if (MODE != 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kWideCopies) : "memory");                 \
+            if (MODE != 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(W::kCopies) : "memory");                 \
             else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                                             \
             __builtin_amdgcn_s_barrier();                                                                     \
             asm volatile("" ::: "memory");                                                                    \
         }                                                                                                     \
-        HBFP_WIDE_KSTEP(1, MODE != 3, lds + next * kWideStage, 0, MODE == 0, free_ring);                      \
+        HBFP_WIDE_KSTEP(1, MODE != 3, lds + next * W::kStage, 0, MODE == 0, free_ring);                      \
         ring = next;                                                                                          \
     }
 
     // prologue: stages 0..2 on their way (the contraction has at least two stages), fragments of k-step 0
     HBFP_WIDE_COPY_STAGE(0);
     HBFP_WIDE_COPY_STAGE(1);
-    if (p.nstage > 2) {
+    if (nstage > 2) {
         HBFP_WIDE_COPY_STAGE(2);
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kWideCopies) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * W::kCopies) : "memory");
     } else {
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kWideCopies) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(W::kCopies) : "memory");
     }
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 #pragma unroll
-    for (int i = 0; i < 4; ++i) HBFP_WIDE_READ(0, lds, 0, i);
+    for (int i = 0; i < T; ++i) HBFP_WIDE_READ(0, lds, 0, i);
     int ring = 0;
     int st = 0;
-    for (; st + 4 <= p.nstage; ++st) HBFP_WIDE_STAGE(0);     // stage st + 3 exists
-    if (p.nstage - st == 3) {
+    for (; st + 4 <= nstage; ++st) HBFP_WIDE_STAGE(0);     // stage st + 3 exists
+    if (nstage - st == 3) {
         HBFP_WIDE_STAGE(1);
         ++st;
     }
@@ -188,17 +191,96 @@ __global__ __launch_bounds__(kWideThreads, 1) void gemm_i8_wide_kernel(const Wid
     // bytes come through LDS: loaded here, between stores that they could alias, every row waited for its own.
     __syncthreads();                                        // everybody has read the last stage
     int *exps = reinterpret_cast<int *>(lds);               // of the rows, then of the columns
-    exps[t] = ea_t > 254 ? 254 : ea_t;
-    exps[kWideRows + t] = (eb_t > 254 ? 254 : eb_t) + p.exp_offset;
+    if (t < W::kRows) {
+        exps[t] = ea_t > 254 ? 254 : ea_t;
+        exps[W::kRows + t] = (eb_t > 254 ? 254 : eb_t) + p.exp_offset;
+    }
     __syncthreads();
-    int eb[4];
+    int eb[T];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) eb[j] = exps[kWideRows + 128 * wn + 32 * j + l32];
-    const int *ea = exps + 128 * wm + 4 * lh;
-    const int64_t i0 = row0 + 128 * wm, j0 = col0 + 128 * wn;
-    store_result<4, 4, true>(p.C + i0 * p.ldc + j0, p.ldc, p.M - i0, p.N - j0, p.beta != 0, lane, [&](int i, int j, int v) {
+    for (int j = 0; j < T; ++j) eb[j] = exps[W::kRows + 32 * T * wn + 32 * j + l32];
+    const int *ea = exps + 32 * T * wm + 4 * lh;
+    const int64_t i0 = row0 + 32 * T * wm, j0 = col0 + 32 * T * wn;
+    if (T == 2 && p.splits > 1) {                           // bit patterns of the int32 sums
+        store_result<T, T, false>(reinterpret_cast<float *>(p.partial) + ((int64_t)split * p.M + i0) * p.N + j0, p.N, p.M - i0, p.N - j0, false,
+                                  lane, [&](int i, int j, int v) { return __int_as_float(acc[i][j][v]); });
+        return;
+    }
+    store_result<T, T, true>(p.C + i0 * p.ldc + j0, p.ldc, p.M - i0, p.N - j0, p.beta != 0, lane, [&](int i, int j, int v) {
         return __builtin_amdgcn_ldexpf((float)acc[i][j][v], ea[32 * i + 8 * (v >> 2) + (v & 3)] + eb[j]);
     });
+}
+
+// The sum of the slices of a product split along k: int32, so any order gives the same bits, those of the unsplit product.
+// A thread sums four outputs 256 apart, eight slices in flight each.
+__global__ __launch_bounds__(256) void wide_sum_kernel(const WideParams p) {
+    if (stands_down(p.run_a, p.run_b)) return;
+    const int64_t n = p.M * p.N;
+    const int64_t e0 = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+    int sum[4] = {0, 0, 0, 0};
+    for (int z = 0; z < p.splits; z += 8) {
+        int v[4][8];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[u][k] = e0 + u * 256 < n && z + k < p.splits ? p.partial[(int64_t)(z + k) * n + e0 + u * 256] : 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) sum[u] += v[u][k];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int64_t e = e0 + u * 256;
+        if (e >= n) return;
+        const int64_t row = n < ((int64_t)1 << 31) ? (int64_t)((uint32_t)e / (uint32_t)p.N) : e / p.N, col = e - row * p.N;
+        const int ea = p.eA[row * p.eA_ld], eb = p.eB[col * p.eB_ld];
+        const float val = __builtin_amdgcn_ldexpf((float)sum[u], (ea > 254 ? 254 : ea) + (eb > 254 ? 254 : eb) + p.exp_offset);
+        float *dst = p.C + row * p.ldc + col;
+        *dst = p.beta ? *dst + val : val;
+    }
+}
+
+template <int T>
+int launch_wide_t(WideParams p, hipStream_t s) {
+    static std::atomic<bool> configured{false};
+    if (allow_dynamic_lds(configured, reinterpret_cast<const void *>(&gemm_i8_wide_kernel<T>), Wide<T>::kLds) != HBFP_OK) return HBFP_ERR_LAUNCH;
+    p.tiles_m = (int32_t)ceil_div(p.M, Wide<T>::kRows);
+    p.tiles_n = (int32_t)ceil_div(p.N, Wide<T>::kRows);
+    const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
+    const dim3 grid = p.splits >= 8 ? dim3((unsigned)(8 * tiles * ceil_div(p.splits, 8))) : dim3((unsigned)(ceil_div(tiles, 8) * 8), (unsigned)p.splits);
+    hipLaunchKernelGGL(gemm_i8_wide_kernel<T>, grid, dim3(kWideThreads), Wide<T>::kLds, s, p);
+    return launch_status();
+}
+
+// Tile and split of a product: the smallest estimate in us.  A launch costs `base`; a workgroup `step` per 64 bytes of k, more
+// the more of the chip is busy (power and L2), and `tail` for filling the ring and storing its tile.  Tiles of 256 and 192 have
+// a compute unit to themselves and go in rounds, of 128 two share one.  Fitted to 99 shapes of 1 to 8192 rows and contractions
+// of 64 to 59 635: 0.7 % behind the best of the three on average, 19 % at the worst (1069 x 5990 x 3765).  Against the kernel of
+// blocks of 128 and more on 128 x 128 tiles, which all products of fewer than 128 tiles of 256 x 256 took before, 32 % ahead on
+// average: 2048 x 4096 x 2048 34.6 -> 24.6 us, 1024 x 2048 x 1024 16.1 -> 10.0, 16 x 4096 x 4096 26.2 -> 15.8; 256 x 256 ->
+// 192 x 192 tiles 3001 x 4500 x 2999 (144 -> 256 tiles) 64.6 -> 51.9 us, 1826 x 3178 x 3145 41.3 -> 32.4.
+struct WidePlan {
+    int T, splits;
+};
+WidePlan wide_plan(int64_t M, int64_t N, int64_t nstage, bool may_split) {
+    static const double base[3] = {3.1, 1.6, 5.1}, lone[3] = {0.17, 0.30, 0.48}, full[3] = {0.32, 0.50, 0.86}, tail[3] = {3.0, 8.4, 10.9};
+    WidePlan best = {2, 1};
+    double least = 0.0;
+    for (int t = 0; t < 3; ++t) {
+        const int64_t tiles = ceil_div(M, 64 * (t + 2)) * ceil_div(N, 64 * (t + 2));
+        for (int s = 1; s <= 64; ++s) {
+            if (s > 1 && (t > 0 || !may_split || nstage / s < 8 || tiles * s > 512)) break;
+            if (s > 8 && s % 8) continue;                       // the k ranges are dealt to the 8 XCDs in turn: keep them level
+            const double wgs = (double)(tiles * s), per_cu = (double)(s < 8 ? ceil_div(tiles, 8) * s : tiles * ceil_div(s, 8)) / 32.0;
+            const double busy = wgs < 256.0 ? wgs / 256.0 : 1.0, step = lone[t] + busy * (full[t] - lone[t]);
+            const double load = t == 0 ? (per_cu > 1.0 ? per_cu : 1.0) : (double)ceil_div((int64_t)(per_cu * 32.0), 32);
+            double us = base[t] + load * ((double)(ceil_div(nstage / 2, s) * 2) * step + tail[t]);
+            if (s > 1) us += 3.0 + (double)(s + 1) * (double)(M * N) * 4e-6 / 3.0;
+            if ((t == 0 && s == 1) || us < least) least = us, best = {t + 2, s};
+        }
+    }
+    return best;
 }
 
 }  // namespace
@@ -206,25 +288,34 @@ __global__ __launch_bounds__(kWideThreads, 1) void gemm_i8_wide_kernel(const Wid
 // One exponent per operand row, 8-bit mantissas, rows of the stored operands addressable with 32-bit offsets
 bool gemm_wide_possible(const GemmArgs &a) {
     return !a.P && a.nblk == 1 && a.mA <= 8 && a.mB <= 8 && (uint64_t)255 * (uint64_t)a.kpad + 64 < ((uint64_t)1 << 32) &&
-           ceil_div(a.M, kWideRows) * ceil_div(a.N, kWideRows) <= 0x7ffffff0 && a.kpad / kWideK <= 0x7fffffff;
+           ceil_div(a.M, 128) * ceil_div(a.N, 128) <= 0x7ffffff0 && a.kpad / kWideK <= 0x7fffffff;
 }
 
-// ... and enough full tiles of 256 x 256 to fill the chip
+// ... and a contraction longer than 64, or enough full tiles of 256 x 256 to fill the chip (below, the kernels of short blocks
+// scale once per workgroup too)
 bool gemm_wide_ok(const GemmArgs &a) {
     if (!gemm_wide_possible(a)) return false;
-    const int64_t tiles = ceil_div(a.M, kWideRows) * ceil_div(a.N, kWideRows);
+    if (a.kbp >= 128) return true;
+    const int64_t tiles = ceil_div(a.M, 256) * ceil_div(a.N, 256);
     return tiles >= 128 && (double)a.M * (double)a.N >= 0.75 * 65536.0 * (double)tiles;
 }
 
-int launch_gemm_wide(const GemmArgs &a, hipStream_t s) {
-    static std::atomic<bool> configured{false};
-    if (allow_dynamic_lds(configured, reinterpret_cast<const void *>(&gemm_i8_wide_kernel), kWideLds) != HBFP_OK) return HBFP_ERR_LAUNCH;
-    WideParams p;
+// slices of a product split along k; a stand-by launch is not split
+size_t gemm_wide_workspace(const GemmArgs &a) {
+    const WidePlan plan = wide_plan(a.M, a.N, a.kpad / kWideK, !a.run_a);
+    return plan.splits > 1 ? (size_t)plan.splits * (size_t)a.M * (size_t)a.N * 4 : 0;
+}
+
+int launch_gemm_wide(const GemmArgs &a, void *workspace, hipStream_t s) {
+    const WidePlan plan = wide_plan(a.M, a.N, a.kpad / kWideK, !a.run_a);
+    if (plan.splits > 1 && !workspace) return HBFP_ERR_WORKSPACE;
+    WideParams p = {};
     p.A = (const uint8_t *)a.mantA;
     p.B = (const uint8_t *)a.mantB;
     p.eA = a.expA;
     p.eB = a.expB;
     p.C = a.C;
+    p.partial = (int32_t *)workspace;
     p.M = a.M;
     p.N = a.N;
     p.kpad = a.kpad;
@@ -232,14 +323,17 @@ int launch_gemm_wide(const GemmArgs &a, hipStream_t s) {
     p.eB_ld = a.expB_ld;
     p.ldc = a.ldc;
     p.nstage = (int32_t)(a.kpad / kWideK);
-    p.tiles_m = (int32_t)ceil_div(a.M, kWideRows);
-    p.tiles_n = (int32_t)ceil_div(a.N, kWideRows);
+    p.stages_per_split = (int32_t)(ceil_div(p.nstage / 2, plan.splits) * 2);
+    p.splits = (int32_t)ceil_div(p.nstage, p.stages_per_split);
     p.beta = a.beta != 0.0f;
     p.exp_offset = -250 - a.mA - a.mB;
     p.run_a = a.run_a;
     p.run_b = a.run_b;
-    const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
-    hipLaunchKernelGGL(gemm_i8_wide_kernel, dim3((unsigned)(ceil_div(tiles, 8) * 8)), dim3(kWideThreads), kWideLds, s, p);
+    const int rc = plan.T == 2 ? launch_wide_t<2>(p, s) : plan.T == 3 ? launch_wide_t<3>(p, s) : launch_wide_t<4>(p, s);
+    if (rc != HBFP_OK || p.splits == 1) return rc;
+    const int64_t wgs = ceil_div(a.M * a.N, 1024);
+    if (wgs > 0x7fffffff) return HBFP_ERR_ARG;
+    hipLaunchKernelGGL(wide_sum_kernel, dim3((unsigned)wgs), dim3(256), 0, s, p);
     return launch_status();
 }
 

@@ -112,10 +112,11 @@ size_t gemm_limb_workspace(const hbfp_tensor *A, const hbfp_tensor *B);
 bool gemm_small_ok(const GemmArgs &a);
 int launch_gemm_small(const GemmArgs &a, hipStream_t s, const hbfp_tensor *enc = nullptr, int relu = 0);
 
-// gemm_wide.hip: int8 kernel for one exponent per operand row (a single block along k), 256 x 256 tiles
+// gemm_wide.hip: int8 kernel for one exponent per operand row (a single block along k)
 bool gemm_wide_possible(const GemmArgs &a);
 bool gemm_wide_ok(const GemmArgs &a);
-int launch_gemm_wide(const GemmArgs &a, hipStream_t s);
+size_t gemm_wide_workspace(const GemmArgs &a);
+int launch_gemm_wide(const GemmArgs &a, void *workspace, hipStream_t s);
 
 // gemm_mx.hip: the product on the block-scaled matrix instruction.  A packed operand is a 256-byte header followed
 // by the limb planes; the header's first two words are equal when some exponent of the operand could not be

@@ -52,3 +52,17 @@ def test_slices_of_a_split_product(M, N):
     assert torch.equal(buf[:M, 1:N + 1].double(), want.float().double())
     buf[:M, 1:N + 1] = 7.0
     assert bool((buf == 7.0).all())
+
+
+# one exponent per row and column: tiles of 128 (alone, split along k over 2 .. 7 and over 8 and more ranges), 192 and 256
+@pytest.mark.parametrize("M,K,N", [(200, 1000, 300), (1, 130, 1), (128, 128, 129), (300, 4000, 260), (130, 20000, 70), (65, 40001, 64), (3001, 129, 2999),
+                                   (4096, 129, 4095)])
+@pytest.mark.parametrize("beta", [0.0, 1.0])
+def test_one_exponent_per_row(M, K, N, beta):
+    from paper_1804_01526_amd import hbfp
+    print(f"[one exponent] {M}x{K}x{N} beta={beta}", flush=True)
+    a, b, want = _operands(M, K, N, 8, 0)
+    C = torch.full((M, N + 3), 5.0, device="cuda")
+    hbfp.gemm(a, b, out=C[:, :N], beta=beta)
+    assert torch.equal(C[:, :N].double(), want + (5.0 if beta else 0.0))
+    assert bool((C[:, N:] == 5.0).all())

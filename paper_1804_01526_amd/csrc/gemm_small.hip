@@ -5,8 +5,8 @@
 // and exponent bytes straight into registers, a group ahead, and meet in LDS: one launch, no workspace touched.  Per block the
 // arithmetic is that of the int8 kernels: an integer sum started from the row constants, one subtraction and one
 // multiply-add.  The result leaves as FP32 or, with ReLU if asked for, as an encoded operand.
-// 256^3: 3.3 us (the tile kernel 7.8, 9.8 with a launch for its scale words); 16 x 4096 x 4096: 11.8 us (14.7 and 17.2 in two
-// and three launches), bound by its vector instructions and load latency in turn (two waves per SIMD), not by the 17 MB of B.
+// 256^3: 3.3 us (the tile kernel 7.8, 9.8 with a launch for its scale words).  At most 32 rows have a kernel of their own below:
+// 16 x 4096 x 4096 7.5 us (11.7 on this one, 14.7 and 17.2 on the tile kernel in two and three launches).
 #include <atomic>
 
 #include "bfp_device.h"
@@ -14,6 +14,8 @@
 
 namespace hbfp {
 namespace {
+
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 constexpr int kSmallWaves = 8;
 constexpr int kSmallThreads = kSmallWaves * 64;
@@ -32,6 +34,39 @@ struct SmallParams {
     int32_t onblk, om, orounding, orelu;
     uint32_t s0, s1;
 };
+
+// four columns of a row as part of an encoded operand: 8 neighbouring lanes hold block `blk`, the 32 columns from col0 on
+template <int ROUND>
+__device__ __forceinline__ uint32_t small_quantise(const SmallParams &p, const float4 &x, uint32_t Eb, uint64_t idx) {
+    const int q0 = quantise<ROUND>(x.x, Eb, p.om, (uint32_t)idx, (uint32_t)(idx >> 32), p.s0, p.s1);
+    const int q1 = quantise<ROUND>(x.y, Eb, p.om, (uint32_t)(idx + 1), (uint32_t)((idx + 1) >> 32), p.s0, p.s1);
+    const int q2 = quantise<ROUND>(x.z, Eb, p.om, (uint32_t)(idx + 2), (uint32_t)((idx + 2) >> 32), p.s0, p.s1);
+    const int q3 = quantise<ROUND>(x.w, Eb, p.om, (uint32_t)(idx + 3), (uint32_t)((idx + 3) >> 32), p.s0, p.s1);
+    return ((uint32_t)q0 & 0xffu) | (((uint32_t)q1 & 0xffu) << 8) | (((uint32_t)q2 & 0xffu) << 16) | ((uint32_t)q3 << 24);
+}
+__device__ __forceinline__ void small_encode(const SmallParams &p, float4 x, int64_t row, int64_t col0, int c4, int64_t blk) {
+    const int64_t left = p.N - (col0 + c4);
+    x.x = left < 1 || (p.orelu && x.x < 0.0f) ? 0.0f : x.x;
+    x.y = left < 2 || (p.orelu && x.y < 0.0f) ? 0.0f : x.y;
+    x.z = left < 3 || (p.orelu && x.z < 0.0f) ? 0.0f : x.z;
+    x.w = left < 4 || (p.orelu && x.w < 0.0f) ? 0.0f : x.w;
+    uint32_t amax = max(max(__float_as_uint(x.x) & 0x7fffffffu, __float_as_uint(x.y) & 0x7fffffffu),
+                        max(__float_as_uint(x.z) & 0x7fffffffu, __float_as_uint(x.w) & 0x7fffffffu));
+    amax = max(amax, (uint32_t)__shfl_xor((int)amax, 1));
+    amax = max(amax, (uint32_t)__shfl_xor((int)amax, 2));
+    amax = max(amax, (uint32_t)__shfl_xor((int)amax, 4));
+    const uint64_t idx = (uint64_t)row * (uint64_t)p.N + (uint64_t)(col0 + c4);
+    uint32_t Eb, w;
+    if (p.orounding) {
+        Eb = block_exponent<1>(amax, p.om);
+        w = small_quantise<1>(p, x, Eb, idx);
+    } else {
+        Eb = block_exponent<0>(amax, p.om);
+        w = small_quantise<0>(p, x, Eb, idx);
+    }
+    *reinterpret_cast<uint32_t *>(p.mant + row * p.okpad + col0 + c4) = w;
+    if (c4 == 0 && blk < p.oexp_ld) p.exps[row * p.oexp_ld + blk] = blk < p.onblk ? (uint8_t)Eb : (uint8_t)1;
+}
 
 // MT: row tiles of 32; ENC: the product leaves as an encoded operand
 template <int MT, bool ENC>
@@ -126,36 +161,191 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const Smal
             if (col0 + c4 + i < p.N) dst[i] = p.beta ? dst[i] + x[i] : x[i];
         return;
     }
-    uint32_t amax = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (col0 + c4 + i >= p.N || (p.orelu && x[i] < 0.0f)) x[i] = 0.0f;
-        amax = max(amax, __float_as_uint(x[i]) & 0x7fffffffu);
-    }
-    amax = max(amax, (uint32_t)__shfl_xor((int)amax, 1));
-    amax = max(amax, (uint32_t)__shfl_xor((int)amax, 2));
-    amax = max(amax, (uint32_t)__shfl_xor((int)amax, 4));
-    const uint32_t Eb = p.orounding ? block_exponent<1>(amax, p.om) : block_exponent<0>(amax, p.om);
-    uint32_t w = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint64_t idx = (uint64_t)row * (uint64_t)p.N + (uint64_t)(col0 + c4 + i);
-        const int q = p.orounding ? quantise<1>(x[i], Eb, p.om, (uint32_t)idx, (uint32_t)(idx >> 32), p.s0, p.s1)
-                                  : quantise<0>(x[i], Eb, p.om, 0u, 0u, 0u, 0u);
-        w |= ((uint32_t)q & 0xffu) << (8 * i);
-    }
-    *reinterpret_cast<uint32_t *>(p.mant + row * p.okpad + col0 + c4) = w;
-    if (c4 == 0) {
-        const int64_t blk = (int64_t)blockIdx.x;
-        if (blk < p.oexp_ld) p.exps[row * p.oexp_ld + blk] = blk < p.onblk ? (uint8_t)Eb : (uint8_t)1;
-    }
+    small_encode(p, make_float4(x[0], x[1], x[2], x[3]), row, col0, c4, (int64_t)blockIdx.x);
 }
+
+// The sum over the waves and what leaves: thread t of the first 64 MT NT adds four columns of a row over the waves, in their
+// order (part: [wave][16 MT][16 NT]); the 4 NT lanes of a row stay together, and with NT = 2 they hold one block of 32.
+template <int MT, int NT, bool ENC>
+__device__ __forceinline__ void few_finish(const SmallParams &p, const float *part, int t, int64_t row0, int64_t col0) {
+    if (t >= 64 * MT * NT) return;
+    const int r = t / (4 * NT), c4 = (t % (4 * NT)) * 4;
+    const int64_t row = row0 + r;
+    if (row >= p.M) return;
+    float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int w = 0; w < kSmallWaves; ++w) {
+        const float4 d = *reinterpret_cast<const float4 *>(part + (w * 16 * MT + r) * 16 * NT + c4);
+        x[0] += d.x, x[1] += d.y, x[2] += d.z, x[3] += d.w;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] *= p.final_scale;
+    if (!ENC) {
+        float *dst = p.C + row * p.ldc + col0 + c4;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (col0 + c4 + i < p.N) dst[i] = p.beta ? dst[i] + x[i] : x[i];
+        return;
+    }
+    small_encode(p, make_float4(x[0], x[1], x[2], x[3]), row, col0, c4, (int64_t)blockIdx.x);
+}
+
+// Few rows (at most 32): inference of a layer on a small batch.  What bounds it is how many bytes of B are on their way: a
+// contraction of 4096 left a wave of the kernel above four groups of blocks, two of them in flight, half of each matrix
+// instruction's 32 rows empty.  Here a wave owns 16 MT rows and 16 columns (32 where the output is converted: a block) and keeps
+// its part of the contraction in flight as asynchronous copies into LDS of its own, up to four chunks of 128 k ahead, no
+// barrier before the waves' sums meet; v_mfma_i32_16x16x32_i8 fits the rows.  As many chunks ahead as the workgroups that share
+// a compute unit leave room for: what is in flight per compute unit counts, not how many workgroups asked for it.  The
+// arithmetic per block, its order over the chunks and over the waves are those of the kernel above, so are the bits.
+// The kernel above -> this one: 16 x 4096 x 4096 11.7 -> 7.5 us (2.2 TB/s of B; converted 12.1 -> 8.7), 32 rows 13.7 -> 9.6,
+// 12 x 5586 x 435 11.9 -> 6.4, 31 x 4277 x 15967 28.5 -> 26.8, 1 x 512 x 512 3.5 -> 3.05.
+// LDS of a chunk: rows of 128 bytes, A's 16 MT, then B's, 16-byte pieces XORed with row % 8 (copies of 8 rows and fragment
+// reads of 16 rows by 8 bytes then cover the banks evenly), behind them the exponent bytes of the chunk's four blocks: rows
+// 0 .. 31, columns 0 .. 31, a word each.
+struct FewParams : SmallParams {
+    int32_t ahead;               // chunks in flight per wave, 1 to 4
+};
+template <int MT, bool ENC>
+struct Few {
+    static constexpr int NT = ENC ? 2 : 1;
+    static constexpr int kChunk = (MT + NT) * 2048 + 256;
+    static constexpr int kCopies = 2 * (MT + NT) + 1;
+};
+template <int MT, bool ENC>
+__global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const FewParams p) {
+    typedef Few<MT, ENC> R;
+    constexpr int NT = R::NT;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    const int t = threadIdx.x, lane = t & 63, l16 = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int64_t col0 = (int64_t)blockIdx.x * (16 * NT);
+    // the columns that exist; a workgroup of nothing but padding (encoded outputs) reads the last one
+    const int64_t bcol0 = col0 < p.N ? col0 : p.N - 1;
+    const int rows = (int)p.M, cols = (int)(p.N - bcol0 < 16 * NT ? p.N - bcol0 : 16 * NT);       // both at least 1
+    const uint32_t base = wave * (uint32_t)(p.ahead * R::kChunk);
+    // a copy moves 8 rows of 128 bytes; rows and columns behind the last read it again
+    const int r8 = lane >> 3, piece = ((lane & 7) ^ r8) * 16;
+    uint32_t voff[2 * (MT + NT)];
+#pragma unroll
+    for (int i = 0; i < 2 * MT; ++i) voff[i] = (uint32_t)(8 * i + r8 < rows ? 8 * i + r8 : rows - 1) * (uint32_t)p.kpad + piece;
+#pragma unroll
+    for (int i = 0; i < 2 * NT; ++i) voff[2 * MT + i] = (uint32_t)(8 * i + r8 < cols ? 8 * i + r8 : cols - 1) * (uint32_t)p.kpad + piece;
+    const int er = lane & 31;
+    const uint8_t *esrc = lane < 32 ? p.eA + (int64_t)(er < rows ? er : rows - 1) * p.eA_ld : p.eB + (bcol0 + (er < cols ? er : cols - 1)) * p.eB_ld;
+    const uint8_t *a0 = p.A, *b0 = p.B + bcol0 * p.kpad;
+    auto request = [&](int chunk, int buf) {
+        const uint32_t to = base + buf * R::kChunk;
+        const int64_t k = (int64_t)chunk * 128;
+#pragma unroll
+        for (int i = 0; i < 2 * MT; ++i) async_copy16(a0 + k, voff[i], to + i * 1024);
+#pragma unroll
+        for (int i = 0; i < 2 * NT; ++i) async_copy16(b0 + k, voff[2 * MT + i], to + (2 * MT + i) * 1024);
+        async_copy4_at(esrc + 4 * (int64_t)chunk, to + (MT + NT) * 2048);
+    };
+    float acc[MT][NT][4] = {};
+    const int mine = p.groups > wave ? (p.groups - wave + kSmallWaves - 1) / kSmallWaves : 0;     // chunks wave, wave + 8, ...
+    const int ahead = mine < p.ahead ? mine : p.ahead;
+    for (int i = 0; i < ahead; ++i) request(wave + i * kSmallWaves, i);
+    const uint32_t frag = l16 * 128 + (q & 1) * 8, sw = l16 & 7;
+    int buf = 0;
+#pragma unroll 1
+    for (int i = 0; i < mine; ++i) {
+        // chunk i has landed when only those behind it are under way
+        const int behind = mine - 1 - i < p.ahead - 1 ? mine - 1 - i : p.ahead - 1;
+        if (behind >= 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * R::kCopies) : "memory");
+        else if (behind == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * R::kCopies) : "memory");
+        else if (behind == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(R::kCopies) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const uint8_t *c = lds + base + buf * R::kChunk;
+        v2i a[MT][4], b[NT][4];
+        v4u ea[MT];
+        uint32_t eb[NT];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t off = frag + (((2 * k + (q >> 1)) ^ sw) * 16);
+#pragma unroll
+            for (int m = 0; m < MT; ++m) a[m][k] = *reinterpret_cast<const v2i *>(c + off + m * 2048);
+#pragma unroll
+            for (int n = 0; n < NT; ++n) b[n][k] = *reinterpret_cast<const v2i *>(c + off + (MT + n) * 2048);
+        }
+#pragma unroll
+        for (int m = 0; m < MT; ++m) ea[m] = *reinterpret_cast<const v4u *>(c + (MT + NT) * 2048 + (m * 16 + 4 * q) * 4);
+#pragma unroll
+        for (int n = 0; n < NT; ++n) eb[n] = *reinterpret_cast<const uint32_t *>(c + (MT + NT) * 2048 + 128 + (n * 16 + l16) * 4);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                     // read: the buffer may be filled again
+        if (i + p.ahead < mine) request(wave + (i + p.ahead) * kSmallWaves, buf);
+        buf = buf + 1 == p.ahead ? 0 : buf + 1;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            float scale[NT];
+#pragma unroll
+            for (int n = 0; n < NT; ++n) {
+                const uint32_t e = (eb[n] >> (8 * k)) & 0xffu;
+                scale[n] = __uint_as_float((e > 254u ? 254u : e) << 23);
+            }
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                v4i from;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const uint32_t e = (ea[m][v] >> (8 * k)) & 0xffu;
+                    from[v] = (int)(((e > 254u ? 254u : e) << 23) | 0x400000u);          // 1.5 * 2^(E - 127)
+                }
+#pragma unroll
+                for (int n = 0; n < NT; ++n) {
+                    const v4i sum = __builtin_amdgcn_mfma_i32_16x16x32_i8(__builtin_bit_cast(long, a[m][k]), __builtin_bit_cast(long, b[n][k]), from, 0, 0, 0);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[m][n][v] = fmaf(__int_as_float(sum[v]) - __int_as_float(from[v]), scale[n], acc[m][n][v]);
+                }
+            }
+        }
+    }
+    __syncthreads();
+    float *part = reinterpret_cast<float *>(lds);
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) part[(wave * 16 * MT + m * 16 + 4 * q + v) * 16 * NT + n * 16 + l16] = acc[m][n][v];
+    __syncthreads();
+    few_finish<MT, NT, ENC>(p, part, t, 0, col0);
+}
+
+constexpr int kFewLds = 160 * 1024;
+template <int MT, bool ENC>
+int launch_few_t(const SmallParams &p, int64_t cols, hipStream_t s) {
+    static std::atomic<bool> configured{false};
+    void (*kernel)(FewParams) = &gemm_small_kernel<MT, ENC>;
+    if (allow_dynamic_lds(configured, reinterpret_cast<const void *>(kernel), kFewLds) != HBFP_OK) return HBFP_ERR_LAUNCH;
+    const int64_t wgs = ceil_div(cols, 16 * Few<MT, ENC>::NT), per_cu = ceil_div(wgs, 256);
+    const int chunk = kSmallWaves * Few<MT, ENC>::kChunk;                  // of all waves
+    FewParams f;
+    static_cast<SmallParams &>(f) = p;
+    int64_t room = kFewLds / per_cu / chunk;
+    const int64_t most = ceil_div(p.groups, kSmallWaves);
+    room = room > most ? most : room;
+    f.ahead = (int32_t)(room > 4 ? 4 : room < 1 ? 1 : room);
+    int bytes = f.ahead * chunk;
+    const int sums = kSmallWaves * 16 * MT * 16 * Few<MT, ENC>::NT * 4;
+    bytes = bytes > sums ? bytes : sums;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)wgs), dim3(kSmallThreads), bytes, s, f);
+    return launch_status();
+}
+int launch_few(const SmallParams &p, bool enc, int64_t cols, hipStream_t s) {
+    const bool two = p.M > 16;
+    if (enc) return two ? launch_few_t<2, true>(p, cols, s) : launch_few_t<1, true>(p, cols, s);
+    return two ? launch_few_t<2, false>(p, cols, s) : launch_few_t<1, false>(p, cols, s);
+}
+// Whether a product that runs here takes the kernel for few rows.  Up to three chunks of k per product (four where it is
+// converted) the start of a workgroup with that much LDS is what counts, and the other kernel is ahead.
+bool few_rows_ok(const SmallParams &p, bool enc) { return p.M <= 32 && p.groups >= (enc ? 5 : 4) && p.kpad <= (1 << 26); }
 
 template <int MT>
 int launch_small(const SmallParams &p, bool enc, unsigned workgroups, hipStream_t s) {
     const dim3 grid(workgroups, (unsigned)ceil_div(p.M, 32 * MT));
-    if (enc) hipLaunchKernelGGL((gemm_small_kernel<MT, true>), grid, dim3(kSmallThreads), 0, s, p);
-    else hipLaunchKernelGGL((gemm_small_kernel<MT, false>), grid, dim3(kSmallThreads), 0, s, p);
+    void (*fp32)(SmallParams) = &gemm_small_kernel<MT, false>, (*encoded)(SmallParams) = &gemm_small_kernel<MT, true>;
+    hipLaunchKernelGGL(enc ? encoded : fp32, grid, dim3(kSmallThreads), 0, s, p);
     return launch_status();
 }
 
@@ -216,6 +406,7 @@ int launch_gemm_small(const GemmArgs &a, hipStream_t s, const hbfp_tensor *enc, 
         p.s1 = (uint32_t)(enc->seed >> 32);
         cols = enc->kpad;                                      // the padding of the rows too
     }
+    if (few_rows_ok(p, enc != nullptr)) return launch_few(p, enc != nullptr, cols, s);
     const unsigned workgroups = (unsigned)ceil_div(cols, 32);
     return small_row_tiles(a, nullptr) == 1 ? launch_small<1>(p, enc != nullptr, workgroups, s) : launch_small<2>(p, enc != nullptr, workgroups, s);
 }

@@ -1,0 +1,40 @@
+"""Products of at most 32 rows: the kernel that keeps a wave's part of the contraction in flight.
+
+Sizes at the edges of its tiles (16 and 32 rows, 16 and 32 columns, chunks of 128 k, 8 waves, the ring of chunks), outputs in
+FP32 with a row pitch and C +=, and converted: padding columns of the encoded output belong to workgroups without columns.
+Integer inputs: every sum is exact, so C equals the FP64 product; the converted product equals hbfp_encode of it.
+"""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _operands(M, K, N, block):
+    from paper_1804_01526_amd import hbfp
+    g = torch.Generator(device="cuda").manual_seed(M * 7919 + K * 31 + N)
+    A = torch.randint(-20, 21, (M, K), device="cuda", generator=g).float() * 2.0 ** torch.randint(-3, 4, (M, 1), device="cuda", generator=g)
+    B = torch.randint(-20, 21, (K, N), device="cuda", generator=g).float() * 2.0 ** torch.randint(-3, 4, (1, N), device="cuda", generator=g)
+    a, b = hbfp.encode(A, 1, hbfp.make_format(8, 1, block, hbfp.RNE)), hbfp.encode(B, 0, hbfp.make_format(8, block, 1, hbfp.RNE))
+    return a, b, hbfp.decode(a).double() @ hbfp.decode(b).double()
+
+
+@pytest.mark.parametrize("M,K,N", [(1, 385, 1), (1, 4096, 15), (16, 512, 17), (17, 640, 16), (32, 1024, 33), (5, 1500, 385), (31, 8200, 100), (16, 3000, 4100),
+                                   (20, 2300, 4097)])
+@pytest.mark.parametrize("block", [32, 24])
+def test_few_rows(M, K, N, block):
+    from paper_1804_01526_amd import hbfp
+    print(f"[rows] {M}x{K}x{N} block={block}", flush=True)
+    a, b, want = _operands(M, K, N, block)
+    buf = torch.full((M, N + 5), 3.0, device="cuda")
+    C = hbfp.gemm(a, b, out=buf[:, :N])
+    assert torch.equal(C.double(), want)
+    hbfp.gemm(a, b, out=buf[:, :N], beta=1.0)
+    assert torch.equal(buf[:, :N].double(), (2 * want).float().double())
+    assert bool((buf[:, N:] == 3.0).all())
+    for relu in (False, True):
+        for rounding, seed in ((hbfp.RNE, 0), (hbfp.STOCHASTIC, 77)):
+            fmt = hbfp.make_format(8, 1, 32, rounding, seed)
+            x = want.float().relu() if relu else want.float()
+            ref, out = hbfp.encode(x, 1, fmt), hbfp.gemm_bfp(a, b, fmt, 1, relu=relu)
+            assert torch.equal(out.mant, ref.mant) and torch.equal(out.exps, ref.exps)

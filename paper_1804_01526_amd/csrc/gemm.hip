@@ -1421,8 +1421,30 @@ int launch_gemm_conv_i8(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int
 // the workspace, then the kernel above runs on them with F16 set.  workspace: [split-k slices][A plane][B plane]
 // [row words of A][column words of B].
 namespace {
-__global__ __launch_bounds__(256) void mant_to_f16_kernel(const int16_t *src, _Float16 *dst, int64_t n8) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += (int64_t)gridDim.x * 256) {
+// Both planes and the scale words in one launch: workgroups 0 .. first[1] - 1 turn A's mantissas, the next up to first[2] B's, 8
+// per thread and step, the others make the words (136 x 3948 x 533: three launches of 3 us each, and their gaps, in front of a
+// product of 10).
+struct F16Prepare {
+    const int16_t *src[2];
+    _Float16 *dst[2];
+    int64_t n8[2];
+    uint32_t first[3];
+    uint32_t word_blocks;                              // of each operand
+    WordParams words;
+};
+__global__ __launch_bounds__(256) void f16_prepare_kernel(const F16Prepare q) {
+    if (blockIdx.x >= q.first[2]) {
+        const uint32_t block = blockIdx.x - q.first[2];
+        const int z = block >= q.word_blocks;
+        scale_words_block(q.words, block - (z ? q.word_blocks : 0u), z, (int)threadIdx.x);
+        return;
+    }
+    const int z = blockIdx.x >= q.first[1];
+    const int16_t *src = z ? q.src[1] : q.src[0];
+    _Float16 *dst = z ? q.dst[1] : q.dst[0];
+    const int64_t n8 = z ? q.n8[1] : q.n8[0];
+    const uint32_t wg = blockIdx.x - (z ? q.first[1] : 0u), wgs = z ? q.first[2] - q.first[1] : q.first[1];
+    for (int64_t i = (int64_t)wg * 256 + threadIdx.x; i < n8; i += (int64_t)wgs * 256) {
         const v4i x = reinterpret_cast<const v4i *>(src)[i];
         v8h y;
 #pragma unroll
@@ -1458,13 +1480,21 @@ int launch_gemm_f16(const GemmArgs &a, void *workspace, hipStream_t s) {
     w += f16_plane_bytes(a.M, a.kpad);
     _Float16 *planeB = (_Float16 *)w;
     w += f16_plane_bytes(a.N, a.kpad);
+    uint32_t *wordsA = (uint32_t *)w, *wordsB = (uint32_t *)(w + word_bytes(a.M, a.expA_ld));
     {
-        const int64_t na = a.M * a.kpad / 8, nb = a.N * a.kpad / 8;       // kpad is a multiple of 128
-        int64_t ga = ceil_div(na, 256), gb = ceil_div(nb, 256);
-        ga = ga > 65536 ? 65536 : ga;
-        gb = gb > 65536 ? 65536 : gb;
-        hipLaunchKernelGGL(mant_to_f16_kernel, dim3((unsigned)ga), dim3(256), 0, s, (const int16_t *)a.mantA, planeA, na);
-        hipLaunchKernelGGL(mant_to_f16_kernel, dim3((unsigned)gb), dim3(256), 0, s, (const int16_t *)a.mantB, planeB, nb);
+        F16Prepare f = {};
+        f.src[0] = (const int16_t *)a.mantA, f.src[1] = (const int16_t *)a.mantB;
+        f.dst[0] = planeA, f.dst[1] = planeB;
+        f.n8[0] = a.M * a.kpad / 8, f.n8[1] = a.N * a.kpad / 8;             // kpad is a multiple of 128
+        for (int z = 0; z < 2; ++z) {
+            const int64_t wgs = ceil_div(f.n8[z], 256);
+            f.first[z + 1] = f.first[z] + (uint32_t)(wgs > 65536 ? 65536 : wgs);
+        }
+        f.words = scale_word_params(a.expA, a.expA_ld, a.M, a.expB, a.expB_ld, a.N, (int)a.expA_ld, 0u, wordsA, wordsB, nullptr, nullptr);
+        const int64_t blocks = scale_word_blocks(f.words);
+        if (blocks > 0x3fffffff) return HBFP_ERR_ARG;
+        f.word_blocks = (uint32_t)blocks;
+        hipLaunchKernelGGL(f16_prepare_kernel, dim3((unsigned)(f.first[2] + 2 * blocks)), dim3(256), 0, s, f);
         if (launch_status() != HBFP_OK) return HBFP_ERR_LAUNCH;
     }
     p.A = (const uint8_t *)planeA;
@@ -1496,11 +1526,8 @@ int launch_gemm_f16(const GemmArgs &a, void *workspace, hipStream_t s) {
     q.g = p;
     q.mpad = ceil_div(a.M, 128) * 128;
     q.npad = ceil_div(a.N, 128) * 128;
-    q.wA = (const uint32_t *)w;
-    q.wB = (const uint32_t *)(w + word_bytes(a.M, a.expA_ld));
-    int rc = launch_scale_words(a.expA, a.expA_ld, a.M, a.expB, a.expB_ld, a.N, (int)a.expA_ld, 0u, const_cast<uint32_t *>(q.wA),
-                                const_cast<uint32_t *>(q.wB), nullptr, nullptr, s);
-    if (rc != HBFP_OK) return rc;
+    q.wA = wordsA;
+    q.wB = wordsB;
     static std::atomic<bool> configured[2];
     const void *const kernels[2] = {reinterpret_cast<const void *>(&gemm_i8_w8_kernel<2, false, true>),
                                     reinterpret_cast<const void *>(&gemm_i8_w8_kernel<0, false, true>)};
@@ -1510,7 +1537,7 @@ int launch_gemm_f16(const GemmArgs &a, void *workspace, hipStream_t s) {
                                     : dim3((unsigned)(ceil_div(tm * tn, 8) * 8), (unsigned)p.splits);
     if (p.spb == 2) hipLaunchKernelGGL((gemm_i8_w8_kernel<2, false, true>), grid, dim3(kW8Threads), kW8LdsBytes, s, q);
     else hipLaunchKernelGGL((gemm_i8_w8_kernel<0, false, true>), grid, dim3(kW8Threads), kW8LdsBytes, s, q);
-    rc = launch_status();
+    int rc = launch_status();
     if (rc != HBFP_OK) return rc;
     if (p.splits > 1) {
         rc = launch_splitk_reduce(p, s);

@@ -66,3 +66,25 @@ def test_one_exponent_per_row(M, K, N, beta):
     hbfp.gemm(a, b, out=C[:, :N], beta=beta)
     assert torch.equal(C[:, :N].double(), want + (5.0 if beta else 0.0))
     assert bool((C[:, N:] == 5.0).all())
+
+
+# 12-bit operands as FP16 planes: a row's factor comes from its largest exponent byte, wherever that lies (16 lanes read four
+# blocks each, the last word of a row may hold 1 to 4 of them); the other kernel prepares planes and words in one launch
+@pytest.mark.parametrize("kernel", [F16P, FP16])
+@pytest.mark.parametrize("blocks,at", [(1, 0), (5, 4), (63, 62), (64, 0), (257, 256), (301, 299)])
+def test_largest_exponent_of_a_row(kernel, blocks, at):
+    from paper_1804_01526_amd import hbfp
+    M, N, K = 33, 40, 64 * blocks
+    g = torch.Generator(device="cuda").manual_seed(blocks)
+    A = torch.randint(-3, 4, (M, K), device="cuda", generator=g).float()
+    B = torch.randint(-3, 4, (K, N), device="cuda", generator=g).float()
+    A[:, ::64] = 2047.0
+    B[::64, :] = 2047.0
+    A[:, 64 * at:64 * at + 64] *= 1024.0
+    A[::2] = A[::2].flip(1)
+    a, b = hbfp.encode(A, 1, hbfp.make_format(12, 1, 64, hbfp.RNE)), hbfp.encode(B, 0, hbfp.make_format(12, 64, 1, hbfp.RNE))
+    want = hbfp.decode(a).double() @ hbfp.decode(b).double()
+    C = hbfp.gemm(a, b, kernel=kernel).double()
+    # FP32 sums of exact products, one rounding per product at the worst
+    bound = 2.0 ** -24 * (K + 2) * (hbfp.decode(a).double().abs() @ hbfp.decode(b).double().abs())
+    assert bool(((C - want).abs() <= bound).all())

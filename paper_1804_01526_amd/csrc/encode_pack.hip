@@ -13,8 +13,9 @@
 // use); block maxima are DPP reductions over the lanes of a tile (tiles), of a tile's row (1 x 24 blocks) or a register
 // maximum and one exchange (24 x 1 blocks).  The mantissas of each output go to an LDS tile [operand row][k] without
 // padding; after one barrier the workgroup streams the stored operand out in 16-byte pieces and writes the packed
-// planes from the same tile with the arithmetic of the pack kernels (bf_pack.h, mx_pack.h).  Two workgroups share a
-// compute unit (2 x 78 KB of LDS, 128 registers), so one converts while the other loads or stores.
+// planes from the same tile with the arithmetic of the pack kernels (bf_pack.h, mx_pack.h).  (Sources of few regions: a half
+// of 96 rows per workgroup, launch_encode_pack_batch.)  Two workgroups share a compute unit (2 x 78 KB of LDS, 128
+// registers), so one converts while the other loads or stores.
 #include "bf_pack.h"
 #include "bfp_device.h"
 #include "mx_pack.h"
@@ -63,17 +64,20 @@ __device__ __forceinline__ uint32_t ep_pack4(int a, int b, int c, int d) {
     return __builtin_amdgcn_perm(cd, ab, 0x05040100u);
 }
 
-template <int ROUND, int L>
+// HV: halves of 96 source rows that a workgroup converts.  One half per workgroup (bf16 planes: 96 rows are 3 k-steps of 32 or 3
+// row tiles) is for sources that would give the chip too few workgroups.
+template <int ROUND, int L, int HV>
 __global__ __launch_bounds__(kEpThreads, 4) void encode_pack_kernel(const EpBatch batch) {
+    static_assert(HV == 2 || L == 2, "limb planes come in k-steps of 64");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const EpParams &p = batch.p[blockIdx.z];
     if ((int)blockIdx.x >= p.gx || (int)blockIdx.y >= p.gy) return;       // the grid is that of the largest source
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int j = lane & 7, h = (lane >> 3) & 1, tw = lane >> 4;
     const int tcl = (wave & 1) * 4 + tw;                                  // tile column of the region
-    for (int half = 0; half < 1024 / kEpThreads; ++half) {
+    for (int half = 0; half < HV; ++half) {
     const int trl = half * (kEpThreads / 128) + (wave >> 1);                               // tile row of the region
-    const int64_t tc = (int64_t)blockIdx.x * 8 + tcl, tr = (int64_t)blockIdx.y * 8 + trl;
+    const int64_t tc = (int64_t)blockIdx.x * 8 + tcl, tr = (int64_t)blockIdx.y * (4 * HV) + trl;
     const int64_t row0 = tr * 24 + h * 12, col0 = tc * 24 + 4 * j;
     float v[12][4];
     const int64_t tc_wave = (int64_t)blockIdx.x * 8 + (wave & 1) * 4;    // first of the wave's four tile columns
@@ -210,25 +214,27 @@ __global__ __launch_bounds__(kEpThreads, 4) void encode_pack_kernel(const EpBatc
         const uint8_t *E = T + kEpTileBytes;
         // Everything that depends only on the workgroup, the wave or the loop trip stays on the scalar unit; a lane adds
         // 32-bit offsets of its own (the host checks that 192 rows of an operand span less than 2^31 bytes).
-        const int64_t orow0 = (int64_t)(o.axis == 1 ? blockIdx.y : blockIdx.x) * kEpRegion;   // first operand row of the region
+        const int region = o.axis == 1 ? 96 * HV : kEpRegion, nb = o.axis == 1 ? 8 : 4 * HV;  // operand rows, blocks along k of the region
+        const int64_t orow0 = (int64_t)(o.axis == 1 ? blockIdx.y : blockIdx.x) * region;      // first operand row of the region
         const int64_t kreg = o.axis == 1 ? blockIdx.x : blockIdx.y;                           // region index along k
         if (blockIdx.x == 0 && blockIdx.y == 0 && t == 0) o.header[1] = o.mark;
-        const int rows_left = (int)(o.R - orow0 < kEpRegion ? (o.R - orow0 < 0 ? 0 : o.R - orow0) : kEpRegion);
+        const int rows_left = (int)(o.R - orow0 < region ? (o.R - orow0 < 0 ? 0 : o.R - orow0) : region);
         // ---- stored operand: 16-byte pieces, two per stored block of 32 (24 mantissas and 8 bytes of padding);
-        // a thread keeps its block and half and walks down the rows, 32 at a time
+        // a thread keeps its block and half and walks down the rows, 32 or 64 at a time
         {
-            const int b = (t >> 1) & 7, sh = t & 1, r0 = t >> 4;
-            const bool blk_ok = kreg * 8 + b < o.nb_stored;
-            uint8_t *dst0 = o.mant + orow0 * o.kpad + kreg * 256;                              // uniform
+            const bool four = HV == 1 && o.axis == 0;
+            const int b = (t >> 1) & (four ? 3 : 7), sh = t & 1, r0 = four ? t >> 3 : t >> 4, step = four ? 64 : 32;
+            const bool blk_ok = kreg * nb + b < o.nb_stored;
+            uint8_t *dst0 = o.mant + orow0 * o.kpad + kreg * (nb * 32);                        // uniform
             const uint32_t goff = (uint32_t)r0 * (uint32_t)o.kpad + (uint32_t)(b * 32 + 16 * sh);
-            const uint32_t gstep = 32u * (uint32_t)o.kpad;
+            const uint32_t gstep = (uint32_t)step * (uint32_t)o.kpad;
             const uint8_t *src0 = T + r0 * kEpStride + 24 * b + 16 * sh;
 #pragma unroll
-            for (int i = 0; i < 16 * kEpRegion / kEpThreads; ++i) {
-                if (blk_ok && r0 + 32 * i < rows_left) {
-                    const v2i lo = *reinterpret_cast<const v2i *>(src0 + 32 * i * kEpStride);
+            for (int i = 0; i < 3 * HV; ++i) {
+                if (blk_ok && r0 + step * i < rows_left) {
+                    const v2i lo = *reinterpret_cast<const v2i *>(src0 + step * i * kEpStride);
                     v2i hi = {0, 0};
-                    if (sh == 0) hi = *reinterpret_cast<const v2i *>(src0 + 32 * i * kEpStride + 8);
+                    if (sh == 0) hi = *reinterpret_cast<const v2i *>(src0 + step * i * kEpStride + 8);
                     typedef unsigned v4u_t __attribute__((ext_vector_type(4)));
                     const v4u_t w = {(unsigned)lo[0], (unsigned)lo[1], (unsigned)hi[0], (unsigned)hi[1]};
                     __builtin_nontemporal_store(w, reinterpret_cast<v4u_t *>(dst0 + (goff + (uint32_t)i * gstep)));
@@ -237,8 +243,8 @@ __global__ __launch_bounds__(kEpThreads, 4) void encode_pack_kernel(const EpBatc
         }
         if (t < 2 * kEpRegion) {
             const int rl = t >> 1, half = t & 1;
-            if (rl < rows_left && kreg * 8 + 4 * half < o.exp_ld)                              // exp_ld is a multiple of 4
-                *reinterpret_cast<uint32_t *>(o.exps + orow0 * o.exp_ld + kreg * 8 + ((uint32_t)rl * (uint32_t)o.exp_ld + 4u * half)) =
+            if (rl < rows_left && 4 * half < nb && kreg * nb + 4 * half < o.exp_ld)           // exp_ld is a multiple of 4
+                *reinterpret_cast<uint32_t *>(o.exps + orow0 * o.exp_ld + kreg * nb + ((uint32_t)rl * (uint32_t)o.exp_ld + 4u * half)) =
                     *reinterpret_cast<const uint32_t *>(E + rl * 8 + 4 * half);
         }
         // ---- packed planes: a wave takes 16 operand rows of one k-step of 64 at a time (lane = row, quarter of the k-step)
@@ -246,13 +252,17 @@ __global__ __launch_bounds__(kEpThreads, 4) void encode_pack_kernel(const EpBatc
         const int q = lane & 3, r4 = lane >> 2;
         const uint8_t *tl = T + r4 * kEpStride + q * 16;     // this lane's 16 mantissas of k-step 0 of rows 0..15
         const uint8_t *el = E + r4 * 8;
+        const int nks = HV == 1 && o.axis == 0 ? 2 : 3, units = region / 16 * nks;            // groups of 16 rows x k-steps of 64
 #pragma unroll
-        for (int i = 0; i < (36 + kEpThreads / 64 - 1) / (kEpThreads / 64); ++i) {
-            const int unit = wave + (kEpThreads / 64) * i;   // 12 groups of 16 rows x 3 k-steps
-            if (unit >= 36) break;
-            const int r16 = unit / 3, ksl = unit - 3 * r16;
-            const int64_t rt = (orow0 >> 5) + (r16 >> 1), ks = kreg * 3 + ksl;
-            if (rt >= o.row_tiles || ks >= o.ksteps) continue;                                 // uniform over the wave
+        for (int i = 0; i < (HV == 2 ? 5 : 3); ++i) {
+            const int unit = wave + (kEpThreads / 64) * i;
+            if (unit >= units) break;
+            const int r16 = nks == 2 ? unit / 2 : unit / 3, ksl = unit - nks * r16;
+            const int64_t rt = (orow0 >> 5) + (r16 >> 1);
+            const int64_t ks = kreg * 3 + ksl;               // HV == 2 (regions of three k-steps of 64)
+            if (rt >= o.row_tiles || (HV == 2 && ks >= o.ksteps)) continue;                    // uniform over the wave
+            const int64_t ks32 = HV == 2 ? 2 * ks + (q >> 1) : kreg * (nb * 3 / 4) + 2 * ksl + (q >> 1);
+            if (HV == 1 && (ks32 >= 2 * (int64_t)o.ksteps || 2 * ksl + (q >> 1) >= nb * 3 / 4)) continue;
             v2i raw[2];
             int ex[2];
 #pragma unroll
@@ -269,7 +279,7 @@ __global__ __launch_bounds__(kEpThreads, 4) void encode_pack_kernel(const EpBatc
                     const int jl = ksl * 8 + q * 2 + oc;
                     const int e = el[r16 * 128 + (jl * 43 >> 7)];
                     bad |= ex[oc] != 255 && !bf_exponent_ok(e);
-                    *reinterpret_cast<v4u *>(o.planes + bf_piece_offset(rt, 2 * ks + (q >> 1), 2 * (int64_t)o.ksteps, q & 1, oc,
+                    *reinterpret_cast<v4u *>(o.planes + bf_piece_offset(rt, ks32, 2 * (int64_t)o.ksteps, q & 1, oc,
                                                                         (r16 & 1) * 16 + r4)) = bf_octet_i8(raw[oc], e, o.m);
                 }
             } else {
@@ -302,7 +312,7 @@ bool encode_pack_ok(const float *src, int64_t ld, int n, const hbfp_tensor *cons
 
 // fills the parameters of one source; marks its packed buffers
 static int ep_params_of(const float *src, int64_t ld, int n, const hbfp_tensor *const *outs, void *const *packed, hipStream_t s,
-                        EpParams *out) {
+                        EpParams *out, int64_t *rows_covered) {
     const hbfp_tensor *f = outs[0];
     EpParams p = {};
     p.src = src;
@@ -347,6 +357,7 @@ static int ep_params_of(const float *src, int64_t ld, int n, const hbfp_tensor *
     }
     p.gx = (int32_t)ceil_div(ext_cols, kEpRegion);
     p.gy = (int32_t)ceil_div(ext_rows, kEpRegion);
+    *rows_covered = ext_rows;
     *out = p;
     return HBFP_OK;
 }
@@ -365,25 +376,31 @@ bool encode_pack_batch_ok(int nsrc, const hbfp_tensor *const *const *outs) {
 int launch_encode_pack_batch(int nsrc, const float *const *src, const int64_t *ld, const int *n, const hbfp_tensor *const *const *outs,
                              void *const *const *packed, hipStream_t s) {
     EpBatch b = {};
+    int64_t ext_rows[kEpBatch], regions = 0;
+    for (int i = 0; i < nsrc; ++i) {
+        const int rc = ep_params_of(src[i], ld[i], n[i], outs[i], packed[i], s, &b.p[i], &ext_rows[i]);
+        if (rc != HBFP_OK) return rc;
+        regions += (int64_t)b.p[i].gx * b.p[i].gy;
+    }
+    const int which = ep_which(outs[0][0]);
+    // One half per workgroup while 192 x 192 regions are at most 400: a workgroup's 15 us are load latency, conversion and packing
+    // one after the other, and a compute unit needs two of them to overlap.  Regions -> halves: 1337 x 1500 (64 regions) 19.2 ->
+    // 13.3 us (stochastic rounding 40.7 -> 23.9), 2000^2 (121) 19.4 -> 14.6, 3000^2 (256) 24.4 -> 22.0, 3000 x 4096 (352) 30.6 ->
+    // 29.3; level at 4096^2 (484), behind at 6000 x 5000 (864) 62.7 and 66.4.
+    const bool halves = (which & 1) && regions <= 400;
     int gx = 0, gy = 0;
     for (int i = 0; i < nsrc; ++i) {
-        const int rc = ep_params_of(src[i], ld[i], n[i], outs[i], packed[i], s, &b.p[i]);
-        if (rc != HBFP_OK) return rc;
+        if (halves) b.p[i].gy = (int32_t)ceil_div(ext_rows[i], 96);
         gx = b.p[i].gx > gx ? b.p[i].gx : gx;
         gy = b.p[i].gy > gy ? b.p[i].gy : gy;
     }
     const dim3 grid((unsigned)gx, (unsigned)gy, (unsigned)nsrc);
-    static std::atomic<bool> configured[4];
-    const void *const kernels[4] = {reinterpret_cast<const void *>(&encode_pack_kernel<0, 1>), reinterpret_cast<const void *>(&encode_pack_kernel<0, 2>),
-                                    reinterpret_cast<const void *>(&encode_pack_kernel<1, 1>), reinterpret_cast<const void *>(&encode_pack_kernel<1, 2>)};
-    const int which = ep_which(outs[0][0]);
-    if (allow_dynamic_lds(configured[which], kernels[which], kEpLds) != HBFP_OK) return HBFP_ERR_LAUNCH;
-    switch (which) {
-        case 0: hipLaunchKernelGGL((encode_pack_kernel<0, 1>), grid, dim3(kEpThreads), kEpLds, s, b); break;
-        case 1: hipLaunchKernelGGL((encode_pack_kernel<0, 2>), grid, dim3(kEpThreads), kEpLds, s, b); break;
-        case 2: hipLaunchKernelGGL((encode_pack_kernel<1, 1>), grid, dim3(kEpThreads), kEpLds, s, b); break;
-        default: hipLaunchKernelGGL((encode_pack_kernel<1, 2>), grid, dim3(kEpThreads), kEpLds, s, b); break;
-    }
+    static std::atomic<bool> configured[6];
+    void (*const kernels[6])(EpBatch) = {&encode_pack_kernel<0, 1, 2>, &encode_pack_kernel<0, 2, 2>, &encode_pack_kernel<1, 1, 2>,
+                                         &encode_pack_kernel<1, 2, 2>, &encode_pack_kernel<0, 2, 1>, &encode_pack_kernel<1, 2, 1>};
+    const int k = halves ? 4 + (which >> 1) : which;
+    if (allow_dynamic_lds(configured[k], reinterpret_cast<const void *>(kernels[k]), kEpLds) != HBFP_OK) return HBFP_ERR_LAUNCH;
+    hipLaunchKernelGGL(kernels[k], grid, dim3(kEpThreads), kEpLds, s, b);
     return launch_status();
 }
 

@@ -746,9 +746,9 @@ __global__ __launch_bounds__(kW8Threads, 4) void gemm_i8_w8_kernel(const W8Param
         rowc = *reinterpret_cast<const uint32_t *>(base_ + offW + (s) * 512);                                 \
         a = *reinterpret_cast<const v4i *>(base_ + ((s_) ? fragA1 : fragA0));                                 \
         b[0] = *reinterpret_cast<const v4i *>(base_ + ((s_) ? fragB1 : fragB0));                              \
-        b[1] = *reinterpret_cast<const v4i *>(base_ + ((s_) ? fragB1 : fragB0) + 2048);                       \
+        if (NI == 2) b[1] = *reinterpret_cast<const v4i *>(base_ + ((s_) ? fragB1 : fragB0) + 2048);          \
         sb[set][0] = *reinterpret_cast<const float *>(base_ + offS + (s) * 512);                              \
-        sb[set][1] = *reinterpret_cast<const float *>(base_ + offS + (s) * 512 + 128);                        \
+        if (NI == 2) sb[set][1] = *reinterpret_cast<const float *>(base_ + offS + (s) * 512 + 128);           \
     }
     // One k-step: both matrix instructions, then whatever has to happen between issue and use (MIDDLE:
     // the stage hand-over and the next step's LDS reads), then 32 subtractions, the next step's row
@@ -757,38 +757,39 @@ __global__ __launch_bounds__(kW8Threads, 4) void gemm_i8_w8_kernel(const W8Param
     {                                                                                                   \
         if (FIRST) {                                                                                    \
             d0 = ops::mma(a, b[0], ops::start(cin));                                                    \
-            d1 = ops::mma(a, b[1], ops::start(cin));                                                    \
+            if (NI == 2) d1 = ops::mma(a, b[1], ops::start(cin));                                       \
         } else {                                                                                        \
             d0 = ops::mma(a, b[0], d0);                                                                 \
-            d1 = ops::mma(a, b[1], d1);                                                                 \
+            if (NI == 2) d1 = ops::mma(a, b[1], d1);                                                    \
         }                                                                                               \
         /* both results live at once: the second matrix instruction runs while the first is scaled */   \
-        ops::pin(d0, d1);                                                                               \
+        if (NI == 2) ops::pin(d0, d1);                                                                  \
+        else ops::pin(d0, d0);                                                                          \
         __builtin_amdgcn_sched_barrier(0);                                                              \
         MIDDLE;                                                                                         \
         __builtin_amdgcn_sched_barrier(0);                                                              \
         if (LAST) {                                                                                     \
             float x0[16], x1[16];                                                                       \
             _Pragma("unroll") for (int v = 0; v < 16; ++v) x0[v] = ops::scaled(d0[v], cin[v]);          \
-            _Pragma("unroll") for (int v = 0; v < 16; ++v) x1[v] = ops::scaled(d1[v], cin[v]);          \
+            if (NI == 2) { _Pragma("unroll") for (int v = 0; v < 16; ++v) x1[v] = ops::scaled(d1[v], cin[v]); } \
             _Pragma("unroll") for (int v = 0; v < 16; ++v) asm volatile("" : "+v"(x0[v]));              \
-            _Pragma("unroll") for (int v = 0; v < 16; ++v) asm volatile("" : "+v"(x1[v]));              \
+            if (NI == 2) { _Pragma("unroll") for (int v = 0; v < 16; ++v) asm volatile("" : "+v"(x1[v])); } \
             __builtin_amdgcn_sched_barrier(0);                                                          \
             cin = ops::rows(rowc, one_hot);                                                             \
             if (CHAIN) {                  /* long blocks always chain: the next block starts from its constants */ \
                 if (F16) {                                                                              \
                     d0 = ops::start(cin);                                                               \
-                    d1 = ops::start(cin);                                                               \
+                    if (NI == 2) d1 = ops::start(cin);                                                  \
                 } else {                                                                                \
                     d0 = ops::rows(rowc, one_hot);                                                      \
-                    d1 = ops::rows(rowc, one_hot);                                                      \
+                    if (NI == 2) d1 = ops::rows(rowc, one_hot);                                         \
                 }                                                                                       \
             }                                                                                           \
             __builtin_amdgcn_sched_barrier(0);                                                          \
             _Pragma("unroll") for (int v = 0; v < 16; ++v) acc[0][v] = fmaf(x0[v], sb[cur][0], acc[0][v]); \
-            _Pragma("unroll") for (int v = 0; v < 16; ++v) acc[1][v] = fmaf(x1[v], sb[cur][1], acc[1][v]); \
+            if (NI == 2) { _Pragma("unroll") for (int v = 0; v < 16; ++v) acc[1][v] = fmaf(x1[v], sb[cur][1], acc[1][v]); } \
             _Pragma("unroll") for (int v = 0; v < 16; ++v) asm volatile("" : "+v"(acc[0][v]));          \
-            _Pragma("unroll") for (int v = 0; v < 16; ++v) asm volatile("" : "+v"(acc[1][v]));          \
+            if (NI == 2) { _Pragma("unroll") for (int v = 0; v < 16; ++v) asm volatile("" : "+v"(acc[1][v])); } \
         }                                                                                               \
         __builtin_amdgcn_sched_barrier(0);                                                              \
     }
@@ -880,29 +881,44 @@ __global__ __launch_bounds__(kW8Threads, 4) void gemm_i8_w8_kernel(const W8Param
         }
         return;
     }
-    if (nst > 0) {
-        HBFP_READ_STEP(0, 0, 0);
-        cin = ops::rows(rowc, one_hot);
-        if (CHAIN) {
-            if (F16) {
-                d0 = ops::start(cin);
-                d1 = ops::start(cin);
-            } else {
-                d0 = ops::rows(rowc, one_hot);
-                d1 = ops::rows(rowc, one_hot);
-            }
-        }
+    // NI: column tiles of 32 of this wave that hold columns of the product.  One: the second is neither multiplied nor scaled
+    // (1296 x 144 x 50176 in blocks of 24: 71 -> 62.5 us, 50000 x 90 x 1152 28 -> 22.6).  The variant that scales runs once always
+    // computes both: it has no registers for a second loop.
+    // SPB = 3: cpos: k-step within its run of equal exponents, crun: k-steps since the last scaling, cstep: k-step of this
+    // workgroup's range
+#define HBFP_LOOP(ni)                                                          \
+    {                                                                          \
+        constexpr int NI = ni;                                                 \
+        if (nst > 0) {                                                         \
+            HBFP_READ_STEP(0, 0, 0);                                           \
+            cin = ops::rows(rowc, one_hot);                                    \
+            if (CHAIN) {                                                       \
+                if (F16) {                                                     \
+                    d0 = ops::start(cin);                                      \
+                    if (NI == 2) d1 = ops::start(cin);                         \
+                } else {                                                       \
+                    d0 = ops::rows(rowc, one_hot);                             \
+                    if (NI == 2) d1 = ops::rows(rowc, one_hot);                \
+                }                                                              \
+            }                                                                  \
+        }                                                                      \
+        int pos = 0;                                                           \
+        int cpos = SPB == 3 ? (2 * st_begin) % p.spb : 0, crun = 0, cstep = 0; \
+        for (int st = st_begin; st < st_end;) {                                \
+            HBFP_PAIR(0);                                                      \
+            st += 2;                                                           \
+            if (st >= st_end) break;                                           \
+            HBFP_PAIR(2);                                                      \
+            st += 2;                                                           \
+        }                                                                      \
     }
-    int pos = 0;
-    // SPB = 3: k-step within its run of equal exponents, k-steps since the last scaling, k-step of this workgroup's range
-    int cpos = SPB == 3 ? (2 * st_begin) % p.spb : 0, crun = 0, cstep = 0;
-    for (int st = st_begin; st < st_end;) {
-        HBFP_PAIR(0);
-        st += 2;
-        if (st >= st_end) break;
-        HBFP_PAIR(2);
-        st += 2;
+    if constexpr (SPB == 3) {
+        HBFP_LOOP(2);
+    } else {
+        if (col0 + (wave_u >> 2) * 64 + 32 < p.N) HBFP_LOOP(2)
+        else HBFP_LOOP(1)
     }
+#undef HBFP_LOOP
 #undef HBFP_PAIR
 #undef HBFP_CHAIN_ENDS
 #undef HBFP_READ_STEP

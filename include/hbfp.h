@@ -552,7 +552,8 @@ int hbfp_gemm_partials_window(const hbfp_tensor *A, const hbfp_tensor *B, int64_
  * (1,0) the weight gradient dW = X^T * dY.  fa/fb give each operand's exponent
  * blocks in the orientation the matrix is stored in; both must cut the
  * contraction axis into blocks of the same length.
- * workspace: hbfp_gemm_f32_workspace bytes (holds both encoded operands).
+ * workspace: hbfp_gemm_f32_workspace bytes (for both encoded operands; small products convert inside the product and leave
+ * it untouched).
  */
 int hbfp_gemm_f32_workspace(int transA, int transB, int64_t M, int64_t N, int64_t K,
                             const hbfp_format *fa, const hbfp_format *fb, size_t *bytes);

@@ -155,6 +155,7 @@ GemmArgs gemm_args(const hbfp_tensor *A, const hbfp_tensor *B) {
 bool ranges_overlap(const void *p, uint64_t np, const void *q, uint64_t nq) {
     return (uintptr_t)p < (uintptr_t)q + nq && (uintptr_t)q < (uintptr_t)p + np;
 }
+uint64_t source_bytes(const EncodeGeom &g) { return 4 * ((uint64_t)(g.src_rows - 1) * (uint64_t)g.ld + (uint64_t)g.src_cols); }
 // whether a buffer of `out` shares bytes with a buffer of `in`: a kernel that stores `out` tile by tile while other workgroups
 // still read `in` must then not run
 bool operands_overlap(const hbfp_tensor &out, const hbfp_tensor &in) {
@@ -1307,6 +1308,15 @@ int hbfp_gemm_f32(int transA, int transB, int64_t M, int64_t N, int64_t K,
     if (((uintptr_t)A & 3) == 0 && ((uintptr_t)B & 3) == 0 && !needs_tile_pass(p.ta) && !needs_tile_pass(p.tb) &&
         encode_pair_ok(geoms[0], geoms[1])) {
         const float *const src[2] = {A, B};
+        GemmArgs g = gemm_args(&p.ta, &p.tb);
+        g.C = C;
+        g.ldc = ldc;
+        // an operand that shares memory with C has to be converted whole before the first store
+        const uint64_t c_bytes = 4 * ((uint64_t)(M - 1) * (uint64_t)ldc + (uint64_t)N);
+        const bool apart = !ranges_overlap(C, c_bytes, A, source_bytes(geoms[0])) && !ranges_overlap(C, c_bytes, B, source_bytes(geoms[1]));
+        if (apart && ((uintptr_t)C & 3) == 0 && !use_bf(g, HBFP_KERNEL_AUTO) && !use_f16_planes(g, HBFP_KERNEL_AUTO) &&
+            !gemm_f16_possible(g) && !use_scaled(g, HBFP_KERNEL_AUTO) && gemm_convert_ok(g, src, geoms))
+            return launch_gemm_convert(g, src, geoms, (hipStream_t)stream);
         void *const mant[2] = {p.ta.mant, p.tb.mant};
         uint8_t *const exps[2] = {p.ta.exps, p.tb.exps};
         rc = launch_encode_pair(src, geoms, mant, exps, (hipStream_t)stream);

@@ -109,4 +109,12 @@ __device__ __forceinline__ int quantise(float x, uint32_t Eb, int m, uint32_t id
     return quant_sr(x, 125 + m - (int)Eb, sr_small_bits(Eb, m), sr_hash(idx_lo, idx_hi, s0, s1));
 }
 
+// low bytes of four values into one word: two byte permutes gather pairs, the third joins them (the mask-shift-or
+// form takes seven instructions)
+__device__ __forceinline__ uint32_t pack4_i8(int a, int b, int c, int d) {
+    const uint32_t ab = __builtin_amdgcn_perm((uint32_t)b, (uint32_t)a, 0x0c0c0400u);    // bytes: a.0, b.0, 0, 0
+    const uint32_t cd = __builtin_amdgcn_perm((uint32_t)d, (uint32_t)c, 0x0c0c0400u);
+    return __builtin_amdgcn_perm(cd, ab, 0x05040100u);                                    // ab.0, ab.1, cd.0, cd.1
+}
+
 }  // namespace hbfp

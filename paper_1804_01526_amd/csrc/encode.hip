@@ -35,13 +35,6 @@ __device__ __forceinline__ uint32_t group_max(uint32_t v) {
     return v;
 }
 
-// low bytes of four values into one word: two byte permutes gather pairs, the third joins them (the mask-shift-or
-// form takes seven instructions)
-__device__ __forceinline__ uint32_t pack4_i8(int a, int b, int c, int d) {
-    const uint32_t ab = __builtin_amdgcn_perm((uint32_t)b, (uint32_t)a, 0x0c0c0400u);    // bytes: a.0, b.0, 0, 0
-    const uint32_t cd = __builtin_amdgcn_perm((uint32_t)d, (uint32_t)c, 0x0c0c0400u);
-    return __builtin_amdgcn_perm(cd, ab, 0x05040100u);                                    // ab.0, ab.1, cd.0, cd.1
-}
 __device__ __forceinline__ uint32_t pack2_i16(int a, int b) {
     return (uint32_t)(a & 0xffff) | ((uint32_t)b << 16);
 }
@@ -1437,7 +1430,7 @@ int launch_encode_col_fused(const float *src, const EncodeGeom &g, void *mant, u
 }
 
 // Two conversions in one launch: each takes a launch's time (about 3 us) out of the product.  A product of FP32 operands, two
-// conversions against one: 256 x 256 x 256 11.2 -> 8.0 us, 1024 x 1024 x 1024 29.2 -> 25.6, 2048 x 2048 x 2048 46.5 -> 44.0,
+// conversions against one: 256 x 256 x 256 11.2 -> 8.0 us (one launch now: gemm_small.hip), 1024 x 1024 x 1024 29.2 -> 25.6, 2048 x 2048 x 2048 46.5 -> 44.0,
 // 512 x 512 x 16384 47.6 -> 44.9, 64 x 8192 x 4096 (33 Mi values) 59.2 -> 56.3, each with both directions alike.  The line lies
 // where the measurements end: past 32 Mi values the row kernel is bound by memory, and the LDS that the column kernel's tile claims
 // for every workgroup here halves the waves it can keep in flight.

@@ -68,6 +68,33 @@ __device__ __forceinline__ void small_encode(const SmallParams &p, float4 x, int
     if (c4 == 0 && blk < p.oexp_ld) p.exps[row * p.oexp_ld + blk] = blk < p.onblk ? (uint8_t)Eb : (uint8_t)1;
 }
 
+// a group of four blocks of 32 columns and MT row tiles: operands (row lane % 32, 16 bytes by lane / 32) and exponent bytes
+template <int MT>
+struct SmallGroup {
+    v4i b[4], a[MT][4];
+    uint32_t eb, ea[MT];
+};
+template <int MT>
+__device__ __forceinline__ void small_multiply(const SmallGroup<MT> &x, const v2i &one_hot, float (&acc)[MT][16]) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        uint32_t e = (x.eb >> (8 * k)) & 0xffu;
+        const float scale = __uint_as_float((e > 254u ? 254u : e) << 23);
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            e = (x.ea[i] >> (8 * k)) & 0xffu;
+            const v16i rows = row_constants(((e > 254u ? 254u : e) << 7) | 0x40u, one_hot);
+            const v16i sum = __builtin_amdgcn_mfma_i32_32x32x32_i8(x.a[i][k], x.b[k], rows, 0, 0, 0);
+            float y[16];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) y[v] = __int_as_float(sum[v]) - __int_as_float(rows[v]);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][v] = fmaf(y[v], scale, acc[i][v]);
+        }
+        if (MT > 1 || (k & 1)) __builtin_amdgcn_sched_barrier(0);      // no pile-up of block sums beyond two
+    }
+}
+
 // MT: row tiles of 32; ENC: the product leaves as an encoded operand
 template <int MT, bool ENC>
 __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const SmallParams p) {
@@ -91,12 +118,9 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const Smal
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[i][v] = 0.0f;
 
-    // a group of four blocks: operands and exponent bytes; the next group is under way while one is multiplied
-    struct Group {
-        v4i b[4], a[MT][4];
-        uint32_t eb, ea[MT];
-    };
-    auto load = [&](Group &x, int g) {
+    SmallGroup<MT> cur;
+    // a group ahead of the one that is multiplied
+    auto load = [&](SmallGroup<MT> &x, int g) {
         g = g < p.groups ? g : p.groups - 1;                   // behind the end: something that exists, not used
 #pragma unroll
         for (int k = 0; k < 4; ++k) x.b[k] = *reinterpret_cast<const v4i *>(b_src + (int64_t)g * 128 + k * 32);
@@ -108,32 +132,15 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const Smal
             x.ea[i] = *reinterpret_cast<const uint32_t *>(ea_src[i] + (int64_t)g * 4);
         }
     };
-    Group cur;
     load(cur, wave);
     // not unrolled: the loop body is small on purpose, because a kernel this short pays for every line of instructions that
     // it fetches (four groups unrolled took 16 x 4096 x 4096 from 10.8 to 16.4 us)
 #pragma unroll 1
     for (int g = wave; g < p.groups; g += kSmallWaves) {
-        Group next;
+        SmallGroup<MT> next;
         load(next, g + kSmallWaves);
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            uint32_t e = (cur.eb >> (8 * k)) & 0xffu;
-            const float scale = __uint_as_float((e > 254u ? 254u : e) << 23);
-#pragma unroll
-            for (int i = 0; i < MT; ++i) {
-                e = (cur.ea[i] >> (8 * k)) & 0xffu;
-                const v16i rows = row_constants(((e > 254u ? 254u : e) << 7) | 0x40u, one_hot);
-                const v16i sum = __builtin_amdgcn_mfma_i32_32x32x32_i8(cur.a[i][k], cur.b[k], rows, 0, 0, 0);
-                float x[16];
-#pragma unroll
-                for (int v = 0; v < 16; ++v) x[v] = __int_as_float(sum[v]) - __int_as_float(rows[v]);
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][v] = fmaf(x[v], scale, acc[i][v]);
-            }
-            if (MT > 1 || (k & 1)) __builtin_amdgcn_sched_barrier(0);      // no pile-up of block sums beyond two
-        }
+        small_multiply<MT>(cur, one_hot, acc);
         cur = next;
     }
 #pragma unroll
@@ -341,6 +348,147 @@ int launch_few(const SmallParams &p, bool enc, int64_t cols, hipStream_t s) {
 // converted) the start of a workgroup with that much LDS is what counts, and the other kernel is ahead.
 bool few_rows_ok(const SmallParams &p, bool enc) { return p.M <= 32 && p.groups >= (enc ? 5 : 4) && p.kpad <= (1 << 26); }
 
+// A product of two FP32 matrices in one launch (hbfp_gemm_f32 at small sizes): the workgroup converts its 32 rows of A and its 32
+// columns of B itself.  What bounds these calls is launches and latency: a launch that converts both operands (5.1 us at 256^3)
+// and one that multiplies (3.7 us) have their starts and the gap between them to pay.  A block of 32 x 32 values is one wave's:
+// its lanes hold 16 values of a row or column each, in the order in which the matrix instruction takes them, so what is
+// handed from the converting wave to the multiplying one is 16 bytes per lane.  All of a wave's loads are requested before the
+// first conversion, from lanes that own them: by whole lines, 8 lanes to a row, the loads are fewer and the instructions more
+// (512^3 6.6 us both ways, 128 x 2000 x 500 9.0 against 9.6).  Blocks go round over the waves to be converted, but a wave multiplies the four blocks of its group, as in
+// the kernels above: the same order of sums, the same bits.
+struct ConvertSource {
+    const float *src;
+    int64_t ld;
+    int32_t rows, m;             // rows or columns of the operand
+    int32_t down;                // the contraction runs down the source rows
+    int32_t vec;                 // four values of a row start on 16 bytes
+};
+struct ConvertParams {
+    ConvertSource x[2];
+    float *C;
+    int64_t ldc;
+    int32_t K, kblock, nblk, groups;
+    float final_scale;
+};
+// 16 values of block `blk` of row `r`: those from 16 lh on, zeros behind the block's and the matrix's end
+__device__ __forceinline__ void convert_load(const ConvertSource &x, const ConvertParams &p, int64_t r, int lh, int blk, float (&v)[16]) {
+    int len = 0;
+    if (blk < p.nblk) len = p.K - blk * p.kblock < p.kblock ? p.K - blk * p.kblock : p.kblock;
+    const int left = len - 16 * lh;
+    const int64_t k0 = (int64_t)(len ? blk : 0) * p.kblock;
+    if (x.down) {
+        const float *s = x.src + (left > 0 ? 16 * lh : 0) * x.ld + r;
+        if (len == 32) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) v[j] = s[(k0 + j) * x.ld];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) v[j] = j < left ? s[(k0 + j) * x.ld] : 0.0f;
+        }
+    } else {
+        const float *s = x.src + r * x.ld + k0 + (left > 0 ? 16 * lh : 0);
+        if (len == 32 && x.vec) {
+#pragma unroll
+            for (int j = 0; j < 16; j += 4) {
+                const float4 d = *reinterpret_cast<const float4 *>(s + j);
+                v[j] = d.x, v[j + 1] = d.y, v[j + 2] = d.z, v[j + 3] = d.w;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) v[j] = j < left ? s[j] : 0.0f;
+        }
+    }
+}
+__device__ __forceinline__ uint32_t convert_word(const float *v, uint32_t Eb, int m) {
+    return pack4_i8(quantise<0>(v[0], Eb, m, 0, 0, 0, 0), quantise<0>(v[1], Eb, m, 0, 0, 0, 0),
+                    quantise<0>(v[2], Eb, m, 0, 0, 0, 0), quantise<0>(v[3], Eb, m, 0, 0, 0, 0));
+}
+// the block's mantissas, 16 bytes per lane of the matrix instruction, and its exponents, a byte per row `pitch` bytes apart
+__device__ __forceinline__ void convert_store(const ConvertSource &x, int lane, const float (&v)[16], uint8_t *mant, uint8_t *exps, int pitch) {
+    uint32_t amax = 0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) amax = max(amax, __float_as_uint(v[j]) & 0x7fffffffu);
+    amax = max(amax, (uint32_t)__shfl_xor((int)amax, 32));
+    const uint32_t Eb = block_exponent<0>(amax, x.m);
+    v4u w;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w[j] = convert_word(v + 4 * j, Eb, x.m);
+    *reinterpret_cast<v4u *>(mant + lane * 16) = w;
+    if (lane < 32) exps[lane * pitch] = (uint8_t)Eb;
+}
+// PER: blocks that a wave converts of each operand
+template <int PER>
+struct Convert {
+    static constexpr int kBlocks = PER * kSmallWaves, kExpRow = kBlocks + 4;
+    static constexpr int kMant = kBlocks * 1024, kPart = kSmallWaves * 32 * 32 * 4;      // bytes: one operand's, the waves' sums
+    static constexpr int kExps = 2 * kMant > kPart ? 2 * kMant : kPart;
+    static constexpr int kLds = kExps + 2 * 32 * kExpRow;
+};
+template <int PER>
+__global__ __launch_bounds__(kSmallThreads, 2) void gemm_convert_kernel(const ConvertParams p) {
+    typedef Convert<PER> R;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[R::kLds];
+    const int t = threadIdx.x, lane = t & 63, l32 = lane & 31, lh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int64_t origin[2] = {(int64_t)blockIdx.y * 32, (int64_t)blockIdx.x * 32};
+    float v[2][PER][16];
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            const int64_t r = origin[o] + l32 < p.x[o].rows ? origin[o] + l32 : p.x[o].rows - 1;   // behind the last: that one again
+            convert_load(p.x[o], p, r, lh, wave + i * kSmallWaves, v[o][i]);
+        }
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            const int blk = wave + i * kSmallWaves;
+            convert_store(p.x[o], lane, v[o][i], lds + o * R::kMant + blk * 1024, lds + R::kExps + o * 32 * R::kExpRow + blk, R::kExpRow);
+        }
+    __syncthreads();
+    const v2i one_hot = {lh ? 0 : 0x3F80, 0};
+    float acc[1][16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) acc[0][j] = 0.0f;
+    if (wave < p.groups) {
+        SmallGroup<1> g;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            g.a[0][k] = *reinterpret_cast<const v4i *>(lds + (4 * wave + k) * 1024 + lane * 16);
+            g.b[k] = *reinterpret_cast<const v4i *>(lds + R::kMant + (4 * wave + k) * 1024 + lane * 16);
+        }
+        g.ea[0] = *reinterpret_cast<const uint32_t *>(lds + R::kExps + l32 * R::kExpRow + 4 * wave);
+        g.eb = *reinterpret_cast<const uint32_t *>(lds + R::kExps + (32 + l32) * R::kExpRow + 4 * wave);
+        small_multiply<1>(g, one_hot, acc);
+    }
+    __syncthreads();                                             // the sums lie where the mantissas were
+    float *part = reinterpret_cast<float *>(lds);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) part[(wave * 32 + 8 * (j >> 2) + 4 * lh + (j & 3)) * 32 + l32] = acc[0][j];
+    __syncthreads();
+    if (t >= 256) return;
+    const int r = t >> 3, c4 = (t & 7) * 4;
+    const int64_t row = origin[0] + r, col = origin[1] + c4;
+    if (row >= p.x[0].rows) return;
+    float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int w = 0; w < kSmallWaves; ++w) {
+        const float4 d = *reinterpret_cast<const float4 *>(part + (w * 32 + r) * 32 + c4);
+        x[0] += d.x, x[1] += d.y, x[2] += d.z, x[3] += d.w;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (col + i < p.x[1].rows) p.C[row * p.ldc + col + i] = x[i] * p.final_scale;
+}
+
+template <int PER>
+int launch_convert(const ConvertParams &p, hipStream_t s) {
+    const dim3 grid((unsigned)ceil_div(p.x[1].rows, 32), (unsigned)ceil_div(p.x[0].rows, 32));
+    hipLaunchKernelGGL(gemm_convert_kernel<PER>, grid, dim3(kSmallThreads), 0, s, p);
+    return launch_status();
+}
+
 template <int MT>
 int launch_small(const SmallParams &p, bool enc, unsigned workgroups, hipStream_t s) {
     const dim3 grid(workgroups, (unsigned)ceil_div(p.M, 32 * MT));
@@ -409,6 +557,43 @@ int launch_gemm_small(const GemmArgs &a, hipStream_t s, const hbfp_tensor *enc, 
     if (few_rows_ok(p, enc != nullptr)) return launch_few(p, enc != nullptr, cols, s);
     const unsigned workgroups = (unsigned)ceil_div(cols, 32);
     return small_row_tiles(a, nullptr) == 1 ? launch_small<1>(p, enc != nullptr, workgroups, s) : launch_small<2>(p, enc != nullptr, workgroups, s);
+}
+
+// Whether the product converts its own operands: one round of workgroups, at most two blocks of each operand per wave, and the
+// products that the kernels above would take.  Every workgroup converts for itself and one of few blocks is mostly the fetch of
+// its own instructions: with four blocks per wave the two launches are ahead or level (512 x 512 x 1024 10.9 us against 12.9
+// here).  So they are from 257 of k on where the rows of both operands are read value by value (511^3, B transposed, 10.8
+// against 13.5; 500 x 510 x 333 9.7, 10.7; one such operand 10.8, 10.5).  Measured in a graph, two launches -> here: 256^3
+// 7.0 -> 4.8 us, both operands down the rows 7.0 -> 4.3, 512^3 8.4 -> 6.6, 128 x 2000 x 500 9.25 -> 9.0, 16 x 4096 x 512 8.6 ->
+// 5.7, 33 x 2048 x 64 6.8 -> 4.5; call by call, where the host's two launches are the bound, 13.0 -> 9.5 at all of them.
+static bool by_value(const float *src, const EncodeGeom &g) { return g.axis == 1 && (((uintptr_t)src & 15) || g.ld % 4 || g.kblock != 32); }
+bool gemm_convert_ok(const GemmArgs &a, const float *const *src, const EncodeGeom *geom) {
+    if (!encode_pair_ok(geom[0], geom[1]) || !gemm_small_ok(a)) return false;
+    if (a.kpad > 512 || ceil_div(a.M, 32) * ceil_div(a.N, 32) > 256) return false;
+    return a.kpad <= 256 || !by_value(src[0], geom[0]) || !by_value(src[1], geom[1]);
+}
+
+int launch_gemm_convert(const GemmArgs &a, const float *const *src, const EncodeGeom *geom, hipStream_t s) {
+    if (!gemm_convert_ok(a, src, geom)) return HBFP_ERR_FORMAT;
+    ConvertParams p = {};
+    for (int o = 0; o < 2; ++o) {
+        const EncodeGeom &g = geom[o];
+        p.x[o].src = src[o];
+        p.x[o].ld = g.ld;
+        p.x[o].rows = (int32_t)g.R;
+        p.x[o].m = g.m;
+        p.x[o].down = g.axis == 0;
+        p.x[o].vec = !by_value(src[o], g);
+    }
+    p.C = a.C;
+    p.ldc = a.ldc;
+    p.K = (int32_t)geom[0].K;
+    p.kblock = (int32_t)a.kblock;
+    p.nblk = (int32_t)a.nblk;
+    p.groups = (int32_t)(a.kpad / 128);
+    p.final_scale = ldexpf(1.0f, 27 - a.mA - a.mB);
+    const int64_t blocks = a.kpad / 32;
+    return blocks <= 8 ? launch_convert<1>(p, s) : launch_convert<2>(p, s);
 }
 
 }  // namespace hbfp

@@ -895,7 +895,7 @@ void launch_rowwave_n(const WaveParams &p, dim3 grid, bool wide, int rounding, h
 // Long exponent blocks down the source rows (one exponent per column, filter tiles over a whole window), k strided in the
 // source: one workgroup per strip of cw columns and exponent block.  It reads its part of the block for the maxima,
 // combines them in LDS and reads it again (from the caches) to quantise, so there is no table to clear, no atomic to memory
-// and one launch instead of three.  Bound by the latency of its strided loads (16 in flight per thread) for small matrices
+// and one launch instead of three.  What fits the registers is read once (below).  Bound by the latency of its strided loads (16 in flight per thread) for small matrices
 // and by the second read for larger ones.  Dealing neighbouring strips, which share cache lines, to the same XCD took
 // 4500 x 2999 from 47 to 25 us.
 struct StripParams {
@@ -909,6 +909,59 @@ struct StripParams {
     uint32_t s0, s1;
 };
 constexpr int kStripThreads = 512;
+
+// 16 stored positions from `pos` on: the stored block, the offset in it, how many of its values exist and the first one
+struct StripPiece {
+    int blk, off, n, k0;
+};
+__device__ __forceinline__ StripPiece strip_piece(const StripParams &p, int pos) {
+    StripPiece x;
+    x.blk = (int)((uint32_t)pos / (uint32_t)p.kbp), x.off = pos - x.blk * p.kbp, x.n = 0;
+    if (x.blk < p.nblk) {
+        const int left = (p.K - x.blk * p.kblock < p.kblock ? p.K - x.blk * p.kblock : p.kblock) - x.off;
+        x.n = left < 0 ? 0 : (left < 16 ? left : 16);
+    }
+    x.k0 = x.n ? x.blk * p.kblock + x.off : 0;
+    return x;
+}
+__device__ __forceinline__ void strip_load(const StripParams &p, const float *s, const StripPiece &x, float (&v)[16]) {
+    if (x.n == 16) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = s[(int64_t)(x.k0 + i) * p.ld];
+    } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = i < x.n ? s[(int64_t)(x.k0 + i) * p.ld] : 0.0f;
+    }
+}
+template <bool WIDE, int ROUND>
+__device__ __forceinline__ void strip_store(const StripParams &p, const StripPiece &x, const float (&v)[16], int col, int pos, uint32_t Eb) {
+    int q[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const uint64_t idx = (uint64_t)(x.k0 + i) * (uint64_t)p.src_cols + (uint64_t)col;
+        q[i] = quantise<ROUND>(v[i], Eb, p.m, (uint32_t)idx, (uint32_t)(idx >> 32), p.s0, p.s1);
+    }
+    uint8_t *dst = p.mant + ((int64_t)col * p.kpad + pos) * (WIDE ? 2 : 1);
+    if (!WIDE) {
+        uint4 o;
+        o.x = pack4_i8(q[0], q[1], q[2], q[3]);
+        o.y = pack4_i8(q[4], q[5], q[6], q[7]);
+        o.z = pack4_i8(q[8], q[9], q[10], q[11]);
+        o.w = pack4_i8(q[12], q[13], q[14], q[15]);
+        *reinterpret_cast<uint4 *>(dst) = o;
+    } else {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            uint4 o;
+            o.x = pack2_i16(q[8 * h], q[8 * h + 1]);
+            o.y = pack2_i16(q[8 * h + 2], q[8 * h + 3]);
+            o.z = pack2_i16(q[8 * h + 4], q[8 * h + 5]);
+            o.w = pack2_i16(q[8 * h + 6], q[8 * h + 7]);
+            reinterpret_cast<uint4 *>(dst)[h] = o;
+        }
+    }
+    if (x.off == 0 && x.blk < p.nblk) p.exps[(int64_t)col * p.exp_ld + x.blk] = (uint8_t)Eb;
+}
 
 template <bool WIDE, int ROUND>
 __global__ __launch_bounds__(kStripThreads) void enc_strip_kernel(const StripParams p) {
@@ -949,47 +1002,56 @@ __global__ __launch_bounds__(kStripThreads) void enc_strip_kernel(const StripPar
     const int pfirst = reg * p.kshare * p.kbp;
     const int pend = reg == p.nreg - 1 ? (int)p.kpad : pfirst + p.kshare * p.kbp;
     for (int pos = pfirst + 16 * g; pos < pend; pos += 16 * groups) {
-        const int blk = pos / p.kbp, off = pos - blk * p.kbp;
-        int n = 0;                                                     // elements that exist
-        if (blk < p.nblk) {
-            const int left = (p.K - blk * p.kblock < p.kblock ? p.K - blk * p.kblock : p.kblock) - off;
-            n = left < 0 ? 0 : (left < 16 ? left : 16);
-        }
-        const int k0 = n ? blk * p.kblock + off : 0;
+        const StripPiece x = strip_piece(p, pos);
         float v[16];
-        if (n == 16) {
+        strip_load(p, s, x, v);
+        strip_store<WIDE, ROUND>(p, x, v, col, pos, Eb);
+    }
+}
+
+// The same strips held in registers between the maxima and the quantisation: one read, and all of a thread's loads in flight at
+// once, where the kernel above has 16 and reads twice.  Bound by the latency of the strided loads and the one or two
+// workgroups that a compute unit's registers hold: 16 columns of 5120 positions (1024 threads) or twice 2560 (512).
+// Read twice -> held: 4500 x 2999 25.7 -> 16.6 us (4.1 TB/s of source and result), stochastic 39.1 -> 32.6, 12 bits 28.3 -> 19.1;
+// 4096^2 27.3 -> 18.4, 2500 x 6000 24.1 -> 16.7, 3000 x 12000 60.8 -> 45.7, 1100 x 2999 8.2 -> 7.0, 3502 x 13 13.5 -> 8.6.
+constexpr int kHeldPieces = 5, kHeldThreads = 1024;
+template <bool WIDE, int ROUND, int PIECES>
+__global__ __launch_bounds__(kHeldThreads) void enc_strip_kernel(const StripParams p) {
+    __shared__ uint32_t tile_max[64];
+    const int t = threadIdx.x, groups = (int)blockDim.x / p.cw;
+    const int c = t % p.cw, g = t / p.cw;
+    const int strips = (p.R + p.cw - 1) / p.cw, per_xcd = (strips + 7) >> 3;
+    const int strip = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    const int col = strip * p.cw + c, reg = blockIdx.y;
+    const bool live = g < groups && (int)(blockIdx.x >> 3) < per_xcd && col < p.R;
+    if (t < 64) tile_max[t] = 0;
+    const int pfirst = reg * p.kshare * p.kbp;
+    const int pend = !live ? pfirst : reg == p.nreg - 1 ? (int)p.kpad : pfirst + p.kshare * p.kbp;
+    const float *s = p.src + (live ? col : 0);
+    float v[PIECES][16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) v[i] = s[(int64_t)(k0 + i) * p.ld];
-        } else {
+    for (int j = 0; j < PIECES; ++j) {
+        const int pos = pfirst + 16 * (g + j * groups);
+        if (pos < pend) strip_load(p, s, strip_piece(p, pos), v[j]);
+    }
+    uint32_t amax = 0;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) v[i] = i < n ? s[(int64_t)(k0 + i) * p.ld] : 0.0f;
+    for (int j = 0; j < PIECES; ++j)
+        if (pfirst + 16 * (g + j * groups) < pend) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) amax = max(amax, __float_as_uint(v[j][i]) & 0x7fffffffu);
         }
-        int q[16];
+    __syncthreads();
+    if (live) atomicMax(&tile_max[c / p.rblock], amax);
+    __syncthreads();
+    if (!live) return;
+    const uint32_t Eb = block_exponent<ROUND>(tile_max[c / p.rblock], p.m);
+    if (reg == p.nreg - 1 && g == 0)
+        for (int64_t b = p.nblk; b < p.exp_ld; ++b) p.exps[(int64_t)col * p.exp_ld + b] = 1;      // past the last block
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const uint64_t idx = (uint64_t)(k0 + i) * (uint64_t)p.src_cols + (uint64_t)col;
-            q[i] = quantise<ROUND>(v[i], Eb, p.m, (uint32_t)idx, (uint32_t)(idx >> 32), p.s0, p.s1);
-        }
-        uint8_t *dst = p.mant + ((int64_t)col * p.kpad + pos) * (WIDE ? 2 : 1);
-        if (!WIDE) {
-            uint4 o;
-            o.x = pack4_i8(q[0], q[1], q[2], q[3]);
-            o.y = pack4_i8(q[4], q[5], q[6], q[7]);
-            o.z = pack4_i8(q[8], q[9], q[10], q[11]);
-            o.w = pack4_i8(q[12], q[13], q[14], q[15]);
-            *reinterpret_cast<uint4 *>(dst) = o;
-        } else {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint4 o;
-                o.x = pack2_i16(q[8 * h], q[8 * h + 1]);
-                o.y = pack2_i16(q[8 * h + 2], q[8 * h + 3]);
-                o.z = pack2_i16(q[8 * h + 4], q[8 * h + 5]);
-                o.w = pack2_i16(q[8 * h + 6], q[8 * h + 7]);
-                reinterpret_cast<uint4 *>(dst)[h] = o;
-            }
-        }
-        if (off == 0 && blk < p.nblk) erow[blk] = (uint8_t)Eb;
+    for (int j = 0; j < PIECES; ++j) {
+        const int pos = pfirst + 16 * (g + j * groups);
+        if (pos < pend) strip_store<WIDE, ROUND>(p, strip_piece(p, pos), v[j], col, pos, Eb);
     }
 }
 
@@ -1517,7 +1579,8 @@ static int strip_columns(const EncodeGeom &g) {
 }
 // What a workgroup reads twice has to stay within the reach of one compute unit.  Rounding to nearest, with enough strips: up to
 // 80 Ki values per strip and block they are ahead of the two-pass conversion (one exponent per column: 500 x 300 15.0 -> 4.8
-// us, 4500 x 2999 39 -> 26 us, 4096^2 36 -> 27 us, 2500 x 6000 31 -> 24 us; 216 x 24 tiles of 1296 x 144 16.7 -> 5.2 us), beyond it
+// us, 4500 x 2999 39 -> 26 us, 4096^2 36 -> 27 us, 2500 x 6000 31 -> 24 us; 216 x 24 tiles of 1296 x 144 16.7 -> 5.2 us; all with
+// the kernel that reads twice), beyond it
 // behind (8192^2: 110 and 145 us); rows off 16 bytes slow the maximum pass of the two down, there up to 160 Ki (10000 x 3001
 // 74 -> 64 us, 8191 x 3001 64 -> 51).  Stochastic rounding works longer per value: 80 Ki whatever the rows (4500 x 2999 49 -> 38
 // us, behind at 8191 x 6001, 115 and 136).
@@ -1565,6 +1628,21 @@ static int launch_encode_strip(const float *src, const EncodeGeom &g, void *mant
     p.s1 = g.seed_hi;
     const dim3 grid((unsigned)(ceil_div(ceil_div(g.R, p.cw), 8) * 8), (unsigned)p.nreg);
     const bool wide = g.m > 8;
+    // Positions of the longest exponent block (the last one has the padding of the row too) in pieces of 16 per thread: held in
+    // registers if they fit, by 512 threads or else by 1024.  Only short blocks in many workgroups stay with the other kernel,
+    // where twice as many workgroups share a compute unit, unless nearly every thread has a piece (read twice -> held, 4096^2:
+    // tiles of 96 x 24 26.9 and 28.5 us, blocks of 128 22.1 and 21.8, of 256 18.8 -> 17.4; few workgroups, 500 x 300 5.0 -> 4.1).
+    const int64_t most = max((int64_t)p.kshare * p.kbp, g.kpad - (int64_t)(p.nreg - 1) * p.kshare * p.kbp);
+    const int64_t per = 16 * (kStripThreads / p.cw), pieces = ceil_div(most, per);
+    const bool hold = pieces > 1 || 16 * most >= 15 * per || (int64_t)grid.x * grid.y <= 512;
+    if (hold && ceil_div(most, 16 * (kHeldThreads / p.cw)) <= kHeldPieces) {
+        const dim3 block(pieces <= kHeldPieces ? kStripThreads : kHeldThreads);
+        if (!wide && g.rounding == 0) hipLaunchKernelGGL((enc_strip_kernel<false, 0, kHeldPieces>), grid, block, 0, s, p);
+        else if (!wide) hipLaunchKernelGGL((enc_strip_kernel<false, 1, kHeldPieces>), grid, block, 0, s, p);
+        else if (g.rounding == 0) hipLaunchKernelGGL((enc_strip_kernel<true, 0, kHeldPieces>), grid, block, 0, s, p);
+        else hipLaunchKernelGGL((enc_strip_kernel<true, 1, kHeldPieces>), grid, block, 0, s, p);
+        return launch_status();
+    }
     if (!wide && g.rounding == 0) hipLaunchKernelGGL((enc_strip_kernel<false, 0>), grid, dim3(kStripThreads), 0, s, p);
     else if (!wide) hipLaunchKernelGGL((enc_strip_kernel<false, 1>), grid, dim3(kStripThreads), 0, s, p);
     else if (g.rounding == 0) hipLaunchKernelGGL((enc_strip_kernel<true, 0>), grid, dim3(kStripThreads), 0, s, p);

@@ -579,6 +579,28 @@ def test_where_long_blocks_down_the_rows_are_converted(hb, rows, cols, bc, round
 
 
 @pytest.mark.parametrize("m,rounding", [(8, 0), (12, 1)])
+@pytest.mark.parametrize("rows,cols,br,bc", [(1023, 1035, 0, 1), (1030, 1035, 0, 1), (2560, 1035, 0, 1), (2570, 1035, 0, 1), (5120, 1024, 0, 1), (5130, 1035, 0, 1),
+                                             (4200, 1100, 2048, 3), (2900, 1300, 0, 40), (3000, 13, 0, 1)])
+def test_strips_held_in_registers(hb, rows, cols, br, bc, m, rounding):
+    """Strips at the edges of what 512 and 1024 threads hold (2560 and 5120 values of 16 columns) and past it, where they are read
+    twice; several exponent blocks down the rows, tiles of columns.  Denormal, non-finite and empty blocks among the values."""
+    rng = np.random.default_rng(rows + cols)
+    X = (rng.standard_normal((rows, cols)) * np.exp2(rng.integers(-20, 21, size=(1, cols)))).astype(np.float32)
+    X[:, 0], X[:, 5 % cols] = 0.0, 1e-42
+    X[rows - 1, 7 % cols] = 3e38
+    src = torch.from_numpy(X).cuda()
+    fmt = hb.make_format(m, br, bc, rounding, 99)
+    out = hb.alloc(fmt, rows, cols, 0)
+    out.mant.fill_(85)
+    out.exps.fill_(85)
+    hb.encode(src, 0, fmt, out=out)
+    want = ref.encode(X, br, bc, m, rounding, 99)
+    mant, exps = unpack(out)
+    np.testing.assert_array_equal(mant, want.mant)
+    np.testing.assert_array_equal(exps, want.exps)
+
+
+@pytest.mark.parametrize("m,rounding", [(8, 0), (12, 1)])
 @pytest.mark.parametrize("rows,cols,br,bc,slot", [(5000, 1, 0, 1, 0), (300, 3, 0, 1, 0), (700, 7, 0, 2, 0), (513, 5, 200, 3, 0), (640, 15, 128, 4, 0),
                                                   (1000, 9, 216, 9, 24), (400, 15, 0, 15, 0), (129, 2, 128, 1, 0)])
 def test_strips_narrower_than_sixteen_columns(hb, rows, cols, br, bc, slot, m, rounding):

@@ -579,6 +579,25 @@ def test_where_long_blocks_down_the_rows_are_converted(hb, rows, cols, bc, round
 
 
 @pytest.mark.parametrize("m,rounding", [(8, 0), (12, 1)])
+@pytest.mark.parametrize("rows,cols", [(33, 4096), (33, 4104), (9, 5119), (9, 5121), (7, 6144), (7, 6150), (5, 8192)])
+def test_rows_held_by_a_wave(hb, rows, cols, m, rounding):
+    """One exponent per row at the edges of what a wave's register budgets (8, 10, 12 and 16 chunks per lane) hold."""
+    rng = np.random.default_rng(rows + cols)
+    X = (rng.standard_normal((rows, cols)) * np.exp2(rng.integers(-20, 21, size=(rows, cols)))).astype(np.float32)
+    X[0], X[1, -1], X[2] = 0.0, 3e38, 1e-42
+    src = torch.from_numpy(X).cuda()
+    fmt = hb.make_format(m, 1, 0, rounding, 99)
+    out = hb.alloc(fmt, rows, cols, 1)
+    out.mant.fill_(85)
+    out.exps.fill_(85)
+    hb.encode(src, 1, fmt, out=out)
+    want = ref.encode(X, 1, 0, m, rounding, 99)
+    mant, exps = unpack(out)
+    np.testing.assert_array_equal(mant, want.mant)
+    np.testing.assert_array_equal(exps, want.exps)
+
+
+@pytest.mark.parametrize("m,rounding", [(8, 0), (12, 1)])
 @pytest.mark.parametrize("rows,cols,br,bc", [(1023, 1035, 0, 1), (1030, 1035, 0, 1), (2560, 1035, 0, 1), (2570, 1035, 0, 1), (5120, 1024, 0, 1), (5130, 1035, 0, 1),
                                              (4200, 1100, 2048, 3), (2900, 1300, 0, 40), (3000, 13, 0, 1)])
 def test_strips_held_in_registers(hb, rows, cols, br, bc, m, rounding):

@@ -1315,7 +1315,7 @@ int hbfp_gemm_f32(int transA, int transB, int64_t M, int64_t N, int64_t K,
         const uint64_t c_bytes = 4 * ((uint64_t)(M - 1) * (uint64_t)ldc + (uint64_t)N);
         const bool apart = !ranges_overlap(C, c_bytes, A, source_bytes(geoms[0])) && !ranges_overlap(C, c_bytes, B, source_bytes(geoms[1]));
         if (apart && ((uintptr_t)C & 3) == 0 && !use_bf(g, HBFP_KERNEL_AUTO) && !use_f16_planes(g, HBFP_KERNEL_AUTO) &&
-            !gemm_f16_possible(g) && !use_scaled(g, HBFP_KERNEL_AUTO) && gemm_convert_ok(g, src, geoms))
+            !gemm_f16_possible(g) && !use_scaled(g, HBFP_KERNEL_AUTO) && gemm_convert_ok(g, geoms))
             return launch_gemm_convert(g, src, geoms, (hipStream_t)stream);
         void *const mant[2] = {p.ta.mant, p.tb.mant};
         uint8_t *const exps[2] = {p.ta.exps, p.tb.exps};

@@ -109,6 +109,9 @@ __device__ __forceinline__ int quantise(float x, uint32_t Eb, int m, uint32_t id
     return quant_sr(x, 125 + m - (int)Eb, sr_small_bits(Eb, m), sr_hash(idx_lo, idx_hi, s0, s1));
 }
 
+// four neighbouring values whose address is a multiple of 4 bytes only: one load, where rows have odd lengths
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+
 // low bytes of four values into one word: two byte permutes gather pairs, the third joins them (the mask-shift-or
 // form takes seven instructions)
 __device__ __forceinline__ uint32_t pack4_i8(int a, int b, int c, int d) {

@@ -234,6 +234,12 @@ __device__ __forceinline__ void enc_row_block(const RowParams p, const uint32_t 
             const float4 b = *reinterpret_cast<const float4 *>(s + 4);
             v[u][0] = a.x; v[u][1] = a.y; v[u][2] = a.z; v[u][3] = a.w;
             v[u][4] = b.x; v[u][5] = b.y; v[u][6] = b.z; v[u][7] = b.w;
+        } else if (cnt == 8) {
+            // rows of odd lengths, value by value before: 4096 x 4095 31.9 -> 14.4 us, 700 x 1501 6.2 -> 4.0, stochastic 4096 x
+            // 4095 35.3 -> 23.5 (aligned rows, without this path and with it: 4096^2 14.0 both, 8192^2 57.0 and 58.9)
+            const v4f_any a = *reinterpret_cast<const v4f_any *>(s), b = *reinterpret_cast<const v4f_any *>(s + 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[u][e] = a[e], v[u][4 + e] = b[e];
         } else {
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[u][e] = (e < cnt) ? s[e] : 0.0f;
@@ -793,6 +799,7 @@ __global__ __launch_bounds__(kThreads) void tile_amax_kernel(const TileParams p,
 // Bound by the waves in flight, which their registers limit: NV is the least of 2, 4, 8, 10, 12 and 16 that holds the block (16
 // for all beyond 8 -> now: 3001 x 4500 17.9 -> 12.5 us, 5.4 TB/s of source and result; 6000 columns 18.7 -> 15.6; 500 x 4500 8.1 ->
 // 5.9; stochastic 3001 x 4500 33.3 -> 21.9).
+// Rows of odd lengths take the same 16-byte loads, aligned to 4 bytes (value by value -> now: 3000 x 4501 27.6 -> 12.6 us).
 struct WaveParams {
     const float *src;
     uint8_t *mant;
@@ -803,7 +810,6 @@ struct WaveParams {
     int32_t kshare;        // stored blocks per exponent block
     int32_t nreg;          // exponent blocks per row
     int32_t chunks;        // chunks per stored row
-    int32_t vec_ok;
     uint32_t s0, s1;
 };
 
@@ -833,11 +839,10 @@ __global__ __launch_bounds__(kThreads) void enc_rowwave_kernel(const WaveParams 
         }
         cnt[i] = c;
         const float *s = srow + (c ? (int64_t)blk * p.kblock + 8 * j : 0);
-        if (c == 8 && p.vec_ok) {
-            const float4 a = *reinterpret_cast<const float4 *>(s);
-            const float4 b = *reinterpret_cast<const float4 *>(s + 4);
-            v[i][0] = a.x; v[i][1] = a.y; v[i][2] = a.z; v[i][3] = a.w;
-            v[i][4] = b.x; v[i][5] = b.y; v[i][6] = b.z; v[i][7] = b.w;
+        if (c == 8) {
+            const v4f_any a = *reinterpret_cast<const v4f_any *>(s), b = *reinterpret_cast<const v4f_any *>(s + 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[i][e] = a[e], v[i][4 + e] = b[e];
         } else {
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[i][e] = (e < c) ? s[e] : 0.0f;
@@ -1551,7 +1556,6 @@ static int launch_encode_rowwave(const float *src, const EncodeGeom &g, void *ma
     p.kshare = (int32_t)(g.kshare > g.nblk ? g.nblk : g.kshare);
     p.nreg = (int32_t)ceil_div(g.nblk, g.kshare);
     p.chunks = (int32_t)(g.kpad / 8);
-    p.vec_ok = (((uintptr_t)src & 15) == 0 && (g.ld % 4) == 0 && (g.kblock % 4) == 0) ? 1 : 0;
     p.s0 = g.seed_lo;
     p.s1 = g.seed_hi;
     const int64_t most = p.nreg == 1 ? p.chunks : max((int64_t)p.kshare * p.gp, p.chunks - (int64_t)(p.nreg - 1) * p.kshare * p.gp);

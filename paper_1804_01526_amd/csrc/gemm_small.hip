@@ -361,7 +361,6 @@ struct ConvertSource {
     int64_t ld;
     int32_t rows, m;             // rows or columns of the operand
     int32_t down;                // the contraction runs down the source rows
-    int32_t vec;                 // four values of a row start on 16 bytes
 };
 struct ConvertParams {
     ConvertSource x[2];
@@ -387,11 +386,11 @@ __device__ __forceinline__ void convert_load(const ConvertSource &x, const Conve
         }
     } else {
         const float *s = x.src + r * x.ld + k0 + (left > 0 ? 16 * lh : 0);
-        if (len == 32 && x.vec) {
+        if (len == 32) {
 #pragma unroll
             for (int j = 0; j < 16; j += 4) {
-                const float4 d = *reinterpret_cast<const float4 *>(s + j);
-                v[j] = d.x, v[j + 1] = d.y, v[j + 2] = d.z, v[j + 3] = d.w;
+                const v4f_any d = *reinterpret_cast<const v4f_any *>(s + j);
+                v[j] = d[0], v[j + 1] = d[1], v[j + 2] = d[2], v[j + 3] = d[3];
             }
         } else {
 #pragma unroll
@@ -562,19 +561,19 @@ int launch_gemm_small(const GemmArgs &a, hipStream_t s, const hbfp_tensor *enc, 
 // Whether the product converts its own operands: one round of workgroups, at most two blocks of each operand per wave, and the
 // products that the kernels above would take.  Every workgroup converts for itself and one of few blocks is mostly the fetch of
 // its own instructions: with four blocks per wave the two launches are ahead or level (512 x 512 x 1024 10.9 us against 12.9
-// here).  So they are from 257 of k on where the rows of both operands are read value by value (511^3, B transposed, 10.8
-// against 13.5; 500 x 510 x 333 9.7, 10.7; one such operand 10.8, 10.5).  Measured in a graph, two launches -> here: 256^3
-// 7.0 -> 4.8 us, both operands down the rows 7.0 -> 4.3, 512^3 8.4 -> 6.6, 128 x 2000 x 500 9.25 -> 9.0, 16 x 4096 x 512 8.6 ->
-// 5.7, 33 x 2048 x 64 6.8 -> 4.5; call by call, where the host's two launches are the bound, 13.0 -> 9.5 at all of them.
-static bool by_value(const float *src, const EncodeGeom &g) { return g.axis == 1 && (((uintptr_t)src & 15) || g.ld % 4 || g.kblock != 32); }
-bool gemm_convert_ok(const GemmArgs &a, const float *const *src, const EncodeGeom *geom) {
+// here).  So they are from 257 of k on where both operands lie along the rows in blocks that are not 32 long and are read value
+// by value (511^3 read so: 10.8 against 13.5; one such operand 10.8, 10.5).  Measured in a graph, two launches -> here: 256^3
+// 7.0 -> 4.7 us, both operands down the rows 7.0 -> 4.2, 512^3 8.4 -> 6.6, 511^3 10.8 -> 8.0, 128 x 2000 x 500 9.25 -> 9.0,
+// 33 x 2047 x 499 10.2 -> 6.6, 16 x 4096 x 512 8.6 -> 5.7, 33 x 2048 x 64 6.8 -> 4.5; call by call, where the host's two launches
+// are the bound, 13.0 -> 9.5 at all of them.
+bool gemm_convert_ok(const GemmArgs &a, const EncodeGeom *geom) {
     if (!encode_pair_ok(geom[0], geom[1]) || !gemm_small_ok(a)) return false;
     if (a.kpad > 512 || ceil_div(a.M, 32) * ceil_div(a.N, 32) > 256) return false;
-    return a.kpad <= 256 || !by_value(src[0], geom[0]) || !by_value(src[1], geom[1]);
+    return a.kpad <= 256 || a.kblock == 32 || geom[0].axis == 0 || geom[1].axis == 0;
 }
 
 int launch_gemm_convert(const GemmArgs &a, const float *const *src, const EncodeGeom *geom, hipStream_t s) {
-    if (!gemm_convert_ok(a, src, geom)) return HBFP_ERR_FORMAT;
+    if (!gemm_convert_ok(a, geom)) return HBFP_ERR_FORMAT;
     ConvertParams p = {};
     for (int o = 0; o < 2; ++o) {
         const EncodeGeom &g = geom[o];
@@ -583,7 +582,6 @@ int launch_gemm_convert(const GemmArgs &a, const float *const *src, const Encode
         p.x[o].rows = (int32_t)g.R;
         p.x[o].m = g.m;
         p.x[o].down = g.axis == 0;
-        p.x[o].vec = !by_value(src[o], g);
     }
     p.C = a.C;
     p.ldc = a.ldc;

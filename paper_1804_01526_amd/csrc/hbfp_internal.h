@@ -112,7 +112,7 @@ size_t gemm_limb_workspace(const hbfp_tensor *A, const hbfp_tensor *B);
 bool gemm_small_ok(const GemmArgs &a);
 int launch_gemm_small(const GemmArgs &a, hipStream_t s, const hbfp_tensor *enc = nullptr, int relu = 0);
 // both operands converted inside the product: FP32 sources, 1-D blocks stored as 32, at most 8 bits, round to nearest
-bool gemm_convert_ok(const GemmArgs &a, const float *const *src, const EncodeGeom *geom);
+bool gemm_convert_ok(const GemmArgs &a, const EncodeGeom *geom);
 int launch_gemm_convert(const GemmArgs &a, const float *const *src, const EncodeGeom *geom, hipStream_t s);
 
 // gemm_wide.hip: int8 kernel for one exponent per operand row (a single block along k)

@@ -33,11 +33,11 @@ def _operands(hb, M, N, K, block, pad, trans_a, trans_b):
 
 @pytest.mark.parametrize("M,N,K,block,pad,inside", [(1, 1, 1, 32, 0, "tt"), (33, 31, 255, 32, 0, "tt"), (64, 97, 256, 32, 1, "tt"),
                                                     (32, 32, 257, 32, 3, "tt"), (100, 130, 512, 32, 0, "tt"), (45, 70, 380, 24, 4, "tf"),
-                                                    (511, 65, 511, 32, 0, "tf"), (40, 64, 513, 32, 3, "ff"),
+                                                    (511, 65, 511, 32, 0, "tt"), (40, 64, 513, 32, 3, "ff"),
                                                     (5, 8192, 61, 17, 3, "tt"), (5, 8193, 61, 32, 0, "ff")])
 @pytest.mark.parametrize("trans_a,trans_b", [(0, 0), (0, 1), (1, 0), (1, 1)])
 def test_products_that_convert_their_operands(hb, M, N, K, block, pad, inside, trans_a, trans_b):
-    """`inside`: whether one launch does it (t), for any direction of the operands and for both along rows read value by value."""
+    """`inside`: whether one launch does it (t), for any direction of the operands but, and for, both along the rows."""
     print(f"[case] gemm_f32 {M}x{N}x{K} block {block} pad {pad} {trans_a}{trans_b}", flush=True)
     A, B, fa, fb = _operands(hb, M, N, K, block, pad, trans_a, trans_b)
     got = hb.gemm_f32(trans_a, trans_b, A, B, fa, fb)

@@ -215,7 +215,8 @@ struct BfGroup {
 // that every 32 x 32 result arrives transposed (same products, same sums) as mx_store_encoded wants them
 // F16: FP16 planes (10..12-bit mantissas relative to their rows' largest exponents): the FP16 matrix instruction, and the
 // rows' and columns' factors applied at the store
-template <bool TR, bool F16>
+// STREAM: how C leaves (stores_stream)
+template <bool TR, bool F16, bool STREAM>
 __global__ __launch_bounds__(kBfThreads, 2) void gemm_bf_kernel(const BfGroup g) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     // which product this workgroup belongs to: selected with constant indices, so that the parameters stay in scalar
@@ -381,9 +382,8 @@ __global__ __launch_bounds__(kBfThreads, 2) void gemm_bf_kernel(const BfGroup g)
 #pragma unroll
         for (int j = 0; j < 4; ++j) sb[j] = col0 + j * 32 + l32 < p.N ? p.sb[col0 + j * 32 + l32] : 0;
     }
-    // streaming stores leave the operand panels in the caches
-    store_result<2, 4, true>(p.C + row0 * p.ldc + col0, p.ldc, p.M - row0, p.N - col0, p.beta != 0, lane,
-                             [&](int i, int j, int v) { return F16 ? __builtin_ldexpf(acc[i][j][v], sa[i][v] + sb[j]) : acc[i][j][v]; });
+    store_result<2, 4, STREAM>(p.C + row0 * p.ldc + col0, p.ldc, p.M - row0, p.N - col0, p.beta != 0, lane,
+                               [&](int i, int j, int v) { return F16 ? __builtin_ldexpf(acc[i][j][v], sa[i][v] + sb[j]) : acc[i][j][v]; });
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -420,7 +420,7 @@ __device__ __forceinline__ int64_t bf_half_start(int rows128, int ksteps) {
     return (int64_t)(rows128 >> 1) * ksteps * kBfStageBytes + (rows128 & 1) * kBfSmallHalf;
 }
 
-template <bool TR, bool F16>
+template <bool TR, bool F16, bool STREAM>
 __global__ __launch_bounds__(kBfSmallThreads, 4) void gemm_bf_small_kernel(const BfGroup g) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     BfParams p = g.p[0];
@@ -566,9 +566,8 @@ __global__ __launch_bounds__(kBfSmallThreads, 4) void gemm_bf_small_kernel(const
 #pragma unroll
         for (int j = 0; j < 2; ++j) sb[j] = col0 + j * 32 + l32 < p.N ? p.sb[col0 + j * 32 + l32] : 0;
     }
-    // streaming stores leave the operand panels in the caches
-    store_result<2, 2, true>(p.C + row0 * p.ldc + col0, p.ldc, p.M - row0, p.N - col0, p.beta != 0, lane,
-                             [&](int i, int j, int v) { return F16 ? __builtin_ldexpf(acc[i][j][v], sa[i][v] + sb[j]) : acc[i][j][v]; });
+    store_result<2, 2, STREAM>(p.C + row0 * p.ldc + col0, p.ldc, p.M - row0, p.N - col0, p.beta != 0, lane,
+                               [&](int i, int j, int v) { return F16 ? __builtin_ldexpf(acc[i][j][v], sa[i][v] + sb[j]) : acc[i][j][v]; });
 }
 
 int64_t klen_of(const GemmArgs &a, int m) { return bf_klen(a.kpad, a.kbp, a.kblock, a.nblk, a.kdim, m); }
@@ -663,14 +662,13 @@ static bool bf_small_tiles(int n, const GemmArgs *args) {
     return ceil_div(small, 256) <= 2 * ceil_div(large, 256);
 }
 
-template <bool TR, bool F16>
+template <bool TR, bool F16, bool STREAM>
 static int launch_bf_kernel(bool small, unsigned workgroups, const BfGroup &g, hipStream_t s) {
     static std::atomic<bool> configured[2];
     const int bytes = small ? kBfSmallRing * kBfSmallStage : kBfRing * kBfStage;
-    const void *kernel = small ? reinterpret_cast<const void *>(&gemm_bf_small_kernel<TR, F16>) : reinterpret_cast<const void *>(&gemm_bf_kernel<TR, F16>);
-    if (allow_dynamic_lds(configured[small], kernel, bytes) != HBFP_OK) return HBFP_ERR_LAUNCH;
-    if (small) hipLaunchKernelGGL((gemm_bf_small_kernel<TR, F16>), dim3(workgroups), dim3(kBfSmallThreads), bytes, s, g);
-    else hipLaunchKernelGGL((gemm_bf_kernel<TR, F16>), dim3(workgroups), dim3(kBfThreads), bytes, s, g);
+    void (*const kernel)(BfGroup) = small ? &gemm_bf_small_kernel<TR, F16, STREAM> : &gemm_bf_kernel<TR, F16, STREAM>;
+    if (allow_dynamic_lds(configured[small], reinterpret_cast<const void *>(kernel), bytes) != HBFP_OK) return HBFP_ERR_LAUNCH;
+    hipLaunchKernelGGL(kernel, dim3(workgroups), dim3(small ? kBfSmallThreads : kBfThreads), bytes, s, g);
     return launch_status();
 }
 
@@ -719,9 +717,10 @@ static int launch_bf_group(int n, const GemmArgs *args, const void *const *packe
         if (first > 0x7ffffff0) return HBFP_ERR_ARG;
     }
     for (int i = n; i <= kBfGroup; ++i) g.first[i] = (int32_t)first;
-    if (f16) return launch_bf_kernel<false, true>(small, (unsigned)first, g, s);
-    if (out) return launch_bf_kernel<true, false>(small, (unsigned)first, g, s);
-    return launch_bf_kernel<false, false>(small, (unsigned)first, g, s);
+    if (out) return launch_bf_kernel<true, false, true>(small, (unsigned)first, g, s);
+    const bool stream = stores_stream(args, n);
+    if (f16) return stream ? launch_bf_kernel<false, true, true>(small, (unsigned)first, g, s) : launch_bf_kernel<false, true, false>(small, (unsigned)first, g, s);
+    return stream ? launch_bf_kernel<false, false, true>(small, (unsigned)first, g, s) : launch_bf_kernel<false, false, false>(small, (unsigned)first, g, s);
 }
 
 int launch_bf_products(int n, const GemmArgs *args, const void *const *packed_a, const void *const *packed_b, hipStream_t s) {

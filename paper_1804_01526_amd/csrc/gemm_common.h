@@ -57,9 +57,27 @@ __device__ __forceinline__ void async_copy4(const void *gbase, uint32_t voff, ui
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_addr), "v"(voff), "s"(gbase) : "memory");
 }
 
+// Whether rows of C go past the caches.  They are written once and not read again by the call, so streaming stores leave the caches to
+// the operands: 2 to 6 Mi outputs are 3 to 11 % faster than with ordinary stores, larger ones in whole lines 2 %.  But where a row ends
+// inside a line the next row writes the rest of it, and once C no longer fits the L2 caches (32 MB) such a line leaves them as two
+// partial writes: packed 4995 x 3043 x 104 29.7 us streaming, 17.8 with ordinary stores, 4037 x 4663 x 55 41.1 and 24.1.  Ordinary
+// stores are ahead from 6 Mi outputs on for rows off 32 bytes (6 to 8 Mi 9 %, 14 to 20 Mi 34 %), from 10 Mi on for rows off 128 (7 %).
+// A group of products shares one launch: the larger part of its outputs decides.  The choice is the host's: in one kernel the compiler
+// makes ordinary stores of two branches that differ in this alone.
+inline bool stores_stream(const GemmArgs *args, int n = 1) {
+    int64_t count = 0, balance = 0;
+    for (int i = 0; i < n; ++i) count += args[i].M * args[i].N;
+    for (int i = 0; i < n; ++i) {
+        const uint64_t off = (uint64_t)(uintptr_t)args[i].C | (uint64_t)args[i].ldc * 4;
+        const bool stream = (off & 127) == 0 || count < ((int64_t)((off & 31) ? 6 : 10) << 20);
+        balance += stream ? args[i].M * args[i].N : -args[i].M * args[i].N;
+    }
+    return balance >= 0;
+}
+
 // Stores a wave's TI x TJ results of 32 x 32 (lane l: column l % 32, register v: row 8 (v / 4) + 4 (l / 32) + v % 4); dst is
-// their first element, rows and cols what is left of the product from there, value(i, j, v) the output.  STREAM: written once
-// and not read again by this call, so past the caches.
+// their first element, rows and cols what is left of the product from there, value(i, j, v) the output.  STREAM: past the caches
+// (stores_stream).
 // Bound by its instructions: with a 64-bit product for every row, and two tests and a branch around every store, the 128
 // stores of a lane of the 256 x 256-tile kernels were 2500 instructions of straight code that the waves fetched once each,
 // and a kernel of a few k-steps spent most of its time there.  Here a whole tile is stores and one addition per row; only

@@ -65,7 +65,7 @@ struct LimbRegs {
 };
 
 // SPB: k-steps per exponent block: 1, 2, or 0 = a multiple of 4 (blocks span whole stages)
-template <int SPB, bool DUMP>
+template <int SPB, bool DUMP, bool STREAM>
 __global__ __launch_bounds__(kThreads, 2) void gemm_limb_kernel(const LimbParams p) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[kLdsBytes];
     if (stands_down(p.run_a, p.run_b)) return;
@@ -245,7 +245,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_limb_kernel(const LimbParams
 
     if (DUMP) return;
     const int64_t i0 = row0 + wm * 32, j0 = col0 + wn * 64;
-    store_result<1, 2, true>(p.C + i0 * p.ldc + j0, p.ldc, p.M - i0, p.N - j0, p.beta != 0, lane,
+    store_result<1, 2, STREAM>(p.C + i0 * p.ldc + j0, p.ldc, p.M - i0, p.N - j0, p.beta != 0, lane,
                              [&](int, int ni, int v) { return acc[ni][v] * p.final_scale; });
 }
 
@@ -270,6 +270,7 @@ struct LimbW8Params {
     int32_t tiles_m;
 };
 
+template <bool STREAM>
 __global__ __launch_bounds__(kLwThreads, 4) void gemm_limb_w8_kernel(const LimbW8Params q) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const LimbParams &p = q.g;
@@ -420,13 +421,14 @@ __global__ __launch_bounds__(kLwThreads, 4) void gemm_limb_w8_kernel(const LimbW
 #undef HBFP_WAIT_COPIES
 
     const int64_t i0 = row0 + wm * 32, j0 = col0 + wn * 32;
-    store_result<1, 1, true>(p.C + i0 * p.ldc + j0, p.ldc, p.M - i0, p.N - j0, p.beta != 0, lane,
+    store_result<1, 1, STREAM>(p.C + i0 * p.ldc + j0, p.ldc, p.M - i0, p.N - j0, p.beta != 0, lane,
                              [&](int, int, int v) { return acc[v] * p.final_scale; });
 }
 
-template <int SPB, bool DUMP>
-int launch_t(const LimbParams &p, dim3 grid, hipStream_t s) {
-    hipLaunchKernelGGL((gemm_limb_kernel<SPB, DUMP>), grid, dim3(kThreads), 0, s, p);
+template <int SPB>
+int launch_t(const LimbParams &p, dim3 grid, bool stream, hipStream_t s) {
+    void (*const kernel)(LimbParams) = p.P ? &gemm_limb_kernel<SPB, true, true> : stream ? &gemm_limb_kernel<SPB, false, true> : &gemm_limb_kernel<SPB, false, false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, p);
     return launch_status();
 }
 
@@ -482,9 +484,11 @@ int launch_gemm_limb(const GemmArgs &a, void *workspace, hipStream_t s) {
     p.run_a = a.run_a;
     p.run_b = a.run_b;
     const dim3 grid((unsigned)(tm * tn));
+    const bool stream = stores_stream(&a);                // how C leaves
     if (!a.P && !a.run_a && p.spb == 2 && (uint64_t)127 * (uint64_t)a.kpad + 64 < ((uint64_t)1 << 32) && ceil_div(tm * tn, 8) * 8 <= 0x7fffffff) {
-        static std::atomic<bool> configured{false};
-        if (allow_dynamic_lds(configured, reinterpret_cast<const void *>(&gemm_limb_w8_kernel), kLwLdsBytes) != HBFP_OK) return HBFP_ERR_LAUNCH;
+        static std::atomic<bool> configured[2];
+        void (*const kernel)(LimbW8Params) = stream ? &gemm_limb_w8_kernel<true> : &gemm_limb_w8_kernel<false>;
+        if (allow_dynamic_lds(configured[stream], reinterpret_cast<const void *>(kernel), kLwLdsBytes) != HBFP_OK) return HBFP_ERR_LAUNCH;
         LimbW8Params q;
         q.g = p;
         q.mpad = ceil_div(a.M, 128) * 128;
@@ -496,11 +500,10 @@ int launch_gemm_limb(const GemmArgs &a, void *workspace, hipStream_t s) {
         const int rc = launch_scale_words(a.expA, a.expA_ld, a.M, a.expB, a.expB_ld, a.N, (int)a.expA_ld, 0u,
                                           const_cast<uint32_t *>(q.wA), const_cast<uint32_t *>(q.wB), a.run_a, a.run_b, s);
         if (rc != HBFP_OK) return rc;
-        hipLaunchKernelGGL(gemm_limb_w8_kernel, dim3((unsigned)(ceil_div(tm * tn, 8) * 8)), dim3(kLwThreads), kLwLdsBytes, s, q);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(ceil_div(tm * tn, 8) * 8)), dim3(kLwThreads), kLwLdsBytes, s, q);
         return launch_status();
     }
-    if (a.P) return p.spb == 1 ? launch_t<1, true>(p, grid, s) : p.spb == 2 ? launch_t<2, true>(p, grid, s) : launch_t<0, true>(p, grid, s);
-    return p.spb == 1 ? launch_t<1, false>(p, grid, s) : p.spb == 2 ? launch_t<2, false>(p, grid, s) : launch_t<0, false>(p, grid, s);
+    return p.spb == 1 ? launch_t<1>(p, grid, stream, s) : p.spb == 2 ? launch_t<2>(p, grid, stream, s) : launch_t<0>(p, grid, stream, s);
 }
 
 }  // namespace hbfp

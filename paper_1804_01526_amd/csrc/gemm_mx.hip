@@ -365,8 +365,8 @@ struct MxGroup {
         }                                                                                                                  \
     }
 
-// TR: the variant whose output is an encoded operand (g.out)
-template <int LA, int LB, bool TR>
+// TR: the variant whose output is an encoded operand (g.out); STREAM: how C leaves (stores_stream), a choice for one limb each
+template <int LA, int LB, bool TR, bool STREAM>
 __global__ __launch_bounds__(kMxThreads, 2) void gemm_mx_kernel(const MxGroup g) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     constexpr int CHA = chunk_bytes(LA), CHB = chunk_bytes(LB);
@@ -630,8 +630,7 @@ __global__ __launch_bounds__(kMxThreads, 2) void gemm_mx_kernel(const MxGroup g)
         return;
     }
     if (LA == 1 && LB == 1) {
-        // streaming stores leave the operand panels in the caches
-        store_result<2, 4, true>(p.C + row0 * p.ldc + col0, p.ldc, p.M - row0, p.N - col0, p.beta != 0, lane,
+        store_result<2, 4, STREAM>(p.C + row0 * p.ldc + col0, p.ldc, p.M - row0, p.N - col0, p.beta != 0, lane,
                                  [&](int i, int j, int v) { return acc[i][j][v]; });
         return;
     }
@@ -771,19 +770,22 @@ __global__ __launch_bounds__(256) void relu_kernel(float *x, int64_t n) {
     if (i < n) x[i] = x[i] < 0.0f ? 0.0f : x[i];
 }
 
-template <int LA, int LB, bool TR>
+template <int LA, int LB, bool TR, bool STREAM>
 int launch_mx_tr(const MxGroup &g, hipStream_t s) {
     constexpr int bytes = mx_lds_bytes(LA, LB);
     static std::atomic<bool> configured{false};
-    if (allow_dynamic_lds(configured, reinterpret_cast<const void *>(&gemm_mx_kernel<LA, LB, TR>), bytes) != HBFP_OK) return HBFP_ERR_LAUNCH;
+    if (allow_dynamic_lds(configured, reinterpret_cast<const void *>(&gemm_mx_kernel<LA, LB, TR, STREAM>), bytes) != HBFP_OK) return HBFP_ERR_LAUNCH;
     const unsigned grid = (unsigned)g.first[g.n] + (g.word_jobs ? (unsigned)(g.n * kMxWordWgs) : 0u);
-    hipLaunchKernelGGL((gemm_mx_kernel<LA, LB, TR>), dim3(grid), dim3(kMxThreads), bytes, s, g);
+    hipLaunchKernelGGL((gemm_mx_kernel<LA, LB, TR, STREAM>), dim3(grid), dim3(kMxThreads), bytes, s, g);
     return launch_status();
 }
 
 template <int LA, int LB>
-int launch_mx_t(const MxGroup &g, hipStream_t s) {
-    return g.out.mant ? launch_mx_tr<LA, LB, true>(g, s) : launch_mx_tr<LA, LB, false>(g, s);
+int launch_mx_t(const MxGroup &g, bool stream, hipStream_t s) {
+    if (g.out.mant) return launch_mx_tr<LA, LB, true, true>(g, s);
+    if constexpr (LA == 1 && LB == 1)
+        if (!stream) return launch_mx_tr<LA, LB, false, false>(g, s);
+    return launch_mx_tr<LA, LB, false, true>(g, s);
 }
 
 }  // namespace
@@ -929,14 +931,15 @@ static int launch_mx_group(int n, GemmArgs *args, const void *const *packed_a, c
         g.word_jobs |= 1 << i;
         args[i].words_ready = 1;
     }
+    const bool stream = stores_stream(args, n);
     switch (LA * 4 + LB) {
-        case 1 * 4 + 1: return launch_mx_t<1, 1>(g, s);
-        case 1 * 4 + 2: return launch_mx_t<1, 2>(g, s);
-        case 2 * 4 + 1: return launch_mx_t<2, 1>(g, s);
-        case 2 * 4 + 2: return launch_mx_t<2, 2>(g, s);
-        case 2 * 4 + 3: return launch_mx_t<2, 3>(g, s);
-        case 3 * 4 + 2: return launch_mx_t<3, 2>(g, s);
-        case 3 * 4 + 3: return launch_mx_t<3, 3>(g, s);
+        case 1 * 4 + 1: return launch_mx_t<1, 1>(g, stream, s);
+        case 1 * 4 + 2: return launch_mx_t<1, 2>(g, stream, s);
+        case 2 * 4 + 1: return launch_mx_t<2, 1>(g, stream, s);
+        case 2 * 4 + 2: return launch_mx_t<2, 2>(g, stream, s);
+        case 2 * 4 + 3: return launch_mx_t<2, 3>(g, stream, s);
+        case 3 * 4 + 2: return launch_mx_t<3, 2>(g, stream, s);
+        case 3 * 4 + 3: return launch_mx_t<3, 3>(g, stream, s);
         default: return HBFP_ERR_FORMAT;
     }
 }

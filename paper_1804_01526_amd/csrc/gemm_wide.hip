@@ -43,7 +43,8 @@ struct WideParams {
     const int *run_a, *run_b;
 };
 
-template <int T>
+// STREAM: how C leaves (stores_stream)
+template <int T, bool STREAM>
 __global__ __launch_bounds__(kWideThreads, T == 4 ? 1 : 2) void gemm_i8_wide_kernel(const WideParams p) {
     typedef Wide<T> W;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
@@ -206,7 +207,7 @@ __global__ __launch_bounds__(kWideThreads, T == 4 ? 1 : 2) void gemm_i8_wide_ker
                                   lane, [&](int i, int j, int v) { return __int_as_float(acc[i][j][v]); });
         return;
     }
-    store_result<T, T, true>(p.C + i0 * p.ldc + j0, p.ldc, p.M - i0, p.N - j0, p.beta != 0, lane, [&](int i, int j, int v) {
+    store_result<T, T, STREAM>(p.C + i0 * p.ldc + j0, p.ldc, p.M - i0, p.N - j0, p.beta != 0, lane, [&](int i, int j, int v) {
         return __builtin_amdgcn_ldexpf((float)acc[i][j][v], ea[32 * i + 8 * (v >> 2) + (v & 3)] + eb[j]);
     });
 }
@@ -242,14 +243,15 @@ __global__ __launch_bounds__(256) void wide_sum_kernel(const WideParams p) {
 }
 
 template <int T>
-int launch_wide_t(WideParams p, hipStream_t s) {
-    static std::atomic<bool> configured{false};
-    if (allow_dynamic_lds(configured, reinterpret_cast<const void *>(&gemm_i8_wide_kernel<T>), Wide<T>::kLds) != HBFP_OK) return HBFP_ERR_LAUNCH;
+int launch_wide_t(WideParams p, bool stream, hipStream_t s) {
+    static std::atomic<bool> configured[2];
+    void (*const kernel)(WideParams) = stream ? &gemm_i8_wide_kernel<T, true> : &gemm_i8_wide_kernel<T, false>;
+    if (allow_dynamic_lds(configured[stream], reinterpret_cast<const void *>(kernel), Wide<T>::kLds) != HBFP_OK) return HBFP_ERR_LAUNCH;
     p.tiles_m = (int32_t)ceil_div(p.M, Wide<T>::kRows);
     p.tiles_n = (int32_t)ceil_div(p.N, Wide<T>::kRows);
     const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
     const dim3 grid = p.splits >= 8 ? dim3((unsigned)(8 * tiles * ceil_div(p.splits, 8))) : dim3((unsigned)(ceil_div(tiles, 8) * 8), (unsigned)p.splits);
-    hipLaunchKernelGGL(gemm_i8_wide_kernel<T>, grid, dim3(kWideThreads), Wide<T>::kLds, s, p);
+    hipLaunchKernelGGL(kernel, grid, dim3(kWideThreads), Wide<T>::kLds, s, p);
     return launch_status();
 }
 
@@ -329,7 +331,8 @@ int launch_gemm_wide(const GemmArgs &a, void *workspace, hipStream_t s) {
     p.exp_offset = -250 - a.mA - a.mB;
     p.run_a = a.run_a;
     p.run_b = a.run_b;
-    const int rc = plan.T == 2 ? launch_wide_t<2>(p, s) : plan.T == 3 ? launch_wide_t<3>(p, s) : launch_wide_t<4>(p, s);
+    const bool stream = stores_stream(&a);
+    const int rc = plan.T == 2 ? launch_wide_t<2>(p, stream, s) : plan.T == 3 ? launch_wide_t<3>(p, stream, s) : launch_wide_t<4>(p, stream, s);
     if (rc != HBFP_OK || p.splits == 1) return rc;
     const int64_t wgs = ceil_div(a.M * a.N, 1024);
     if (wgs > 0x7fffffff) return HBFP_ERR_ARG;

@@ -6,6 +6,8 @@ product of the decoded operands; the bytes of the buffer around C must stay as t
 import pytest
 import torch
 
+from tests.util import launched_kernels
+
 pytestmark = pytest.mark.gpu
 
 INT8, SCALED, WIDE, FP16, BF16, F16P = 1, 2, 3, 4, 5, 6
@@ -41,6 +43,57 @@ def test_edges_pitch_and_accumulation(kernel, bits, block, edge, dm, dn, beta):
     assert torch.equal(C.double(), want)
     buf[1:M + 1, 2:N + 2] = 7.0
     assert bool((buf == 7.0).all())
+
+
+# Large outputs whose rows are not whole lines leave by ordinary stores, others past the caches: rows off 32 bytes from 6 Mi outputs on,
+# rows off 128 from 10 Mi on; the base of C counts like its pitch
+@pytest.mark.parametrize("kernel,bits,block", [(BF16, 8, 24), (F16P, 12, 64), (SCALED, 4, 32), (WIDE, 8, 0), (INT8, 12, 128), (INT8, 12, 64)])
+@pytest.mark.parametrize("M,N,pad,at,stream", [(2419, 2601, 0, 0, False), (2420, 2600, 1, 0, False), (2432, 2592, 0, 1, False), (2430, 2600, 0, 0, True),
+                                               (2417, 2601, 0, 0, True), (2560, 2560, 32, 0, True), (2600, 4040, 0, 0, False)])
+def test_how_large_outputs_leave(kernel, bits, block, M, N, pad, at, stream):
+    from paper_1804_01526_amd import hbfp
+    print(f"[store] kernel={kernel} bits={bits} block={block} {M}x{N} pitch {N + pad}", flush=True)
+    a, b, want = _operands(M, 192, N, bits, block)
+    buf = torch.full((M * (N + pad) + 32,), 7.0, device="cuda")
+    C = buf[at:at + M * (N + pad)].view(M, N + pad)[:, :N]
+    names = launched_kernels(lambda: hbfp.gemm(a, b, out=C, kernel=kernel))
+    assert torch.equal(C.double(), want)
+    C.fill_(7.0)
+    assert bool((buf == 7.0).all())
+    product = [n for n in names if n.startswith("gemm_")][0]
+    assert product.endswith(f"{str(stream).lower()}>"), names
+
+
+@pytest.mark.parametrize("M,K,N", [(4995, 104, 3043), (4037, 55, 4663)])
+def test_ragged_rows_are_not_far_behind_whole_lines(M, K, N):
+    """A large product whose rows end inside cache lines against the same one with a pitch of whole lines: streaming stores took it to
+    1.8 times, ordinary ones leave it within a third."""
+    from paper_1804_01526_amd import hbfp
+    a = hbfp.encode(torch.randn((M, K), device="cuda"), 1, hbfp.make_format(8, 1, 24))
+    b = hbfp.encode(torch.randn((K, N), device="cuda"), 0, hbfp.make_format(8, 24, 1))
+    pa, pb = hbfp.pack(a), hbfp.pack(b)
+
+    def fastest(out):
+        hbfp.gemm_packed(a, pa, b, pb, out=out)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                hbfp.gemm_packed(a, pa, b, pb, out=out)
+        times = []
+        for _ in range(10):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            graph.replay()
+            t1.record()
+            torch.cuda.synchronize()
+            times.append(t0.elapsed_time(t1) * 50)
+        return min(times)
+
+    lines = fastest(torch.empty((M, (N + 31) // 32 * 32), device="cuda")[:, :N])
+    ragged = fastest(torch.empty((M, N), device="cuda"))
+    print(f"[store] {M}x{K}x{N}: rows of whole lines {lines:.1f} us, ragged {ragged:.1f} us", flush=True)
+    assert ragged <= lines * 4 / 3
 
 
 @pytest.mark.parametrize("M,N", [(128, 128), (127, 130), (64, 257)])

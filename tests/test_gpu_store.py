@@ -64,6 +64,25 @@ def test_how_large_outputs_leave(kernel, bits, block, M, N, pad, at, stream):
     assert product.endswith(f"{str(stream).lower()}>"), names
 
 
+def _fastest(call):
+    """us of a call among others, replayed from a graph"""
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(20):
+            call()
+    times = []
+    for _ in range(10):
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        graph.replay()
+        t1.record()
+        torch.cuda.synchronize()
+        times.append(t0.elapsed_time(t1) * 50)
+    return min(times)
+
+
 @pytest.mark.parametrize("M,K,N", [(4995, 104, 3043), (4037, 55, 4663)])
 def test_ragged_rows_are_not_far_behind_whole_lines(M, K, N):
     """A large product whose rows end inside cache lines against the same one with a pitch of whole lines: streaming stores took it to
@@ -73,27 +92,26 @@ def test_ragged_rows_are_not_far_behind_whole_lines(M, K, N):
     b = hbfp.encode(torch.randn((K, N), device="cuda"), 0, hbfp.make_format(8, 24, 1))
     pa, pb = hbfp.pack(a), hbfp.pack(b)
 
-    def fastest(out):
-        hbfp.gemm_packed(a, pa, b, pb, out=out)
-        torch.cuda.synchronize()
-        graph = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(graph):
-            for _ in range(20):
-                hbfp.gemm_packed(a, pa, b, pb, out=out)
-        times = []
-        for _ in range(10):
-            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            t0.record()
-            graph.replay()
-            t1.record()
-            torch.cuda.synchronize()
-            times.append(t0.elapsed_time(t1) * 50)
-        return min(times)
-
-    lines = fastest(torch.empty((M, (N + 31) // 32 * 32), device="cuda")[:, :N])
-    ragged = fastest(torch.empty((M, N), device="cuda"))
+    whole, own = torch.empty((M, (N + 31) // 32 * 32), device="cuda")[:, :N], torch.empty((M, N), device="cuda")
+    lines = _fastest(lambda: hbfp.gemm_packed(a, pa, b, pb, out=whole))
+    ragged = _fastest(lambda: hbfp.gemm_packed(a, pa, b, pb, out=own))
     print(f"[store] {M}x{K}x{N}: rows of whole lines {lines:.1f} us, ragged {ragged:.1f} us", flush=True)
     assert ragged <= lines * 4 / 3
+
+
+@pytest.mark.parametrize("M,K,N", [(4092, 78, 3748), (1000, 512, 1000)])
+def test_factors_of_rows_and_columns_cost_little(M, K, N):
+    """FP16 planes against bf16 planes of the same size: the same matrix instructions and bytes, and a factor per row and column before
+    the stores (applied as part of every store they took half as long again)."""
+    from paper_1804_01526_amd import hbfp
+    out, times = torch.empty((M, N), device="cuda"), []
+    for bits in (8, 12):
+        a = hbfp.encode(torch.randn((M, K), device="cuda"), 1, hbfp.make_format(bits, 1, 32))
+        b = hbfp.encode(torch.randn((K, N), device="cuda"), 0, hbfp.make_format(bits, 32, 1))
+        pa, pb = hbfp.pack(a), hbfp.pack(b)
+        times.append(_fastest(lambda: hbfp.gemm_packed(a, pa, b, pb, out=out)))
+    print(f"[store] {M}x{K}x{N}: bf16 planes {times[0]:.1f} us, FP16 planes {times[1]:.1f} us", flush=True)
+    assert times[1] <= times[0] * 4 / 3
 
 
 @pytest.mark.parametrize("M,N", [(128, 128), (127, 130), (64, 257)])

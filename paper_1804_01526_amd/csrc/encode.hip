@@ -1024,7 +1024,7 @@ __global__ __launch_bounds__(kStripThreads) void enc_strip_kernel(const StripPar
 // 4096^2 27.3 -> 18.4, 2500 x 6000 24.1 -> 16.7, 3000 x 12000 60.8 -> 45.7, 1100 x 2999 8.2 -> 7.0, 3502 x 13 13.5 -> 8.6.
 constexpr int kHeldPieces = 5, kHeldThreads = 1024;
 template <bool WIDE, int ROUND, int PIECES>
-__global__ __launch_bounds__(kHeldThreads) void enc_strip_kernel(const StripParams p) {
+__global__ __launch_bounds__(kHeldThreads) void enc_strip_held_kernel(const StripParams p) {
     __shared__ uint32_t tile_max[64];
     const int t = threadIdx.x, groups = (int)blockDim.x / p.cw;
     const int c = t % p.cw, g = t / p.cw;
@@ -1646,10 +1646,10 @@ static int launch_encode_strip(const float *src, const EncodeGeom &g, void *mant
     const bool hold = pieces > 1 || 16 * most >= 15 * per || (int64_t)grid.x * grid.y <= 512;
     if (hold && ceil_div(most, 16 * (kHeldThreads / p.cw)) <= kHeldPieces) {
         const dim3 block(pieces <= kHeldPieces ? kStripThreads : kHeldThreads);
-        if (!wide && g.rounding == 0) hipLaunchKernelGGL((enc_strip_kernel<false, 0, kHeldPieces>), grid, block, 0, s, p);
-        else if (!wide) hipLaunchKernelGGL((enc_strip_kernel<false, 1, kHeldPieces>), grid, block, 0, s, p);
-        else if (g.rounding == 0) hipLaunchKernelGGL((enc_strip_kernel<true, 0, kHeldPieces>), grid, block, 0, s, p);
-        else hipLaunchKernelGGL((enc_strip_kernel<true, 1, kHeldPieces>), grid, block, 0, s, p);
+        if (!wide && g.rounding == 0) hipLaunchKernelGGL((enc_strip_held_kernel<false, 0, kHeldPieces>), grid, block, 0, s, p);
+        else if (!wide) hipLaunchKernelGGL((enc_strip_held_kernel<false, 1, kHeldPieces>), grid, block, 0, s, p);
+        else if (g.rounding == 0) hipLaunchKernelGGL((enc_strip_held_kernel<true, 0, kHeldPieces>), grid, block, 0, s, p);
+        else hipLaunchKernelGGL((enc_strip_held_kernel<true, 1, kHeldPieces>), grid, block, 0, s, p);
         return launch_status();
     }
     if (!wide && g.rounding == 0) hipLaunchKernelGGL((enc_strip_kernel<false, 0>), grid, dim3(kStripThreads), 0, s, p);

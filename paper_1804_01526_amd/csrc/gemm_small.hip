@@ -219,7 +219,7 @@ struct Few {
     static constexpr int kCopies = 2 * (MT + NT) + 1;
 };
 template <int MT, bool ENC>
-__global__ __launch_bounds__(kSmallThreads, 2) void gemm_small_kernel(const FewParams p) {
+__global__ __launch_bounds__(kSmallThreads, 2) void gemm_few_kernel(const FewParams p) {
     typedef Few<MT, ENC> R;
     constexpr int NT = R::NT;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
@@ -323,7 +323,7 @@ constexpr int kFewLds = 160 * 1024;
 template <int MT, bool ENC>
 int launch_few_t(const SmallParams &p, int64_t cols, hipStream_t s) {
     static std::atomic<bool> configured{false};
-    void (*kernel)(FewParams) = &gemm_small_kernel<MT, ENC>;
+    void (*kernel)(FewParams) = &gemm_few_kernel<MT, ENC>;
     if (allow_dynamic_lds(configured, reinterpret_cast<const void *>(kernel), kFewLds) != HBFP_OK) return HBFP_ERR_LAUNCH;
     const int64_t wgs = ceil_div(cols, 16 * Few<MT, ENC>::NT), per_cu = ceil_div(wgs, 256);
     const int chunk = kSmallWaves * Few<MT, ENC>::kChunk;                  // of all waves

@@ -563,19 +563,31 @@ def test_column_conversion_of_few_and_many_workgroups(hb, rows, cols, blk, m):
 
 
 @pytest.mark.parametrize("rows,cols,bc,rounding,where", [
-    (500, 300, 1, 0, "strip"), (4500, 2999, 1, 0, "strip"), (2560, 200, 1, 0, "strip"), (5120, 200, 1, 0, "two passes"),
-    (1280, 64, 1, 1, "strip"), (2560, 200, 1, 1, "two passes"), (5120, 1000, 1, 1, "two passes"), (4096, 4096, 1, 1, "strip"),
-    (2000, 38, 1, 1, "strip"), (5000, 33, 1, 1, "two passes"), (10000, 501, 1, 0, "two passes"), (10000, 3001, 1, 0, "strip"),
-    (8191, 6001, 1, 1, "two passes"), (861, 559, 64, 1, "strip"),
-    (5000, 1, 1, 0, "strip"), (7261, 3, 1, 1, "strip"), (11040, 4, 4, 1, "two passes")])
+    (500, 300, 1, 0, "strip held"), (4500, 2999, 1, 0, "strip held"), (2560, 200, 1, 0, "strip held"), (5120, 200, 1, 0, "two passes"),
+    (1280, 64, 1, 1, "strip held"), (2560, 200, 1, 1, "two passes"), (5120, 1000, 1, 1, "two passes"), (4096, 4096, 1, 1, "strip held"),
+    (2000, 38, 1, 1, "strip held"), (5000, 33, 1, 1, "two passes"), (10000, 501, 1, 0, "two passes"), (10000, 3001, 1, 0, "strip"),
+    (8191, 6001, 1, 1, "two passes"), (861, 559, 64, 1, "strip held"),
+    (5000, 1, 1, 0, "strip held"), (7261, 3, 1, 1, "strip held"), (11040, 4, 4, 1, "two passes")])
 def test_where_long_blocks_down_the_rows_are_converted(hb, rows, cols, bc, rounding, where):
-    """One exponent per `bc` columns: strips, or two passes where few strips would be too long; each case on the side that was
-    measured faster."""
+    """One exponent per `bc` columns: strips, held in registers or read twice, or two passes where few strips would be too long; each
+    case on the side that was measured faster."""
     x = torch.randn((rows, cols), device="cuda")
     fmt = hb.make_format(8, 0, bc, rounding, 3)
     out = hb.alloc(fmt, rows, cols, 0)
     names = launched_kernels(lambda: hb.encode(x, 0, fmt, out=out))
-    assert any(n.startswith("enc_strip_kernel") for n in names) == (where == "strip"), names
+    strips = [n.split("<")[0] for n in names if n.startswith("enc_strip_")]
+    assert strips == {"strip": ["enc_strip_kernel"], "strip held": ["enc_strip_held_kernel"], "two passes": []}[where], names
+
+
+@pytest.mark.parametrize("rows,cols,br,held", [(5120, 1035, 0, True), (5121, 1035, 0, False), (1024, 1024, 128, True), (1024, 1040, 128, False),
+                                               (4096, 4096, 240, True), (4096, 4096, 128, False), (4096, 4096, 512, True)])
+def test_which_strips_are_held_in_registers(hb, rows, cols, br, held):
+    """What fits the registers; blocks that give half of the threads nothing only in at most 512 workgroups."""
+    x = torch.randn((rows, cols), device="cuda")
+    fmt = hb.make_format(8, br, 1)
+    out = hb.alloc(fmt, rows, cols, 0)
+    names = launched_kernels(lambda: hb.encode(x, 0, fmt, out=out))
+    assert len(names) == 1 and names[0].startswith("enc_strip_held_kernel<" if held else "enc_strip_kernel<"), names
 
 
 @pytest.mark.parametrize("m,rounding", [(8, 0), (12, 1)])
@@ -631,7 +643,7 @@ def test_strips_narrower_than_sixteen_columns(hb, rows, cols, br, bc, slot, m, r
     out = hb.alloc(fmt, rows, cols, 0)
     out.mant.fill_(85)
     out.exps.fill_(85)
-    assert any(n.startswith("enc_strip_kernel") for n in launched_kernels(lambda: hb.encode(src, 0, fmt, out=out)))
+    assert any(n.startswith("enc_strip_") for n in launched_kernels(lambda: hb.encode(src, 0, fmt, out=out)))
     want = ref.encode(X, br, bc, m, rounding, 99)
     mant, exps = unpack(out)
     np.testing.assert_array_equal(mant, want.mant)

@@ -1664,11 +1664,11 @@ def test_where_the_scale_words_come_from(hb, M, N, K, blk, bytes_inside):
 
 
 @pytest.mark.parametrize("M,N,K,blk,where", [
-    (1, 1, 8, 32, "small 1"), (33, 32, 1000, 24, "small 1"), (256, 256, 256, 32, "small 1"), (16, 4096, 4096, 32, "small 1"),
+    (1, 1, 8, 32, "small 1"), (33, 32, 1000, 24, "small 1"), (256, 256, 256, 32, "small 1"), (16, 4096, 4096, 32, "few 1"),
     (600, 600, 600, 32, "small 2"), (700, 690, 300, 32, "small 2"), (128, 4096, 1024, 32, "small 2"),
     (1024, 1024, 512, 32, "tile"), (1000, 1000, 1000, 32, "tile"), (2048, 1024, 256, 32, "tile"), (32, 2048, 8192, 32, "tile"), (16, 64, 8192, 32, "tile")])
 def test_where_small_products_run(hb, M, N, K, blk, where):
-    """The automatic choice between the kernel for small products (tiles of 32 or 64 rows) and the tile kernels, both measured with
+    """The automatic choice between the kernels for small products (tiles of 32 or 64 rows, few rows) and the tile kernels, both measured with
     scale words made inside the tile kernel: each case on the side that is at least 4 % faster."""
     x = hb.encode(torch.randn((M, K), device="cuda"), 1, hb.make_format(8, 1, blk))
     w = hb.encode(torch.randn((K, N), device="cuda"), 0, hb.make_format(8, blk, 1))
@@ -1678,7 +1678,7 @@ def test_where_small_products_run(hb, M, N, K, blk, where):
         if where == "tile":
             assert names[0].startswith("gemm_i8_w8_kernel<1, false, false, 0"), names
         elif N >= 32 or enc == "false":                              # (shorter blocks: the conversion is a launch of its own)
-            assert names == [f"gemm_small_kernel<{where[-1]}, {enc}>"], names
+            assert names == [f"gemm_{where[:-2]}_kernel<{where[-1]}, {enc}>"], names
 
 
 @pytest.mark.parametrize("M,N,K,kernel", [(40, 70, 300, 0), (130, 100, 1100, 1), (130, 70, 9000, 1)])

@@ -1063,6 +1063,15 @@ __global__ __launch_bounds__(kHeldThreads) void enc_strip_held_kernel(const Stri
     }
 }
 
+template <int PIECES>
+int launch_held_n(const StripParams &p, dim3 grid, int threads, bool wide, int rounding, hipStream_t s) {
+    if (!wide && rounding == 0) hipLaunchKernelGGL((enc_strip_held_kernel<false, 0, PIECES>), grid, dim3(threads), 0, s, p);
+    else if (!wide) hipLaunchKernelGGL((enc_strip_held_kernel<false, 1, PIECES>), grid, dim3(threads), 0, s, p);
+    else if (rounding == 0) hipLaunchKernelGGL((enc_strip_held_kernel<true, 0, PIECES>), grid, dim3(threads), 0, s, p);
+    else hipLaunchKernelGGL((enc_strip_held_kernel<true, 1, PIECES>), grid, dim3(threads), 0, s, p);
+    return launch_status();
+}
+
 void magic_of(uint32_t d, uint32_t (&magic)[2]) {
     if (d == 1) {
         magic[0] = magic[1] = 0;
@@ -1640,17 +1649,18 @@ static int launch_encode_strip(const float *src, const EncodeGeom &g, void *mant
     // Positions of the longest exponent block (the last one has the padding of the row too) in pieces of 16 per thread: held in
     // registers if they fit, by 512 threads or else by 1024.  Only short blocks in many workgroups stay with the other kernel,
     // where twice as many workgroups share a compute unit, unless nearly every thread has a piece (read twice -> held, 4096^2:
-    // tiles of 96 x 24 26.9 and 28.5 us, blocks of 128 22.1 and 21.8, of 256 18.8 -> 17.4; few workgroups, 500 x 300 5.0 -> 4.1).
+    // tiles of 96 x 24 26.9 and 28.5 us, blocks of 128 22.1 and 21.8, of 256 18.9 -> 15.4; few workgroups, 500 x 300 4.9 -> 3.8).
     const int64_t most = max((int64_t)p.kshare * p.kbp, g.kpad - (int64_t)(p.nreg - 1) * p.kshare * p.kbp);
     const int64_t per = 16 * (kStripThreads / p.cw), pieces = ceil_div(most, per);
     const bool hold = pieces > 1 || 16 * most >= 15 * per || (int64_t)grid.x * grid.y <= 512;
     if (hold && ceil_div(most, 16 * (kHeldThreads / p.cw)) <= kHeldPieces) {
-        const dim3 block(pieces <= kHeldPieces ? kStripThreads : kHeldThreads);
-        if (!wide && g.rounding == 0) hipLaunchKernelGGL((enc_strip_held_kernel<false, 0, kHeldPieces>), grid, block, 0, s, p);
-        else if (!wide) hipLaunchKernelGGL((enc_strip_held_kernel<false, 1, kHeldPieces>), grid, block, 0, s, p);
-        else if (g.rounding == 0) hipLaunchKernelGGL((enc_strip_held_kernel<true, 0, kHeldPieces>), grid, block, 0, s, p);
-        else hipLaunchKernelGGL((enc_strip_held_kernel<true, 1, kHeldPieces>), grid, block, 0, s, p);
-        return launch_status();
+        // instances for one and for three pieces: code for five, most of it passed over, took longer than it saved where a strip is
+        // short and rounding stochastic (read twice, held by five, by what it has: 270 x 30 in blocks of 256 4.6, 5.2, 4.7 us, 671 x 281
+        // in 128 x 24 5.4, 6.0, 5.4, 1639 x 257 in 256, 12 bits 5.2, 6.2, 5.3)
+        if (pieces > kHeldPieces) return launch_held_n<kHeldPieces>(p, grid, kHeldThreads, wide, g.rounding, s);
+        if (pieces == 1) return launch_held_n<1>(p, grid, kStripThreads, wide, g.rounding, s);
+        if (pieces <= 3) return launch_held_n<3>(p, grid, kStripThreads, wide, g.rounding, s);
+        return launch_held_n<kHeldPieces>(p, grid, kStripThreads, wide, g.rounding, s);
     }
     if (!wide && g.rounding == 0) hipLaunchKernelGGL((enc_strip_kernel<false, 0>), grid, dim3(kStripThreads), 0, s, p);
     else if (!wide) hipLaunchKernelGGL((enc_strip_kernel<false, 1>), grid, dim3(kStripThreads), 0, s, p);

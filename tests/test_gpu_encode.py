@@ -579,6 +579,18 @@ def test_where_long_blocks_down_the_rows_are_converted(hb, rows, cols, bc, round
     assert strips == {"strip": ["enc_strip_kernel"], "strip held": ["enc_strip_held_kernel"], "two passes": []}[where], names
 
 
+@pytest.mark.parametrize("rows,cols,br,bc,pieces", [(270, 30, 256, 1, 1), (512, 300, 0, 1, 1), (520, 300, 0, 1, 3), (1536, 300, 0, 1, 3), (1540, 300, 0, 1, 5),
+                                                    (2600, 1300, 0, 1, 5), (2100, 4, 0, 8, 3)])
+@pytest.mark.parametrize("rounding", [0, 1])
+def test_held_strips_run_no_more_code_than_they_have_pieces(hb, rows, cols, br, bc, pieces, rounding):
+    """A short strip takes the instance that is unrolled for its own number of pieces, not the one for five."""
+    x = torch.randn((rows, cols), device="cuda")
+    fmt = hb.make_format(8, br, bc, rounding, 3)
+    out = hb.alloc(fmt, rows, cols, 0)
+    names = launched_kernels(lambda: hb.encode(x, 0, fmt, out=out))
+    assert names == [f"enc_strip_held_kernel<false, {rounding}, {pieces}>"], names
+
+
 @pytest.mark.parametrize("rows,cols,br,held", [(5120, 1035, 0, True), (5121, 1035, 0, False), (1024, 1024, 128, True), (1024, 1040, 128, False),
                                                (4096, 4096, 240, True), (4096, 4096, 128, False), (4096, 4096, 512, True)])
 def test_which_strips_are_held_in_registers(hb, rows, cols, br, held):
@@ -611,10 +623,11 @@ def test_rows_held_by_a_wave(hb, rows, cols, m, rounding):
 
 @pytest.mark.parametrize("m,rounding", [(8, 0), (12, 1)])
 @pytest.mark.parametrize("rows,cols,br,bc", [(1023, 1035, 0, 1), (1030, 1035, 0, 1), (2560, 1035, 0, 1), (2570, 1035, 0, 1), (5120, 1024, 0, 1), (5130, 1035, 0, 1),
-                                             (4200, 1100, 2048, 3), (2900, 1300, 0, 40), (3000, 13, 0, 1)])
+                                             (4200, 1100, 2048, 3), (2900, 1300, 0, 40), (3000, 13, 0, 1), (500, 140, 0, 1), (512, 70, 0, 1), (513, 70, 0, 1),
+                                             (1530, 100, 0, 1), (1540, 100, 0, 1), (270, 30, 256, 1), (671, 281, 128, 24), (2058, 4, 0, 8)])
 def test_strips_held_in_registers(hb, rows, cols, br, bc, m, rounding):
-    """Strips at the edges of what 512 and 1024 threads hold (2560 and 5120 values of 16 columns) and past it, where they are read
-    twice; several exponent blocks down the rows, tiles of columns.  Denormal, non-finite and empty blocks among the values."""
+    """Strips at the edges of what 512 and 1024 threads hold (one, three and five pieces: 512, 1536 and 2560 values of 16 columns; 5120)
+    and past it, where they are read twice; several exponent blocks down the rows, tiles of columns.  Denormal, non-finite and empty blocks among the values."""
     rng = np.random.default_rng(rows + cols)
     X = (rng.standard_normal((rows, cols)) * np.exp2(rng.integers(-20, 21, size=(1, cols)))).astype(np.float32)
     X[:, 0], X[:, 5 % cols] = 0.0, 1e-42

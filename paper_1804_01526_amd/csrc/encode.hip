@@ -132,7 +132,8 @@ struct RowParams {
 };
 
 
-template <int GP, bool WIDE, int ROUND, int U, bool CONV = false>
+// ANY: 16-byte loads that are aligned to 4 bytes only (launch_row_t)
+template <int GP, bool WIDE, int ROUND, int U, bool CONV = false, bool ANY = false>
 __device__ __forceinline__ void enc_row_block(const RowParams p, const uint32_t wg) {
     // The (row, chunk) pairs of the whole operand form one flat index space: a workgroup takes U * 256
     // consecutive chunks.  A row holds a multiple of 16 chunks, so the 4/8/16 lanes of a block never
@@ -229,14 +230,14 @@ __device__ __forceinline__ void enc_row_block(const RowParams p, const uint32_t 
             s = p.src + off;
             at[u] = (p.table && inside) ? off : -1;
         }
-        if (cnt == 8 && p.vec_ok) {
+        if (!ANY && cnt == 8 && p.vec_ok) {
             const float4 a = *reinterpret_cast<const float4 *>(s);
             const float4 b = *reinterpret_cast<const float4 *>(s + 4);
             v[u][0] = a.x; v[u][1] = a.y; v[u][2] = a.z; v[u][3] = a.w;
             v[u][4] = b.x; v[u][5] = b.y; v[u][6] = b.z; v[u][7] = b.w;
-        } else if (cnt == 8) {
+        } else if ((ANY || CONV) && cnt == 8) {
             // rows of odd lengths, value by value before: 4096 x 4095 31.9 -> 14.4 us, 700 x 1501 6.2 -> 4.0, stochastic 4096 x
-            // 4095 35.3 -> 23.5 (aligned rows, without this path and with it: 4096^2 14.0 both, 8192^2 57.0 and 58.9)
+            // 4095 35.3 -> 23.5
             const v4f_any a = *reinterpret_cast<const v4f_any *>(s), b = *reinterpret_cast<const v4f_any *>(s + 4);
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[u][e] = a[e], v[u][4 + e] = b[e];
@@ -336,9 +337,9 @@ __device__ __forceinline__ void enc_row_block(const RowParams p, const uint32_t 
     }
 }
 
-template <int GP, bool WIDE, int ROUND, int U, bool CONV = false>
+template <int GP, bool WIDE, int ROUND, int U, bool CONV = false, bool ANY = false>
 __global__ __launch_bounds__(kThreads) void enc_row_kernel(const RowParams p) {
-    enc_row_block<GP, WIDE, ROUND, U, CONV>(p, blockIdx.x);
+    enc_row_block<GP, WIDE, ROUND, U, CONV, ANY>(p, blockIdx.x);
 }
 
 // 2-D tiles whose k axis is contiguous in the source: a workgroup owns the rblock source rows of one
@@ -434,8 +435,12 @@ template <int GP, bool WIDE, int ROUND>
 void launch_row_t(const RowParams &p, dim3 grid, hipStream_t s) {
     // stochastic rounding is bound by its vector instructions and holds more registers: two chunks per thread instead of
     // four keep more waves on a SIMD (config 2, 8-bit: 67 us against 71-75 us)
-    if (ROUND) hipLaunchKernelGGL((enc_row_kernel<GP, WIDE, ROUND, 2>), dim3(grid.x * 2), dim3(kThreads), 0, s, p);
-    else hipLaunchKernelGGL((enc_row_kernel<GP, WIDE, ROUND, 4>), grid, dim3(kThreads), 0, s, p);
+    constexpr int U = ROUND ? 2 : 4;
+    // Loads aligned to 16 bytes where rows are and there are at least 6 Mi values, else the instance that aligns to 4 (its code is
+    // shorter).  That one, aligned loads: 256 x 512 3.4, 3.5 us, 1024 x 4096 5.6, 5.9, 2048 x 4096 8.3 both, 8192^2 58.8, 57.5; both in
+    // one kernel 59.2.
+    void (*const kernel)(RowParams) = p.vec_ok && p.R * p.K >= (int64_t)6 << 20 ? &enc_row_kernel<GP, WIDE, ROUND, U> : &enc_row_kernel<GP, WIDE, ROUND, U, false, true>;
+    hipLaunchKernelGGL(kernel, dim3(grid.x * (4 / U)), dim3(kThreads), 0, s, p);
 }
 
 template <int GP>
@@ -646,7 +651,8 @@ __global__ __launch_bounds__(kThreads) void enc_pair_kernel(const EncPair q) {
     const int j = blockIdx.x >= q.first ? 1 : 0;
     const uint32_t wg = blockIdx.x - (j ? q.first : 0u);
     if (q.down[j]) enc_col_block<32, false, 0, false>(q.col[j], wg);
-    else enc_row_block<4, false, 0, 4>(q.row[j], wg);
+    else if (q.row[j].vec_ok) enc_row_block<4, false, 0, 4>(q.row[j], wg);
+    else enc_row_block<4, false, 0, 4, false, true>(q.row[j], wg);
 }
 
 // How far a workgroup's share is cut down.  A wave walks its pieces one after the other (about 1.5 us each: 32 strided

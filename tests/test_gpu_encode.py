@@ -686,3 +686,20 @@ def test_one_value_out_of_range_spoils_its_own_block_only(hb, rows, cols, br, bc
         full = ref.encode(X, br, bc, 8)
         np.testing.assert_array_equal(mant, full.mant)
         np.testing.assert_array_equal(exps, full.exps)
+
+
+@pytest.mark.parametrize("rows,cols,pad,aligned16", [(64, 256, 0, False), (1535, 4096, 0, False), (1536, 4096, 0, True), (3000, 2100, 0, True), (3001, 2099, 0, False),
+                                                     (3000, 2100, 2, False), (1536, 4096, 4, True)])
+@pytest.mark.parametrize("rounding,unroll", [(0, 4), (1, 2)])
+def test_which_loads_rows_are_read_with(hb, rows, cols, pad, aligned16, rounding, unroll):
+    """Rows that start on 16 bytes and hold at least 6 Mi values have the instance that reads nothing else to themselves; the bytes are
+    those of the oracle either way."""
+    x = torch.randn((rows, cols + pad), device="cuda", generator=torch.Generator(device="cuda").manual_seed(cols))[:, :cols]
+    fmt = hb.make_format(8, 1, 24, rounding, 5)
+    out = hb.alloc(fmt, rows, cols, 1)
+    names = launched_kernels(lambda: hb.encode(x, 1, fmt, out=out))
+    assert names == [f"enc_row_kernel<4, false, {rounding}, {unroll}, false, {str(not aligned16).lower()}>"], names
+    want = ref.encode(x.cpu().numpy(), 1, 24, 8, rounding, 5)
+    mant, exps = unpack(out)
+    np.testing.assert_array_equal(mant, want.mant)
+    np.testing.assert_array_equal(exps, want.exps)

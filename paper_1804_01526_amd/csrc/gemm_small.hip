@@ -369,7 +369,9 @@ struct ConvertParams {
     int32_t K, kblock, nblk, groups;
     float final_scale;
 };
-// 16 values of block `blk` of row `r`: those from 16 lh on, zeros behind the block's and the matrix's end
+// 16 values of block `blk` of row `r`: those from 16 lh on, zeros behind the block's and the matrix's end.  QUADS: what is left of a
+// block by whole quadruples (launch_gemm_convert)
+template <bool QUADS>
 __device__ __forceinline__ void convert_load(const ConvertSource &x, const ConvertParams &p, int64_t r, int lh, int blk, float (&v)[16]) {
     int len = 0;
     if (blk < p.nblk) len = p.K - blk * p.kblock < p.kblock ? p.K - blk * p.kblock : p.kblock;
@@ -380,6 +382,17 @@ __device__ __forceinline__ void convert_load(const ConvertSource &x, const Conve
         if (len == 32) {
 #pragma unroll
             for (int j = 0; j < 16; ++j) v[j] = s[(k0 + j) * x.ld];
+        } else if (QUADS) {
+#pragma unroll
+            for (int j = 0; j < 16; j += 4) {
+                if (j + 4 <= left) {
+#pragma unroll
+                    for (int e = j; e < j + 4; ++e) v[e] = s[(k0 + e) * x.ld];
+                } else {
+#pragma unroll
+                    for (int e = j; e < j + 4; ++e) v[e] = e < left ? s[(k0 + e) * x.ld] : 0.0f;
+                }
+            }
         } else {
 #pragma unroll
             for (int j = 0; j < 16; ++j) v[j] = j < left ? s[(k0 + j) * x.ld] : 0.0f;
@@ -391,6 +404,17 @@ __device__ __forceinline__ void convert_load(const ConvertSource &x, const Conve
             for (int j = 0; j < 16; j += 4) {
                 const v4f_any d = *reinterpret_cast<const v4f_any *>(s + j);
                 v[j] = d[0], v[j + 1] = d[1], v[j + 2] = d[2], v[j + 3] = d[3];
+            }
+        } else if (QUADS) {
+#pragma unroll
+            for (int j = 0; j < 16; j += 4) {
+                if (j + 4 <= left) {
+                    const v4f_any d = *reinterpret_cast<const v4f_any *>(s + j);
+                    v[j] = d[0], v[j + 1] = d[1], v[j + 2] = d[2], v[j + 3] = d[3];
+                } else {
+#pragma unroll
+                    for (int e = j; e < j + 4; ++e) v[e] = e < left ? s[e] : 0.0f;
+                }
             }
         } else {
 #pragma unroll
@@ -423,7 +447,7 @@ struct Convert {
     static constexpr int kExps = 2 * kMant > kPart ? 2 * kMant : kPart;
     static constexpr int kLds = kExps + 2 * 32 * kExpRow;
 };
-template <int PER>
+template <int PER, bool QUADS>
 __global__ __launch_bounds__(kSmallThreads, 2) void gemm_convert_kernel(const ConvertParams p) {
     typedef Convert<PER> R;
     __shared__ __attribute__((aligned(16))) uint8_t lds[R::kLds];
@@ -436,7 +460,7 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_convert_kernel(const Co
 #pragma unroll
         for (int o = 0; o < 2; ++o) {
             const int64_t r = origin[o] + l32 < p.x[o].rows ? origin[o] + l32 : p.x[o].rows - 1;   // behind the last: that one again
-            convert_load(p.x[o], p, r, lh, wave + i * kSmallWaves, v[o][i]);
+            convert_load<QUADS>(p.x[o], p, r, lh, wave + i * kSmallWaves, v[o][i]);
         }
 #pragma unroll
     for (int i = 0; i < PER; ++i)
@@ -481,10 +505,10 @@ __global__ __launch_bounds__(kSmallThreads, 2) void gemm_convert_kernel(const Co
         if (col + i < p.x[1].rows) p.C[row * p.ldc + col + i] = x[i] * p.final_scale;
 }
 
-template <int PER>
+template <int PER, bool QUADS>
 int launch_convert(const ConvertParams &p, hipStream_t s) {
     const dim3 grid((unsigned)ceil_div(p.x[1].rows, 32), (unsigned)ceil_div(p.x[0].rows, 32));
-    hipLaunchKernelGGL(gemm_convert_kernel<PER>, grid, dim3(kSmallThreads), 0, s, p);
+    hipLaunchKernelGGL((gemm_convert_kernel<PER, QUADS>), grid, dim3(kSmallThreads), 0, s, p);
     return launch_status();
 }
 
@@ -591,7 +615,12 @@ int launch_gemm_convert(const GemmArgs &a, const float *const *src, const Encode
     p.groups = (int32_t)(a.kpad / 128);
     p.final_scale = ldexpf(1.0f, 27 - a.mA - a.mB);
     const int64_t blocks = a.kpad / 32;
-    return blocks <= 8 ? launch_convert<1>(p, s) : launch_convert<2>(p, s);
+    // Blocks of 16 to 31 in contractions beyond 128 are read by quadruples: value by value they were up to 23 % behind the two launches
+    // (two launches, value by value, quadruples: 134 x 829 x 248 in blocks of 24 8.5, 9.4, 7.0 us, 84 x 48 x 192 7.5, 8.9, 5.4).
+    // Shorter blocks and contractions stay ahead without and pay for the longer code with 2 to 10 %.
+    const bool quads = a.kblock >= 16 && a.kblock < 32 && a.kpad > 128;
+    if (blocks <= 8) return quads ? launch_convert<1, true>(p, s) : launch_convert<1, false>(p, s);
+    return quads ? launch_convert<2, true>(p, s) : launch_convert<2, false>(p, s);
 }
 
 }  // namespace hbfp

@@ -1050,7 +1050,7 @@ int hbfp_gemm_bfp(const hbfp_tensor *A, const hbfp_tensor *B, const hbfp_tensor 
         const bool int8 = (kernel == HBFP_KERNEL_AUTO || kernel == HBFP_KERNEL_INT8) && !use_bf(g, kernel) && !use_f16_planes(g, kernel) &&
                           !use_scaled(g, kernel);
         if (int8 && gemm_i8_encoded_output_ok(g, *out) && !operands_overlap(*out, *A) && !operands_overlap(*out, *B))
-            return kernel == HBFP_KERNEL_AUTO && gemm_small_ok(g) ? launch_gemm_small(g, s, out, relu) : launch_gemm_i8(g, ws_gemm, s, out, relu);
+            return kernel == HBFP_KERNEL_AUTO && gemm_small_ok(g, true) ? launch_gemm_small(g, s, out, relu) : launch_gemm_i8(g, ws_gemm, s, out, relu);
         rc = run_gemm(A, B, C, N, 0.0f, nullptr, kernel, ws_gemm, part[1], stream);
         if (rc == HBFP_OK && relu) rc = launch_relu(C, M * N, s);
         if (rc != HBFP_OK) return rc;

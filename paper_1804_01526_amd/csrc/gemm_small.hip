@@ -346,7 +346,7 @@ int launch_few(const SmallParams &p, bool enc, int64_t cols, hipStream_t s) {
 }
 // Whether a product that runs here takes the kernel for few rows.  Up to three chunks of k per product (four where it is
 // converted) the start of a workgroup with that much LDS is what counts, and the other kernel is ahead.
-bool few_rows_ok(const SmallParams &p, bool enc) { return p.M <= 32 && p.groups >= (enc ? 5 : 4) && p.kpad <= (1 << 26); }
+bool few_rows_ok(int64_t M, int64_t kpad, bool enc) { return M <= 32 && kpad / 128 >= (enc ? 5 : 4) && kpad <= (1 << 26); }
 
 // A product of two FP32 matrices in one launch (hbfp_gemm_f32 at small sizes): the workgroup converts its 32 rows of A and its 32
 // columns of B itself.  What bounds these calls is launches and latency: a launch that converts both operands (5.1 us at 256^3)
@@ -533,21 +533,35 @@ static int small_row_tiles(const GemmArgs &a, double *us) {
     return t1 <= t2 ? 1 : 2;
 }
 
+// What the kernel for few rows takes: a start, and for every 1024 of k and every workgroup of a compute unit what was measured with
+// one workgroup on the chip and with all of it busy (fitted to 345 shapes of 1 to 32 rows, 16 to 20 000 columns and 1024 to 20 000 of
+// k, and to 240 with an encoded output, whose workgroups have twice the columns).
+static double few_rows_us(const GemmArgs &a, bool enc) {
+    const int64_t wgs = ceil_div(a.N, enc ? 32 : 16);
+    const double busy = wgs < 256 ? (double)wgs / 256.0 : 1.0;
+    const double step = a.M <= 16 ? (enc ? 0.82 + 0.5 * busy : 0.6 + 0.2 * busy) : (enc ? 1.3 + 0.5 * busy : 0.95 + 0.15 * busy);
+    return (enc ? 3.3 : 2.7) + (double)a.kpad / 1024.0 * (double)ceil_div(wgs, 256) * step;
+}
+
 // Whether the product runs here: its estimate against that of the 128 x 128-tile kernels, which make their scale words inside the
 // kernel at these sizes.  Measured, tile kernels -> here: 256^3 7.8 -> 3.3 us, 512^3 10.2 -> 4.6, 300 x 300 x 2000 12.4 -> 8.9,
-// 128 x 4096 x 1024 14.9 -> 9.5, 512 x 512 x 4096 16.5 -> 14.2, 16 x 4096 x 4096 14.7 -> 11.8; behind at 1024 x 1024 x 512
-// (10.5, 11.0), 1000^3 (15.8, 18.7), 2048 x 1024 x 256 (8.8, 14.2), 32 x 2048 x 8192 (16.7, 22.3), 16 x 64 x 8192 (10.1, 17.8).
-// Of 175 shapes the rule is more than 3 % from the faster side at 11, nine of them left to the tile kernels (2 x 4623 x 8192
-// 21.3 against 16.0 us: the estimate knows nothing of rows that are all one).
-bool gemm_small_ok(const GemmArgs &a) {
+// 128 x 4096 x 1024 14.9 -> 9.5, 512 x 512 x 4096 16.5 -> 14.2; behind at 1024 x 1024 x 512 (10.5, 11.0), 1000^3 (15.8, 18.7),
+// 2048 x 1024 x 256 (8.8, 14.2).
+// At most 32 rows are weighed by the kernel that they run on; the tile kernels' estimate is 2 to 5 us too high where few columns
+// are split along k.  Tile kernels -> here: 16 x 4096 x 4096 14.3 -> 7.5, 1 x 4096 x 8192 18.5 -> 10.5, 16 x 1024 x 8192 12.2 -> 8.9,
+// 32 x 2048 x 8192 15.1 -> 12.9, 17 x 16384 x 16384 92.6 -> 73.0; behind at 16 x 64 x 16384 (10.3, 12.6), 32 x 64 x 8192 (9.3, 11.4),
+// 32 x 1024 x 12288 (14.4, 16.8).  Of the 345 shapes 8 are more than 3 % from the faster side, all together 0.3 % behind it (11 %
+// by the estimate of the kernel above, which left most contractions from 6144 on to the tile kernels).
+bool gemm_small_ok(const GemmArgs &a, bool enc) {
     if (a.P || a.mA > 8 || a.mB > 8 || a.kbp != 32 || a.M > (1 << 20) || a.N > (1 << 20)) return false;
+    if (few_rows_ok(a.M, a.kpad, enc)) return few_rows_us(a, enc) < gemm_i8_estimate(a) - (a.N <= 512 ? 3.5 : 0.0);
     double us;
     small_row_tiles(a, &us);
     return us < gemm_i8_estimate(a);
 }
 
 int launch_gemm_small(const GemmArgs &a, hipStream_t s, const hbfp_tensor *enc, int relu) {
-    if (!gemm_small_ok(a)) return HBFP_ERR_FORMAT;
+    if (!gemm_small_ok(a, enc != nullptr)) return HBFP_ERR_FORMAT;
     SmallParams p = {};
     p.A = (const uint8_t *)a.mantA;
     p.B = (const uint8_t *)a.mantB;
@@ -577,7 +591,7 @@ int launch_gemm_small(const GemmArgs &a, hipStream_t s, const hbfp_tensor *enc, 
         p.s1 = (uint32_t)(enc->seed >> 32);
         cols = enc->kpad;                                      // the padding of the rows too
     }
-    if (few_rows_ok(p, enc != nullptr)) return launch_few(p, enc != nullptr, cols, s);
+    if (few_rows_ok(p.M, p.kpad, enc != nullptr)) return launch_few(p, enc != nullptr, cols, s);
     const unsigned workgroups = (unsigned)ceil_div(cols, 32);
     return small_row_tiles(a, nullptr) == 1 ? launch_small<1>(p, enc != nullptr, workgroups, s) : launch_small<2>(p, enc != nullptr, workgroups, s);
 }

@@ -109,7 +109,7 @@ size_t gemm_limb_workspace(const hbfp_tensor *A, const hbfp_tensor *B);
 
 // gemm_small.hip: small int8 products in one launch without workspace; enc: the product leaves as this encoded operand
 // (blocks of 32 along its columns, at most 8 bits)
-bool gemm_small_ok(const GemmArgs &a);
+bool gemm_small_ok(const GemmArgs &a, bool enc = false);
 int launch_gemm_small(const GemmArgs &a, hipStream_t s, const hbfp_tensor *enc = nullptr, int relu = 0);
 // both operands converted inside the product: FP32 sources, 1-D blocks stored as 32, at most 8 bits, round to nearest
 bool gemm_convert_ok(const GemmArgs &a, const EncodeGeom *geom);

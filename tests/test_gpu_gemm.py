@@ -1666,7 +1666,8 @@ def test_where_the_scale_words_come_from(hb, M, N, K, blk, bytes_inside):
 @pytest.mark.parametrize("M,N,K,blk,where", [
     (1, 1, 8, 32, "small 1"), (33, 32, 1000, 24, "small 1"), (256, 256, 256, 32, "small 1"), (16, 4096, 4096, 32, "few 1"),
     (600, 600, 600, 32, "small 2"), (700, 690, 300, 32, "small 2"), (128, 4096, 1024, 32, "small 2"),
-    (1024, 1024, 512, 32, "tile"), (1000, 1000, 1000, 32, "tile"), (2048, 1024, 256, 32, "tile"), (32, 2048, 8192, 32, "tile"), (16, 64, 8192, 32, "tile")])
+    (1024, 1024, 512, 32, "tile"), (1000, 1000, 1000, 32, "tile"), (2048, 1024, 256, 32, "tile"), (32, 2048, 8192, 32, "few 2"), (16, 256, 6144, 32, "few 1"),
+    (1, 4096, 8192, 32, "few 1"), (16, 1024, 8192, 32, "few 1"), (16, 64, 16384, 32, "tile"), (32, 64, 8192, 32, "tile"), (32, 1024, 12288, 32, "tile")])
 def test_where_small_products_run(hb, M, N, K, blk, where):
     """The automatic choice between the kernels for small products (tiles of 32 or 64 rows, few rows) and the tile kernels, both measured with
     scale words made inside the tile kernel: each case on the side that is at least 4 % faster."""

@@ -7,6 +7,8 @@ Integer inputs: every sum is exact, so C equals the FP64 product; the converted 
 import pytest
 import torch
 
+from tests.util import launched_kernels
+
 pytestmark = pytest.mark.gpu
 
 
@@ -19,7 +21,7 @@ def _operands(M, K, N, block):
     return a, b, hbfp.decode(a).double() @ hbfp.decode(b).double()
 
 
-@pytest.mark.parametrize("M,K,N", [(1, 385, 1), (1, 4096, 15), (16, 512, 17), (17, 640, 16), (32, 1024, 33), (5, 1500, 385), (31, 8200, 100), (16, 3000, 4100),
+@pytest.mark.parametrize("M,K,N", [(1, 385, 1), (1, 4096, 15), (16, 512, 17), (17, 640, 16), (32, 1024, 33), (5, 1500, 385), (31, 8200, 2100), (1, 16000, 1030), (16, 3000, 4100),
                                    (20, 2300, 4097)])
 @pytest.mark.parametrize("block", [32, 24])
 def test_few_rows(M, K, N, block):
@@ -29,6 +31,8 @@ def test_few_rows(M, K, N, block):
     buf = torch.full((M, N + 5), 3.0, device="cuda")
     C = hbfp.gemm(a, b, out=buf[:, :N])
     assert torch.equal(C.double(), want)
+    names = launched_kernels(lambda: hbfp.gemm(a, b, out=buf[:, :N]))
+    assert names == [f"gemm_few_kernel<{1 if M <= 16 else 2}, false>"], names
     hbfp.gemm(a, b, out=buf[:, :N], beta=1.0)
     assert torch.equal(buf[:, :N].double(), (2 * want).float().double())
     assert bool((buf[:, N:] == 3.0).all())

@@ -357,7 +357,9 @@ int hbfp_gemm_conv2d_dgrad(const hbfp_tensor *dy, const hbfp_conv2d *conv, const
  *              output tiles, long k), two int8 limb planes per operand for mantissas wider
  *              than 8 bits, and the limb planes of both operands when the block-scaled
  *              kernel is chosen.  It is what the shape can need: a product that uses less
- *              (small ones, words made inside the kernel) still has to bring all of it
+ *              (small ones, words made inside the kernel) still has to bring all of it.
+ *              Only the slices of a product of one exponent per row (int32) may be left
+ *              out, here and in the calls that run such a product: it is then not split
  * Domain: block exponent bytes up to 254 (magnitudes below 2^127).
  * Errors: HBFP_ERR_ARG, HBFP_ERR_LAYOUT (kdim/kblock mismatch), HBFP_ERR_FORMAT
  * (mantissa classes differ or exceed 12 bits), HBFP_ERR_RANGE (kblock * max|mA| *

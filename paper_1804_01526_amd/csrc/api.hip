@@ -797,7 +797,9 @@ static bool use_scaled(const GemmArgs &g, int kernel) {
     return kernel == HBFP_KERNEL_SCALED ? gemm_mx_possible(g) : gemm_mx_ok(g);
 }
 
-int hbfp_gemm_select_workspace(const hbfp_tensor *A, const hbfp_tensor *B, int kernel, size_t *bytes) {
+// hbfp_gemm_select_workspace.  slices: with room for those of a product of one exponent per row that is split along k; without it the
+// product runs unsplit (GemmArgs::unsplit), so that what a caller always brought for such a product stays enough.
+static int select_workspace(const hbfp_tensor *A, const hbfp_tensor *B, int kernel, bool slices, size_t *bytes) {
     if (!bytes || kernel < HBFP_KERNEL_AUTO || kernel > HBFP_KERNEL_FP16_PLANES) return HBFP_ERR_ARG;
     int rc = check_tensor(A, false);
     if (rc != HBFP_OK) return rc;
@@ -806,7 +808,6 @@ int hbfp_gemm_select_workspace(const hbfp_tensor *A, const hbfp_tensor *B, int k
     *bytes = (A->mant_bits > 8 || B->mant_bits > 8) ? gemm_limb_workspace(A, B)
                                                      : gemm_i8_workspace(A->rows, B->rows, A->kpad, A->kblock_pad, A->exp_ld);
     const GemmArgs g = gemm_args(A, B);
-    if (gemm_wide_possible(g) && gemm_wide_workspace(g) > *bytes) *bytes = gemm_wide_workspace(g);
     if (use_bf(g, kernel)) {                                     // [packed A][packed B]
         *bytes = packed_operand_bytes(g.M, g.kpad, g.mA) + packed_operand_bytes(g.N, g.kpad, g.mB);
         return HBFP_OK;
@@ -822,7 +823,13 @@ int hbfp_gemm_select_workspace(const hbfp_tensor *A, const hbfp_tensor *B, int k
     }
     if (use_scaled(g, kernel))                                   // [packed A][packed B][int8 path behind the block-scaled kernel]
         *bytes = align256(*bytes) + mx_packed_bytes(g.M, g.kpad, g.mA) + mx_packed_bytes(g.N, g.kpad, g.mB);
+    else if (slices && (kernel == HBFP_KERNEL_INT8_WIDE ? gemm_wide_possible(g) : gemm_wide_ok(g)) && gemm_wide_workspace(g) > *bytes)
+        *bytes = gemm_wide_workspace(g);
     return HBFP_OK;
+}
+
+int hbfp_gemm_select_workspace(const hbfp_tensor *A, const hbfp_tensor *B, int kernel, size_t *bytes) {
+    return select_workspace(A, B, kernel, true, bytes);
 }
 
 int hbfp_gemm_workspace(const hbfp_tensor *A, const hbfp_tensor *B, size_t *bytes) {
@@ -842,7 +849,11 @@ static int run_gemm(const hbfp_tensor *A, const hbfp_tensor *B, float *C, int64_
     if (kernel == HBFP_KERNEL_BF16 && !P && !gemm_bf_possible(g)) return HBFP_ERR_FORMAT;
     if (kernel == HBFP_KERNEL_FP16_PLANES && !P && !gemm_f16_planes_possible(g)) return HBFP_ERR_FORMAT;
     size_t need = 0;
-    hbfp_gemm_select_workspace(A, B, kernel, &need);
+    select_workspace(A, B, kernel, !P, &need);
+    if (ws_bytes < need) {
+        select_workspace(A, B, kernel, false, &need);
+        g.unsplit = 1;
+    }
     if (need && (!workspace || ws_bytes < need || ((uintptr_t)workspace & 255))) return HBFP_ERR_WORKSPACE;
     if (kernel == HBFP_KERNEL_INT8_WIDE) {
         if (!gemm_wide_possible(g)) return HBFP_ERR_FORMAT;
@@ -895,8 +906,8 @@ int hbfp_gemm(const hbfp_tensor *A, const hbfp_tensor *B, float *C, int64_t ldc,
 
 // Checks the products of a batch and decides whether they share one launch of the bf16 or the block-scaled kernel; part[i] is
 // product i's share of the workspace.
-static int batch_plan(int n, const hbfp_tensor *const *A, const hbfp_tensor *const *B, int kernel, GemmArgs *g, size_t *part,
-                      bool *grouped, int *group_kernel) {
+static int batch_plan(int n, const hbfp_tensor *const *A, const hbfp_tensor *const *B, int kernel, bool slices, GemmArgs *g, size_t *part,
+                      bool *grouped, int *group_kernel, size_t *need) {
     if (!A || !B || n < 1 || n > HBFP_BATCH_MAX) return HBFP_ERR_ARG;
     if (kernel < HBFP_KERNEL_AUTO || kernel > HBFP_KERNEL_FP16_PLANES) return HBFP_ERR_ARG;
     bool all_scaled = true, all_bf = true, bf_class = true, same = true;
@@ -915,9 +926,11 @@ static int batch_plan(int n, const hbfp_tensor *const *A, const hbfp_tensor *con
     const bool together = kernel == HBFP_KERNEL_AUTO && gemm_mx_group_ok(n, g);
     *grouped = n > 1 && same && (all_scaled || all_bf || together);
     *group_kernel = !*grouped ? kernel : (all_bf || (together && bf_class)) ? HBFP_KERNEL_BF16 : HBFP_KERNEL_SCALED;
+    *need = 0;
     for (int i = 0; i < n; ++i) {
-        hbfp_gemm_select_workspace(A[i], B[i], *group_kernel, &part[i]);
+        select_workspace(A[i], B[i], *group_kernel, slices, &part[i]);
         part[i] = align256(part[i]);
+        *need += part[i];
     }
     return HBFP_OK;
 }
@@ -928,11 +941,7 @@ int hbfp_gemm_batch_workspace(int n, const hbfp_tensor *const *A, const hbfp_ten
     size_t part[HBFP_BATCH_MAX];
     bool grouped = false;
     int group_kernel = kernel;
-    const int rc = batch_plan(n, A, B, kernel, g, part, &grouped, &group_kernel);
-    if (rc != HBFP_OK) return rc;
-    *bytes = 0;
-    for (int i = 0; i < n; ++i) *bytes += part[i];
-    return HBFP_OK;
+    return batch_plan(n, A, B, kernel, true, g, part, &grouped, &group_kernel, bytes);
 }
 
 int hbfp_gemm_batch(int n, const hbfp_tensor *const *A, const hbfp_tensor *const *B, float *const *C, const int64_t *ldc,
@@ -943,12 +952,12 @@ int hbfp_gemm_batch(int n, const hbfp_tensor *const *A, const hbfp_tensor *const
     size_t part[HBFP_BATCH_MAX], need = 0;
     bool grouped = false;
     int group_kernel = kernel;
-    int rc = batch_plan(n, A, B, kernel, g, part, &grouped, &group_kernel);
+    int rc = batch_plan(n, A, B, kernel, true, g, part, &grouped, &group_kernel, &need);
+    if (rc == HBFP_OK && ws_bytes < need) rc = batch_plan(n, A, B, kernel, false, g, part, &grouped, &group_kernel, &need);
     if (rc != HBFP_OK) return rc;
     for (int i = 0; i < n; ++i) {
         if (!C[i] || ldc[i] < B[i]->rows || ((uintptr_t)C[i] & 3)) return HBFP_ERR_ARG;
         if (kernel == HBFP_KERNEL_INT8_WIDE && !gemm_wide_possible(g[i])) return HBFP_ERR_FORMAT;
-        need += part[i];
         g[i].C = C[i];
         g[i].ldc = ldc[i];
         g[i].beta = beta;
@@ -1000,7 +1009,7 @@ int hbfp_gemm_batch(int n, const hbfp_tensor *const *A, const hbfp_tensor *const
 }
 
 // Workspace of hbfp_gemm_bfp: [FP32 product M x N][workspace of the product][workspace of the conversion]
-static int gemm_bfp_plan(const hbfp_tensor *A, const hbfp_tensor *B, const hbfp_tensor *out, int kernel, bool need_ptrs,
+static int gemm_bfp_plan(const hbfp_tensor *A, const hbfp_tensor *B, const hbfp_tensor *out, int kernel, bool need_ptrs, bool slices,
                          bool *fused, size_t part[3], int *kernel_used) {
     if (!A || !B || !out) return HBFP_ERR_ARG;
     if (kernel < HBFP_KERNEL_AUTO || kernel > HBFP_KERNEL_FP16_PLANES) return HBFP_ERR_ARG;
@@ -1013,7 +1022,7 @@ static int gemm_bfp_plan(const hbfp_tensor *A, const hbfp_tensor *B, const hbfp_
     *kernel_used = kernel;
     *fused = (use_scaled(g, kernel) || use_bf(g, kernel)) && mx_encoded_output_ok(*out);
     part[0] = align256((size_t)A->rows * (size_t)B->rows * sizeof(float));
-    hbfp_gemm_select_workspace(A, B, kernel, &part[1]);
+    select_workspace(A, B, kernel, slices, &part[1]);
     part[1] = align256(part[1]);
     part[2] = 0;
     if (!*fused) hbfp_encode_workspace(out, &part[2]);
@@ -1025,7 +1034,7 @@ int hbfp_gemm_bfp_workspace(const hbfp_tensor *A, const hbfp_tensor *B, const hb
     if (!bytes) return HBFP_ERR_ARG;
     bool fused = false;
     size_t part[3];
-    const int rc = gemm_bfp_plan(A, B, out, kernel, false, &fused, part, &kernel);
+    const int rc = gemm_bfp_plan(A, B, out, kernel, false, true, &fused, part, &kernel);
     if (rc != HBFP_OK) return rc;
     *bytes = part[0] + part[1] + part[2];
     return HBFP_OK;
@@ -1035,7 +1044,8 @@ int hbfp_gemm_bfp(const hbfp_tensor *A, const hbfp_tensor *B, const hbfp_tensor 
                   size_t ws_bytes, void *stream) {
     bool fused = false;
     size_t part[3];
-    int rc = gemm_bfp_plan(A, B, out, kernel, true, &fused, part, &kernel);
+    int rc = gemm_bfp_plan(A, B, out, kernel, true, true, &fused, part, &kernel);
+    if (rc == HBFP_OK && ws_bytes < part[0] + part[1] + part[2]) rc = gemm_bfp_plan(A, B, out, kernel, true, false, &fused, part, &kernel);
     if (rc != HBFP_OK) return rc;
     if (relu != 0 && relu != 1) return HBFP_ERR_ARG;
     if (!workspace || ws_bytes < part[0] + part[1] + part[2] || ((uintptr_t)workspace & 255)) return HBFP_ERR_WORKSPACE;
@@ -1112,11 +1122,14 @@ static int packed_kind(const hbfp_tensor *A, const hbfp_tensor *B) {
     return a != b ? kPackedMixed : a == 1 ? kPackedBf : a == 2 ? kPackedF16 : kPackedMx;
 }
 
-int hbfp_gemm_packed_workspace(const hbfp_tensor *A, const hbfp_tensor *B, size_t *bytes) {
-    const int rc = hbfp_gemm_select_workspace(A, B, HBFP_KERNEL_INT8, bytes);
+static int packed_workspace(const hbfp_tensor *A, const hbfp_tensor *B, bool slices, size_t *bytes) {
+    // of a mixed pair the int8 kernels are the product, else they stand by and never split it
+    const int rc = select_workspace(A, B, HBFP_KERNEL_INT8, slices && A && B && packed_kind(A, B) == kPackedMixed, bytes);
     if (rc == HBFP_OK && (packed_kind(A, B) == kPackedBf || packed_kind(A, B) == kPackedF16)) *bytes = 0;      // no stand-by kernels behind the bf16 / FP16 kernel
     return rc;
 }
+
+int hbfp_gemm_packed_workspace(const hbfp_tensor *A, const hbfp_tensor *B, size_t *bytes) { return packed_workspace(A, B, true, bytes); }
 
 int hbfp_gemm_packed(const hbfp_tensor *A, const void *packed_a, const hbfp_tensor *B, const void *packed_b, float *C,
                      int64_t ldc, float beta, void *workspace, size_t ws_bytes, void *stream) {
@@ -1127,9 +1140,13 @@ int hbfp_gemm_packed(const hbfp_tensor *A, const void *packed_a, const hbfp_tens
     if (rc != HBFP_OK) return rc;
     if (ldc < B->rows || ((uintptr_t)C & 3)) return HBFP_ERR_ARG;
     size_t need = 0;
-    hbfp_gemm_packed_workspace(A, B, &need);
-    if (need && (!workspace || ws_bytes < need || ((uintptr_t)workspace & 255))) return HBFP_ERR_WORKSPACE;
     GemmArgs g = gemm_args(A, B);
+    packed_workspace(A, B, true, &need);
+    if (ws_bytes < need) {
+        packed_workspace(A, B, false, &need);
+        g.unsplit = 1;
+    }
+    if (need && (!workspace || ws_bytes < need || ((uintptr_t)workspace & 255))) return HBFP_ERR_WORKSPACE;
     g.C = C;
     g.ldc = ldc;
     g.beta = beta;
@@ -1165,17 +1182,20 @@ int hbfp_gemm_packed_batch(int n, const hbfp_tensor *const *A, const void *const
     if (!A || !B || !C || !ldc || !packed_a || !packed_b || n < 1 || n > HBFP_BATCH_MAX) return HBFP_ERR_ARG;
     if (beta != 0.0f && beta != 1.0f) return HBFP_ERR_ARG;
     GemmArgs g[HBFP_BATCH_MAX];
-    size_t part[HBFP_BATCH_MAX], need = 0;
+    size_t part[HBFP_BATCH_MAX], unsplit[HBFP_BATCH_MAX], need = 0, least = 0;
     for (int i = 0; i < n; ++i) {
         if (!A[i] || !B[i] || !C[i] || !packed_a[i] || !packed_b[i]) return HBFP_ERR_ARG;
         if (((uintptr_t)packed_a[i] & 255) || ((uintptr_t)packed_b[i] & 255) || ((uintptr_t)C[i] & 3)) return HBFP_ERR_ARG;
         int rc = check_pair(A[i], B[i]);
         if (rc != HBFP_OK) return rc;
         if (ldc[i] < B[i]->rows) return HBFP_ERR_ARG;
-        rc = hbfp_gemm_packed_workspace(A[i], B[i], &part[i]);
+        rc = packed_workspace(A[i], B[i], true, &part[i]);
+        if (rc == HBFP_OK) rc = packed_workspace(A[i], B[i], false, &unsplit[i]);
         if (rc != HBFP_OK) return rc;
         part[i] = align256(part[i]);
+        unsplit[i] = align256(unsplit[i]);
         need += part[i];
+        least += unsplit[i];
         g[i] = gemm_args(A[i], B[i]);
         g[i].C = C[i];
         g[i].ldc = ldc[i];
@@ -1185,6 +1205,10 @@ int hbfp_gemm_packed_batch(int n, const hbfp_tensor *const *A, const void *const
         if (packed_kind(A[i], B[i]) != packed_kind(A[0], B[0])) return HBFP_ERR_FORMAT;
     }
     const int kind = packed_kind(A[0], B[0]);
+    if (ws_bytes < need) {
+        need = least;
+        for (int i = 0; i < n; ++i) part[i] = unsplit[i], g[i].unsplit = 1;
+    }
     if (need && (!workspace || ws_bytes < need || ((uintptr_t)workspace & 255))) return HBFP_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     void *standby[HBFP_BATCH_MAX];
@@ -1227,7 +1251,7 @@ int hbfp_gemm_partials_window(const hbfp_tensor *A, const hbfp_tensor *B, int64_
     if (row0 < 0 || col0 < 0 || rows <= 0 || cols <= 0 || rows > A->rows || cols > B->rows || row0 > A->rows - rows || col0 > B->rows - cols)
         return HBFP_ERR_ARG;
     size_t need = 0;
-    hbfp_gemm_select_workspace(A, B, HBFP_KERNEL_INT8, &need);      // that of the whole product covers any window
+    select_workspace(A, B, HBFP_KERNEL_INT8, false, &need);         // that of the whole product covers any window
     if (need && (!workspace || ws_bytes < need || ((uintptr_t)workspace & 255))) return HBFP_ERR_WORKSPACE;
     // rows of an operand are kpad mantissas and exp_ld exponent bytes apart, so a window of the product is the
     // product of two operands that start further down and have fewer rows
@@ -1248,6 +1272,7 @@ int hbfp_gemm_partials_window(const hbfp_tensor *A, const hbfp_tensor *B, int64_
 struct F32Plan {
     hbfp_tensor ta, tb;
     size_t off_am, off_ae, off_bm, off_be, off_enc, off_gemm, total;
+    size_t least;                // total without the slices of a product of one exponent per row
 };
 
 static int plan_f32(int transA, int transB, int64_t M, int64_t N, int64_t K,
@@ -1272,6 +1297,8 @@ static int plan_f32(int transA, int transB, int64_t M, int64_t N, int64_t K,
     p->off_enc = o; o += align256(ea > eb ? ea : eb);
     p->off_gemm = o; o += align256(gw);
     p->total = o;
+    select_workspace(&p->ta, &p->tb, HBFP_KERNEL_AUTO, false, &gw);
+    p->least = p->off_gemm + align256(gw);
     return HBFP_OK;
 }
 
@@ -1294,7 +1321,7 @@ int hbfp_gemm_f32(int transA, int transB, int64_t M, int64_t N, int64_t K,
     int rc = plan_f32(transA, transB, M, N, K, fa, fb, &p);
     if (rc != HBFP_OK) return rc;
     if (lda < (transA ? M : K) || ldb < (transB ? K : N) || ldc < N) return HBFP_ERR_ARG;
-    if (!workspace || ws_bytes < p.total || ((uintptr_t)workspace & 255)) return HBFP_ERR_WORKSPACE;
+    if (!workspace || ws_bytes < p.least || ((uintptr_t)workspace & 255)) return HBFP_ERR_WORKSPACE;
     char *w = (char *)workspace;
     p.ta.mant = w + p.off_am;
     p.ta.exps = (uint8_t *)(w + p.off_ae);
@@ -1302,7 +1329,7 @@ int hbfp_gemm_f32(int transA, int transB, int64_t M, int64_t N, int64_t K,
     p.tb.exps = (uint8_t *)(w + p.off_be);
     rc = check_pair(&p.ta, &p.tb);  // mantissa classes and accumulator bound, before any launch
     if (rc != HBFP_OK) return rc;
-    const size_t enc_bytes = p.off_gemm - p.off_enc, gemm_bytes = p.total - p.off_gemm;
+    const size_t enc_bytes = p.off_gemm - p.off_enc, gemm_bytes = (ws_bytes < p.total ? p.least : p.total) - p.off_gemm;
     const EncodeGeom geoms[2] = {geom_of(p.ta, lda), geom_of(p.tb, ldb)};
     // sources off their element's alignment go on to hbfp_encode and its answer
     if (((uintptr_t)A & 3) == 0 && ((uintptr_t)B & 3) == 0 && !needs_tile_pass(p.ta) && !needs_tile_pass(p.tb) &&

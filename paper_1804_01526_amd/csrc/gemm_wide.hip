@@ -302,14 +302,14 @@ bool gemm_wide_ok(const GemmArgs &a) {
     return tiles >= 128 && (double)a.M * (double)a.N >= 0.75 * 65536.0 * (double)tiles;
 }
 
-// slices of a product split along k; a stand-by launch is not split
+// slices of a product split along k; a stand-by launch is not split, nor one whose caller brought no room for them
 size_t gemm_wide_workspace(const GemmArgs &a) {
-    const WidePlan plan = wide_plan(a.M, a.N, a.kpad / kWideK, !a.run_a);
+    const WidePlan plan = wide_plan(a.M, a.N, a.kpad / kWideK, !a.run_a && !a.unsplit);
     return plan.splits > 1 ? (size_t)plan.splits * (size_t)a.M * (size_t)a.N * 4 : 0;
 }
 
 int launch_gemm_wide(const GemmArgs &a, void *workspace, hipStream_t s) {
-    const WidePlan plan = wide_plan(a.M, a.N, a.kpad / kWideK, !a.run_a);
+    const WidePlan plan = wide_plan(a.M, a.N, a.kpad / kWideK, !a.run_a && !a.unsplit);
     if (plan.splits > 1 && !workspace) return HBFP_ERR_WORKSPACE;
     WideParams p = {};
     p.A = (const uint8_t *)a.mantA;

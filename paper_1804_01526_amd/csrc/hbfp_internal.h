@@ -71,6 +71,7 @@ struct GemmArgs {
     // every kernel of the launch does nothing unless one of them is marked out of range (word 0 == word 1)
     const int *run_a, *run_b;
     int32_t wide;                     // 1: the caller asked for the 256 x 256-tile int8 kernel whatever the shape
+    int32_t unsplit;                  // 1: the workspace has no room for the slices of a product of one exponent per row
     int32_t words_ready;              // stand-by launches: the scale words of the 8-wave int8 kernel are in the workspace already
 };
 // What the block-scaled product kernel needs in order to prepare the scale words of the int8 stand-by launch behind it

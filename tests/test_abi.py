@@ -569,3 +569,24 @@ def test_slices_of_products_split_along_k(M, N, K, m, blk, slices):
     planes = sum(-(-r * a.kpad * 2 // 256) * 256 for r in (M, N)) if m > 8 else 0
     got = hbfp.gemm_select_workspace(a, b, hbfp.KERNEL_INT8 if m <= 8 else hbfp.KERNEL_FP16) - words - planes
     assert got // (4 * M * N) == (slices if slices > 1 else 0)
+
+
+def test_slices_only_for_products_that_can_be_split():
+    """One exponent per row and a long contraction of few tiles: the slices are in the size of the kernels that split such a product, and
+    of a pair of packed operands of two forms, whose product the int8 kernels are; not in that of stand-by launches."""
+    M, N, K = 300, 260, 40000
+
+    def pair(ma, mb):
+        return hbfp.plan(hbfp.make_format(ma, 1, 0), M, K, 1), hbfp.plan(hbfp.make_format(mb, 0, 1), K, N, 0)
+
+    a, b = pair(8, 8)
+    words = 4 * a.exp_ld * (384 + 384)                               # rows up to whole tiles of 128
+    for kernel in (0, 1, 3):
+        size = hbfp.gemm_select_workspace(a, b, kernel)
+        assert size > words and size % (4 * M * N) == 0
+    a, b = pair(4, 5)
+    packed = hbfp.pack_bytes(a) + hbfp.pack_bytes(b)
+    assert hbfp.gemm_packed_workspace(a, b) == words
+    assert hbfp.gemm_select_workspace(a, b, 2) == (words + 255) // 256 * 256 + packed
+    assert hbfp.gemm_packed_workspace(*pair(4, 8)) > words
+

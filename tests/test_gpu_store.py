@@ -159,3 +159,50 @@ def test_largest_exponent_of_a_row(kernel, blocks, at):
     # FP32 sums of exact products, one rounding per product at the worst
     bound = 2.0 ** -24 * (K + 2) * (hbfp.decode(a).double().abs() @ hbfp.decode(b).double().abs())
     assert bool(((C - want).abs() <= bound).all())
+
+
+# a product of one exponent per row that is split along k: a workspace without its slices is as good as ever, the product then runs
+# unsplit with the same bits; less than the words is refused
+@pytest.mark.parametrize("call", ["gemm", "int8", "wide", "partials", "batch", "bfp", "f32", "packed", "packed batch"])
+def test_split_product_without_room_for_its_slices(call):
+    from paper_1804_01526_amd import hbfp
+    M, K, N = 130, 20000, 70
+    mixed = call.startswith("packed")
+    g = torch.Generator(device="cuda").manual_seed(1)
+    A = torch.randn((M, K), device="cuda", generator=g) * 2.0 ** torch.randint(-4, 5, (M, 1), device="cuda", generator=g)
+    B = torch.randn((K, N), device="cuda", generator=g) * 2.0 ** torch.randint(-4, 5, (1, N), device="cuda", generator=g)
+    fa, fb, fo = hbfp.make_format(4 if mixed else 8, 1, 0), hbfp.make_format(8, 0, 1), hbfp.make_format(8, 1, 32)
+    a, b = hbfp.encode(A, 1, fa), hbfp.encode(B, 0, fb)
+    slices = (hbfp.gemm_select_workspace(a.desc, b.desc, INT8) + 255) // 256 * 256
+    words = 4 * a.desc.exp_ld * (256 + 128)
+    assert slices > words and words % 256 == 0
+    C, C2 = torch.empty((M, N), device="cuda"), torch.empty((M, N), device="cuda")
+    if call in ("gemm", "int8", "wide"):
+        kernel = {"gemm": 0, "int8": INT8, "wide": WIDE}[call]
+        full, run = hbfp.gemm_select_workspace(a.desc, b.desc, kernel), lambda ws: hbfp.gemm(a, b, out=C, kernel=kernel, workspace=ws)
+    elif call == "partials":
+        full, run = slices, lambda ws: hbfp.gemm_partials(a, b, workspace=ws)
+    elif call == "batch":
+        full, run = 2 * slices, lambda ws: hbfp.gemm_batch([(a, b), (a, b)], [C, C2], kernel=INT8, workspace=ws)[1]
+    elif call == "bfp":
+        out = hbfp.alloc(fo, M, N, 1)
+        full, run = hbfp.gemm_bfp_workspace(a.desc, b.desc, out.desc, 0), lambda ws: hbfp.gemm_bfp(a, b, fo, 1, out=out, workspace=ws).mant
+    elif call == "f32":
+        full = hbfp.gemm_f32_workspace(0, 0, M, N, K, fa, fb)
+        run = lambda ws: hbfp.gemm_f32(0, 0, A, B, fa, fb, out=C, workspace=ws)
+    elif call == "packed":
+        full, run = hbfp.gemm_packed_workspace(a.desc, b.desc), lambda ws: hbfp.gemm_packed(a, hbfp.pack(a), b, hbfp.pack(b), out=C, workspace=ws)
+    else:
+        pa, pb = hbfp.pack(a), hbfp.pack(b)
+        full, run = 2 * slices, lambda ws: hbfp.gemm_packed_batch([(a, pa, b, pb)] * 2, [C, C2], workspace=ws)[1]
+    full = (full + 255) // 256 * 256
+    least = full - (slices - words) * (2 if "batch" in call else 1)
+    print(f"[store] {call}: {least} of {full} bytes", flush=True)
+    want = run(torch.empty(full, dtype=torch.uint8, device="cuda")).clone()
+    C.fill_(-1.0), C2.fill_(-1.0)
+    guarded = torch.full((least + 4096,), 85, dtype=torch.uint8, device="cuda")
+    assert torch.equal(run(guarded[:least]), want)
+    assert bool((guarded[least:] == 85).all())
+    with pytest.raises(hbfp.HbfpError):
+        run(guarded[:least - 256])
+

@@ -14,8 +14,6 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("blocks", [((1, 24), (24, 1)), ((24, 24), (24, 24)), ((24, 24), (24, 1))])
 def test_halves_and_regions(rows, cols, blocks, rounding):
     from paper_1804_01526_amd import hbfp
-    if rows > 2000 and blocks[1] == (24, 1) and blocks[0] == (24, 24):
-        pytest.skip("one large case per block shape is enough")
     print(f"[halves] {rows}x{cols} {blocks} rounding={rounding}", flush=True)
     x = _rand((rows, cols), rows + cols)
     _check_against_separate_calls(hbfp, x, [(*blocks[0], 8, rounding, 3, 1), (*blocks[1], 8, rounding, 9, 0)])

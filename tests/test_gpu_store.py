@@ -1,7 +1,8 @@
 """Where the product kernels store C: whole tiles, edges of one row or column more or less, a row pitch, and C += .
 
-The inputs are integers whose blocks all hold a 1 in the top bit, so every sum is exact in FP32 and C must equal the FP64
-product of the decoded operands; the bytes of the buffer around C must stay as they were.
+The inputs are integers, scaled by a power of two per row and per column, whose blocks all hold a 1 in the top bit: every sum is exact
+in FP32, C must equal the FP64 product of the operands, and an exponent taken from another row or column shows.  The bytes of the
+buffer around C must stay as they were.
 """
 import pytest
 import torch
@@ -21,6 +22,8 @@ def _operands(M, K, N, bits, block):
     B = torch.randint(-3, 4, (K, N), device="cuda", generator=g).float()
     A[:, ::block or K] = top
     B[::block or K, :] = top
+    A *= 2.0 ** torch.randint(-3, 4, (M, 1), device="cuda", generator=g)
+    B *= 2.0 ** torch.randint(-3, 4, (1, N), device="cuda", generator=g)
     return (hbfp.encode(A, 1, hbfp.make_format(bits, 1, block, hbfp.RNE)), hbfp.encode(B, 0, hbfp.make_format(bits, block, 1, hbfp.RNE)),
             A.double() @ B.double())
 
@@ -38,7 +41,7 @@ def test_edges_pitch_and_accumulation(kernel, bits, block, edge, dm, dn, beta):
     C = buf[1:M + 1, 2:N + 2]
     if beta:
         C.copy_(torch.arange(N, device="cuda").float().expand(M, N))
-        want = want + torch.arange(N, device="cuda").double()
+        want = (want + torch.arange(N, device="cuda").double()).float().double()
     hbfp.gemm(a, b, out=C, beta=beta, kernel=kernel)
     assert torch.equal(C.double(), want)
     buf[1:M + 1, 2:N + 2] = 7.0
@@ -125,18 +128,24 @@ def test_slices_of_a_split_product(M, N):
     assert bool((buf == 7.0).all())
 
 
-# one exponent per row and column: tiles of 128 (alone, split along k over 2 .. 7 and over 8 and more ranges), 192 and 256
-@pytest.mark.parametrize("M,K,N", [(200, 1000, 300), (1, 130, 1), (128, 128, 129), (300, 4000, 260), (130, 20000, 70), (65, 40001, 64), (3001, 129, 2999),
-                                   (4096, 129, 4095)])
+# one exponent per row and column: tiles of 128 (2; alone, split along k over 2 .. 7 and over 8 and more ranges), 192 (3) and 256 (4),
+# those with 4 stages and with so many that every buffer of the ring is filled again
+@pytest.mark.parametrize("M,K,N,tile,splits", [(200, 1000, 300, 2, 1), (1, 130, 1, 2, 1), (128, 128, 129, 2, 1), (300, 4100, 520, 2, 7), (640, 3000, 641, 2, 4),
+                                               (300, 4000, 260, 2, 8), (130, 20000, 70, 2, 32), (65, 40001, 64, 2, 64), (3001, 129, 2999, 3, 1),
+                                               (2900, 1000, 2901, 3, 1), (4096, 129, 4095, 4, 1), (3700, 1100, 3651, 4, 1)])
 @pytest.mark.parametrize("beta", [0.0, 1.0])
-def test_one_exponent_per_row(M, K, N, beta):
+def test_one_exponent_per_row(M, K, N, tile, splits, beta):
     from paper_1804_01526_amd import hbfp
     print(f"[one exponent] {M}x{K}x{N} beta={beta}", flush=True)
     a, b, want = _operands(M, K, N, 8, 0)
     C = torch.full((M, N + 3), 5.0, device="cuda")
     hbfp.gemm(a, b, out=C[:, :N], beta=beta)
-    assert torch.equal(C[:, :N].double(), want + (5.0 if beta else 0.0))
+    assert torch.equal(C[:, :N], (want + (5.0 if beta else 0.0)).float())
     assert bool((C[:, N:] == 5.0).all())
+    names = launched_kernels(lambda: hbfp.gemm(a, b, out=C[:, :N], beta=beta))
+    assert names[0].startswith(f"gemm_i8_wide_kernel<{tile}, ") and names[1:] == (["wide_sum_kernel"] if splits > 1 else []), names
+    if splits > 1:
+        assert hbfp.gemm_select_workspace(a.desc, b.desc, 0) == splits * 4 * M * N
 
 
 # 12-bit operands as FP16 planes: a row's factor comes from its largest exponent byte, wherever that lies (16 lanes read four

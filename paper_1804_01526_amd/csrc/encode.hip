@@ -804,7 +804,8 @@ __global__ __launch_bounds__(kThreads) void tile_amax_kernel(const TileParams p,
 // in registers, so the source is read once: all loads first, maximum across the wave, quantise, store.
 // Bound by the waves in flight, which their registers limit: NV is the least of 2, 4, 8, 10, 12 and 16 that holds the block (16
 // for all beyond 8 -> now: 3001 x 4500 17.9 -> 12.5 us, 5.4 TB/s of source and result; 6000 columns 18.7 -> 15.6; 500 x 4500 8.1 ->
-// 5.9; stochastic 3001 x 4500 33.3 -> 21.9).
+// 5.9; stochastic 3001 x 4500 33.3 -> 21.9; replayed over three sources, which stay in the last-level cache: between the other
+// launches of a step 3001 x 4500 takes 15.4).
 // Rows of odd lengths take the same 16-byte loads, aligned to 4 bytes (value by value -> now: 3000 x 4501 27.6 -> 12.6 us).
 struct WaveParams {
     const float *src;
@@ -1026,8 +1027,9 @@ __global__ __launch_bounds__(kStripThreads) void enc_strip_kernel(const StripPar
 // The same strips held in registers between the maxima and the quantisation: one read, and all of a thread's loads in flight at
 // once, where the kernel above has 16 and reads twice.  Bound by the latency of the strided loads and the one or two
 // workgroups that a compute unit's registers hold: 16 columns of 5120 positions (1024 threads) or twice 2560 (512).
-// Read twice -> held: 4500 x 2999 25.7 -> 16.6 us (4.1 TB/s of source and result), stochastic 39.1 -> 32.6, 12 bits 28.3 -> 19.1;
-// 4096^2 27.3 -> 18.4, 2500 x 6000 24.1 -> 16.7, 3000 x 12000 60.8 -> 45.7, 1100 x 2999 8.2 -> 7.0, 3502 x 13 13.5 -> 8.6.
+// Read twice -> held, replayed over three sources that stay in the last-level cache (between the other launches of a step 4500 x 2999
+// takes 22.5): 4500 x 2999 25.7 -> 16.6 us (4.1 TB/s of source and result), stochastic 39.1 -> 32.6, 12 bits 28.3 -> 19.1; 4096^2
+// 27.3 -> 18.4, 2500 x 6000 24.1 -> 16.7, 3000 x 12000 60.8 -> 45.7, 1100 x 2999 8.2 -> 7.0, 3502 x 13 13.5 -> 8.6.
 constexpr int kHeldPieces = 5, kHeldThreads = 1024;
 template <bool WIDE, int ROUND, int PIECES>
 __global__ __launch_bounds__(kHeldThreads) void enc_strip_held_kernel(const StripParams p) {

@@ -331,7 +331,10 @@ int launch_gemm_wide(const GemmArgs &a, void *workspace, hipStream_t s) {
     p.exp_offset = -250 - a.mA - a.mB;
     p.run_a = a.run_a;
     p.run_b = a.run_b;
-    const bool stream = stores_stream(&a);
+    // Only contractions up to 1024 end in so much of a burst that ordinary stores pay for what C takes of the last-level cache from the
+    // conversions beside the product (conversions and product, streaming -> ordinary: 3001 x 600 x 2999 29.3 -> 26.9 us, 5000 x 1024 x
+    // 4001 54.6 -> 54.1, 4100 x 1024 x 2501 38.9 -> 34.7, but 5000 x 1200 x 4001 60.5 -> 63.7, 3001 x 4500 x 2999 86.9 -> 88.4)
+    const bool stream = a.kpad > 1024 || stores_stream(&a);
     const int rc = plan.T == 2 ? launch_wide_t<2>(p, stream, s) : plan.T == 3 ? launch_wide_t<3>(p, stream, s) : launch_wide_t<4>(p, stream, s);
     if (rc != HBFP_OK || p.splits == 1) return rc;
     const int64_t wgs = ceil_div(a.M * a.N, 1024);

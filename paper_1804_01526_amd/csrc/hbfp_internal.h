@@ -70,7 +70,7 @@ struct GemmArgs {
     // stand-by launches (behind the block-scaled kernel): non-null pointers to the headers of the two packed operands;
     // every kernel of the launch does nothing unless one of them is marked out of range (word 0 == word 1)
     const int *run_a, *run_b;
-    int32_t wide;                     // 1: the caller asked for the 256 x 256-tile int8 kernel whatever the shape
+    int32_t wide;                     // 1: the caller asked for the int8 kernel of one exponent per row whatever the shape
     int32_t unsplit;                  // 1: the workspace has no room for the slices of a product of one exponent per row
     int32_t words_ready;              // stand-by launches: the scale words of the 8-wave int8 kernel are in the workspace already
 };

@@ -49,14 +49,16 @@ def test_edges_pitch_and_accumulation(kernel, bits, block, edge, dm, dn, beta):
 
 
 # Large outputs whose rows are not whole lines leave by ordinary stores, others past the caches: rows off 32 bytes from 6 Mi outputs on,
-# rows off 128 from 10 Mi on; the base of C counts like its pitch
-@pytest.mark.parametrize("kernel,bits,block", [(BF16, 8, 24), (F16P, 12, 64), (SCALED, 4, 32), (WIDE, 8, 0), (INT8, 12, 128), (INT8, 12, 64)])
+# rows off 128 from 10 Mi on; the base of C counts like its pitch; with one exponent per row up to 1024 of k
+@pytest.mark.parametrize("kernel,bits,block,K", [(BF16, 8, 24, 192), (F16P, 12, 64, 192), (SCALED, 4, 32, 192), (WIDE, 8, 0, 192), (WIDE, 8, 0, 1100),
+                                                 (INT8, 12, 128, 192), (INT8, 12, 64, 192)])
 @pytest.mark.parametrize("M,N,pad,at,stream", [(2419, 2601, 0, 0, False), (2420, 2600, 1, 0, False), (2432, 2592, 0, 1, False), (2430, 2600, 0, 0, True),
                                                (2417, 2601, 0, 0, True), (2560, 2560, 32, 0, True), (2600, 4040, 0, 0, False)])
-def test_how_large_outputs_leave(kernel, bits, block, M, N, pad, at, stream):
+def test_how_large_outputs_leave(kernel, bits, block, K, M, N, pad, at, stream):
     from paper_1804_01526_amd import hbfp
-    print(f"[store] kernel={kernel} bits={bits} block={block} {M}x{N} pitch {N + pad}", flush=True)
-    a, b, want = _operands(M, 192, N, bits, block)
+    print(f"[store] kernel={kernel} bits={bits} block={block} {M}x{N}x{K} pitch {N + pad}", flush=True)
+    stream = stream or (kernel == WIDE and K > 1024)
+    a, b, want = _operands(M, K, N, bits, block)
     buf = torch.full((M * (N + pad) + 32,), 7.0, device="cuda")
     C = buf[at:at + M * (N + pad)].view(M, N + pad)[:, :N]
     names = launched_kernels(lambda: hbfp.gemm(a, b, out=C, kernel=kernel))

@@ -436,10 +436,10 @@ void launch_row_t(const RowParams &p, dim3 grid, hipStream_t s) {
     // stochastic rounding is bound by its vector instructions and holds more registers: two chunks per thread instead of
     // four keep more waves on a SIMD (config 2, 8-bit: 67 us against 71-75 us)
     constexpr int U = ROUND ? 2 : 4;
-    // Loads aligned to 16 bytes where rows are and there are at least 6 Mi values, else the instance that aligns to 4 (its code is
-    // shorter).  That one, aligned loads: 256 x 512 3.4, 3.5 us, 1024 x 4096 5.6, 5.9, 2048 x 4096 8.3 both, 8192^2 58.8, 57.5; both in
-    // one kernel 59.2.
-    void (*const kernel)(RowParams) = p.vec_ok && p.R * p.K >= (int64_t)6 << 20 ? &enc_row_kernel<GP, WIDE, ROUND, U> : &enc_row_kernel<GP, WIDE, ROUND, U, false, true>;
+    // Loads aligned to 16 bytes where rows are and there are at least 16 Mi values, else the instance that aligns to 4 (its code is
+    // shorter).  That one, aligned loads: 256 x 512 3.4, 3.5 us, 1024 x 4096 5.6, 5.9, 100352 x 128 11.8, 12.0, 4096^2 14.0, 13.9,
+    // 3000 x 6000 15.4, 15.2, 8192^2 58.8, 57.5; both in one kernel 59.2.
+    void (*const kernel)(RowParams) = p.vec_ok && p.R * p.K >= (int64_t)16 << 20 ? &enc_row_kernel<GP, WIDE, ROUND, U> : &enc_row_kernel<GP, WIDE, ROUND, U, false, true>;
     hipLaunchKernelGGL(kernel, dim3(grid.x * (4 / U)), dim3(kThreads), 0, s, p);
 }
 

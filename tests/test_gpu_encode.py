@@ -688,11 +688,11 @@ def test_one_value_out_of_range_spoils_its_own_block_only(hb, rows, cols, br, bc
         np.testing.assert_array_equal(exps, full.exps)
 
 
-@pytest.mark.parametrize("rows,cols,pad,aligned16", [(64, 256, 0, False), (1535, 4096, 0, False), (1536, 4096, 0, True), (3000, 2100, 0, True), (3001, 2099, 0, False),
-                                                     (3000, 2100, 2, False), (1536, 4096, 4, True)])
+@pytest.mark.parametrize("rows,cols,pad,aligned16", [(64, 256, 0, False), (4095, 4096, 0, False), (4096, 4096, 0, True), (3000, 5600, 0, True), (3001, 5599, 0, False),
+                                                     (3000, 5600, 2, False), (4096, 4096, 4, True)])
 @pytest.mark.parametrize("rounding,unroll", [(0, 4), (1, 2)])
 def test_which_loads_rows_are_read_with(hb, rows, cols, pad, aligned16, rounding, unroll):
-    """Rows that start on 16 bytes and hold at least 6 Mi values have the instance that reads nothing else to themselves; the bytes are
+    """Rows that start on 16 bytes and hold at least 16 Mi values have the instance that reads nothing else to themselves; the bytes are
     those of the oracle either way."""
     x = torch.randn((rows, cols + pad), device="cuda", generator=torch.Generator(device="cuda").manual_seed(cols))[:, :cols]
     fmt = hb.make_format(8, 1, 24, rounding, 5)

@@ -1182,7 +1182,7 @@ int hbfp_gemm_packed_batch(int n, const hbfp_tensor *const *A, const void *const
     if (!A || !B || !C || !ldc || !packed_a || !packed_b || n < 1 || n > HBFP_BATCH_MAX) return HBFP_ERR_ARG;
     if (beta != 0.0f && beta != 1.0f) return HBFP_ERR_ARG;
     GemmArgs g[HBFP_BATCH_MAX];
-    size_t part[HBFP_BATCH_MAX], unsplit[HBFP_BATCH_MAX], need = 0, least = 0;
+    size_t part[HBFP_BATCH_MAX], need = 0;
     for (int i = 0; i < n; ++i) {
         if (!A[i] || !B[i] || !C[i] || !packed_a[i] || !packed_b[i]) return HBFP_ERR_ARG;
         if (((uintptr_t)packed_a[i] & 255) || ((uintptr_t)packed_b[i] & 255) || ((uintptr_t)C[i] & 3)) return HBFP_ERR_ARG;
@@ -1190,12 +1190,9 @@ int hbfp_gemm_packed_batch(int n, const hbfp_tensor *const *A, const void *const
         if (rc != HBFP_OK) return rc;
         if (ldc[i] < B[i]->rows) return HBFP_ERR_ARG;
         rc = packed_workspace(A[i], B[i], true, &part[i]);
-        if (rc == HBFP_OK) rc = packed_workspace(A[i], B[i], false, &unsplit[i]);
         if (rc != HBFP_OK) return rc;
         part[i] = align256(part[i]);
-        unsplit[i] = align256(unsplit[i]);
         need += part[i];
-        least += unsplit[i];
         g[i] = gemm_args(A[i], B[i]);
         g[i].C = C[i];
         g[i].ldc = ldc[i];
@@ -1206,8 +1203,13 @@ int hbfp_gemm_packed_batch(int n, const hbfp_tensor *const *A, const void *const
     }
     const int kind = packed_kind(A[0], B[0]);
     if (ws_bytes < need) {
-        need = least;
-        for (int i = 0; i < n; ++i) part[i] = unsplit[i], g[i].unsplit = 1;
+        need = 0;
+        for (int i = 0; i < n; ++i) {
+            packed_workspace(A[i], B[i], false, &part[i]);
+            part[i] = align256(part[i]);
+            need += part[i];
+            g[i].unsplit = 1;
+        }
     }
     if (need && (!workspace || ws_bytes < need || ((uintptr_t)workspace & 255))) return HBFP_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
@@ -1272,7 +1274,6 @@ int hbfp_gemm_partials_window(const hbfp_tensor *A, const hbfp_tensor *B, int64_
 struct F32Plan {
     hbfp_tensor ta, tb;
     size_t off_am, off_ae, off_bm, off_be, off_enc, off_gemm, total;
-    size_t least;                // total without the slices of a product of one exponent per row
 };
 
 static int plan_f32(int transA, int transB, int64_t M, int64_t N, int64_t K,
@@ -1297,8 +1298,6 @@ static int plan_f32(int transA, int transB, int64_t M, int64_t N, int64_t K,
     p->off_enc = o; o += align256(ea > eb ? ea : eb);
     p->off_gemm = o; o += align256(gw);
     p->total = o;
-    select_workspace(&p->ta, &p->tb, HBFP_KERNEL_AUTO, false, &gw);
-    p->least = p->off_gemm + align256(gw);
     return HBFP_OK;
 }
 
@@ -1321,7 +1320,12 @@ int hbfp_gemm_f32(int transA, int transB, int64_t M, int64_t N, int64_t K,
     int rc = plan_f32(transA, transB, M, N, K, fa, fb, &p);
     if (rc != HBFP_OK) return rc;
     if (lda < (transA ? M : K) || ldb < (transB ? K : N) || ldc < N) return HBFP_ERR_ARG;
-    if (!workspace || ws_bytes < p.least || ((uintptr_t)workspace & 255)) return HBFP_ERR_WORKSPACE;
+    if (ws_bytes < p.total) {                                    // without the slices of a product of one exponent per row
+        size_t gw = 0;
+        select_workspace(&p.ta, &p.tb, HBFP_KERNEL_AUTO, false, &gw);
+        p.total = p.off_gemm + align256(gw);
+    }
+    if (!workspace || ws_bytes < p.total || ((uintptr_t)workspace & 255)) return HBFP_ERR_WORKSPACE;
     char *w = (char *)workspace;
     p.ta.mant = w + p.off_am;
     p.ta.exps = (uint8_t *)(w + p.off_ae);
@@ -1329,7 +1333,7 @@ int hbfp_gemm_f32(int transA, int transB, int64_t M, int64_t N, int64_t K,
     p.tb.exps = (uint8_t *)(w + p.off_be);
     rc = check_pair(&p.ta, &p.tb);  // mantissa classes and accumulator bound, before any launch
     if (rc != HBFP_OK) return rc;
-    const size_t enc_bytes = p.off_gemm - p.off_enc, gemm_bytes = (ws_bytes < p.total ? p.least : p.total) - p.off_gemm;
+    const size_t enc_bytes = p.off_gemm - p.off_enc, gemm_bytes = p.total - p.off_gemm;
     const EncodeGeom geoms[2] = {geom_of(p.ta, lda), geom_of(p.tb, ldb)};
     // sources off their element's alignment go on to hbfp_encode and its answer
     if (((uintptr_t)A & 3) == 0 && ((uintptr_t)B & 3) == 0 && !needs_tile_pass(p.ta) && !needs_tile_pass(p.tb) &&

@@ -6,28 +6,33 @@
 // The kernel is therefore built for the matrix core alone: four waves of 32 T x 32 T, T = 4 (a tile of 256 x 256 of C
 // per workgroup, 256 int32 accumulators per lane at one wave per SIMD, a pair of matrix instructions needs one 16-byte
 // LDS read per lane: 64 B/clk per CU at the full matrix rate, where a 64 x 128 wave tile would need 94 of the 128 the
-// LDS can deliver), 3 or 2 (128 x 128, two workgroups per CU).  Large products are bound by the chip's power and go
-// furthest on the largest tile; the smaller ones fill the chip where those are too few, and long contractions of few
-// tiles are split (wide_plan).  Operands are read as they are stored (int8 [rows][kpad]): 64 bytes of k of the tile's
-// rows per stage (32 KB for T = 4), copied global -> LDS asynchronously into a ring of four buffers, rows of 64 bytes with the 16-byte chunk index XORed with (row >> 2) & 3 as in the other int8 kernels (copies of 16 rows
-// and fragment reads of 32 rows then both cover all banks).  Fragments are read one k-step (32) ahead, between
-// the matrix instructions, and the hand-over of a ring buffer (one barrier per stage) sits in the middle of a stage.
+// LDS can deliver), 3 or 2 (128 x 128, two workgroups per CU).  Large products are bound by the chip's power (3001 x 4500 x
+// 2999 on T = 3: matrix instructions 70 % of the loop's clocks at 1.7 GHz; 2.3 us until the first stage is there, 34 us of
+// loop, 10 us in which all compute units store C at once) and go furthest on the largest tile; the smaller ones fill the chip
+// where those are too few, and long contractions of few tiles are split (wide_plan).  Operands are read as they are stored
+// (int8 [rows][kpad]): 128 bytes of k of the tile's rows per stage, whole cache lines (64 bytes: launch_gemm_wide), copied global ->
+// LDS asynchronously into a ring of as many stages as fit, rows of 128 bytes with the 16-byte chunk index XORed with
+// (row >> 1) & 7, so that copies and the fragment reads of 16 rows cover all banks.  Fragments are read one k-step (32)
+// ahead, between the matrix instructions, and the hand-over of a ring buffer (one barrier per stage) sits in the stage's last
+// k-step.
 #include "gemm_common.h"
 
 namespace hbfp {
 namespace {
 
 constexpr int kWideThreads = 256;
-constexpr int kWideK = 64;                              // bytes of k per stage
-constexpr int kWideRing = 4;
-// T: 32 x 32 tiles along a side of a wave's part of C; the workgroup's tile is 64 T x 64 T
-template <int T>
+// T: 32 x 32 tiles along a side of a wave's part of C; the workgroup's tile is 64 T x 64 T.  K: bytes of k per stage and operand row,
+// RING: stages in LDS.
+template <int T, int K, int RING>
 struct Wide {
     static constexpr int kRows = 64 * T;
-    static constexpr int kOperand = kRows * kWideK;      // 16 KB for T = 4
+    static constexpr int kChunks = K / 16, kSteps = K / 32;
+    static constexpr int kOperand = kRows * K;           // 32 KB for T = 4
     static constexpr int kStage = 2 * kOperand;
-    static constexpr int kLds = kWideRing * kStage;      // 128 KB for T = 4
-    static constexpr int kCopies = kStage / 1024 / 4;    // copies of 1 KB (16 rows x 64 B) per wave and stage: 2 T
+    static constexpr int kLds = RING * kStage;
+    static constexpr int kCopies = kStage / 1024 / 4;    // copies of 1 KB per wave and stage
+    // rows of K bytes whose 16-byte chunks are exchanged so that the reads of 16 consecutive rows at one k cover all banks
+    static __device__ __forceinline__ int swizzle(int row) { return K == 128 ? (row >> 1) & 7 : (row >> 2) & 3; }
 };
 
 struct WideParams {
@@ -36,7 +41,7 @@ struct WideParams {
     float *C;
     int64_t M, N, kpad, eA_ld, eB_ld, ldc;
     int32_t *partial;            // split along k: int32 sums [splits][M][N]
-    int32_t nstage;              // kpad / 64 (even)
+    int32_t nstage;              // kpad / K
     int32_t splits, stages_per_split;
     int32_t tiles_m, tiles_n, beta;
     int32_t exp_offset;          // C = acc * 2^(Ea + Eb + exp_offset)
@@ -44,9 +49,9 @@ struct WideParams {
 };
 
 // STREAM: how C leaves (stores_stream)
-template <int T, bool STREAM>
-__global__ __launch_bounds__(kWideThreads, T == 4 ? 1 : 2) void gemm_i8_wide_kernel(const WideParams p) {
-    typedef Wide<T> W;
+template <int T, int K, int RING, bool STREAM>
+__global__ __launch_bounds__(kWideThreads, (Wide<T, K, RING>::kLds <= 80 * 1024 ? 2 : 1)) void gemm_i8_wide_kernel(const WideParams p) {
+    typedef Wide<T, K, RING> W;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     if (stands_down(p.run_a, p.run_b)) return;
     int tm, tn, split = blockIdx.y;
@@ -54,7 +59,7 @@ __global__ __launch_bounds__(kWideThreads, T == 4 ? 1 : 2) void gemm_i8_wide_ker
                       : !tile_of_workgroup(blockIdx.x, p.tiles_m, p.tiles_n, tm, tn))
         return;                                                                 // whole workgroup, before any barrier
     const int st_begin = split * p.stages_per_split;
-    const int nstage = p.nstage - st_begin < p.stages_per_split ? p.nstage - st_begin : p.stages_per_split;   // even, at least 2
+    const int nstage = p.nstage - st_begin < p.stages_per_split ? p.nstage - st_begin : p.stages_per_split;   // at least 1
 
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -66,27 +71,28 @@ __global__ __launch_bounds__(kWideThreads, T == 4 ? 1 : 2) void gemm_i8_wide_ker
     const int64_t row_t = row0 + (t < W::kRows ? t : 0), col_t = col0 + (t < W::kRows ? t : 0);
     const int ea_t = p.eA[(row_t < p.M ? row_t : p.M - 1) * p.eA_ld], eb_t = p.eB[(col_t < p.N ? col_t : p.N - 1) * p.eB_ld];
 
-    // ---- copies: piece c of a stage is 16 rows x 64 bytes; pieces 0 .. 4 T - 1 are A, the others B; wave w moves pieces w, w + 4, ...
-    // A lane copies 16 bytes: row 16 c + lane / 4, LDS chunk lane % 4, which holds source chunk (lane % 4) ^ ((row >> 2) & 3).
-    // Rows past the edge re-read the last row (their results are never stored).
+    // ---- copies: piece c of a stage is 1 KB, 8 rows x 128 or 16 rows x 64 bytes; the first half are pieces of A, the others of B; wave w
+    // moves pieces w, w + 4, ...  A lane copies 16 bytes: LDS chunk lane % kChunks of its row, which holds source chunk
+    // (lane % kChunks) ^ swizzle(row).  Rows past the edge re-read the last row (their results are never stored).
+    constexpr int kPieces = W::kOperand / 1024;
     const uint8_t *cbase[W::kCopies];
     uint32_t cvoff[W::kCopies], coff[W::kCopies];
 #pragma unroll
     for (int i = 0; i < W::kCopies; ++i) {
         const int c = wave + 4 * i;
-        const bool is_a = c < 4 * T;
-        const int r = 16 * (is_a ? c : c - 4 * T) + (lane >> 2);
+        const bool is_a = c < kPieces;
+        const int r = (is_a ? c : c - kPieces) * (1024 / K) + lane / W::kChunks;
         const int64_t lim = is_a ? p.M - row0 : p.N - col0;
         const int rr = r < lim ? r : (int)lim - 1;
-        const int chunk = (lane & 3) ^ ((r >> 2) & 3);
-        cbase[i] = (is_a ? p.A + row0 * p.kpad : p.B + col0 * p.kpad) + (int64_t)st_begin * kWideK;
+        const int chunk = (lane % W::kChunks) ^ W::swizzle(r);
+        cbase[i] = (is_a ? p.A + row0 * p.kpad : p.B + col0 * p.kpad) + (int64_t)st_begin * K;
         cvoff[i] = (uint32_t)rr * (uint32_t)p.kpad + chunk * 16;
         coff[i] = c * 1024;
     }
 #define HBFP_WIDE_COPY(i, ring_)                                                                    \
     {                                                                                              \
         async_copy16(cbase[i], cvoff[i], (uint32_t)((ring_) * W::kStage) + coff[i]);              \
-        cbase[i] += kWideK;                                                                        \
+        cbase[i] += K;                                                                         \
     }
 #define HBFP_WIDE_COPY_STAGE(ring_)                                                                 \
     {                                                                                              \
@@ -94,13 +100,13 @@ __global__ __launch_bounds__(kWideThreads, T == 4 ? 1 : 2) void gemm_i8_wide_ker
     }
 
     // ---- fragment addresses inside a stage: row tile i of A is rows 32 T wm + 32 i + l32, k-step s the chunks 2 s + lh
-    int fa[2], fb[2];                                   // per k-step: byte offset of (row tile 0, this lane); tiles are 2 KB apart
+    int fa[W::kSteps], fb[W::kSteps];                 // per k-step: byte offset of (row tile 0, this lane); tiles are 32 rows apart
     {
         const int ra = 32 * T * wm + l32, rb = 32 * T * wn + l32;
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            fa[s] = ra * kWideK + (((2 * s + lh) ^ ((ra >> 2) & 3)) * 16);
-            fb[s] = W::kOperand + rb * kWideK + (((2 * s + lh) ^ ((rb >> 2) & 3)) * 16);
+        for (int s = 0; s < W::kSteps; ++s) {
+            fa[s] = ra * K + (((2 * s + lh) ^ W::swizzle(ra)) * 16);
+            fb[s] = W::kOperand + rb * K + (((2 * s + lh) ^ W::swizzle(rb)) * 16);
         }
     }
 
@@ -118,68 +124,75 @@ __global__ __launch_bounds__(kWideThreads, T == 4 ? 1 : 2) void gemm_i8_wide_ker
     __builtin_amdgcn_sched_barrier(0)
 #define HBFP_WIDE_READ(buf, base_, s, i)                                                                       \
     {                                                                                                         \
-        a[buf][i] = *reinterpret_cast<const v4i *>((base_) + fa[s] + (i) * 2048);                             \
-        b[buf][i] = *reinterpret_cast<const v4i *>((base_) + fb[s] + (i) * 2048);                             \
+        a[buf][i] = *reinterpret_cast<const v4i *>((base_) + fa[s] + (i) * 32 * K);                        \
+        b[buf][i] = *reinterpret_cast<const v4i *>((base_) + fb[s] + (i) * 32 * K);                        \
     }
-    // one k-step of 32: T x T matrix instructions on buffer `buf`; after each row of them, one row tile and one column
-    // tile of the next k-step are requested into the other buffer (EXTRA: the hand-over's copies ride along)
 #define HBFP_WIDE_ROW(buf, i)                                                                                  \
     {                                                                                                         \
         _Pragma("unroll") for (int j = 0; j < T; ++j)                                                         \
             acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[buf][i], b[buf][j], acc[i][j], 0, 0, 0);      \
     }
-#define HBFP_WIDE_KSTEP(buf, NEXT, nbase_, ns, COPY, ring_)                                                     \
+    // one k-step of 32: T x T matrix instructions on buffer `buf`; after each row of them, one row tile and one column
+    // tile of the next k-step are requested into the other buffer.  HAND: the hand-over sits behind the first row;
+    // COPY: the copies into the ring buffer that it frees ride along
+#define HBFP_WIDE_KSTEP(buf, NEXT, nbase_, ns, HAND, COPY)                                                      \
     {                                                                                                         \
         _Pragma("unroll") for (int i_ = 0; i_ < T; ++i_) {                                                    \
             HBFP_WIDE_ROW(buf, i_);                                                                           \
+            if (i_ == 0) { HAND; }                                                                            \
             if (NEXT) HBFP_WIDE_READ(1 - (buf), nbase_, ns, i_);                                              \
-            if (COPY) { HBFP_WIDE_COPY(2 * i_, ring_); HBFP_WIDE_COPY(2 * i_ + 1, ring_); }                   \
+            if (COPY) { _Pragma("unroll") for (int c_ = 0; c_ < W::kCopies / T; ++c_) HBFP_WIDE_COPY(W::kCopies / T * i_ + c_, ring); } \
             HBFP_WIDE_FENCE;                                                                                  \
         }                                                                                                     \
     }
-    // A stage: k-step 0 (its fragments were requested during the stage before), then the hand-over: this wave's copies
-    // of the next stage have landed when only those of the stage after it are in flight; after the barrier everybody's
-    // have, and everybody has read the last fragment of the stage before this one, whose buffer takes the copies of
-    // stage st + 3 (issued between the matrix instructions of k-step 1).
-    // MODE 0: hand-over with copies;  1: hand-over, nothing left to copy, one more stage in flight;  2: hand-over,
-    // the next stage is the last;  3: last stage
-#define HBFP_WIDE_STAGE(MODE)                                                                                  \
+    // A stage is kSteps k-steps; the fragments of its first were requested during the stage before.  The hand-over, in its last: this
+    // wave has its last fragments of the stage, and its copies of the next stage have landed when only those of the AFTER stages
+    // behind it are in flight; after the barrier that holds for everybody, and the stage's own buffer takes the copies of stage
+    // st + RING (COPY).  LAST: nothing follows.
+#define HBFP_WIDE_STAGE(AFTER, COPY, LAST)                                                                     \
     {                                                                                                         \
         const uint8_t *base = lds + ring * W::kStage;                                                        \
-        const int next = (ring + 1) & 3, free_ring = (ring + 3) & 3;                                          \
-        HBFP_WIDE_KSTEP(0, true, base, 1, false, 0);                                                          \
-        if (MODE != 3) {                                                                                      \
-            if (MODE != 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(W::kCopies) : "memory");                 \
-            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                                             \
-            __builtin_amdgcn_s_barrier();                                                                     \
-            asm volatile("" ::: "memory");                                                                    \
-        }                                                                                                     \
-        HBFP_WIDE_KSTEP(1, MODE != 3, lds + next * W::kStage, 0, MODE == 0, free_ring);                      \
+        const int next = ring + 1 == RING ? 0 : ring + 1;                                                 \
+        _Pragma("unroll") for (int s_ = 0; s_ < W::kSteps - 1; ++s_)                                          \
+            HBFP_WIDE_KSTEP(s_ & 1, true, base, s_ + 1, {}, false);                                           \
+        HBFP_WIDE_KSTEP(1, !(LAST), lds + next * W::kStage, 0, {                                              \
+            if (!(LAST)) {                                                                                    \
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((AFTER) * W::kCopies) : "memory");        \
+                __builtin_amdgcn_s_barrier();                                                                 \
+                asm volatile("" ::: "memory");                                                                \
+            }                                                                                                 \
+        }, COPY);                                                                                             \
         ring = next;                                                                                          \
     }
 
-    // prologue: stages 0..2 on their way (the contraction has at least two stages), fragments of k-step 0
+    // prologue: two stages on their way; those behind them are requested when the first has landed, or it would wait for its share
+    // of what all compute units ask for at once (RING x 32 KB each); then the fragments of k-step 0
     HBFP_WIDE_COPY_STAGE(0);
-    HBFP_WIDE_COPY_STAGE(1);
-    if (nstage > 2) {
-        HBFP_WIDE_COPY_STAGE(2);
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * W::kCopies) : "memory");
-    } else {
+    if (nstage > 1) {
+        HBFP_WIDE_COPY_STAGE(1);
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(W::kCopies) : "memory");
+    } else {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+    if (RING > 2 && nstage > 2) HBFP_WIDE_COPY_STAGE(2);
+    if (RING > 3 && nstage > 3) HBFP_WIDE_COPY_STAGE(3);
 #pragma unroll
     for (int i = 0; i < T; ++i) HBFP_WIDE_READ(0, lds, 0, i);
     int ring = 0;
     int st = 0;
-    for (; st + 4 <= nstage; ++st) HBFP_WIDE_STAGE(0);     // stage st + 3 exists
-    if (nstage - st == 3) {
-        HBFP_WIDE_STAGE(1);
+    for (; st + RING < nstage; ++st) HBFP_WIDE_STAGE(RING - 2, true, false);
+    if (RING > 3 && nstage - st == 4) {
+        HBFP_WIDE_STAGE(2, false, false);
         ++st;
     }
-    HBFP_WIDE_STAGE(2);
-    HBFP_WIDE_STAGE(3);
+    if (RING > 2 && nstage - st == 3) {
+        HBFP_WIDE_STAGE(1, false, false);
+        ++st;
+    }
+    if (nstage - st == 2) HBFP_WIDE_STAGE(0, false, false);
+    HBFP_WIDE_STAGE(0, false, true);
 #undef HBFP_WIDE_STAGE
 #undef HBFP_WIDE_KSTEP
 #undef HBFP_WIDE_ROW
@@ -242,16 +255,17 @@ __global__ __launch_bounds__(256) void wide_sum_kernel(const WideParams p) {
     }
 }
 
-template <int T>
+template <int T, int K, int RING>
 int launch_wide_t(WideParams p, bool stream, hipStream_t s) {
     static std::atomic<bool> configured[2];
-    void (*const kernel)(WideParams) = stream ? &gemm_i8_wide_kernel<T, true> : &gemm_i8_wide_kernel<T, false>;
-    if (allow_dynamic_lds(configured[stream], reinterpret_cast<const void *>(kernel), Wide<T>::kLds) != HBFP_OK) return HBFP_ERR_LAUNCH;
-    p.tiles_m = (int32_t)ceil_div(p.M, Wide<T>::kRows);
-    p.tiles_n = (int32_t)ceil_div(p.N, Wide<T>::kRows);
+    constexpr int lds_bytes = Wide<T, K, RING>::kLds;
+    void (*const kernel)(WideParams) = stream ? &gemm_i8_wide_kernel<T, K, RING, true> : &gemm_i8_wide_kernel<T, K, RING, false>;
+    if (allow_dynamic_lds(configured[stream], reinterpret_cast<const void *>(kernel), lds_bytes) != HBFP_OK) return HBFP_ERR_LAUNCH;
+    p.nstage *= 128 / K;
+    p.stages_per_split *= 128 / K;
     const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
     const dim3 grid = p.splits >= 8 ? dim3((unsigned)(8 * tiles * ceil_div(p.splits, 8))) : dim3((unsigned)(ceil_div(tiles, 8) * 8), (unsigned)p.splits);
-    hipLaunchKernelGGL(kernel, grid, dim3(kWideThreads), Wide<T>::kLds, s, p);
+    hipLaunchKernelGGL(kernel, grid, dim3(kWideThreads), lds_bytes, s, p);
     return launch_status();
 }
 
@@ -290,7 +304,7 @@ WidePlan wide_plan(int64_t M, int64_t N, int64_t nstage, bool may_split) {
 // One exponent per operand row, 8-bit mantissas, rows of the stored operands addressable with 32-bit offsets
 bool gemm_wide_possible(const GemmArgs &a) {
     return !a.P && a.nblk == 1 && a.mA <= 8 && a.mB <= 8 && (uint64_t)255 * (uint64_t)a.kpad + 64 < ((uint64_t)1 << 32) &&
-           ceil_div(a.M, 128) * ceil_div(a.N, 128) <= 0x7ffffff0 && a.kpad / kWideK <= 0x7fffffff;
+           ceil_div(a.M, 128) * ceil_div(a.N, 128) <= 0x7ffffff0 && a.kpad / 64 <= 0x7fffffff;
 }
 
 // ... and a contraction longer than 64, or enough full tiles of 256 x 256 to fill the chip (below, the kernels of short blocks
@@ -304,12 +318,12 @@ bool gemm_wide_ok(const GemmArgs &a) {
 
 // slices of a product split along k; a stand-by launch is not split, nor one whose caller brought no room for them
 size_t gemm_wide_workspace(const GemmArgs &a) {
-    const WidePlan plan = wide_plan(a.M, a.N, a.kpad / kWideK, !a.run_a && !a.unsplit);
+    const WidePlan plan = wide_plan(a.M, a.N, a.kpad / 64, !a.run_a && !a.unsplit);
     return plan.splits > 1 ? (size_t)plan.splits * (size_t)a.M * (size_t)a.N * 4 : 0;
 }
 
 int launch_gemm_wide(const GemmArgs &a, void *workspace, hipStream_t s) {
-    const WidePlan plan = wide_plan(a.M, a.N, a.kpad / kWideK, !a.run_a && !a.unsplit);
+    const WidePlan plan = wide_plan(a.M, a.N, a.kpad / 64, !a.run_a && !a.unsplit);
     if (plan.splits > 1 && !workspace) return HBFP_ERR_WORKSPACE;
     WideParams p = {};
     p.A = (const uint8_t *)a.mantA;
@@ -324,9 +338,11 @@ int launch_gemm_wide(const GemmArgs &a, void *workspace, hipStream_t s) {
     p.eA_ld = a.expA_ld;
     p.eB_ld = a.expB_ld;
     p.ldc = a.ldc;
-    p.nstage = (int32_t)(a.kpad / kWideK);
-    p.stages_per_split = (int32_t)(ceil_div(p.nstage / 2, plan.splits) * 2);
+    p.nstage = (int32_t)(a.kpad / 128);                          // in stages of 128 bytes here
+    p.stages_per_split = (int32_t)ceil_div(p.nstage, plan.splits);
     p.splits = (int32_t)ceil_div(p.nstage, p.stages_per_split);
+    p.tiles_m = (int32_t)ceil_div(a.M, 64 * plan.T);
+    p.tiles_n = (int32_t)ceil_div(a.N, 64 * plan.T);
     p.beta = a.beta != 0.0f;
     p.exp_offset = -250 - a.mA - a.mB;
     p.run_a = a.run_a;
@@ -335,7 +351,17 @@ int launch_gemm_wide(const GemmArgs &a, void *workspace, hipStream_t s) {
     // conversions beside the product (conversions and product, streaming -> ordinary: 3001 x 600 x 2999 29.3 -> 26.9 us, 5000 x 1024 x
     // 4001 54.6 -> 54.1, 4100 x 1024 x 2501 38.9 -> 34.7, but 5000 x 1200 x 4001 60.5 -> 63.7, 3001 x 4500 x 2999 86.9 -> 88.4)
     const bool stream = a.kpad > 1024 || stores_stream(&a);
-    const int rc = plan.T == 2 ? launch_wide_t<2>(p, stream, s) : plan.T == 3 ? launch_wide_t<3>(p, stream, s) : launch_wide_t<4>(p, stream, s);
+    // Whole cache lines of 128 bytes a row halve the requests of 64: 3001 x 4500 x 2999 (T = 3) 58 -> 55 us, 8192^3 (T = 4) 465 -> 447.
+    // A ring of two such stages is enough where two workgroups share a compute unit and cover each other's waits (T = 2: 1826 x
+    // 3178 x 3145 31 -> 27, 5000 x 2000 x 1000 20.8 -> 19.5); one alone wants four (2048 x 4096 x 2048 25.9 -> 23.6).  But the first
+    // stage is then twice as much to wait for, 0.7 us: contractions up to 2048 keep 64 bytes a row in a lone workgroup
+    // (1000^3 10.4 us, 11.2 with whole lines; 1024 x 2048 x 1024 10.3, 11.2).
+    const bool lone = (int64_t)p.tiles_m * p.tiles_n * p.splits <= 256;
+    const int rc = plan.T == 4                       ? launch_wide_t<4, 128, 2>(p, stream, s)
+                   : plan.T == 3                     ? launch_wide_t<3, 128, 3>(p, stream, s)
+                   : !lone                           ? launch_wide_t<2, 128, 2>(p, stream, s)
+                   : p.stages_per_split * 128 > 2048 ? launch_wide_t<2, 128, 4>(p, stream, s)
+                                                     : launch_wide_t<2, 64, 4>(p, stream, s);
     if (rc != HBFP_OK || p.splits == 1) return rc;
     const int64_t wgs = ceil_div(a.M * a.N, 1024);
     if (wgs > 0x7fffffff) return HBFP_ERR_ARG;

@@ -1119,6 +1119,21 @@ def test_wide_kernel_large_product_sampled(hb):
     _run(hb, A, B, (1, 0, 8, 0, 0), (0, 1, 8, 0, 0), partials=False, rows=rows, kernel=WIDE)
 
 
+@pytest.mark.parametrize("M,N,ks", [(3900, 4090, (100, 256, 300, 520)), (3001, 2999, (100, 256, 300, 400, 520)), (1826, 3145, (60, 256, 300, 520)),
+                                    (2040, 2000, (2100, 2304, 2400, 2600)), (500, 300, (2050, 2100, 2200, 2400, 2560))])
+def test_wide_kernel_every_tile_and_ring(hb, M, N, ks):
+    """Tiles of 256, 192 and 128, stages of 128 bytes in rings of two, three and four and of 64 bytes: contractions of 1 to 5 stages and
+    more.  The integer sums stay below 2^24, so the product of the converted values in FP64 is the result to the bit."""
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    for K in ks:
+        print(f"[case] wide {M}x{K}x{N}", flush=True)
+        A, B = torch.randn((M, K), device="cuda", generator=g), torch.randn((K, N), device="cuda", generator=g)
+        ta, tb = hb.encode(A, 1, hb.make_format(8, 1, 0)), hb.encode(B, 0, hb.make_format(8, 0, 1))
+        C = hb.gemm(ta, tb, kernel=WIDE)
+        want = hb.decode(ta).double() @ hb.decode(tb).double()
+        assert torch.equal(C.double(), want)
+
+
 @pytest.mark.parametrize("m,blk,kernel", [(8, 32, SCALED), (12, 64, SCALED), (8, 24, 0), (8, 32, 1)])
 def test_batch_of_products(hb, m, blk, kernel):
     """hbfp_gemm_batch: products of different shapes in one call (block-scaled kernel: one grouped launch; otherwise

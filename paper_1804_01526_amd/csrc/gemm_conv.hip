@@ -27,21 +27,23 @@ namespace {
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 constexpr int kStripThreads = 256;
-constexpr int kStripRows = 256;                  // output positions of a workgroup
-constexpr int kStripCols = 128;                  // filters of a workgroup
+constexpr int kStripUnit = 64;                   // output positions: 32 for each of the two waves along them
 constexpr int kStripLds = 80 * 1024;             // two workgroups per compute unit
+constexpr int strip_units_most(int nt) { return nt == 2 ? 4 : 3; }
 
 struct StripParams {
     const uint8_t *img, *eimg;   // int8 mantissas [pixels][pix_bytes], exponent bytes [pixels][eimg_ld], a stored block of 32 bytes each
     const uint8_t *panels;       // filters as bf16: [32 filters][step][lane][8 values]
     float *C;
     int64_t pix_bytes, eimg_ld, ldc, M, N;
+    float inv_wo, inv_ho;        // 1 / Wo, 1 / Ho
     int32_t H, W, Ho, Wo, S, taps, pad_h, pad_w, str_h, str_w, pixels;
-    int32_t ncb, octets;         // stored blocks per pixel, 8-channel pieces of a block
+    int32_t ncb;                 // stored blocks per pixel
     int32_t steps;               // matrix instructions' steps of 16 of a whole contraction
     int32_t tail;                // pixels of the strip behind the last position's corner
     int32_t zero_at;             // LDS offset of the pixel of zeros
-    int32_t tiles_m, tiles_n, beta, m;
+    int32_t units, slots, tiles_n;   // units of 64 positions; workgroups per XCD along them and, times tiles_n, in all
+    int32_t beta, m;
     MxOut enc;                   // ENC only
 };
 
@@ -50,26 +52,19 @@ struct StripPanels {
     const uint8_t *mant, *exps;
     uint8_t *out;
     int64_t kpad, exp_ld, N;
-    int32_t ncb, octets, taps, by_block, m, steps, full, last;   // full, last: steps per tap of a chunk of two blocks, of the last chunk
-    int32_t tiles;
+    int32_t ncb, octets, taps, by_block, m, steps, tiles;
 };
 __global__ __launch_bounds__(256) void strip_panels_kernel(const StripPanels p) {
     const int lane = threadIdx.x & 63;
     const int64_t piece = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int nt = (int)(piece / p.steps), step = (int)(piece % p.steps);
     if (nt >= p.tiles) return;
-    const int per_chunk = p.taps * p.full;
-    int chunk = step / per_chunk, rest = step % per_chunk, per_tap = p.full;
-    if (2 * chunk + 1 >= p.ncb || chunk * 2 >= p.ncb) {                          // the last chunk holds one block
-        chunk = p.ncb / 2;
-        rest = step - chunk * per_chunk;
-        per_tap = p.last;
-    }
-    const int tap = rest / per_tap, oct = 2 * (rest % per_tap) + (lane >> 5);
+    const int per_chunk = p.taps * p.octets, chunk = step / per_chunk, rest = step % per_chunk;
+    const int tap = rest / p.octets, oct = 2 * (rest % p.octets) + (lane >> 5);
     const int cb = 2 * chunk + oct / p.octets, in_block = oct % p.octets;
     const int64_t f = (int64_t)nt * 32 + (lane & 31);
     v4u v = {0, 0, 0, 0};
-    if (f < p.N && oct < 2 * p.octets && cb < p.ncb) {
+    if (f < p.N && cb < p.ncb) {                                                  // (an odd number of blocks is filled up with zeros)
         const int64_t slot = p.by_block ? (int64_t)cb * p.taps + tap : (int64_t)tap * p.ncb + cb;
         const int e = p.exps[f * p.exp_ld + slot];
         v = bf_octet_i8(*reinterpret_cast<const v2i *>(p.mant + f * p.kpad + slot * 32 + in_block * 8), e > 254 ? 254 : e, p.m);
@@ -77,184 +72,271 @@ __global__ __launch_bounds__(256) void strip_panels_kernel(const StripPanels p) 
     *reinterpret_cast<v4u *>(p.out + piece * 1024 + lane * 16) = v;
 }
 
-// KS: steps of 16 per tap of a chunk (two blocks of 8 KS channels); ENC: the product leaves as the next layer's image
-template <int KS, bool ENC, bool STREAM>
-__global__ __launch_bounds__(kStripThreads, 2) void gemm_strip_kernel(const StripParams p) {
-    constexpr int MT = 4, NT = 2;
-    constexpr int kPitch = KS * 32 + 16, kHalf = (KS + 1) / 2;
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    int tm, tn;
-    if (!tile_of_workgroup(blockIdx.x, p.tiles_m, p.tiles_n, tm, tn)) return;    // whole workgroup, before any barrier
+// 2^(biased - 127), subnormal for biased <= 0 (-22 at the least)
+__device__ __forceinline__ float strip_unit(int biased) { return __uint_as_float(biased > 0 ? (uint32_t)biased << 23 : 1u << (22 + biased)); }
+// an octet of int8 mantissas times the unit of their block as bf16 numbers (exact: at most 7 significant bits)
+__device__ __forceinline__ v4u strip_octet(int w0, int w1, float unit) {
+    v4u out;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int w = (i < 2 ? w0 : w1) >> (16 * (i & 1));
+        const float lo = (float)(int8_t)w * unit, hi = (float)(int8_t)(w >> 8) * unit;
+        out[i] = __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+    }
+    return out;
+}
+
+// One wave's part of a workgroup: MT x NT results of 32 x 32 (MT: the workgroup's units, NT: column tiles of this wave).
+// row0: the workgroup's first position, i0: this wave's, tile0: its first column tile.
+template <int KS, int MT, int NT, bool ENC, bool STREAM>
+__device__ __forceinline__ void strip_wave(const StripParams &p, uint8_t *lds, int64_t row0, int wm, int tile0, bool idle) {
+    constexpr int kPitch = KS * 32 + 16;
     const int t = threadIdx.x, lane = t & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int wm = wave & 1, wn = wave >> 1;
     const int l32 = lane & 31, lh = lane >> 5;
-    const int64_t row0 = (int64_t)tm * kStripRows, col0 = (int64_t)tn * kStripCols;
 
-    // the input pixel under filter tap (0, 0) of an output position, and its row and column (which may lie outside)
-    const auto corner = [&](int64_t pos, int &cy, int &cx) {
-        const uint32_t per_img = (uint32_t)(p.Ho * p.Wo), i = (uint32_t)pos / per_img, rem = (uint32_t)pos % per_img;
-        cy = (int)(rem / (uint32_t)p.Wo) * p.str_h - p.pad_h;
-        cx = (int)(rem % (uint32_t)p.Wo) * p.str_w - p.pad_w;
-        return ((int)i * p.H + cy) * p.W + cx;
+    // the input pixel under filter tap (0, 0) of the output position `d` behind the workgroup's first, and its row and column (which may
+    // lie outside).  Divisions of small numbers in FP32: exact, the host keeps Wo and Ho below 2^20.
+    const uint32_t per_img = (uint32_t)(p.Ho * p.Wo), img0 = (uint32_t)row0 / per_img, rem0 = (uint32_t)row0 - img0 * per_img;
+    const int oy0 = (int)(rem0 / (uint32_t)p.Wo), ox0 = (int)rem0 - oy0 * p.Wo;
+    const auto corner = [&](int d, int &cy, int &cx) {
+        const int dy = (int)(((float)(ox0 + d) + 0.5f) * p.inv_wo), y = oy0 + dy, di = (int)(((float)y + 0.5f) * p.inv_ho);
+        cy = (y - di * p.Ho) * p.str_h - p.pad_h;
+        cx = (ox0 + d - dy * p.Wo) * p.str_w - p.pad_w;
+        return (((int)img0 + di) * p.H + cy) * p.W + cx;
     };
-    const int64_t last_row = (p.M < row0 + kStripRows ? p.M : row0 + kStripRows) - 1;
+    const int rows = (int)(p.M - row0 < MT * kStripUnit ? p.M - row0 : MT * kStripUnit);
     int y_, x_;
-    const int first = corner(row0, y_, x_), length = corner(last_row, y_, x_) - first + p.tail;
+    const int first = __builtin_amdgcn_readfirstlane(corner(0, y_, x_));
+    const int units = 4 * (__builtin_amdgcn_readfirstlane(corner(rows - 1, y_, x_)) - first + p.tail);
 
-    // this lane's rows: where they sit in the strip, and which taps meet the image there
+    // ---- strip: a unit is 16 bytes of a pixel, half a stored block; a thread has kUnits of them in flight
+    constexpr int kUnits = 5;
+    v4i raw[kUnits];
+    int e[kUnits];
+    const auto request = [&](int chunk, int u0) {
+#pragma unroll
+        for (int i = 0; i < kUnits; ++i) {
+            const int at = u0 + i * kStripThreads, u = at < units ? at : units - 1;   // (no branch: the loads leave together)
+            int px = first + (u >> 2);
+            px = px < 0 ? 0 : px >= p.pixels ? p.pixels - 1 : px;
+            raw[i] = *reinterpret_cast<const v4i *>(p.img + px * p.pix_bytes + chunk * 64 + (u & 3) * 16);
+            e[i] = p.eimg[px * p.eimg_ld + 2 * chunk + ((u >> 1) & 1)];
+        }
+    };
+    const auto convert = [&](int u0) {
+#pragma unroll
+        for (int i = 0; i < kUnits; ++i) {
+            const int u = u0 + i * kStripThreads, oct = 2 * (u & 1);             // of the block
+            uint8_t *dst = lds + (u >> 2) * kPitch + (((u >> 1) & 1) * KS + oct) * 16;
+            const float unit = strip_unit((e[i] > 254 ? 254 : e[i]) + 2 - p.m);
+            const v4u lo = strip_octet(raw[i][0], raw[i][1], unit), hi = strip_octet(raw[i][2], raw[i][3], unit);
+            if (u < units && oct < KS) *reinterpret_cast<v4u *>(dst) = lo;
+            if (u < units && oct + 1 < KS) *reinterpret_cast<v4u *>(dst + 16) = hi;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    request(0, t);
+
+    // this lane's rows: where they sit in the strip, and which taps meet the image there (while the first loads are on their way)
     int abase[MT];
     uint32_t amask[MT];
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
-        int64_t r = row0 + wm * 32 * MT + 32 * i + l32;
-        if (r > last_row) r = last_row;
+        const int d = wm * 32 * MT + 32 * i + l32;
         int cy, cx;
-        abase[i] = (corner(r, cy, cx) - first) * kPitch + lh * 16;
+        abase[i] = (corner(d < rows ? d : rows - 1, cy, cx) - first) * kPitch + lh * 16;
+        const int lo = cx < 0 ? -cx : 0, hi = p.W - cx < p.S ? p.W - cx : p.S;   // columns lo .. hi - 1 of the window
+        const uint32_t cols = hi > lo ? (0xffffffffu >> (32 - hi)) & ~((1u << lo) - 1u) : 0;
         amask[i] = 0;
-        for (int tap = 0, fr = 0, fs = 0; tap < p.taps; ++tap) {
-            if ((unsigned)(cy + fr) < (unsigned)p.H && (unsigned)(cx + fs) < (unsigned)p.W) amask[i] |= 1u << tap;
-            if (++fs == p.S) fs = 0, ++fr;
-        }
+        for (int fr = 0, at = 0; at < p.taps; ++fr, at += p.S)
+            if ((unsigned)(cy + fr) < (unsigned)p.H) amask[i] |= cols << at;
     }
     const int zero = p.zero_at + lh * 16;
     if (t < kPitch / 16) *reinterpret_cast<v4u *>(lds + p.zero_at + t * 16) = v4u{0, 0, 0, 0};
 
-    v16f acc[MT / 2][2][NT];
+    // filters: a tile past the last column re-reads the last one (its products are not stored); the loads are bounded by the buffer
+    const int tiles32 = (int)((p.N + 31) / 32), taps = idle ? 0 : p.taps;
+    const __amdgpu_buffer_rsrc_t panels = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.panels), 0, (tiles32 * p.steps + 4) * 1024, 0x00020000);
+    int pb[NT];
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+    for (int j = 0; j < NT; ++j) pb[j] = (tile0 + j < tiles32 ? tile0 + j : tiles32 - 1) * p.steps * 1024;
+    const auto filters = [&](int at) { return __builtin_bit_cast(v8bf, __builtin_amdgcn_raw_buffer_load_b128(panels, lane * 16, at, 0)); };
+
+    constexpr int kAcc = ENC ? (MT + 1) / 2 * 2 : MT;                            // (the encoding takes two row tiles at a time)
+    v16f acc[kAcc][NT];
+#pragma unroll
+    for (int i = 0; i < kAcc; ++i)
 #pragma unroll
         for (int j = 0; j < NT; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i / 2][i % 2][j][v] = 0.0f;
-
-    // filters: tiles 4 tn + 2 wn and the next; a tile past the last column re-reads the last one (never stored)
-    const int tiles32 = (int)((p.N + 31) / 32);
-    const uint8_t *pb[NT];
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-        const int nt = 4 * tn + NT * wn + j;
-        pb[j] = p.panels + (int64_t)(nt < tiles32 ? nt : tiles32 - 1) * p.steps * 1024;
-    }
-    const uint32_t lane16 = lane * 16;
-    const int taps = col0 + 64 * wn < p.N ? p.taps : 0;                          // uniform; 0: this wave has no column to compute
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
     const int chunks = (p.ncb + 1) / 2;
-    const int units = length * 4;
     for (int chunk = 0; chunk < chunks; ++chunk) {
-        // ---- strip: a unit is 16 bytes of a pixel, half a stored block
-        for (int u0 = t; u0 - t < units; u0 += 4 * kStripThreads) {
-            v4i raw[4];
-            int e[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int u = u0 + i * kStripThreads;
-                int px = first + (u >> 2);
-                px = px < 0 ? 0 : px >= p.pixels ? p.pixels - 1 : px;
-                if (u < units) {
-                    raw[i] = *reinterpret_cast<const v4i *>(p.img + px * p.pix_bytes + chunk * 64 + (u & 3) * 16);
-                    e[i] = p.eimg[px * p.eimg_ld + 2 * chunk + ((u >> 1) & 1)];
-                }
-            }
-            if (u0 == t && chunk) __syncthreads();                               // everybody has read the chunk before
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int u = u0 + i * kStripThreads;
-                if (u < units) {
-                    const int oct = 2 * (u & 1);                                 // of the block
-                    uint8_t *dst = lds + (u >> 2) * kPitch + (((u >> 1) & 1) * p.octets + oct) * 16;
-                    const int eb = e[i] > 254 ? 254 : e[i];
-                    if (oct < p.octets) *reinterpret_cast<v4u *>(dst) = bf_octet_i8(v2i{raw[i][0], raw[i][1]}, eb, p.m);
-                    if (oct + 1 < p.octets) *reinterpret_cast<v4u *>(dst + 16) = bf_octet_i8(v2i{raw[i][2], raw[i][3]}, eb, p.m);
-                }
-            }
+        if (chunk) {
+            request(chunk, t);
+            __syncthreads();                                                     // everybody has read the chunk before
+        }
+        convert(t);
+        for (int u0 = t + kUnits * kStripThreads; u0 - t < units; u0 += kUnits * kStripThreads) {
+            request(chunk, u0);
+            convert(u0);
         }
         // ---- the taps of the window
-        const bool full = 2 * chunk + 1 < p.ncb;                                 // two blocks, or the last one alone
-        const int bytes = (full ? KS : kHalf) * 1024;                            // of a filter tile and tap
         v8bf b[KS][NT];
 #pragma unroll
         for (int s = 0; s < KS; ++s)
 #pragma unroll
-            for (int j = 0; j < NT; ++j) b[s][j] = *reinterpret_cast<const v8bf *>(pb[j] + s * 1024 + lane16);
+            for (int j = 0; j < NT; ++j) b[s][j] = filters(pb[j] + s * 1024);
         __syncthreads();
-        int fr = 0, fs = 0;
+        // Fragments of A are requested one step ahead, each into the registers that its matrix instructions have just read: the
+        // others of the step pass before it is used.  The compiler would request it right in front of its use.
+        int fr = 0, fs = 0, off = 0;
+        int pa[MT];
+        v8bf a[MT];
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            pa[i] = amask[i] & 1 ? abase[i] : zero;
+            a[i] = *reinterpret_cast<const v8bf *>(lds + pa[i]);
+        }
         for (int tap = 0; tap < taps; ++tap) {
-            const int off = (fr * p.W + fs) * kPitch;
-            if (++fs == p.S) fs = 0, ++fr;
-            int pa[MT];
+            off += kPitch;
+            if (++fs == p.S) fs = 0, ++fr, off = fr * p.W * kPitch;
+            const uint32_t bit = tap + 1 < taps ? 2u << tap : 0u;                // of the next tap
 #pragma unroll
-            for (int i = 0; i < MT; ++i) pa[i] = (amask[i] >> tap) & 1 ? abase[i] + off : zero;
-#pragma unroll
-            for (int j = 0; j < NT; ++j) pb[j] += bytes;
+            for (int j = 0; j < NT; ++j) pb[j] += KS * 1024;
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
-                if (s >= kHalf && !full) break;
-                v8bf a[MT];
 #pragma unroll
-                for (int i = 0; i < MT; ++i) a[i] = *reinterpret_cast<const v8bf *>(lds + pa[i] + s * 32);
-#pragma unroll
-                for (int i = 0; i < MT; ++i)
+                for (int i = 0; i < MT; ++i) {
 #pragma unroll
                     for (int j = 0; j < NT; ++j)
-                        acc[i / 2][i % 2][j] = ENC ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[s][j], a[i], acc[i / 2][i % 2][j], 0, 0, 0)
-                                                   : __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[s][j], acc[i / 2][i % 2][j], 0, 0, 0);
+                        acc[i][j] = ENC ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[s][j], a[i], acc[i][j], 0, 0, 0)
+                                        : __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[s][j], acc[i][j], 0, 0, 0);
+                    if (s == KS - 1) pa[i] = amask[i] & bit ? abase[i] + off : zero;
+                    a[i] = *reinterpret_cast<const v8bf *>(lds + pa[i] + (s + 1) % KS * 32);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
 #pragma unroll
-                for (int j = 0; j < NT; ++j)                                     // of the next tap; behind the last one not used
-                    b[s][j] = *reinterpret_cast<const v8bf *>(pb[j] + s * 1024 + lane16);
+                for (int j = 0; j < NT; ++j) b[s][j] = filters(pb[j] + s * 1024);   // of the next tap; behind the last one not used
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
     }
 
-    const int64_t i0 = row0 + wm * 32 * MT, j0 = col0 + wn * 32 * NT;
-    if (ENC) {
+    const int64_t i0 = row0 + wm * 32 * MT, j0 = (int64_t)tile0 * 32;
+    const int64_t end = p.M < i0 + 32 * MT ? p.M : i0 + 32 * MT;
+    if constexpr (ENC) {
+        static_assert(NT == 2, "two column tiles at a time");
 #pragma unroll
-        for (int h = 0; h < MT / 2; ++h) {
-            if (p.enc.rounding) mx_store_encoded<1, NT>(p.enc, acc[h], i0 + 64 * h, j0, p.M, p.N, lane);
-            else mx_store_encoded<0, NT>(p.enc, acc[h], i0 + 64 * h, j0, p.M, p.N, lane);
+        for (int h = 0; h < MT; h += 2) {
+            v16f(&two)[2][NT] = *reinterpret_cast<v16f(*)[2][NT]>(&acc[h]);
+            if (p.enc.rounding) mx_store_encoded<1, NT>(p.enc, two, i0 + 32 * h, j0, end, p.N, lane);
+            else mx_store_encoded<0, NT>(p.enc, two, i0 + 32 * h, j0, end, p.N, lane);
         }
-        return;
+    } else if (!idle) {
+        store_result<MT, NT, STREAM>(p.C + i0 * p.ldc + j0, p.ldc, end - i0, p.N - j0, p.beta != 0, lane, [&](int i, int j, int v) { return acc[i][j][v]; });
     }
-    store_result<MT, NT, STREAM>(p.C + i0 * p.ldc + j0, p.ldc, p.M - i0, p.N - j0, p.beta != 0, lane,
-                                 [&](int i, int j, int v) { return acc[i / 2][i % 2][j][v]; });
+}
+
+// KS: steps of 16 per tap of a chunk (two blocks of 8 KS channels); NT: column tiles of a wave at most; ENC: the product leaves as the
+// next layer's image.  The code of every number of units and of column tiles is its own: with tests inside the loops the
+// accumulators did not stay in their registers.
+template <int KS, int NT, bool ENC, bool STREAM>
+__global__ __launch_bounds__(kStripThreads, 2) void gemm_strip_kernel(const StripParams p) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    // Every XCD gets an eighth of the units and deals them to its slots; two workgroups that meet on a compute unit are 32 places
+    // apart, so that the larger shares, which come first, meet smaller ones.
+    const int xcd = blockIdx.x & 7, place = blockIdx.x >> 3;
+    const int slot = place / p.tiles_n, tn = place - slot * p.tiles_n;
+    const int from = (int)((int64_t)p.units * xcd / 8), share = (int)((int64_t)p.units * (xcd + 1) / 8) - from;
+    const int base = share / p.slots, more = share - base * p.slots;
+    const int mt = base + (slot < more ? 1 : 0);                                 // this workgroup's units
+    const int64_t row0 = (int64_t)(from + base * slot + (slot < more ? slot : more)) * kStripUnit;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int wm = wave & 1, wn = (wave >> 1) ^ ((place >> 5) & 1);              // (the other way round 32 places on: the same SIMDs)
+    // the column tiles that hold filters, half of them for either wave (ENC: NT for the first)
+    const int tiles32 = (int)((p.N + 31) / 32), here = tiles32 - 2 * NT * tn < 2 * NT ? tiles32 - 2 * NT * tn : 2 * NT;
+    const int split = ENC ? NT : (here + 1) / 2;
+    const int tile0 = 2 * NT * tn + wn * split;
+    const bool idle = here <= wn * split;                                        // this wave has no column to compute
+    if constexpr (NT == 2) {
+        if (mt == 4) strip_wave<KS, 4, NT, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
+        else if (mt == 3) strip_wave<KS, 3, NT, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
+        else if (mt == 2) strip_wave<KS, 2, NT, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
+        else if (mt == 1) strip_wave<KS, 1, NT, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
+    } else {
+        const bool narrow = wn == 1 && here - split < NT;                        // (the barriers of both kinds of wave are the same)
+        if (mt == 3) {
+            if (narrow) strip_wave<KS, 3, NT - 1, false, STREAM>(p, lds, row0, wm, tile0, idle);
+            else strip_wave<KS, 3, NT, false, STREAM>(p, lds, row0, wm, tile0, idle);
+        } else if (mt == 2) {
+            if (narrow) strip_wave<KS, 2, NT - 1, false, STREAM>(p, lds, row0, wm, tile0, idle);
+            else strip_wave<KS, 2, NT, false, STREAM>(p, lds, row0, wm, tile0, idle);
+        } else if (mt == 1) {
+            if (narrow) strip_wave<KS, 1, NT - 1, false, STREAM>(p, lds, row0, wm, tile0, idle);
+            else strip_wave<KS, 1, NT, false, STREAM>(p, lds, row0, wm, tile0, idle);
+        }
+    }
 }
 
 // pixels that the strip of any workgroup holds at most: from the corner of its first position to the far corner of its last.
 // Between neighbouring positions the corner moves by the stride, by more at the end of a row and of an image.
-int64_t strip_pixels(const hbfp_conv2d &c, int64_t ho, int64_t wo) {
+int64_t strip_pixels(const hbfp_conv2d &c, int64_t ho, int64_t wo, int64_t rows) {
     const int64_t per_row = c.stride_h * (int64_t)c.w - wo * c.stride_w, per_img = (c.h - ho * c.stride_h) * c.w;
-    return (kStripRows - 1) * (int64_t)c.stride_w + ceil_div(kStripRows - 1, wo) * (per_row > 0 ? per_row : 0) +
-           ceil_div(kStripRows - 1, ho * wo) * (per_img > 0 ? per_img : 0) + (int64_t)(c.r - 1) * c.w + c.s;
+    return (rows - 1) * (int64_t)c.stride_w + ceil_div(rows - 1, wo) * (per_row > 0 ? per_row : 0) +
+           ceil_div(rows - 1, ho * wo) * (per_img > 0 ? per_img : 0) + (int64_t)(c.r - 1) * c.w + c.s;
 }
 
-template <int KS, bool ENC>
+template <int KS, int NT, bool ENC>
 int launch_strip_t(const StripParams &p, bool stream, int lds_bytes, hipStream_t s) {
     static std::atomic<bool> configured[2];
-    void (*const kernel)(StripParams) = stream ? &gemm_strip_kernel<KS, ENC, true> : &gemm_strip_kernel<KS, ENC, false>;
+    void (*const kernel)(StripParams) = stream ? &gemm_strip_kernel<KS, NT, ENC, true> : &gemm_strip_kernel<KS, NT, ENC, ENC>;
     if (allow_dynamic_lds(configured[stream], reinterpret_cast<const void *>(kernel), kStripLds) != HBFP_OK) return HBFP_ERR_LAUNCH;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(ceil_div((int64_t)p.tiles_m * p.tiles_n, 8) * 8)), dim3(kStripThreads), lds_bytes, s, p);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * p.slots * p.tiles_n)), dim3(kStripThreads), lds_bytes, s, p);
     return launch_status();
 }
 
-int strip_steps(int64_t ncb, int64_t kblock, int64_t taps) {
-    const int64_t full = kblock / 8, last = (full + 1) / 2;      // steps of 16 per tap of two blocks, of one
-    return (int)(taps * (ncb / 2 * full + ncb % 2 * last));
+// How the output is dealt: column tiles of 128 or 192 filters, whichever computes fewer columns that do not exist, and as many
+// workgroups as fill 2 x 32 places of every XCD, once or as often as it takes with at most 256 (192) positions each.
+struct StripPlan {
+    int nt, tiles_n, units, slots;
+};
+StripPlan strip_plan(int64_t M, int64_t N, bool enc) {
+    StripPlan q;
+    const int64_t two = ceil_div(N, 128) * 128, three = ceil_div(N, 192) * 192;
+    q.nt = enc || two <= three ? 2 : 3;
+    q.tiles_n = (int)ceil_div(N, 64 * q.nt);
+    q.units = (int)ceil_div(M, kStripUnit);
+    const int64_t share = ceil_div(q.units, 8);
+    for (int64_t rounds = 1;; ++rounds) {
+        const int64_t slots = 64 * rounds / q.tiles_n;
+        if (slots < 1 || ceil_div(share, slots) > strip_units_most(q.nt)) continue;
+        q.slots = (int)(slots < share ? slots : share);
+        return q;
+    }
 }
+
+// steps of 16: kblock / 8 per tap of two blocks
+int strip_steps(int64_t ncb, int64_t kblock, int64_t taps) { return (int)(taps * ((ncb + 1) / 2) * (kblock / 8)); }
 
 }  // namespace
 
 // Whether the convolution runs on this kernel (a: as for launch_gemm_conv_i8; room: bytes of workspace, which holds the panels)
-bool gemm_strip_ok(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64_t wo, int kblock, size_t room) {
+bool gemm_strip_ok(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64_t wo, int kblock, bool enc, size_t room) {
     const int64_t taps = (int64_t)c.r * c.s;
-    if (kblock % 8 || kblock > 32 || c.c % kblock || taps > 32 || taps < 2) return false;
+    if ((kblock != 24 && kblock != 32) || c.c % kblock || taps > 32 || taps < 2) return false;
     // corners in increasing order, positions within one window of their input
+    if (ho >= (1 << 20) || wo >= (1 << 20)) return false;
     if (2 * c.pad_h > c.r - 1 || 2 * c.pad_w > c.s - 1) return false;
-    const int64_t pitch = kblock / 8 * 32 + 16, pixels = strip_pixels(c, ho, wo);
+    if (a.M > 0x7fffffff || a.N > 0x7fffff) return false;
+    const StripPlan plan = strip_plan(a.M, a.N, enc);
+    const int64_t pitch = kblock / 8 * 32 + 16, pixels = strip_pixels(c, ho, wo, kStripUnit * strip_units_most(plan.nt));
     if ((pixels + 1) * pitch > kStripLds) return false;
     const int64_t steps = strip_steps(c.c / kblock, kblock, taps);
-    if (((size_t)ceil_div(a.N, 32) * steps + 4) * 1024 > room) return false;
-    const int64_t tiles = ceil_div(a.M, kStripRows) * ceil_div(a.N, kStripCols);
-    return tiles >= 128 && tiles <= 0x7ffffff0;
+    const size_t panels = ((size_t)ceil_div(a.N, 32) * steps + 4) * 1024;         // (addressed with 31 bits)
+    if (panels > room || panels > 0x7fffffff) return false;
+    return ceil_div(a.M, 256) * ceil_div(a.N, 128) >= 128 && (int64_t)plan.slots * plan.tiles_n <= 0x7ffffff;
 }
 
 int launch_gemm_strip(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64_t wo, int64_t pix_bytes, bool by_block, int kblock, void *workspace,
@@ -271,14 +353,13 @@ int launch_gemm_strip(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64
     q.taps = c.r * c.s;
     q.by_block = by_block;
     q.m = a.mB;
-    q.full = kblock / 8;
-    q.last = (q.full + 1) / 2;
     q.steps = strip_steps(q.ncb, kblock, q.taps);
     q.tiles = (int32_t)ceil_div(a.N, 32);
     hipLaunchKernelGGL(strip_panels_kernel, dim3((unsigned)ceil_div((int64_t)q.tiles * q.steps, 4)), dim3(256), 0, s, q);
     if (launch_status() != HBFP_OK) return HBFP_ERR_LAUNCH;
 
-    const int64_t pitch = kblock / 8 * 32 + 16, strip = strip_pixels(c, ho, wo);
+    const StripPlan plan = strip_plan(a.M, a.N, enc != nullptr);
+    const int64_t pitch = kblock / 8 * 32 + 16, strip = strip_pixels(c, ho, wo, kStripUnit * strip_units_most(plan.nt));
     StripParams p = {};
     p.img = (const uint8_t *)a.mantA;
     p.eimg = a.expA;
@@ -294,6 +375,8 @@ int launch_gemm_strip(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64
     p.Ho = (int32_t)ho;
     p.Wo = (int32_t)wo;
     p.S = c.s;
+    p.inv_wo = 1.0f / (float)wo;
+    p.inv_ho = 1.0f / (float)ho;
     p.taps = q.taps;
     p.pad_h = c.pad_h;
     p.pad_w = c.pad_w;
@@ -301,31 +384,22 @@ int launch_gemm_strip(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64
     p.str_w = c.stride_w;
     p.pixels = (int32_t)(c.n * c.h * c.w);
     p.ncb = q.ncb;
-    p.octets = q.octets;
     p.steps = q.steps;
     p.tail = (int32_t)((c.r - 1) * c.w + c.s);
     p.zero_at = (int32_t)(strip * pitch);
-    p.tiles_m = (int32_t)ceil_div(a.M, kStripRows);
-    p.tiles_n = (int32_t)ceil_div(a.N, kStripCols);
+    p.units = plan.units;
+    p.slots = plan.slots;
+    p.tiles_n = plan.tiles_n;
     p.beta = a.beta != 0.0f;
     p.m = a.mA;
     const int lds_bytes = (int)((strip + 1) * pitch);
     if (enc) {
         p.enc = mx_out_of(*enc, relu);
-        switch (kblock) {
-            case 8: return launch_strip_t<1, true>(p, true, lds_bytes, s);
-            case 16: return launch_strip_t<2, true>(p, true, lds_bytes, s);
-            case 24: return launch_strip_t<3, true>(p, true, lds_bytes, s);
-            default: return launch_strip_t<4, true>(p, true, lds_bytes, s);
-        }
+        return kblock == 24 ? launch_strip_t<3, 2, true>(p, true, lds_bytes, s) : launch_strip_t<4, 2, true>(p, true, lds_bytes, s);
     }
     const bool stream = stores_stream(&a);
-    switch (kblock) {
-        case 8: return launch_strip_t<1, false>(p, stream, lds_bytes, s);
-        case 16: return launch_strip_t<2, false>(p, stream, lds_bytes, s);
-        case 24: return launch_strip_t<3, false>(p, stream, lds_bytes, s);
-        default: return launch_strip_t<4, false>(p, stream, lds_bytes, s);
-    }
+    if (plan.nt == 3) return kblock == 24 ? launch_strip_t<3, 3, false>(p, stream, lds_bytes, s) : launch_strip_t<4, 3, false>(p, stream, lds_bytes, s);
+    return kblock == 24 ? launch_strip_t<3, 2, false>(p, stream, lds_bytes, s) : launch_strip_t<4, 2, false>(p, stream, lds_bytes, s);
 }
 
 }  // namespace hbfp

@@ -522,3 +522,31 @@ def test_conv_bfp_over_its_own_image(hb, n, h, w, c, r):
     hb.gemm_conv2d_bfp(img, conv, flt, act, relu=True, out=img)
     torch.cuda.synchronize()
     assert torch.equal(img.mant, want.mant) and torch.equal(img.exps, want.exps)
+
+
+@pytest.mark.parametrize("n,h,w,c,f,r,s,pad,stride,kb", [
+    (64, 23, 23, 64, 40, 3, 3, 1, 1, 32),            # two column tiles, a wave of one
+    (50, 26, 26, 48, 100, 3, 3, 1, 1, 24),           # blocks of 24, block by block along k
+    (30, 24, 24, 96, 160, 3, 3, 1, 1, 32),           # tiles of 192 filters, an odd number of channel blocks
+    (16, 33, 32, 72, 192, 3, 3, 1, 1, 24),           # whole tiles of 192
+    (130, 33, 31, 32, 128, 3, 3, 1, 2, 32),          # strided, a single channel block
+    (2100, 4, 4, 24, 33, 3, 3, 1, 1, 24),            # several images in a unit of 64 positions
+    (60, 25, 25, 64, 30, 2, 2, 0, 1, 32),            # no padding, fewer filters than a column tile
+    (45, 28, 27, 32, 128, 1, 5, 0, 1, 32),           # a window of one row
+])
+def test_conv_strips_against_the_lowered_product(hb, n, h, w, c, f, r, s, pad, stride, kb):
+    """Sizes at which the product runs from strips of the image on the bf16 instruction, against the int8 product on the lowered operand.
+    Values are small integers, so that every sum is exact in FP32 whatever its order: equal to the bit, delivered encoded too."""
+    g = torch.Generator(device="cuda").manual_seed(n + f)
+    x = torch.randint(-7, 8, (n, h, w, c), device="cuda", generator=g) * torch.randint(0, 3, (n, h, w, 1), device="cuda", generator=g)
+    wm = torch.randint(-7, 8, (r * s * c, f), device="cuda", generator=g).float()
+    conv = hb.Conv2d(n, h, w, c, r, s, pad, pad, stride, stride, kb if kb < 32 else 0, 0)
+    print(f"[conv] n={n} h={h} w={w} c={c} f={f} window {r}x{s} pad={pad} stride={stride} blocks of {kb}", flush=True)
+    img = hb.encode(x.float().view(n * h * w, c), 1, hb.make_format(8, 1, kb))
+    flt = hb.encode(wm, 0, hb.make_format(8, kb, 1))
+    low = hb.encode_im2col(x.float(), conv, hb.make_format(8, 1, kb))
+    y = hb.gemm_conv2d(img, conv, flt)
+    assert torch.equal(y, hb.gemm(low, flt, kernel=hb.KERNEL_INT8))
+    fmt = hb.make_format(8, 1, 32)
+    enc, want = hb.gemm_conv2d_bfp(img, conv, flt, fmt, relu=True), hb.encode(torch.relu(y), 1, fmt)
+    assert torch.equal(enc.mant, want.mant) and torch.equal(enc.exps, want.exps)

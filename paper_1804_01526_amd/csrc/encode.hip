@@ -471,6 +471,7 @@ struct ColParams {
     int32_t lanes;      // lanes of a wave that carry operand rows: the largest multiple of rblock <= 64
     int32_t narrow;     // a workgroup covers 1 / 2^narrow of the pieces that its LDS tile has room for (col_narrow)
     uint32_t row_groups;   // workgroups per group of blocks (the grid is flat: block group = blockIdx.x / row_groups)
+    uint32_t blk_groups8;  // CONV: groups of blocks per XCD; the grid is 8 times as many times row_groups
     uint32_t s0, s1;
     // TABLE (second pass of the two-pass conversion): the largest magnitude of every exponent block has been computed
     // already, table[(block / kshare) * ntc + row / rblock_t]; the kernel then walks stored pieces of KBP elements,
@@ -481,6 +482,8 @@ struct ColParams {
     // CONV: the source is an NHWC image tensor; operand row = (fr * S + fs) * C + ch of the lowered matrix, k = the
     // output position (img, oy, ox): the operand of the weight-gradient product, never materialised
     ConvGeom cv;
+    // corners 0 .. corner_last (element index) have every window entry inside the tensor (-1: no such rule)
+    int64_t corner_last;
 };
 
 constexpr int kColRowBytes = 512;   // bytes of one operand row in an LDS tile
@@ -514,6 +517,36 @@ __device__ __forceinline__ void conv_col_gather(const ColParams &p, uint32_t img
     }
 }
 
+// The same for the first LEN (at most 32) positions of a piece whose corners all lie where no window entry leaves the tensor: nearly all
+// pieces.  Every lane loads every position - a uniform base address and a constant offset, no vector instruction at all - and what
+// lies outside the image is cleared afterwards by a mask of the lane: one bit per position, made row by row of the output from the
+// lane's first and last column inside.  With the two checks, the branch and the address made per value (above) the conversion was
+// bound by its vector instructions: 64 x 28 x 28 x 128, 3 x 3, blocks of 24 45.8 -> 37.3 us (steps walked on the scalar unit
+// instead of by a lane per position cost 20 scalar instructions each: 52.8).
+template <int LEN, int KBP>
+__device__ __forceinline__ void conv_col_gather_inside(const ColParams &p, const float *corner, int corners, int y0, int oy, int ox, bool r_ok, int fr,
+                                                       uint32_t off_bytes, int ox_lo, int ox_hi, float (&v)[KBP]) {
+    static_assert(LEN <= 32 && LEN <= KBP, "one bit per position");
+    const __amdgpu_buffer_rsrc_t from = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(corner), 0, 0xffffffff, 0x00020000);
+#pragma unroll
+    for (int kk = 0; kk < LEN; ++kk)
+        v[kk] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(from, (int)off_bytes, __builtin_amdgcn_readlane(corners, kk), 0));
+    uint32_t inside = 0;
+    for (int at = 0; at < LEN;) {                                                         // rows of the output that the piece meets (uniform)
+        const int end = p.cv.Wo < ox + LEN - at ? p.cv.Wo : ox + LEN - at;
+        const int lo = ox_lo > ox ? ox_lo : ox, hi = ox_hi < end ? ox_hi : end;
+        if (hi > lo && (unsigned)(y0 + fr) < (unsigned)p.cv.H) inside |= (0xffffffffu >> (32 - (hi - lo))) << (at + lo - ox);
+        at += end - ox;
+        ox = 0, y0 += p.cv.str_h;
+        if (++oy == p.cv.Ho) oy = 0, y0 = -p.cv.pad_h;
+    }
+    if (!r_ok) inside = 0;
+#pragma unroll
+    for (int kk = 0; kk < LEN; ++kk) v[kk] = __uint_as_float(__float_as_uint(v[kk]) & (uint32_t)((int32_t)(inside << (31 - kk)) >> 31));
+#pragma unroll
+    for (int kk = LEN; kk < KBP; ++kk) v[kk] = 0.0f;
+}
+
 template <int KBP, bool WIDE, int ROUND, bool TABLE, bool CONV = false>
 __device__ __forceinline__ void enc_col_block(const ColParams p, const uint32_t wg) {
     constexpr int ESZ = WIDE ? 2 : 1;
@@ -524,15 +557,25 @@ __device__ __forceinline__ void enc_col_block(const ColParams p, const uint32_t 
 
     // the wave index as a scalar: block indices, block lengths and (CONV) output positions stay on the scalar unit
     const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
-    const int64_t r = (int64_t)(wg % p.row_groups) * p.lanes + lane;
+    // CONV: every XCD has an eighth of the positions and all row groups of them: a pixel enters one L2 instead of all eight (64 x 28 x 28
+    // x 144, 3 x 3: 54.6 -> 39.0 us; 128 channels 37.3 -> 34.6).  The price is a last wave of up to 7 idle groups of blocks.
+    const uint32_t row_group = CONV ? (wg >> 3) % p.row_groups : wg % p.row_groups;
+    const uint32_t blk_group = CONV ? (wg & 7) * p.blk_groups8 + (wg >> 3) / p.row_groups : wg / p.row_groups;
+    const int64_t r = (int64_t)row_group * p.lanes + lane;
     const int narrow = NBT > 4 ? p.narrow : 0;         // four pieces are one per wave, never cut further: a constant there
     const int nbt = NBT >> narrow;
-    const int64_t blk0 = (int64_t)(wg / p.row_groups) * nbt;
+    const int64_t blk0 = (int64_t)blk_group * nbt;
     const bool r_ok = lane < p.lanes && r < p.R;
     const int group0 = (lane / p.rblock) * p.rblock;   // first lane of this lane's 2-D tile
     int conv_fr = 0, conv_fs = 0, conv_ch = 0;          // CONV: this lane's filter tap and channel
     if (CONV) conv_window_entry(p.cv, r_ok ? (uint32_t)r : 0u, conv_fr, conv_fs, conv_ch);
     const int conv_off = CONV ? (conv_fr * p.cv.W + conv_fs) * p.cv.C + conv_ch : 0;    // of the lane's window entry from the corner
+    int ox_lo = 0, ox_hi = 0;                           // CONV: output columns at which it lies inside the image: ox_lo .. ox_hi - 1
+    if (CONV) {
+        const int lo = p.cv.pad_w - conv_fs + p.cv.str_w - 1, hi = p.cv.W - 1 + p.cv.pad_w - conv_fs;
+        ox_lo = lo < 0 ? 0 : p.cv.str_w == 1 ? lo : lo / p.cv.str_w;
+        ox_hi = hi < 0 ? 0 : (p.cv.str_w == 1 ? hi : hi / p.cv.str_w) + 1;
+    }
 
     for (int bi = wave; bi < nbt; bi += 4) {
         const int64_t piece = blk0 + bi;                                  // stored piece of KBP elements
@@ -557,7 +600,25 @@ __device__ __forceinline__ void enc_col_block(const ColParams p, const uint32_t 
             uint32_t img;
             int y0, x0, oy, ox;
             conv_position(p.cv, (uint32_t)kfirst, img, y0, x0, oy, ox);
-            if (blen == KBP) conv_col_gather<KBP, true>(p, img, y0, x0, oy, ox, blen, r_ok, conv_fr, conv_fs, conv_off, v);
+            // Pieces inside the tensor: lane kk works out the corner of position kk, in bytes from the first (the host keeps the
+            // distance within 30 bits; corners never move back, so the first and the last tell where all of them lie).
+            const int64_t first = (((int64_t)img * p.cv.H + y0) * p.cv.W + x0) * p.cv.C;
+            int64_t last = p.corner_last + 1;
+            int corners = 0;
+            if (KBP == 32 && first >= 0 && (blen == 32 || blen == 24)) {
+                uint32_t img1;
+                int y1, x1;
+                conv_position(p.cv, (uint32_t)kfirst + (uint32_t)(lane < blen ? lane : blen - 1), img1, y1, x1);
+                corners = (int)((((uint32_t)img1 - img) * p.cv.H + (uint32_t)(y1 - y0)) * p.cv.W + (uint32_t)(x1 - x0)) * p.cv.C;
+                last = first + __builtin_amdgcn_readlane(corners, 31);
+                corners *= 4;
+            }
+            if (KBP == 32 && last <= p.corner_last) {
+                constexpr int kFull = KBP == 32 ? 32 : 0, kShort = KBP == 32 ? 24 : 0;
+                const uint32_t off = (uint32_t)conv_off * 4u;
+                if (blen == 32) conv_col_gather_inside<kFull, KBP>(p, p.src + first, corners, y0, oy, ox, r_ok, conv_fr, off, ox_lo, ox_hi, v);
+                else conv_col_gather_inside<kShort, KBP>(p, p.src + first, corners, y0, oy, ox, r_ok, conv_fr, off, ox_lo, ox_hi, v);
+            } else if (blen == KBP) conv_col_gather<KBP, true>(p, img, y0, x0, oy, ox, blen, r_ok, conv_fr, conv_fs, conv_off, v);
             else conv_col_gather<KBP, false>(p, img, y0, x0, oy, ox, blen, r_ok, conv_fr, conv_fs, conv_off, v);
         }
         uint32_t amax = 0;
@@ -580,11 +641,13 @@ __device__ __forceinline__ void enc_col_block(const ColParams p, const uint32_t 
         uint8_t *out = tile + lane * kColStride + bi * KBP * ESZ;
 #pragma unroll
         for (int kk = 0; kk < KBP; kk += 8) {
-            int q[8];
+            int q[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+            if (!CONV || kk < blen) {                                         // uniform; behind the block's end: zeros
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const uint64_t idx = (uint64_t)(kfirst + kk + e) * (uint64_t)p.src_cols + (uint64_t)r;
-                q[e] = quantise<ROUND>(v[kk + e], Eb, p.m, (uint32_t)idx, (uint32_t)(idx >> 32), p.s0, p.s1);
+                for (int e = 0; e < 8; ++e) {
+                    const uint64_t idx = (uint64_t)(kfirst + kk + e) * (uint64_t)p.src_cols + (uint64_t)r;
+                    q[e] = quantise<ROUND>(v[kk + e], Eb, p.m, (uint32_t)idx, (uint32_t)(idx >> 32), p.s0, p.s1);
+                }
             }
             if (!WIDE) {
                 uint2 o;
@@ -611,7 +674,7 @@ __device__ __forceinline__ void enc_col_block(const ColParams p, const uint32_t 
     for (int pass = 0; pass < 8; ++pass) {
         if (pass >= (8 >> narrow)) break;                                  // uniform
         const int rl = (pass << (3 + narrow)) + (t >> (5 - narrow));
-        const int64_t rr = (int64_t)(wg % p.row_groups) * p.lanes + rl;
+        const int64_t rr = (int64_t)row_group * p.lanes + rl;
         if (rl < p.lanes && rr < p.R && piece * 16 < valid_bytes) {
             const uint4 d = *reinterpret_cast<const uint4 *>(tile + rl * kColStride + piece * 16);
             typedef unsigned v4u __attribute__((ext_vector_type(4)));
@@ -1404,15 +1467,23 @@ int launch_encode_im2col(const float *x, const hbfp_conv2d &c, int64_t ho, int64
         p.spb = 1;
         p.kshare = 1;
         p.cv = conv_geom(c, ho, wo);
+        // Pieces inside the tensor (conv_col_gather_inside): corners that never move back, 32 of them within 28 bits
+        const int64_t row = c.stride_h * c.w - (wo - 1) * c.stride_w, img = c.h * c.w - (ho - 1) * c.stride_h * c.w - (wo - 1) * c.stride_w;
+        const int64_t reach = ((c.r - 1) * c.w + c.s) * c.c - 1, most = (int64_t)1 << 23;
+        const bool forward = c.r <= 4096 && c.stride_h <= 4096 && c.stride_w <= 4096 && row >= 0 && img >= 0 && row * c.c < most &&
+                             img * c.c < most && (int64_t)c.stride_w * c.c < most && reach < ((int64_t)1 << 29);
+        p.corner_last = forward ? c.n * c.h * c.w * c.c - 1 - reach : -1;
         const bool wide = g.m > 8;
         const int nbt = kColRowBytes / ((int)g.kbp * (wide ? 2 : 1));
         const int64_t nb_cover = p.nb_stored > g.exp_ld ? p.nb_stored : g.exp_ld;
         const int64_t gx = ceil_div(g.R, 64);
         p.narrow = col_narrow(gx, nb_cover, nbt);
         const int64_t gy = ceil_div(nb_cover, nbt >> p.narrow);
-        if (gx > 0x7fffffff || gx * gy > 0x7fffffff) return HBFP_ERR_ARG;
+        const int64_t gy8 = ceil_div(gy, 8);
+        if (gx > 0x7fffffff || gx * gy > 0x7fffffff || gx * gy8 > 0x7fffffff / 8) return HBFP_ERR_ARG;
         p.row_groups = (uint32_t)gx;
-        const dim3 grid((unsigned)(gx * gy));
+        p.blk_groups8 = (uint32_t)gy8;
+        const dim3 grid((unsigned)(8 * gx * gy8));
         if (g.kbp == 32) launch_col_conv_k<32>(p, grid, wide, g.rounding, s);
         else if (g.kbp == 64) launch_col_conv_k<64>(p, grid, wide, g.rounding, s);
         else return HBFP_ERR_FORMAT;

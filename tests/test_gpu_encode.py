@@ -162,6 +162,32 @@ def test_encode_im2col_weight_gradient_orientation(hb, n, h, w, c, r, s, ph, pw,
     np.testing.assert_array_equal(mant, want.mant)
 
 
+@pytest.mark.parametrize("B,m,rounding", [(24, 8, 0), (32, 8, 0), (32, 8, 1), (24, 12, 0), (20, 8, 0)])
+@pytest.mark.parametrize("n,h,w,c,r,s,ph,pw,sh,sw", [
+    (5, 9, 7, 20, 3, 3, 1, 1, 1, 1),        # several rows and images in a piece of 24 or 32 positions
+    (3, 28, 28, 7, 3, 3, 1, 1, 1, 1),       # at most two rows in a piece
+    (2, 5, 70, 30, 3, 5, 1, 2, 1, 1),       # rows longer than two pieces
+    (4, 15, 16, 33, 3, 3, 1, 1, 2, 2),      # strided
+    (4, 9, 13, 18, 2, 3, 0, 1, 1, 3),       # strides that differ
+    (40, 3, 3, 11, 3, 3, 0, 0, 1, 1),       # a position per image
+    (6, 4, 4, 16, 3, 3, 3, 3, 1, 1),        # more padding than the window: corners move back
+    (3, 6, 6, 9, 2, 2, 0, 0, 3, 3),         # a stride beyond the window
+])
+def test_encode_im2col_pieces_inside_the_tensor(hb, n, h, w, c, r, s, ph, pw, sh, sw, B, m, rounding):
+    """The weight-gradient orientation where whole pieces of positions are loaded without a check per value, and where they are not, bit
+    for bit against the oracle's encode of the lowered matrix."""
+    rng = np.random.default_rng(n * h * w + c)
+    x = rng.standard_normal((n, h, w, c)).astype(np.float32)
+    conv = hb.Conv2d(n, h, w, c, r, s, ph, pw, sh, sw, 0, 0)
+    print(f"[case] im2col {n}x{h}x{w}x{c} window {r}x{s} pad ({ph},{pw}) stride ({sh},{sw}) B={B} m={m}", flush=True)
+    bt = hb.encode_im2col(torch.from_numpy(x).cuda(), conv, hb.make_format(m, B, 1, rounding, 0xBEEF), contract_axis=0)
+    torch.cuda.synchronize()
+    want = ref.encode(ref.im2col(x, r, s, ph, pw, sh, sw), B, 1, m, rounding, 0xBEEF)
+    mant, exps = unpack(bt)
+    np.testing.assert_array_equal(exps, want.exps)
+    np.testing.assert_array_equal(mant, want.mant)
+
+
 @pytest.mark.parametrize("n,h,w,c,r,s,ph,pw,sh,sw,slot,m,rounding", [
     (3, 9, 10, 16, 3, 3, 1, 1, 1, 1, 24, 8, 0), (2, 8, 7, 8, 3, 3, 1, 1, 1, 1, 24, 8, 1), (4, 12, 11, 40, 1, 1, 0, 0, 1, 1, 8, 12, 1),
     (2, 11, 13, 24, 5, 3, 2, 1, 2, 1, 64, 8, 0), (2, 15, 15, 32, 2, 2, 0, 0, 3, 3, 32, 8, 1), (70, 6, 6, 16, 3, 3, 1, 1, 1, 1, 16, 8, 0),

@@ -47,29 +47,28 @@ struct StripParams {
     MxOut enc;                   // ENC only
 };
 
-// filters -> panels.  A lane makes 8 values: filter 32 nt + lane % 32, channels 16 step + 8 (lane / 32) of the chunk.
+// Filters -> panels.  A lane makes 8 values: filter 32 tile + lane % 32, channels 16 step + 8 (lane / 32) of the chunk.  A workgroup has
+// one tap of a chunk and one column tile, a wave each of its steps: what it reads is known after one division of scalars.  Bound by
+// its latency; found out from a running number of the piece by four divisions of 64 bits it was 5.0 us at 1152 x 128 filters.
 struct StripPanels {
     const uint8_t *mant, *exps;
     uint8_t *out;
     int64_t kpad, exp_ld, N;
-    int32_t ncb, octets, taps, by_block, m, steps, tiles;
+    int32_t ncb, taps, by_block, m, steps;
 };
-__global__ __launch_bounds__(256) void strip_panels_kernel(const StripPanels p) {
-    const int lane = threadIdx.x & 63;
-    const int64_t piece = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int nt = (int)(piece / p.steps), step = (int)(piece % p.steps);
-    if (nt >= p.tiles) return;
-    const int per_chunk = p.taps * p.octets, chunk = step / per_chunk, rest = step % per_chunk;
-    const int tap = rest / p.octets, oct = 2 * (rest % p.octets) + (lane >> 5);
-    const int cb = 2 * chunk + oct / p.octets, in_block = oct % p.octets;
-    const int64_t f = (int64_t)nt * 32 + (lane & 31);
+template <int KS>
+__global__ __launch_bounds__(64 * KS) void strip_panels_kernel(const StripPanels p) {
+    const int lane = threadIdx.x & 63, step = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const uint32_t g = blockIdx.x, tile = blockIdx.y, chunk = g / (uint32_t)p.taps, tap = g - chunk * (uint32_t)p.taps;
+    const int oct = 2 * step + (lane >> 5), cb = 2 * (int)chunk + (oct >= KS ? 1 : 0), in_block = oct >= KS ? oct - KS : oct;
+    const int64_t f = (int64_t)tile * 32 + (lane & 31);
     v4u v = {0, 0, 0, 0};
     if (f < p.N && cb < p.ncb) {                                                  // (an odd number of blocks is filled up with zeros)
         const int64_t slot = p.by_block ? (int64_t)cb * p.taps + tap : (int64_t)tap * p.ncb + cb;
         const int e = p.exps[f * p.exp_ld + slot];
         v = bf_octet_i8(*reinterpret_cast<const v2i *>(p.mant + f * p.kpad + slot * 32 + in_block * 8), e > 254 ? 254 : e, p.m);
     }
-    *reinterpret_cast<v4u *>(p.out + piece * 1024 + lane * 16) = v;
+    *reinterpret_cast<v4u *>(p.out + ((int64_t)tile * p.steps + (int64_t)g * KS + step) * 1024 + lane * 16) = v;
 }
 
 // 2^(biased - 127), subnormal for biased <= 0 (-22 at the least)
@@ -329,7 +328,7 @@ bool gemm_strip_ok(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64_t 
     // corners in increasing order, positions within one window of their input
     if (ho >= (1 << 20) || wo >= (1 << 20)) return false;
     if (2 * c.pad_h > c.r - 1 || 2 * c.pad_w > c.s - 1) return false;
-    if (a.M > 0x7fffffff || a.N > 0x7fffff) return false;
+    if (a.M > 0x7fffffff || a.N > 32 * 65535) return false;        // (column tiles are the panel launch's blockIdx.y)
     const StripPlan plan = strip_plan(a.M, a.N, enc);
     const int64_t pitch = kblock / 8 * 32 + 16, pixels = strip_pixels(c, ho, wo, kStripUnit * strip_units_most(plan.nt));
     if ((pixels + 1) * pitch > kStripLds) return false;
@@ -349,13 +348,13 @@ int launch_gemm_strip(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64
     q.exp_ld = a.expB_ld;
     q.N = a.N;
     q.ncb = (int32_t)(c.c / kblock);
-    q.octets = kblock / 8;
     q.taps = c.r * c.s;
     q.by_block = by_block;
     q.m = a.mB;
     q.steps = strip_steps(q.ncb, kblock, q.taps);
-    q.tiles = (int32_t)ceil_div(a.N, 32);
-    hipLaunchKernelGGL(strip_panels_kernel, dim3((unsigned)ceil_div((int64_t)q.tiles * q.steps, 4)), dim3(256), 0, s, q);
+    const dim3 pieces((unsigned)(q.steps / (kblock / 8)), (unsigned)ceil_div(a.N, 32));
+    if (kblock == 24) hipLaunchKernelGGL(strip_panels_kernel<3>, pieces, dim3(192), 0, s, q);
+    else hipLaunchKernelGGL(strip_panels_kernel<4>, pieces, dim3(256), 0, s, q);
     if (launch_status() != HBFP_OK) return HBFP_ERR_LAUNCH;
 
     const StripPlan plan = strip_plan(a.M, a.N, enc != nullptr);

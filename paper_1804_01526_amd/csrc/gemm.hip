@@ -47,6 +47,7 @@ struct GemmParams {
     int32_t chain_limit;         // gemm_i8_w8_kernel<3>: most k-steps chained before their sum is scaled
     int32_t stages_per_split;
     int32_t splits;
+    int32_t tail_splits = 0, tail_stages = 0;   // the same of the last column of tiles where it is split less often (tail_split); 0: as the others
     int32_t tiles_m, tiles_n;
     int32_t beta;
     float final_scale;
@@ -526,12 +527,22 @@ __global__ __launch_bounds__(kW8Threads, 4) void gemm_i8_w8_kernel(const W8Param
         tiles_m = f.tiles_m, ph_nst = f.nst, ph_py = f.py, ph_px = f.px, ph_fr0 = f.fr0, ph_fs0 = f.fs0;
         M = (int64_t)q.ph.n * f.Hp * f.Wp;
     }
-    if (p.splits >= 8 && !PHASE ? !tile_and_split_of_workgroup(blockIdx.x, tiles_m, p.tiles_n, p.splits, tm, tn, split)
-                                : !tile_of_workgroup(blockIdx.x, tiles_m, p.tiles_n, tm, tn))
+    int wg = blockIdx.x, per_split = p.stages_per_split;
+    if (EB && p.tail_splits) {
+        // the last column of tiles behind the others, in ranges of its own
+        const int before = 8 * tiles_m * (p.tiles_n - 1) * ((p.splits + 7) >> 3);
+        if (wg >= before) {
+            wg -= before;
+            per_split = p.tail_stages;
+            if (!tile_and_split_of_workgroup(wg, tiles_m, 1, p.tail_splits, tm, tn, split)) return;
+            tn = p.tiles_n - 1;
+        } else if (!tile_and_split_of_workgroup(wg, tiles_m, p.tiles_n - 1, p.splits, tm, tn, split)) return;
+    } else if (p.splits >= 8 && !PHASE ? !tile_and_split_of_workgroup(wg, tiles_m, p.tiles_n, p.splits, tm, tn, split)
+                                       : !tile_of_workgroup(wg, tiles_m, p.tiles_n, tm, tn))
         return;                                                                  // whole workgroup, before any barrier
     const int64_t row0 = (int64_t)tm * BM, col0 = (int64_t)tn * BN;
-    const int st_begin = 2 * split * p.stages_per_split;                         // in 64-byte stages
-    int st_end = st_begin + 2 * p.stages_per_split;
+    const int st_begin = 2 * split * per_split;                                  // in 64-byte stages
+    int st_end = st_begin + 2 * per_split;
     if (st_end > 2 * p.nstage) st_end = 2 * p.nstage;
     if (PHASE) st_end = ph_nst;
     const int nst = st_end - st_begin;
@@ -996,8 +1007,8 @@ __global__ __launch_bounds__(kW8Threads, 4) void gemm_i8_w8_kernel(const W8Param
 // divisions and 4-byte loads had it at 7.4 us for 7 slices of 700 x 1500, 8 us for 4 of 1024^2).
 template <bool VEC>
 __global__ __launch_bounds__(kThreads) void splitk_reduce_kernel(const float *partial, float *C, int64_t M, int64_t N,
-                                                                  int64_t ldc, int splits, int beta, const int *run_a,
-                                                                  const int *run_b) {
+                                                                  int64_t ldc, int splits, int64_t tail_col, int tail_splits, int beta,
+                                                                  const int *run_a, const int *run_b) {
     if (stands_down(run_a, run_b)) return;
     constexpr int W = VEC ? 4 : 1;
     typedef float vec __attribute__((ext_vector_type(W)));
@@ -1006,8 +1017,9 @@ __global__ __launch_bounds__(kThreads) void splitk_reduce_kernel(const float *pa
         const int64_t i = n < ((int64_t)1 << 31) ? (int64_t)((uint32_t)e / (uint32_t)N) : e / N;
         float *out = C + i * ldc + (e - i * N);
         vec s = beta ? *reinterpret_cast<const vec *>(out) : vec(0.0f);
+        const int slices = e - i * N >= tail_col ? tail_splits : splits;
         int z = 0;
-        for (; z + 8 <= splits; z += 8) {
+        for (; z + 8 <= slices; z += 8) {
             vec t[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) t[u] = *reinterpret_cast<const vec *>(partial + (int64_t)(z + u) * n + e);
@@ -1017,10 +1029,10 @@ __global__ __launch_bounds__(kThreads) void splitk_reduce_kernel(const float *pa
         vec t[7];
 #pragma unroll
         for (int u = 0; u < 7; ++u)
-            if (z + u < splits) t[u] = *reinterpret_cast<const vec *>(partial + (int64_t)(z + u) * n + e);
+            if (z + u < slices) t[u] = *reinterpret_cast<const vec *>(partial + (int64_t)(z + u) * n + e);
 #pragma unroll
         for (int u = 0; u < 7; ++u)
-            if (z + u < splits) s += t[u];
+            if (z + u < slices) s += t[u];
         *reinterpret_cast<vec *>(out) = s;
     }
 }
@@ -1125,10 +1137,11 @@ int launch_splitk_reduce(const GemmParams &p, hipStream_t s) {
     // Few outputs: one per thread keeps more loads in flight (whole calls of 110 shapes, 2 to 72 slices: up to 0.8 us ahead below
     // 64 Ki outputs, level to 128 Ki, then four per thread: 191 672 outputs 24.1 -> 22.3 us, 364 700 43.7 -> 42.0, 1 Mi 51.5 -> 47.2).
     const bool vec = p.M * p.N >= 96 * 1024 && p.N % 4 == 0 && p.ldc % 4 == 0 && ((uintptr_t)p.C & 15) == 0;
+    const int64_t tail_col = p.tail_splits ? (p.tiles_n - 1) * (int64_t)BN : p.N;
     int64_t nb = ceil_div(p.M * p.N, kThreads * (vec ? 4 : 1));
     if (nb > 8192) nb = 8192;
-    if (vec) hipLaunchKernelGGL(splitk_reduce_kernel<true>, dim3((unsigned)nb), dim3(kThreads), 0, s, p.partial, p.C, p.M, p.N, p.ldc, p.splits, p.beta, p.run_a, p.run_b);
-    else hipLaunchKernelGGL(splitk_reduce_kernel<false>, dim3((unsigned)nb), dim3(kThreads), 0, s, p.partial, p.C, p.M, p.N, p.ldc, p.splits, p.beta, p.run_a, p.run_b);
+    if (vec) hipLaunchKernelGGL(splitk_reduce_kernel<true>, dim3((unsigned)nb), dim3(kThreads), 0, s, p.partial, p.C, p.M, p.N, p.ldc, p.splits, tail_col, p.tail_splits, p.beta, p.run_a, p.run_b);
+    else hipLaunchKernelGGL(splitk_reduce_kernel<false>, dim3((unsigned)nb), dim3(kThreads), 0, s, p.partial, p.C, p.M, p.N, p.ldc, p.splits, tail_col, p.tail_splits, p.beta, p.run_a, p.run_b);
     return launch_status();
 }
 
@@ -1574,6 +1587,22 @@ static void split_plan(const GemmArgs &a, int32_t *splits, int32_t *stages_per_s
     *splits = (int32_t)ceil_div(nstage, *stages_per_split);
 }
 
+// A last column of tiles with at most 64 columns, of a product with several k ranges on an XCD: half of its waves multiply, so its
+// workgroups come behind all others and meet one of those, or none, on their compute unit; range by range two whole ones met on some.
+// Where there are more workgroups than the 64 places of an XCD, the column is split into fewer ranges, at most half as long again: the
+// ones beyond the 64th started when the first were through (ranges twice as long: 2300 x 140 x 20000 36.5 -> 38.8 us).  With one
+// range on an XCD this is the order as it was.  Before -> behind: 1152 x 144 x 50176 in blocks of 24 56 -> 47.7 us, 432 x 144 x
+// 100000 46 -> 39, 1296 x 144 x 50176 59 -> 56, 1296 x 160 x 50176 72.6 -> 57.8, 1400 x 150 x 30000 in blocks of 32 40.7 -> 33.7,
+// 1024 x 160 x 50176 41.5 -> 35.8, 432 x 192 x 50176 31.6 -> 29.8, 900 x 190 x 30000 level.
+static void tail_split(GemmParams &p) {
+    const int64_t last = p.N - (int64_t)(p.tiles_n - 1) * BN, per = ceil_div(p.splits, 8);
+    if (per < 2 || p.tiles_n < 2 || last > 64) return;
+    const int64_t places = (64 - (int64_t)p.tiles_m * (p.tiles_n - 1) * per) / p.tiles_m;
+    if (3 * places < 2 * per) return;
+    p.tail_stages = places < per ? (int32_t)ceil_div(p.nstage, 8 * places) : p.stages_per_split;
+    p.tail_splits = (int32_t)ceil_div(p.nstage, p.tail_stages);
+}
+
 bool gemm_i8_standby_words(const GemmArgs &a, void *workspace, StandbyWords *w) {
     if (!workspace || a.P || a.mA > 8 || a.mB > 8 || !use_w8(a.kpad)) return false;
     if (a.wide ? gemm_wide_possible(a) : gemm_wide_ok(a)) return false;                  // that kernel reads exponent bytes itself
@@ -1669,7 +1698,10 @@ int launch_gemm_i8(const GemmArgs &a, void *workspace, hipStream_t s, const hbfp
                 hipLaunchKernelGGL((gemm_i8_w8_kernel<1, false, false, 0, true, true>), grid, dim3(kW8Threads), kW8LdsBytes, s, q);
                 return launch_status();
             }
-            if (bytes) hipLaunchKernelGGL((gemm_i8_w8_kernel<1, false, false, 0, false, true>), grid, dim3(kW8Threads), kW8LdsBytes, s, q);
+            if (bytes && !enc) tail_split(p);
+            q.g = p;
+            const unsigned wgs = p.tail_splits ? (unsigned)(8 * tm * ((tn - 1) * ceil_div(p.splits, 8) + ceil_div(p.tail_splits, 8))) : grid.x;
+            if (bytes) hipLaunchKernelGGL((gemm_i8_w8_kernel<1, false, false, 0, false, true>), dim3(wgs, grid.y), dim3(kW8Threads), kW8LdsBytes, s, q);
             else if (p.spb == 1) hipLaunchKernelGGL(gemm_i8_w8_kernel<1>, grid, dim3(kW8Threads), kW8LdsBytes, s, q);
             else if (p.spb == 2) hipLaunchKernelGGL(gemm_i8_w8_kernel<2>, grid, dim3(kW8Threads), kW8LdsBytes, s, q);
             else hipLaunchKernelGGL(gemm_i8_w8_kernel<0>, grid, dim3(kW8Threads), kW8LdsBytes, s, q);

@@ -1134,6 +1134,24 @@ def test_wide_kernel_every_tile_and_ring(hb, M, N, ks):
         assert torch.equal(C.double(), want)
 
 
+@pytest.mark.parametrize("M,K,N,blk,beta", [
+    (1296, 20000, 144, 24, 0.0),             # fewer ranges for the last column of tiles, a last row of tiles with 16 rows
+    (300, 30000, 150, 32, 1.0),              # C +=, rows off 16 bytes
+    (432, 24000, 192, 24, 0.0), (129, 30000, 129, 32, 0.0), (640, 40000, 300, 32, 0.0), (97, 9000, 33, 24, 1.0),
+    (700, 1500, 3000, 24, 0.0),              # unsplit, a last row of tiles with 60 rows
+])
+def test_last_columns_and_rows_of_tiles(hb, M, K, N, blk, beta):
+    """Last tiles of few columns, in k ranges of their own, and of few rows.  Values are small integers, so every sum is exact in FP32
+    whatever its order: equal to the bit."""
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    print(f"[case] {M}x{K}x{N} blocks of {blk} beta {beta}", flush=True)
+    A, B = (torch.randint(-7, 8, shape, device="cuda", generator=g).float() for shape in ((M, K), (K, N)))
+    ta, tb = hb.encode(A, 1, hb.make_format(8, 1, blk)), hb.encode(B, 0, hb.make_format(8, blk, 1))
+    C = torch.randint(-7, 8, (M, N), device="cuda", generator=g).float()
+    want = A.double() @ B.double() + (C.double() if beta else 0.0)
+    assert torch.equal(hb.gemm(ta, tb, out=C, beta=beta).double(), want)
+
+
 @pytest.mark.parametrize("m,blk,kernel", [(8, 32, SCALED), (12, 64, SCALED), (8, 24, 0), (8, 32, 1)])
 def test_batch_of_products(hb, m, blk, kernel):
     """hbfp_gemm_batch: products of different shapes in one call (block-scaled kernel: one grouped launch; otherwise

@@ -1592,7 +1592,7 @@ static void split_plan(const GemmArgs &a, int32_t *splits, int32_t *stages_per_s
 // Where there are more workgroups than the 64 places of an XCD, the column is split into fewer ranges, at most half as long again: the
 // ones beyond the 64th started when the first were through (ranges twice as long: 2300 x 140 x 20000 36.5 -> 38.8 us).  With one
 // range on an XCD this is the order as it was.  Before -> behind: 1152 x 144 x 50176 in blocks of 24 56 -> 47.7 us, 432 x 144 x
-// 100000 46 -> 39, 1296 x 144 x 50176 59 -> 56, 1296 x 160 x 50176 72.6 -> 57.8, 1400 x 150 x 30000 in blocks of 32 40.7 -> 33.7,
+// 100000 46 -> 39, 1296 x 144 x 50176 59 -> 57, 1296 x 160 x 50176 72.6 -> 57.8, 1400 x 150 x 30000 in blocks of 32 40.7 -> 33.7,
 // 1024 x 160 x 50176 41.5 -> 35.8, 432 x 192 x 50176 31.6 -> 29.8, 900 x 190 x 30000 level.
 static void tail_split(GemmParams &p) {
     const int64_t last = p.N - (int64_t)(p.tiles_n - 1) * BN, per = ceil_div(p.splits, 8);

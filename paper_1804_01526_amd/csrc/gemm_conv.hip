@@ -8,13 +8,18 @@
 // consecutive output positions and all taps of the window read the same pixels, so a workgroup converts the strip of image
 // that its 256 output positions meet once per 64 channels, and the r * s taps multiply from it.
 //
-// A workgroup of four waves computes 256 positions x 128 filters (each wave 128 x 64).  Per chunk of two stored channel blocks
+// A workgroup of four waves computes up to 256 positions x 128 filters, or 192 x 192 (each wave half of either).  Per chunk of two stored channel blocks
 // it reads the strip - pixels are consecutive in memory, whole rows of the image with what lies left and right of the window -
 // converts it to bf16 (3 instructions an element) and stores it in LDS as [pixel][channels] at a pitch of an odd number of 16 bytes, where the
 // fragments of 16 consecutive pixels cover all banks whatever the tap.  Fragments of positions whose tap lies outside the image
 // are read from a pixel of zeros.  The filters come as bf16 panels that a small kernel has laid out in the order in which they
 // are used; each wave loads its fragments straight from the caches (every one serves four matrix instructions), a tap
 // ahead.  One barrier before and one behind each strip; two workgroups per compute unit cover each other's conversions.
+// The int8 kernel -> this one, with the launch that lays out the panels: 128 x 28 x 28 x 128, 128 filters of 3 x 3 58 -> 32.2 us
+// (delivered encoded 62 -> 40), 64 x 28 x 28 x 144, 144 filters, blocks of 24 60 -> 31.8.  Its matrix instructions alone would take 13
+// and 11 us: all workgroups start together, store together (51 MB, 10 us) and wait for their first strip together.  Panels that go
+// through a ring in LDS, where two waves share a fragment, cost a barrier per tap and more than they save (38 and 40 us); a higher
+// priority for one of the two workgroups of a compute unit changes nothing.
 #include <atomic>
 
 #include "bf_pack.h"
@@ -49,7 +54,8 @@ struct StripParams {
 
 // Filters -> panels.  A lane makes 8 values: filter 32 tile + lane % 32, channels 16 step + 8 (lane / 32) of the chunk.  A workgroup has
 // one tap of a chunk and one column tile, a wave each of its steps: what it reads is known after one division of scalars.  Bound by
-// its latency; found out from a running number of the piece by four divisions of 64 bits it was 5.0 us at 1152 x 128 filters.
+// its latency; with four 64-bit divisions per lane, from a running number of the piece, 1296 x 144 in blocks of 24 took 4.1 us
+// (3.0 now), 1152 x 128 as long as now (5.0).
 struct StripPanels {
     const uint8_t *mant, *exps;
     uint8_t *out;
@@ -329,12 +335,16 @@ bool gemm_strip_ok(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64_t 
     if (ho >= (1 << 20) || wo >= (1 << 20)) return false;
     if (2 * c.pad_h > c.r - 1 || 2 * c.pad_w > c.s - 1) return false;
     if (a.M > 0x7fffffff || a.N > 32 * 65535) return false;        // (column tiles are the panel launch's blockIdx.y)
+    if (c.n * c.h * c.w > (1 << 30)) return false;                 // pixel numbers behind the last one, of a strip's end, fit an int
     const StripPlan plan = strip_plan(a.M, a.N, enc);
     const int64_t pitch = kblock / 8 * 32 + 16, pixels = strip_pixels(c, ho, wo, kStripUnit * strip_units_most(plan.nt));
     if ((pixels + 1) * pitch > kStripLds) return false;
     const int64_t steps = strip_steps(c.c / kblock, kblock, taps);
     const size_t panels = ((size_t)ceil_div(a.N, 32) * steps + 4) * 1024;         // (addressed with 31 bits)
     if (panels > room || panels > 0x7fffffff) return false;
+    // Below 128 tiles the start of a workgroup and its first strip count, and the int8 kernel splits long contractions.  int8 -> here with 129
+    // tiles 27.6 -> 18.1 and 15.4 -> 12.7 us, 147 22.6 -> 16.6, 154 19.9 -> 12.6, 196 28.3 -> 20.5, 784 41.5 -> 36.0; with fewer it gains at
+    // some and loses at others: 62 tiles 23.2 -> 17.7 and 19.0 -> 19.1, 74 17.0 -> 15.3 and, 2304 of k, 26.6 -> 28.0, 98 30.1 -> 30.7.
     return ceil_div(a.M, 256) * ceil_div(a.N, 128) >= 128 && (int64_t)plan.slots * plan.tiles_n <= 0x7ffffff;
 }
 

@@ -260,18 +260,18 @@ __global__ __launch_bounds__(kStripThreads, 2) void gemm_strip_kernel(const Stri
     const int64_t row0 = (int64_t)(from + base * slot + (slot < more ? slot : more)) * kStripUnit;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int wm = wave & 1, wn = (wave >> 1) ^ ((place >> 5) & 1);              // (the other way round 32 places on: the same SIMDs)
-    // the column tiles that hold filters, half of them for either wave (ENC: NT for the first)
+    // Column tiles: NT for either wave, so that no two waves store the same column (with beta both would add to it).  Beyond the last
+    // tile that holds filters the second wave has fewer, or none.
     const int tiles32 = (int)((p.N + 31) / 32), here = tiles32 - 2 * NT * tn < 2 * NT ? tiles32 - 2 * NT * tn : 2 * NT;
-    const int split = ENC ? NT : (here + 1) / 2;
-    const int tile0 = 2 * NT * tn + wn * split;
-    const bool idle = here <= wn * split;                                        // this wave has no column to compute
+    const int tile0 = 2 * NT * tn + wn * NT;
+    const bool idle = here <= wn * NT;                                           // this wave has no column to compute
     if constexpr (NT == 2) {
         if (mt == 4) strip_wave<KS, 4, NT, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
         else if (mt == 3) strip_wave<KS, 3, NT, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
         else if (mt == 2) strip_wave<KS, 2, NT, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
         else if (mt == 1) strip_wave<KS, 1, NT, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
     } else {
-        const bool narrow = wn == 1 && here - split < NT;                        // (the barriers of both kinds of wave are the same)
+        const bool narrow = wn == 1 && here < 2 * NT;                            // (the barriers of both kinds of wave are the same)
         if (mt == 3) {
             if (narrow) strip_wave<KS, 3, NT - 1, false, STREAM>(p, lds, row0, wm, tile0, idle);
             else strip_wave<KS, 3, NT, false, STREAM>(p, lds, row0, wm, tile0, idle);

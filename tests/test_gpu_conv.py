@@ -550,3 +550,36 @@ def test_conv_strips_against_the_lowered_product(hb, n, h, w, c, f, r, s, pad, s
     fmt = hb.make_format(8, 1, 32)
     enc, want = hb.gemm_conv2d_bfp(img, conv, flt, fmt, relu=True), hb.encode(torch.relu(y), 1, fmt)
     assert torch.equal(enc.mant, want.mant) and torch.equal(enc.exps, want.exps)
+
+
+@pytest.mark.parametrize("n,f,kb,per_image", [
+    (54, 40, 32, False),             # a column tile of 32 and one of 8: both the first wave's
+    (54, 64, 32, False), (54, 64, 24, True), (80, 320, 32, False),       # two whole ones alone in the last 128 columns
+    (54, 100, 24, False),            # three and a part
+    (54, 160, 32, False), (54, 192, 24, True),                           # tiles of 192: a second wave of two and of three
+])
+def test_conv_strips_add_to_c_once(hb, n, f, kb, per_image):
+    """beta = 1 from strips: no column belongs to two waves, which would both add to it.  Small integers: equal to the bit to the int8
+    product on the lowered operand added in FP32, forward and as the data gradient of stride 1."""
+    from tests.util import launched_kernels
+    c, h = 2 * kb, 25
+    g = torch.Generator(device="cuda").manual_seed(n + f)
+    whole = dict(k_slot=kb) if per_image else {}
+    cb = kb if kb < 32 else 0
+    x = torch.randint(-7, 8, (n, h, h, c), device="cuda", generator=g).float()
+    wm = torch.randint(-7, 8, (9 * c, f), device="cuda", generator=g).float()
+    y0 = torch.randint(-99, 100, (n * h * h, f), device="cuda", generator=g).float()
+    img = hb.encode(x.view(-1, c), 1, hb.make_format(8, h * h, 0, k_slot=kb) if per_image else hb.make_format(8, 1, kb))
+    flt = hb.encode(wm, 0, hb.make_format(8, 9 * kb, kb, k_slot=kb) if per_image else hb.make_format(8, kb, 1))
+    conv = hb.Conv2d(n, h, h, c, 3, 3, 1, 1, 1, 1, cb, 0)
+    low = hb.encode_im2col(hb.decode(img).view(n, h, h, c), conv, hb.make_format(8, 1, kb))
+    want = y0 + hb.gemm(low, flt, kernel=hb.KERNEL_INT8)
+    fw = hb.Conv2d(n, h, h, f, 3, 3, 1, 1, 1, 1, cb, 0)                  # dY has c columns, dX f: the same product
+    for call in (lambda out, beta: hb.gemm_conv2d(img, conv, flt, out=out, beta=beta),
+                 lambda out, beta: hb.gemm_conv2d_dgrad(img, fw, flt, out=out, beta=beta)):
+        print(f"[conv strips, beta] n={n} f={f} blocks of {kb}", flush=True)
+        got = call(y0.clone(), 1.0)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+        names = launched_kernels(lambda: call(got, 0.0))
+        assert any(k.startswith("gemm_strip_kernel") for k in names), names

@@ -1283,7 +1283,7 @@ int launch_gemm_conv_i8(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int
                         hipStream_t s, int dil_h, int dil_w, bool by_phase, int slot_order, int kblock, int chain, const hbfp_tensor *enc,
                         int relu) {
     if (dil_h == 1 && dil_w == 1 && !by_phase &&
-        gemm_strip_ok(a, c, ho, wo, kblock, enc != nullptr, gemm_conv_workspace(a.M, a.N, a.kpad, c.n * c.h * c.w, (int)(c.c / kblock))))
+        gemm_strip_ok(a, c, ho, wo, kblock, gemm_conv_workspace(a.M, a.N, a.kpad, c.n * c.h * c.w, (int)(c.c / kblock))))
         return launch_gemm_strip(a, c, ho, wo, pix_bytes, slot_order > 0, kblock, workspace, s, enc, relu);
     GemmParams p = {};
     p.A = (const uint8_t *)a.mantA;

@@ -293,6 +293,11 @@ int64_t strip_pixels(const hbfp_conv2d &c, int64_t ho, int64_t wo, int64_t rows)
            ceil_div(rows - 1, ho * wo) * (per_img > 0 ? per_img : 0) + (int64_t)(c.r - 1) * c.w + c.s;
 }
 
+// bytes of LDS: the strip of that many units of positions and the pixel of zeros
+int64_t strip_lds(const hbfp_conv2d &c, int64_t ho, int64_t wo, int kblock, int units) {
+    return (strip_pixels(c, ho, wo, kStripUnit * units) + 1) * (kblock / 8 * 32 + 16);
+}
+
 template <int KS, int NT, bool ENC>
 int launch_strip_t(const StripParams &p, bool stream, int lds_bytes, hipStream_t s) {
     static std::atomic<bool> configured[2];
@@ -304,19 +309,19 @@ int launch_strip_t(const StripParams &p, bool stream, int lds_bytes, hipStream_t
 
 // How the output is dealt: column tiles of 128 or 192 filters, whichever computes fewer columns that do not exist, and as many
 // workgroups as fill 2 x 32 places of every XCD, once or as often as it takes with at most 256 (192) positions each.
+int strip_nt(int64_t N) { return ceil_div(N, 128) * 128 <= ceil_div(N, 192) * 192 ? 2 : 3; }
 struct StripPlan {
     int nt, tiles_n, units, slots;
 };
-StripPlan strip_plan(int64_t M, int64_t N, bool enc) {
+StripPlan strip_plan(int64_t M, int64_t N, bool enc, int units_most) {
     StripPlan q;
-    const int64_t two = ceil_div(N, 128) * 128, three = ceil_div(N, 192) * 192;
-    q.nt = enc || two <= three ? 2 : 3;
+    q.nt = enc ? 2 : strip_nt(N);
     q.tiles_n = (int)ceil_div(N, 64 * q.nt);
     q.units = (int)ceil_div(M, kStripUnit);
     const int64_t share = ceil_div(q.units, 8);
     for (int64_t rounds = 1;; ++rounds) {
         const int64_t slots = 64 * rounds / q.tiles_n;
-        if (slots < 1 || ceil_div(share, slots) > strip_units_most(q.nt)) continue;
+        if (slots < 1 || ceil_div(share, slots) > units_most) continue;
         q.slots = (int)(slots < share ? slots : share);
         return q;
     }
@@ -327,8 +332,9 @@ int strip_steps(int64_t ncb, int64_t kblock, int64_t taps) { return (int)(taps *
 
 }  // namespace
 
-// Whether the convolution runs on this kernel (a: as for launch_gemm_conv_i8; room: bytes of workspace, which holds the panels)
-bool gemm_strip_ok(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64_t wo, int kblock, bool enc, size_t room) {
+// Whether the convolution runs on this kernel (a: as for launch_gemm_conv_i8; room: bytes of workspace, which holds the panels).  The
+// answer is the same for a result delivered encoded, whose bytes are those of the FP32 result's conversion.
+bool gemm_strip_ok(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64_t wo, int kblock, size_t room) {
     const int64_t taps = (int64_t)c.r * c.s;
     if ((kblock != 24 && kblock != 32) || c.c % kblock || taps > 32 || taps < 2) return false;
     // corners in increasing order, positions within one window of their input
@@ -336,16 +342,15 @@ bool gemm_strip_ok(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64_t 
     if (2 * c.pad_h > c.r - 1 || 2 * c.pad_w > c.s - 1) return false;
     if (a.M > 0x7fffffff || a.N > 32 * 65535) return false;        // (column tiles are the panel launch's blockIdx.y)
     if (c.n * c.h * c.w > (1 << 30)) return false;                 // pixel numbers behind the last one, of a strip's end, fit an int
-    const StripPlan plan = strip_plan(a.M, a.N, enc);
-    const int64_t pitch = kblock / 8 * 32 + 16, pixels = strip_pixels(c, ho, wo, kStripUnit * strip_units_most(plan.nt));
-    if ((pixels + 1) * pitch > kStripLds) return false;
+    if (strip_lds(c, ho, wo, kblock, strip_units_most(strip_nt(a.N))) > kStripLds) return false;
     const int64_t steps = strip_steps(c.c / kblock, kblock, taps);
     const size_t panels = ((size_t)ceil_div(a.N, 32) * steps + 4) * 1024;         // (addressed with 31 bits)
     if (panels > room || panels > 0x7fffffff) return false;
     // Below 128 tiles the start of a workgroup and its first strip count, and the int8 kernel splits long contractions.  int8 -> here with 129
     // tiles 27.6 -> 18.1 and 15.4 -> 12.7 us, 147 22.6 -> 16.6, 154 19.9 -> 12.6, 196 28.3 -> 20.5, 784 41.5 -> 36.0; with fewer it gains at
     // some and loses at others: 62 tiles 23.2 -> 17.7 and 19.0 -> 19.1, 74 17.0 -> 15.3 and, 2304 of k, 26.6 -> 28.0, 98 30.1 -> 30.7.
-    return ceil_div(a.M, 256) * ceil_div(a.N, 128) >= 128 && (int64_t)plan.slots * plan.tiles_n <= 0x7ffffff;
+    // (Slots are at most an XCD's units, which with the column tiles bounds the grid.)
+    return ceil_div(a.M, 256) * ceil_div(a.N, 128) >= 128 && ceil_div(a.M, 8 * kStripUnit) * ceil_div(a.N, 128) <= 0x7ffffff;
 }
 
 int launch_gemm_strip(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64_t wo, int64_t pix_bytes, bool by_block, int kblock, void *workspace,
@@ -367,8 +372,11 @@ int launch_gemm_strip(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64
     else hipLaunchKernelGGL(strip_panels_kernel<4>, pieces, dim3(256), 0, s, q);
     if (launch_status() != HBFP_OK) return HBFP_ERR_LAUNCH;
 
-    const StripPlan plan = strip_plan(a.M, a.N, enc != nullptr);
-    const int64_t pitch = kblock / 8 * 32 + 16, strip = strip_pixels(c, ho, wo, kStripUnit * strip_units_most(plan.nt));
+    // An encoded result is computed on tiles of 128 filters, whose shares of four units need a longer strip than the three of tiles of
+    // 192: three units there too where the fourth does not fit.
+    const int most = !enc ? strip_units_most(strip_nt(a.N)) : strip_lds(c, ho, wo, kblock, 4) <= kStripLds ? 4 : 3;
+    const StripPlan plan = strip_plan(a.M, a.N, enc != nullptr, most);
+    const int lds_bytes = (int)strip_lds(c, ho, wo, kblock, most);
     StripParams p = {};
     p.img = (const uint8_t *)a.mantA;
     p.eimg = a.expA;
@@ -395,13 +403,12 @@ int launch_gemm_strip(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64
     p.ncb = q.ncb;
     p.steps = q.steps;
     p.tail = (int32_t)((c.r - 1) * c.w + c.s);
-    p.zero_at = (int32_t)(strip * pitch);
+    p.zero_at = lds_bytes - (kblock / 8 * 32 + 16);
     p.units = plan.units;
     p.slots = plan.slots;
     p.tiles_n = plan.tiles_n;
     p.beta = a.beta != 0.0f;
     p.m = a.mA;
-    const int lds_bytes = (int)((strip + 1) * pitch);
     if (enc) {
         p.enc = mx_out_of(*enc, relu);
         return kblock == 24 ? launch_strip_t<3, 2, true>(p, true, lds_bytes, s) : launch_strip_t<4, 2, true>(p, true, lds_bytes, s);

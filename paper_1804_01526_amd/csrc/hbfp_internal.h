@@ -100,7 +100,7 @@ int launch_gemm_conv_i8(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int
                         hipStream_t s, int dil_h = 1, int dil_w = 1, bool by_phase = false, int slot_order = -1,
                         int kblock = 32, int chain = 0, const hbfp_tensor *enc = nullptr, int relu = 0);
 // gemm_conv.hip: the same product from strips of the image in LDS on the bf16 matrix instruction; room: bytes of workspace
-bool gemm_strip_ok(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64_t wo, int kblock, bool enc, size_t room);
+bool gemm_strip_ok(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64_t wo, int kblock, size_t room);
 int launch_gemm_strip(const GemmArgs &a, const hbfp_conv2d &c, int64_t ho, int64_t wo, int64_t pix_bytes, bool by_block, int kblock, void *workspace,
                       hipStream_t s, const hbfp_tensor *enc, int relu);
 bool conv_encoded_output_ok(int64_t M, int64_t N, int64_t kpad, const hbfp_tensor &out);

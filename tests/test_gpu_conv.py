@@ -583,3 +583,31 @@ def test_conv_strips_add_to_c_once(hb, n, f, kb, per_image):
         assert torch.equal(got, want)
         names = launched_kernels(lambda: call(got, 0.0))
         assert any(k.startswith("gemm_strip_kernel") for k in names), names
+
+
+@pytest.mark.parametrize("n,h,w,c,f,kb,bits,sr", [
+    (2, 160, 160, 64, 192, 32, 8, 0),        # rows so long that a strip of 192 positions fits, one of 256 does not
+    (2, 156, 158, 96, 129, 32, 8, 1),        # ... ragged, an odd number of channel blocks, stochastic
+    (4, 170, 170, 48, 144, 24, 8, 0),        # three and four units of positions, the FP32 product on tiles of 192 filters
+    (130, 28, 28, 64, 128, 32, 4, 1),        # three and four units on tiles of 128 both
+    (100, 20, 20, 72, 60, 24, 8, 1),         # one wave of columns only
+])
+def test_conv_strips_delivered_encoded_are_the_conversion_of_the_product(hb, n, h, w, c, f, kb, bits, sr):
+    """Sums that round (exponents far apart): the encoded result has the bytes of the FP32 result's conversion, so both come from strips
+    and add in one order, whatever the tiles."""
+    from tests.util import launched_kernels
+    g = torch.Generator(device="cuda").manual_seed(n + f)
+    x = torch.randn((n * h * w, c), device="cuda", generator=g) * torch.exp2(torch.rand((n * h * w, 1), device="cuda", generator=g) * 24.0)
+    wm = torch.randn((9 * c, f), device="cuda", generator=g) * torch.exp(torch.randn((9 * c, f), device="cuda", generator=g) * 3.0)
+    conv = hb.Conv2d(n, h, w, c, 3, 3, 1, 1, 1, 1, kb if kb < 32 else 0, 0)
+    img, flt = hb.encode(x, 1, hb.make_format(8, 1, kb)), hb.encode(wm, 0, hb.make_format(8, kb, 1))
+    fmt = hb.make_format(bits, 1, 32, hb.STOCHASTIC if sr else hb.RNE, 77)
+    print(f"[conv strips, encoded] n={n} {h}x{w}x{c} f={f} blocks of {kb} bits={bits} sr={sr}", flush=True)
+    for relu in (False, True):
+        y = hb.gemm_conv2d(img, conv, flt)
+        enc, want = hb.gemm_conv2d_bfp(img, conv, flt, fmt, relu=relu), hb.encode(torch.relu(y) if relu else y, 1, fmt)
+        torch.cuda.synchronize()
+        assert torch.equal(enc.mant, want.mant) and torch.equal(enc.exps, want.exps)
+    for call in (lambda: hb.gemm_conv2d(img, conv, flt), lambda: hb.gemm_conv2d_bfp(img, conv, flt, fmt)):
+        names = launched_kernels(call)
+        assert sum(k.startswith("gemm_strip_kernel") for k in names) == 1, names

@@ -471,7 +471,7 @@ struct ColParams {
     int32_t lanes;      // lanes of a wave that carry operand rows: the largest multiple of rblock <= 64
     int32_t narrow;     // a workgroup covers 1 / 2^narrow of the pieces that its LDS tile has room for (col_narrow)
     uint32_t row_groups;   // workgroups per group of blocks (the grid is flat: block group = blockIdx.x / row_groups)
-    uint32_t blk_groups8;  // CONV: groups of blocks per XCD; the grid is 8 times as many times row_groups
+    uint32_t wgs, wgs8;    // INSIDE: workgroups with work, and how many of them an XCD has; the grid is 8 times as many
     uint32_t s0, s1;
     // TABLE (second pass of the two-pass conversion): the largest magnitude of every exponent block has been computed
     // already, table[(block / kshare) * ntc + row / rblock_t]; the kernel then walks stored pieces of KBP elements,
@@ -547,7 +547,8 @@ __device__ __forceinline__ void conv_col_gather_inside(const ColParams &p, const
     for (int kk = LEN; kk < KBP; ++kk) v[kk] = 0.0f;
 }
 
-template <int KBP, bool WIDE, int ROUND, bool TABLE, bool CONV = false>
+// INSIDE (CONV): pieces inside the tensor by conv_col_gather_inside, workgroups dealt to the XCDs by position (launch_encode_im2col)
+template <int KBP, bool WIDE, int ROUND, bool TABLE, bool CONV = false, bool INSIDE = false>
 __device__ __forceinline__ void enc_col_block(const ColParams p, const uint32_t wg) {
     constexpr int ESZ = WIDE ? 2 : 1;
     constexpr int NBT = kColRowBytes / (KBP * ESZ);  // exponent blocks per tile row: 16, 8, 8 or 4
@@ -557,10 +558,11 @@ __device__ __forceinline__ void enc_col_block(const ColParams p, const uint32_t 
 
     // the wave index as a scalar: block indices, block lengths and (CONV) output positions stay on the scalar unit
     const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
-    // CONV: every XCD has an eighth of the positions and all row groups of them: a pixel enters one L2 instead of all eight (64 x 28 x 28
-    // x 144, 3 x 3: 54.6 -> 39.0 us; 128 channels 37.3 -> 34.6).  The price is a last wave of up to 7 idle groups of blocks.
-    const uint32_t row_group = CONV ? (wg >> 3) % p.row_groups : wg % p.row_groups;
-    const uint32_t blk_group = CONV ? (wg & 7) * p.blk_groups8 + (wg >> 3) / p.row_groups : wg / p.row_groups;
+    // INSIDE: every XCD has an eighth of the workgroups, consecutive ones: all row groups of its positions, so that a pixel enters one or
+    // two L2s instead of all eight (64 x 28 x 28 x 144, 3 x 3: 54.6 -> 39.0 us; 128 channels 37.3 -> 34.6).
+    const uint32_t at = INSIDE ? (wg & 7) * p.wgs8 + (wg >> 3) : wg;
+    if (INSIDE && at >= p.wgs) return;                 // whole workgroup, before any barrier
+    const uint32_t row_group = at % p.row_groups, blk_group = at / p.row_groups;
     const int64_t r = (int64_t)row_group * p.lanes + lane;
     const int narrow = NBT > 4 ? p.narrow : 0;         // four pieces are one per wave, never cut further: a constant there
     const int nbt = NBT >> narrow;
@@ -570,8 +572,8 @@ __device__ __forceinline__ void enc_col_block(const ColParams p, const uint32_t 
     int conv_fr = 0, conv_fs = 0, conv_ch = 0;          // CONV: this lane's filter tap and channel
     if (CONV) conv_window_entry(p.cv, r_ok ? (uint32_t)r : 0u, conv_fr, conv_fs, conv_ch);
     const int conv_off = CONV ? (conv_fr * p.cv.W + conv_fs) * p.cv.C + conv_ch : 0;    // of the lane's window entry from the corner
-    int ox_lo = 0, ox_hi = 0;                           // CONV: output columns at which it lies inside the image: ox_lo .. ox_hi - 1
-    if (CONV) {
+    int ox_lo = 0, ox_hi = 0;                           // INSIDE: output columns at which it lies inside the image: ox_lo .. ox_hi - 1
+    if (INSIDE) {
         const int lo = p.cv.pad_w - conv_fs + p.cv.str_w - 1, hi = p.cv.W - 1 + p.cv.pad_w - conv_fs;
         ox_lo = lo < 0 ? 0 : p.cv.str_w == 1 ? lo : lo / p.cv.str_w;
         ox_hi = hi < 0 ? 0 : (p.cv.str_w == 1 ? hi : hi / p.cv.str_w) + 1;
@@ -605,7 +607,7 @@ __device__ __forceinline__ void enc_col_block(const ColParams p, const uint32_t 
             const int64_t first = (((int64_t)img * p.cv.H + y0) * p.cv.W + x0) * p.cv.C;
             int64_t last = p.corner_last + 1;
             int corners = 0;
-            if (KBP == 32 && first >= 0 && (blen == 32 || blen == 24)) {
+            if (INSIDE && first >= 0 && (blen == 32 || blen == 24)) {
                 uint32_t img1;
                 int y1, x1;
                 conv_position(p.cv, (uint32_t)kfirst + (uint32_t)(lane < blen ? lane : blen - 1), img1, y1, x1);
@@ -613,8 +615,8 @@ __device__ __forceinline__ void enc_col_block(const ColParams p, const uint32_t 
                 last = first + __builtin_amdgcn_readlane(corners, 31);
                 corners *= 4;
             }
-            if (KBP == 32 && last <= p.corner_last) {
-                constexpr int kFull = KBP == 32 ? 32 : 0, kShort = KBP == 32 ? 24 : 0;
+            if (INSIDE && last <= p.corner_last) {
+                constexpr int kFull = INSIDE ? 32 : 0, kShort = INSIDE ? 24 : 0;
                 const uint32_t off = (uint32_t)conv_off * 4u;
                 if (blen == 32) conv_col_gather_inside<kFull, KBP>(p, p.src + first, corners, y0, oy, ox, r_ok, conv_fr, off, ox_lo, ox_hi, v);
                 else conv_col_gather_inside<kShort, KBP>(p, p.src + first, corners, y0, oy, ox, r_ok, conv_fr, off, ox_lo, ox_hi, v);
@@ -642,7 +644,7 @@ __device__ __forceinline__ void enc_col_block(const ColParams p, const uint32_t 
 #pragma unroll
         for (int kk = 0; kk < KBP; kk += 8) {
             int q[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-            if (!CONV || kk < blen) {                                         // uniform; behind the block's end: zeros
+            if (!INSIDE || kk < blen) {                                        // uniform; behind the block's end: zeros
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const uint64_t idx = (uint64_t)(kfirst + kk + e) * (uint64_t)p.src_cols + (uint64_t)r;
@@ -696,9 +698,9 @@ __device__ __forceinline__ void enc_col_block(const ColParams p, const uint32_t 
     }
 }
 
-template <int KBP, bool WIDE, int ROUND, bool TABLE, bool CONV = false>
+template <int KBP, bool WIDE, int ROUND, bool TABLE, bool CONV = false, bool INSIDE = false>
 __global__ __launch_bounds__(kThreads) void enc_col_kernel(const ColParams p) {
-    enc_col_block<KBP, WIDE, ROUND, TABLE, CONV>(p, blockIdx.x);
+    enc_col_block<KBP, WIDE, ROUND, TABLE, CONV, INSIDE>(p, blockIdx.x);
 }
 
 // Two conversions in one launch (both operands of hbfp_gemm_f32): each along the rows or down them, blocks stored as 32, at
@@ -738,12 +740,12 @@ void launch_col_k(const ColParams &p, dim3 grid, bool wide, int rounding, hipStr
     else hipLaunchKernelGGL((enc_col_kernel<KBP, true, 1, false>), grid, dim3(kThreads), 0, s, p);
 }
 
-template <int KBP>
+template <int KBP, bool INSIDE>
 void launch_col_conv_k(const ColParams &p, dim3 grid, bool wide, int rounding, hipStream_t s) {
-    if (!wide && rounding == 0) hipLaunchKernelGGL((enc_col_kernel<KBP, false, 0, false, true>), grid, dim3(kThreads), 0, s, p);
-    else if (!wide) hipLaunchKernelGGL((enc_col_kernel<KBP, false, 1, false, true>), grid, dim3(kThreads), 0, s, p);
-    else if (rounding == 0) hipLaunchKernelGGL((enc_col_kernel<KBP, true, 0, false, true>), grid, dim3(kThreads), 0, s, p);
-    else hipLaunchKernelGGL((enc_col_kernel<KBP, true, 1, false, true>), grid, dim3(kThreads), 0, s, p);
+    if (!wide && rounding == 0) hipLaunchKernelGGL((enc_col_kernel<KBP, false, 0, false, true, INSIDE>), grid, dim3(kThreads), 0, s, p);
+    else if (!wide) hipLaunchKernelGGL((enc_col_kernel<KBP, false, 1, false, true, INSIDE>), grid, dim3(kThreads), 0, s, p);
+    else if (rounding == 0) hipLaunchKernelGGL((enc_col_kernel<KBP, true, 0, false, true, INSIDE>), grid, dim3(kThreads), 0, s, p);
+    else hipLaunchKernelGGL((enc_col_kernel<KBP, true, 1, false, true, INSIDE>), grid, dim3(kThreads), 0, s, p);
 }
 
 void launch_col_table(const ColParams &p, dim3 grid, bool wide, int rounding, hipStream_t s) {
@@ -1479,13 +1481,26 @@ int launch_encode_im2col(const float *x, const hbfp_conv2d &c, int64_t ho, int64
         const int64_t gx = ceil_div(g.R, 64);
         p.narrow = col_narrow(gx, nb_cover, nbt);
         const int64_t gy = ceil_div(nb_cover, nbt >> p.narrow);
-        const int64_t gy8 = ceil_div(gy, 8);
-        if (gx > 0x7fffffff || gx * gy > 0x7fffffff || gx * gy8 > 0x7fffffff / 8) return HBFP_ERR_ARG;
+        if (gx > 0x7fffffff || gx * gy > 0x7fffffff) return HBFP_ERR_ARG;
         p.row_groups = (uint32_t)gx;
-        p.blk_groups8 = (uint32_t)gy8;
-        const dim3 grid((unsigned)(8 * gx * gy8));
-        if (g.kbp == 32) launch_col_conv_k<32>(p, grid, wide, g.rounding, s);
-        else if (g.kbp == 64) launch_col_conv_k<64>(p, grid, wide, g.rounding, s);
+        p.wgs = (uint32_t)(gx * gy);
+        // Every XCD takes whole groups of blocks (a pixel then enters one L2, or two at its borders) where its fullest compute unit has no
+        // more workgroups for it, else an even share.  Even -> whole: 24 x 14 x 14 x 128 (666 workgroups) 6.7 -> 6.2 us, 16 x 28 x 28 x 64
+        // 7.1 -> 6.5; whole -> even: 16 x 14 x 14 x 256 (25 groups of 36) 9.1 -> 7.3, 64 x 14 x 14 x 256 24.1 -> 18.6.
+        const int64_t even = ceil_div(gx * gy, 8), whole = gx * ceil_div(gy, 8);
+        const bool groups = ceil_div(whole, 32) == ceil_div(even, 32);
+        p.wgs8 = (uint32_t)(groups ? whole : even);
+        // The unchecked loads and the dealing pay from some thousand pieces of 64 rows on; below, the longer kernel's start counts.  Checked
+        // loads, workgroups in turn -> unchecked, dealt; blocks of 32, whole groups: 1764 pieces 5.73 -> 6.04 us, 2232 6.20 -> 5.95,
+        // 5292 14.6 -> 11.5; even shares: 72 4.9 -> 5.25, 2700 6.65 -> 6.82, 2880 6.48 -> 6.85, 3600 7.3 both, 14 112 19.8 -> 18.6.  Of 24,
+        // whose checked loads are slower: whole groups, 1092 5.56 -> 5.23, 1372 5.55 -> 5.60, 2100 6.57 -> 5.70; even shares, 924
+        // 5.0 -> 5.05.  Blocks of other lengths have no unchecked loads, and the dealing by itself gives them nothing (16: 56.6 -> 57.7).
+        const int64_t pieces = gx * nb_cover;
+        const bool inside = forward && ((g.kblock == 32 && pieces >= (groups ? 2000 : 3500)) || (g.kblock == 24 && pieces >= (groups ? 1000 : 1500)));
+        const dim3 grid(inside ? 8 * p.wgs8 : p.wgs);
+        if (g.kbp == 32 && inside) launch_col_conv_k<32, true>(p, grid, wide, g.rounding, s);
+        else if (g.kbp == 32) launch_col_conv_k<32, false>(p, grid, wide, g.rounding, s);
+        else if (g.kbp == 64) launch_col_conv_k<64, false>(p, grid, wide, g.rounding, s);
         else return HBFP_ERR_FORMAT;
         return launch_status();
     }

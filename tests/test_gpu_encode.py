@@ -188,6 +188,38 @@ def test_encode_im2col_pieces_inside_the_tensor(hb, n, h, w, c, r, s, ph, pw, sh
     np.testing.assert_array_equal(mant, want.mant)
 
 
+@pytest.mark.parametrize("B,m,rounding", [(32, 8, 0), (24, 8, 1), (24, 12, 0)])
+@pytest.mark.parametrize("n,h,w,c,r,s,ph,pw,sh,sw,unchecked", [
+    (600, 9, 7, 20, 3, 3, 1, 1, 1, 1, True),
+    (50, 28, 28, 21, 3, 3, 1, 1, 1, 1, True),
+    (42, 5, 70, 30, 3, 5, 1, 2, 1, 1, True),
+    (360, 15, 16, 33, 3, 3, 1, 1, 2, 2, True),
+    (560, 9, 13, 50, 2, 3, 0, 1, 1, 3, True),
+    (12500, 3, 3, 60, 3, 3, 0, 0, 1, 1, True),
+    (600, 4, 4, 16, 3, 3, 3, 3, 1, 1, False),        # corners move back
+    (7000, 6, 6, 64, 2, 2, 0, 0, 3, 3, True),
+    (3, 9, 10, 300, 3, 3, 1, 1, 1, 1, False),        # few pieces
+])
+def test_encode_im2col_weight_gradient_of_many_pieces(hb, n, h, w, c, r, s, ph, pw, sh, sw, unchecked, B, m, rounding):
+    """The geometries above at sizes from which pieces inside the tensor are loaded without a check and workgroups are dealt to the XCDs
+    by position, against the oracle, and by the instance that the sizes call for."""
+    from tests.util import launched_kernels
+    rng = np.random.default_rng(n + c)
+    x = rng.standard_normal((n, h, w, c)).astype(np.float32)
+    xd = torch.from_numpy(x).cuda()
+    conv, fmt = hb.Conv2d(n, h, w, c, r, s, ph, pw, sh, sw, 0, 0), hb.make_format(m, B, 1, rounding, 0xBEEF)
+    print(f"[case] im2col {n}x{h}x{w}x{c} window {r}x{s} pad ({ph},{pw}) stride ({sh},{sw}) B={B} m={m}", flush=True)
+    bt = hb.encode_im2col(xd, conv, fmt, contract_axis=0)
+    torch.cuda.synchronize()
+    want = ref.encode(ref.im2col(x, r, s, ph, pw, sh, sw), B, 1, m, rounding, 0xBEEF)
+    mant, exps = unpack(bt)
+    np.testing.assert_array_equal(exps, want.exps)
+    np.testing.assert_array_equal(mant, want.mant)
+    names = launched_kernels(lambda: hb.encode_im2col(xd, conv, fmt, contract_axis=0, out=bt))
+    kernel = f"enc_col_kernel<32, {str(m > 8).lower()}, {rounding}, false, true, {str(unchecked).lower()}>"
+    assert names == [kernel], (names, kernel)
+
+
 @pytest.mark.parametrize("n,h,w,c,r,s,ph,pw,sh,sw,slot,m,rounding", [
     (3, 9, 10, 16, 3, 3, 1, 1, 1, 1, 24, 8, 0), (2, 8, 7, 8, 3, 3, 1, 1, 1, 1, 24, 8, 1), (4, 12, 11, 40, 1, 1, 0, 0, 1, 1, 8, 12, 1),
     (2, 11, 13, 24, 5, 3, 2, 1, 2, 1, 64, 8, 0), (2, 15, 15, 32, 2, 2, 0, 0, 3, 3, 32, 8, 1), (70, 6, 6, 16, 3, 3, 1, 1, 1, 1, 16, 8, 0),

@@ -524,24 +524,29 @@ def test_conv_bfp_over_its_own_image(hb, n, h, w, c, r):
     assert torch.equal(img.mant, want.mant) and torch.equal(img.exps, want.exps)
 
 
-@pytest.mark.parametrize("n,h,w,c,f,r,s,pad,stride,kb", [
-    (64, 23, 23, 64, 40, 3, 3, 1, 1, 32),            # two column tiles, a wave of one
-    (50, 26, 26, 48, 100, 3, 3, 1, 1, 24),           # blocks of 24, block by block along k
-    (30, 24, 24, 96, 160, 3, 3, 1, 1, 32),           # tiles of 192 filters, an odd number of channel blocks
-    (16, 33, 32, 72, 192, 3, 3, 1, 1, 24),           # whole tiles of 192
-    (130, 33, 31, 32, 128, 3, 3, 1, 2, 32),          # strided, a single channel block
-    (2100, 4, 4, 24, 33, 3, 3, 1, 1, 24),            # several images in a unit of 64 positions
-    (60, 25, 25, 64, 30, 2, 2, 0, 1, 32),            # no padding, fewer filters than a column tile
-    (45, 28, 27, 32, 128, 1, 5, 0, 1, 32),           # a window of one row
+@pytest.mark.parametrize("n,h,w,c,f,r,s,pad,sh,sw,kb", [
+    (64, 23, 23, 64, 40, 3, 3, 1, 1, 1, 32),         # two column tiles of one wave
+    (50, 26, 26, 48, 100, 3, 3, 1, 1, 1, 24),        # blocks of 24, block by block along k
+    (54, 25, 25, 96, 160, 3, 3, 1, 1, 1, 32),        # tiles of 192 filters, an odd number of channel blocks
+    (34, 33, 32, 72, 192, 3, 3, 1, 1, 1, 24),        # whole tiles of 192
+    (40, 30, 60, 48, 128, 3, 3, 1, 1, 2, 24),        # strided along the rows (in both directions no strip fits)
+    (520, 16, 8, 32, 128, 3, 3, 1, 2, 1, 32),        # strided down the image, a single channel block
+    (2100, 4, 4, 24, 33, 3, 3, 1, 1, 1, 24),         # several images in a unit of 64 positions
+    (60, 25, 25, 64, 30, 2, 2, 0, 1, 1, 32),         # no padding, fewer filters than a column tile
+    (52, 28, 27, 32, 128, 1, 5, 0, 1, 1, 32),        # a window of one row
+    (130, 28, 28, 72, 100, 3, 3, 1, 1, 1, 24),       # three and four units of positions, blocks of 24
+    (100, 28, 28, 64, 160, 3, 3, 1, 1, 1, 32),       # two and three units on tiles of 192
+    (100, 28, 28, 48, 192, 3, 3, 1, 1, 1, 24),
 ])
-def test_conv_strips_against_the_lowered_product(hb, n, h, w, c, f, r, s, pad, stride, kb):
+def test_conv_strips_against_the_lowered_product(hb, n, h, w, c, f, r, s, pad, sh, sw, kb):
     """Sizes at which the product runs from strips of the image on the bf16 instruction, against the int8 product on the lowered operand.
     Values are small integers, so that every sum is exact in FP32 whatever its order: equal to the bit, delivered encoded too."""
+    from tests.util import launched_kernels
     g = torch.Generator(device="cuda").manual_seed(n + f)
     x = torch.randint(-7, 8, (n, h, w, c), device="cuda", generator=g) * torch.randint(0, 3, (n, h, w, 1), device="cuda", generator=g)
     wm = torch.randint(-7, 8, (r * s * c, f), device="cuda", generator=g).float()
-    conv = hb.Conv2d(n, h, w, c, r, s, pad, pad, stride, stride, kb if kb < 32 else 0, 0)
-    print(f"[conv] n={n} h={h} w={w} c={c} f={f} window {r}x{s} pad={pad} stride={stride} blocks of {kb}", flush=True)
+    conv = hb.Conv2d(n, h, w, c, r, s, pad, pad, sh, sw, kb if kb < 32 else 0, 0)
+    print(f"[conv] n={n} h={h} w={w} c={c} f={f} window {r}x{s} pad={pad} stride=({sh},{sw}) blocks of {kb}", flush=True)
     img = hb.encode(x.float().view(n * h * w, c), 1, hb.make_format(8, 1, kb))
     flt = hb.encode(wm, 0, hb.make_format(8, kb, 1))
     low = hb.encode_im2col(x.float(), conv, hb.make_format(8, 1, kb))
@@ -550,6 +555,8 @@ def test_conv_strips_against_the_lowered_product(hb, n, h, w, c, f, r, s, pad, s
     fmt = hb.make_format(8, 1, 32)
     enc, want = hb.gemm_conv2d_bfp(img, conv, flt, fmt, relu=True), hb.encode(torch.relu(y), 1, fmt)
     assert torch.equal(enc.mant, want.mant) and torch.equal(enc.exps, want.exps)
+    names = launched_kernels(lambda: hb.gemm_conv2d(img, conv, flt, out=y))
+    assert any(k.startswith("gemm_strip_kernel") for k in names), names
 
 
 @pytest.mark.parametrize("n,f,kb,per_image", [
@@ -611,3 +618,52 @@ def test_conv_strips_delivered_encoded_are_the_conversion_of_the_product(hb, n, 
     for call in (lambda: hb.gemm_conv2d(img, conv, flt), lambda: hb.gemm_conv2d_bfp(img, conv, flt, fmt)):
         names = launched_kernels(call)
         assert sum(k.startswith("gemm_strip_kernel") for k in names) == 1, names
+
+
+@pytest.mark.parametrize("n,h,w,c,f,pad,sw,kb,bits,per_image,log2_x,log2_w", [
+    (60, 25, 25, 64, 128, 1, 1, 32, 8, False, 0, 0),
+    (64, 25, 25, 96, 60, 0, 1, 32, 4, False, 0, 0),          # an odd number of channel blocks, narrow mantissas
+    (60, 25, 25, 72, 144, 1, 1, 24, 8, True, 0, 0),          # the tiling of Sec. 5.1
+    (40, 30, 60, 48, 100, 1, 2, 24, 8, False, 0, 0),         # strided
+    (60, 25, 25, 64, 128, 1, 1, 32, 8, False, -70, -62),     # sums below the normal range
+    (60, 25, 25, 64, 128, 1, 1, 32, 8, False, -127, 60),     # blocks whose last bits lie below the normal range
+    (60, 25, 25, 48, 40, 1, 1, 24, 6, True, -126, 80),
+    (60, 25, 25, 64, 128, 1, 1, 32, 8, False, 124, -60),     # the largest exponent bytes
+    (60, 25, 25, 72, 192, 1, 1, 24, 8, True, -60, 124),
+])
+def test_conv_strips_are_fp32_sums_of_exact_products(hb, n, h, w, c, f, pad, sw, kb, bits, per_image, log2_x, log2_w):
+    """Exponents far apart and at both ends of their range, forward and (stride 1) as the data gradient, against 64 bits.  Every product is
+    exact and each of the K additions rounds by at most 2^-23 of a partial sum, which is at most sum |a||b| (2^-149 where that is
+    subnormal); over the whole result the roundings do not conspire: sqrt(K) 2^-24 of its norm."""
+    from tests.util import launched_kernels
+    g = torch.Generator(device="cuda").manual_seed(n + c + f + bits)
+    spread = 0.0 if log2_x or log2_w else 24.0
+    x = torch.randn((n, h, w, c), device="cuda", generator=g) * torch.exp2(torch.rand((n, h, w, 1), device="cuda", generator=g) * spread)
+    x = (x.double() * 2.0 ** log2_x).clamp(-3.4e38, 3.4e38).float()
+    wm = (torch.randn((9 * c, f), device="cuda", generator=g).double() * 2.0 ** log2_w).clamp(-3.4e38, 3.4e38).float()
+    cb = kb if kb < 32 else 0
+    conv = hb.Conv2d(n, h, w, c, 3, 3, pad, pad, 1, sw, cb, 0)
+    ho, wo = conv.out_hw()
+    print(f"[conv strips, fp64] n={n} {h}x{w}x{c} f={f} pad={pad} stride (1,{sw}) blocks of {kb} bits={bits} per image={per_image} "
+          f"2^{log2_x} 2^{log2_w}", flush=True)
+    img = hb.encode(x.view(-1, c), 1, hb.make_format(bits, h * w, 0, k_slot=kb) if per_image else hb.make_format(bits, 1, kb))
+    flt = hb.encode(wm, 0, hb.make_format(bits, 9 * kb, kb, k_slot=kb) if per_image else hb.make_format(bits, kb, 1))
+    # the lowered image and the filter matrix in 64 bits, window entries tap by tap
+    xd = torch.nn.functional.pad(hb.decode(img).double().view(n, h, w, c), (0, 0, pad, pad, pad, pad))
+    low = torch.cat([xd[:, a:a + ho, b:b + (wo - 1) * sw + 1:sw] for a in range(3) for b in range(3)], 3).reshape(n * ho * wo, 9 * c)
+    wd = hb.decode(flt).double()
+    if cb:
+        wd = wd.view(c // kb, 9, kb, f).transpose(0, 1).reshape(9 * c, f)
+    want, K = low @ wd, 9 * c
+    bound = K * (2.0 ** -23 * (low.abs() @ wd.abs()) + 2.0 ** -149)
+    calls = [lambda: hb.gemm_conv2d(img, conv, flt)]
+    if sw == 1 and pad == 1:                                # dY has c columns, dX f: the same sum
+        calls.append(lambda: hb.gemm_conv2d_dgrad(img, hb.Conv2d(n, h, w, f, 3, 3, 1, 1, 1, 1, cb, 0), flt))
+    for call in calls:
+        y = call().double()
+        assert bool(torch.isfinite(y).all()) and float(want.norm()) > 0
+        err = (y - want).abs()
+        print(f"        largest error / bound = {float((err / bound).max()):.3e}, rel. norm {float(err.norm() / want.norm()):.3e}", flush=True)
+        assert bool((err <= bound).all()) and float(err.norm()) <= K ** 0.5 * 2.0 ** -24 * float(want.norm())
+        names = launched_kernels(call)
+        assert any(k.startswith("gemm_strip_kernel") for k in names), names

@@ -251,10 +251,22 @@ int hbfp_encode_im2col(const float *x, const hbfp_conv2d *conv, const hbfp_tenso
  * operand (one address per operand row and stage; taps outside the image read zeros).
  *     Y[(img, oy, ox)][f] = beta * Y + sum over (fr, fs, ch) of x[img][oy*stride_h - pad_h + fr][ox*stride_w - pad_w + fs][ch]
  *                                                             * w[(fr * s + fs) * c + ch][f]
- * with both factors as their BFP values and the sum taken as Eq. (2) takes it (integer sums over the channels of one
- * stored block of one tap, scaled by the two block exponents, accumulated in FP32).  Because a block of the lowered
- * matrix is a block of the image, the result equals hbfp_gemm_select(HBFP_KERNEL_INT8) on hbfp_encode_im2col's operand bit for bit (with
- * round to nearest; stochastic rounding draws by position in the image here, by position in the lowered matrix there).
+ * with both factors as their BFP values.  How the sum is taken depends on the sizes:
+ *   gather  the product gathers the taps from the stored image and sums as Eq. (2) does: integer sums over the channels of one
+ *           stored block of one tap, scaled by the two block exponents, accumulated in FP32.  Because a block of the lowered
+ *           matrix is a block of the image, the result then equals hbfp_gemm_select(HBFP_KERNEL_INT8) on hbfp_encode_im2col's
+ *           operand bit for bit (with round to nearest; stochastic rounding draws by position in the image here, by position
+ *           in the lowered matrix there).
+ *   strips  large convolutions (at least 128 tiles of 256 output positions x 128 filters) with B = 24 or 32, windows of 2 to 32
+ *           taps, 2 * pad_h < r and 2 * pad_w < s, whose strip of the image (what consecutive output positions meet) fits on
+ *           chip and whose filter panels fit the workspace: a mantissa times its block's power of two is a bf16 number, and
+ *           the bf16 matrix instruction multiplies those exactly and accumulates in FP32, as HBFP_KERNEL_BF16 does for a
+ *           matrix product.  A sum that FP32 holds exactly has the same bits both ways; where exponents lie far apart each
+ *           addition rounds instead of each block, and the two agree to FP32 rounding (3 x 3 x 128, pixels scaled over 40
+ *           binades: 1.2e-7 of the result's norm from the 64-bit sum, 0.5e-7 by gather).
+ * Which of the two runs is a matter of the geometry, the batch included, never of the values, of beta or of the form of the
+ * result.  A program that wants integer block sums at every size has them from hbfp_encode_im2col and
+ * hbfp_gemm_select(HBFP_KERNEL_INT8).
  * The data gradient of a stride-1 convolution is the same call on the output gradient (as the image, with padding
  * r - 1 - pad) and the mirrored filter with its channel axes exchanged; hbfp_gemm_conv2d_dgrad does that for any stride.
  *   image    encoded [n*h*w][c], contraction axis 1, stored blocks of B <= 32 channels (block_cols = B, or k_slot = B
@@ -266,8 +278,9 @@ int hbfp_encode_im2col(const float *x, const hbfp_conv2d *conv, const hbfp_tenso
  *   filters  encoded filter matrix [r*s*c][filters] in the same order, contraction axis 0, stored blocks of B down its
  *            rows (block_rows = B or k_slot = B; any sharing of exponents), <= 8 bits
  *   Y        device FP32 [n*ho*wo][ldy], ldy >= filters; beta 0 or 1
- *   workspace  hbfp_gemm_conv2d_workspace bytes (scale words of both operands, split-k slices), 256-byte aligned
- * Where both operands repeat their exponents over the r*s taps of a channel block (c_block = B, the image with one
+ *   workspace  hbfp_gemm_conv2d_workspace bytes (scale words of both operands and split-k slices, or the filter panels), 256-byte
+ *            aligned
+ * By gather, where both operands repeat their exponents over the r*s taps of a channel block (c_block = B, the image with one
  * exponent per training input, filter tiles over the whole window), the integer sums of such a run of blocks are added
  * up before they are scaled (as Sec. 4 has it: one FP operation per tile, not per block; at most as many blocks as keep
  * the sum below 2^22): fewer FP32 roundings than block by block, so that case equals the product on the lowered operand
@@ -332,8 +345,8 @@ int hbfp_gemm_conv2d_bfp(const hbfp_tensor *image, const hbfp_conv2d *conv, cons
  * in both directions (and stride_h * stride_w <= 16), the zeros are not multiplied either: the input positions fall
  * into stride_h * stride_w phases (iy mod stride_h, ix mod stride_w), a phase meets only every stride-th filter tap and reads dy without gaps, and one launch walks all phases, each storing
  * to the rows of its input positions.  The taps that do contribute are accumulated in the same order both ways, so the
- * result is bit for bit that of hbfp_gemm_conv2d on a dy whose zeros are stored.  Otherwise (a window smaller than the
- * stride, the other formats) every tap of the spread-out dy is multiplied, zeros included: stride_h * stride_w times the
+ * result is bit for bit that of hbfp_gemm_conv2d by gather on a dy whose zeros are stored (to FP32 rounding where that call runs
+ * from strips).  Otherwise (a window smaller than the stride, the other formats) every tap of the spread-out dy is multiplied, zeros included: stride_h * stride_w times the
  * work the sum needs.
  * Errors: as hbfp_gemm_conv2d; HBFP_ERR_ARG also for extents from 2^21 on.
  */

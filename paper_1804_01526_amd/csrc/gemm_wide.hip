@@ -31,6 +31,11 @@ struct Wide {
     static constexpr int kStage = 2 * kOperand;
     static constexpr int kLds = RING * kStage;
     static constexpr int kCopies = kStage / 1024 / 4;    // copies of 1 KB per wave and stage
+    // Stages ahead of the one multiplied from.  Of 128 bytes: RING, the hand-over waits for the wave's last fragments and frees the
+    // stage's own buffer.  Of 64, whose last k-step has too little left to hide that wait behind: RING - 1, the hand-over comes a row
+    // earlier and frees the buffer of the stage before (1704 x 2914 x 811 13.6 -> 12.8 us).
+    static constexpr bool kOwn = K == 128;
+    static constexpr int kAhead = kOwn ? RING : RING - 1;
     // rows of K bytes whose 16-byte chunks are exchanged so that the reads of 16 consecutive rows at one k cover all banks
     static __device__ __forceinline__ int swizzle(int row) { return K == 128 ? (row >> 1) & 7 : (row >> 2) & 3; }
 };
@@ -50,7 +55,7 @@ struct WideParams {
 
 // STREAM: how C leaves (stores_stream)
 template <int T, int K, int RING, bool STREAM>
-__global__ __launch_bounds__(kWideThreads, (Wide<T, K, RING>::kLds <= 80 * 1024 ? 2 : 1)) void gemm_i8_wide_kernel(const WideParams p) {
+__global__ __launch_bounds__(kWideThreads, T == 4 ? 1 : 2) void gemm_i8_wide_kernel(const WideParams p) {
     typedef Wide<T, K, RING> W;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     if (stands_down(p.run_a, p.run_b)) return;
@@ -133,31 +138,33 @@ __global__ __launch_bounds__(kWideThreads, (Wide<T, K, RING>::kLds <= 80 * 1024 
             acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[buf][i], b[buf][j], acc[i][j], 0, 0, 0);      \
     }
     // one k-step of 32: T x T matrix instructions on buffer `buf`; after each row of them, one row tile and one column
-    // tile of the next k-step are requested into the other buffer.  HAND: the hand-over sits behind the first row;
-    // COPY: the copies into the ring buffer that it frees ride along
+    // tile of the next k-step are requested into the other buffer.  HAND: the hand-over sits behind the first row, or in front
+    // of it; COPY: the copies into the ring buffer that it frees ride along
 #define HBFP_WIDE_KSTEP(buf, NEXT, nbase_, ns, HAND, COPY)                                                      \
     {                                                                                                         \
         _Pragma("unroll") for (int i_ = 0; i_ < T; ++i_) {                                                    \
+            if (i_ == 0 && !W::kOwn) { HAND; }                                                                \
             HBFP_WIDE_ROW(buf, i_);                                                                           \
-            if (i_ == 0) { HAND; }                                                                            \
+            if (i_ == 0 && W::kOwn) { HAND; }                                                                 \
             if (NEXT) HBFP_WIDE_READ(1 - (buf), nbase_, ns, i_);                                              \
-            if (COPY) { _Pragma("unroll") for (int c_ = 0; c_ < W::kCopies / T; ++c_) HBFP_WIDE_COPY(W::kCopies / T * i_ + c_, ring); } \
+            if (COPY) { _Pragma("unroll") for (int c_ = 0; c_ < W::kCopies / T; ++c_) HBFP_WIDE_COPY(W::kCopies / T * i_ + c_, taken); } \
             HBFP_WIDE_FENCE;                                                                                  \
         }                                                                                                     \
     }
     // A stage is kSteps k-steps; the fragments of its first were requested during the stage before.  The hand-over, in its last: this
-    // wave has its last fragments of the stage, and its copies of the next stage have landed when only those of the AFTER stages
-    // behind it are in flight; after the barrier that holds for everybody, and the stage's own buffer takes the copies of stage
-    // st + RING (COPY).  LAST: nothing follows.
+    // wave has its last fragments of the stage (kOwn; otherwise those of the stage before, which it has multiplied), and its copies of
+    // the next stage have landed when only those of the AFTER stages behind it are in flight; after the barrier that holds for
+    // everybody, and the buffer of the stage (or of the one before) takes the copies of stage st + kAhead (COPY).  LAST: nothing follows.
 #define HBFP_WIDE_STAGE(AFTER, COPY, LAST)                                                                     \
     {                                                                                                         \
         const uint8_t *base = lds + ring * W::kStage;                                                        \
-        const int next = ring + 1 == RING ? 0 : ring + 1;                                                 \
+        const int next = ring + 1 == RING ? 0 : ring + 1, taken = W::kOwn ? ring : ring == 0 ? RING - 1 : ring - 1; \
         _Pragma("unroll") for (int s_ = 0; s_ < W::kSteps - 1; ++s_)                                          \
             HBFP_WIDE_KSTEP(s_ & 1, true, base, s_ + 1, {}, false);                                           \
         HBFP_WIDE_KSTEP(1, !(LAST), lds + next * W::kStage, 0, {                                              \
             if (!(LAST)) {                                                                                    \
-                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((AFTER) * W::kCopies) : "memory");        \
+                if (W::kOwn) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((AFTER) * W::kCopies) : "memory"); \
+                else asm volatile("s_waitcnt vmcnt(%0)" ::"n"((AFTER) * W::kCopies) : "memory");              \
                 __builtin_amdgcn_s_barrier();                                                                 \
                 asm volatile("" ::: "memory");                                                                \
             }                                                                                                 \
@@ -165,10 +172,14 @@ __global__ __launch_bounds__(kWideThreads, (Wide<T, K, RING>::kLds <= 80 * 1024 
         ring = next;                                                                                          \
     }
 
-    // prologue: two stages on their way; those behind them are requested when the first has landed, or it would wait for its share
-    // of what all compute units ask for at once (RING x 32 KB each); then the fragments of k-step 0
+    // prologue: up to three stages on their way (with two, contractions of 2 to 20 stages on 192 x 192 tiles take 1 % longer), the
+    // fragments of k-step 0 when the first has landed, then the fourth stage
     HBFP_WIDE_COPY_STAGE(0);
-    if (nstage > 1) {
+    if (W::kAhead > 2 && nstage > 2) {
+        HBFP_WIDE_COPY_STAGE(1);
+        HBFP_WIDE_COPY_STAGE(2);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * W::kCopies) : "memory");
+    } else if (nstage > 1) {
         HBFP_WIDE_COPY_STAGE(1);
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(W::kCopies) : "memory");
     } else {
@@ -176,18 +187,18 @@ __global__ __launch_bounds__(kWideThreads, (Wide<T, K, RING>::kLds <= 80 * 1024 
     }
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    if (RING > 2 && nstage > 2) HBFP_WIDE_COPY_STAGE(2);
-    if (RING > 3 && nstage > 3) HBFP_WIDE_COPY_STAGE(3);
 #pragma unroll
     for (int i = 0; i < T; ++i) HBFP_WIDE_READ(0, lds, 0, i);
+    __builtin_amdgcn_sched_barrier(0);                            // (the copies in front of the reads: 1 % more)
+    if (W::kAhead > 3 && nstage > 3) HBFP_WIDE_COPY_STAGE(3);
     int ring = 0;
     int st = 0;
-    for (; st + RING < nstage; ++st) HBFP_WIDE_STAGE(RING - 2, true, false);
-    if (RING > 3 && nstage - st == 4) {
+    for (; st + W::kAhead < nstage; ++st) HBFP_WIDE_STAGE(W::kAhead - 2, true, false);
+    if (W::kAhead > 3 && nstage - st == 4) {
         HBFP_WIDE_STAGE(2, false, false);
         ++st;
     }
-    if (RING > 2 && nstage - st == 3) {
+    if (W::kAhead > 2 && nstage - st == 3) {
         HBFP_WIDE_STAGE(1, false, false);
         ++st;
     }
@@ -351,17 +362,30 @@ int launch_gemm_wide(const GemmArgs &a, void *workspace, hipStream_t s) {
     // conversions beside the product (conversions and product, streaming -> ordinary: 3001 x 600 x 2999 29.3 -> 26.9 us, 5000 x 1024 x
     // 4001 54.6 -> 54.1, 4100 x 1024 x 2501 38.9 -> 34.7, but 5000 x 1200 x 4001 60.5 -> 63.7, 3001 x 4500 x 2999 86.9 -> 88.4)
     const bool stream = a.kpad > 1024 || stores_stream(&a);
-    // Whole cache lines of 128 bytes a row halve the requests of 64: 3001 x 4500 x 2999 (T = 3) 58 -> 55 us, 8192^3 (T = 4) 465 -> 447.
-    // A ring of two such stages is enough where two workgroups share a compute unit and cover each other's waits (T = 2: 1826 x
-    // 3178 x 3145 31 -> 27, 5000 x 2000 x 1000 20.8 -> 19.5); one alone wants four (2048 x 4096 x 2048 25.9 -> 23.6).  But the first
-    // stage is then twice as much to wait for, 0.7 us: contractions up to 2048 keep 64 bytes a row in a lone workgroup
-    // (1000^3 10.4 us, 11.2 with whole lines; 1024 x 2048 x 1024 10.3, 11.2).
-    const bool lone = (int64_t)p.tiles_m * p.tiles_n * p.splits <= 256;
-    const int rc = plan.T == 4                       ? launch_wide_t<4, 128, 2>(p, stream, s)
-                   : plan.T == 3                     ? launch_wide_t<3, 128, 3>(p, stream, s)
-                   : !lone                           ? launch_wide_t<2, 128, 2>(p, stream, s)
-                   : p.stages_per_split * 128 > 2048 ? launch_wide_t<2, 128, 4>(p, stream, s)
-                                                     : launch_wide_t<2, 64, 4>(p, stream, s);
+    // Stages of whole cache lines (128 bytes a row) halve the requests of 64, but the first is twice as much to wait for, and the chip
+    // asks for all first stages at once: they pay where a workgroup has enough of them, or a compute unit another workgroup to turn
+    // to.  64 -> 128, in stages of 128:
+    //   128 x 128, two workgroups on a compute unit (a ring of two is enough): up to 512 from 10, or 6 with more than 400, 1826 x 3178 x
+    //   3145 31.8 -> 27.5 us, 535 x 6827 x 2014 19.3 -> 17.6, 1947 x 3347 x 718 14.6 -> 13.6; 2254 x 2228 x 917 14.8 -> 15.5.  More
+    //   than 512: 7 and 8, and from 20 on, 4265 x 2872 x 920 27.5 -> 25.1, 3320 x 5698 x 4356 120 -> 106; 7445 x 1553 x 468 17.4 ->
+    //   18.2, 2657 x 3534 x 2002 36.6 -> 38.4
+    //   128 x 128, one (a ring of four): from 25, 2709 x 848 x 3095 17.4 -> 16.6, 600 x 6000 x 5000 27.5 -> 26.2, 365 x 4670 x 6800
+    //   32.8 -> 27.9; 224 x 4343 x 2613 13.8 -> 15.2, 1000^3 9.8 -> 10.5.  At most four rows of tiles, one column or fewer than 64
+    //   tiles: from 33, 256 x 5120 x 5120 27.2 -> 20.8; 256 x 4096 x 4096 14.9 -> 16.7, 326 x 3601 x 3843 16.7 -> 18.0
+    //   192 x 192 (a ring of three): from 9 with most of the chip busy, 1661 x 5106 x 10233 92 -> 86, 3001 x 2999 x 3001 38.2 -> 36.4,
+    //   6000^3 230 -> 209; 1543 x 4809 x 423 14.2 -> 14.5; with less of it 1283 x 4381 x 3908 32.8 -> 35.2, 3673 x 2042 x 4843 45 both
+    //   256 x 256 (two): 8192^3 468 -> 451, 8192 x 8192 x 512 98.8 -> 95; with less of the chip busy fewer than 20, 4580 x 2944 x 880
+    //   29.8 -> 28.7; 3543 x 3523 x 3371 59.2 -> 61.5, 1704 x 5736 x 5564 69 -> 76
+    const int64_t wgs_all = (int64_t)p.tiles_m * p.tiles_n * p.splits;
+    const int stages = p.stages_per_split;
+    const bool few = p.tiles_m <= 4 || p.tiles_n == 1 || wgs_all < 64;
+    const int rc = plan.T == 4   ? (wgs_all >= 240 || stages < 20 ? launch_wide_t<4, 128, 2>(p, stream, s) : launch_wide_t<4, 64, 4>(p, stream, s))
+                   : plan.T == 3 ? (wgs_all >= 228 && stages >= 9 ? launch_wide_t<3, 128, 3>(p, stream, s) : launch_wide_t<3, 64, 4>(p, stream, s))
+                   : wgs_all > 256
+                       ? (stages >= 20 || (wgs_all > 512 ? stages == 7 || stages == 8 : stages >= (wgs_all > 400 ? 6 : 10))
+                              ? launch_wide_t<2, 128, 2>(p, stream, s)
+                              : launch_wide_t<2, 64, 4>(p, stream, s))
+                       : (stages >= (few ? 33 : 25) ? launch_wide_t<2, 128, 4>(p, stream, s) : launch_wide_t<2, 64, 4>(p, stream, s));
     if (rc != HBFP_OK || p.splits == 1) return rc;
     const int64_t wgs = ceil_div(a.M * a.N, 1024);
     if (wgs > 0x7fffffff) return HBFP_ERR_ARG;

@@ -1134,6 +1134,25 @@ def test_wide_kernel_every_tile_and_ring(hb, M, N, ks):
         assert torch.equal(C.double(), want)
 
 
+@pytest.mark.parametrize("M,N,K,instance", [
+    (3543, 3523, 3371, "4, 64, 4"), (3543, 3523, 2400, "4, 128, 2"), (4096, 4090, 256, "4, 128, 2"),
+    (1283, 4381, 3908, "3, 64, 4"), (3001, 2999, 1000, "3, 64, 4"), (3001, 2999, 1100, "3, 128, 3"),
+    (256, 4096, 4096, "2, 64, 4"), (256, 5120, 4225, "2, 128, 4"), (600, 6000, 3072, "2, 64, 4"), (600, 6000, 3073, "2, 128, 4"),
+    (980, 5684, 659, "2, 64, 4"), (1638, 2614, 1249, "2, 128, 2"), (1947, 3347, 718, "2, 128, 2"), (7445, 1553, 468, "2, 64, 4"),
+    (4265, 2872, 920, "2, 128, 2"), (2657, 3534, 2002, "2, 64, 4"),
+])
+def test_wide_kernel_instance_by_size(hb, M, N, K, instance):
+    """Whole cache lines a row only where they pay, and either way the product of the converted values (sums below 2^24: to the bit)."""
+    print(f"[case] wide {M}x{K}x{N}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    A, B = torch.randn((M, K), device="cuda", generator=g), torch.randn((N, K), device="cuda", generator=g)
+    ta, tb = (hb.encode(x, 1, hb.make_format(8, 1, 0)) for x in (A, B))
+    C = hb.gemm(ta, tb, kernel=WIDE)
+    assert torch.equal(C.double(), hb.decode(ta).double() @ hb.decode(tb).double().t())
+    names = launched_kernels(lambda: hb.gemm(ta, tb, out=C, kernel=WIDE))
+    assert any(n.startswith(f"gemm_i8_wide_kernel<{instance},") for n in names), names
+
+
 @pytest.mark.parametrize("M,K,N,blk,beta", [
     (1296, 20000, 144, 24, 0.0),             # fewer ranges for the last column of tiles, a last row of tiles with 16 rows
     (300, 30000, 150, 32, 1.0),              # C +=, rows off 16 bytes

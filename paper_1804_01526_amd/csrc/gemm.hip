@@ -1593,12 +1593,15 @@ static void split_plan(const GemmArgs &a, int32_t *splits, int32_t *stages_per_s
 // ones beyond the 64th started when the first were through (ranges twice as long: 2300 x 140 x 20000 36.5 -> 38.8 us).  With one
 // range on an XCD this is the order as it was.  Before -> behind: 1152 x 144 x 50176 in blocks of 24 56 -> 47.7 us, 432 x 144 x
 // 100000 46 -> 39, 1296 x 144 x 50176 59 -> 57, 1296 x 160 x 50176 72.6 -> 57.8, 1400 x 150 x 30000 in blocks of 32 40.7 -> 33.7,
-// 1024 x 160 x 50176 41.5 -> 35.8, 432 x 192 x 50176 31.6 -> 29.8, 900 x 190 x 30000 level.
+// 1024 x 160 x 50176 41.5 -> 35.8, 432 x 192 x 50176 31.6 -> 29.8, 900 x 190 x 30000 level.  Of three columns and more, range by range,
+// few whole workgroups meet that would not meet anyway, and a range's columns share its rows of A in the L2 only while they run
+// together: 1209 x 320 x 29581 52.0 -> 53.7, 300 x 300 x 50000 27.9 -> 28.6, 892 x 416 x 22000 in four columns 35.0 -> 35.9.  There only
+// where the whole ones have a compute unit each that way: 1000 x 272 x 40000 49.5 -> 40.7.
 static void tail_split(GemmParams &p) {
     const int64_t last = p.N - (int64_t)(p.tiles_n - 1) * BN, per = ceil_div(p.splits, 8);
     if (per < 2 || p.tiles_n < 2 || last > 64) return;
-    const int64_t places = (64 - (int64_t)p.tiles_m * (p.tiles_n - 1) * per) / p.tiles_m;
-    if (3 * places < 2 * per) return;
+    const int64_t whole = p.tiles_m * (p.tiles_n - 1) * per, places = (64 - whole) / p.tiles_m;
+    if (3 * places < 2 * per || (p.tiles_n > 2 && whole > 32)) return;
     p.tail_stages = places < per ? (int32_t)ceil_div(p.nstage, 8 * places) : p.stages_per_split;
     p.tail_splits = (int32_t)ceil_div(p.nstage, p.tail_stages);
 }

@@ -1157,6 +1157,8 @@ def test_wide_kernel_instance_by_size(hb, M, N, K, instance):
     (1296, 20000, 144, 24, 0.0),             # fewer ranges for the last column of tiles, a last row of tiles with 16 rows
     (300, 30000, 150, 32, 1.0),              # C +=, rows off 16 bytes
     (432, 24000, 192, 24, 0.0), (129, 30000, 129, 32, 0.0), (640, 40000, 300, 32, 0.0), (97, 9000, 33, 24, 1.0),
+    (1000, 24000, 272, 24, 1.0),             # three columns whose whole workgroups have a compute unit each: the last behind them
+    (300, 30000, 300, 32, 0.0), (250, 20000, 416, 24, 1.0),   # ... and more of them than that: range by range
     (700, 1500, 3000, 24, 0.0),              # unsplit, a last row of tiles with 60 rows
 ])
 def test_last_columns_and_rows_of_tiles(hb, M, K, N, blk, beta):

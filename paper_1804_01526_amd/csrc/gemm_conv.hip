@@ -232,12 +232,18 @@ __device__ __forceinline__ void strip_wave(const StripParams &p, uint8_t *lds, i
     const int64_t i0 = row0 + wm * 32 * MT, j0 = (int64_t)tile0 * 32;
     const int64_t end = p.M < i0 + 32 * MT ? p.M : i0 + 32 * MT;
     if constexpr (ENC) {
-        static_assert(NT == 2, "two column tiles at a time");
+        static_assert(NT <= 2, "two column tiles at a time, the second one of zeros if there is none");
 #pragma unroll
         for (int h = 0; h < MT; h += 2) {
-            v16f(&two)[2][NT] = *reinterpret_cast<v16f(*)[2][NT]>(&acc[h]);
-            if (p.enc.rounding) mx_store_encoded<1, NT>(p.enc, two, i0 + 32 * h, j0, end, p.N, lane);
-            else mx_store_encoded<0, NT>(p.enc, two, i0 + 32 * h, j0, end, p.N, lane);
+            v16f two[2][2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) two[i][j][v] = j < NT ? acc[h + i][j < NT ? j : 0][v] : 0.0f;
+            if (p.enc.rounding) mx_store_encoded<1, 2>(p.enc, two, i0 + 32 * h, j0, end, p.N, lane);
+            else mx_store_encoded<0, 2>(p.enc, two, i0 + 32 * h, j0, end, p.N, lane);
         }
     } else if (!idle) {
         store_result<MT, NT, STREAM>(p.C + i0 * p.ldc + j0, p.ldc, end - i0, p.N - j0, p.beta != 0, lane, [&](int i, int j, int v) { return acc[i][j][v]; });
@@ -260,18 +266,31 @@ __global__ __launch_bounds__(kStripThreads, 2) void gemm_strip_kernel(const Stri
     const int64_t row0 = (int64_t)(from + base * slot + (slot < more ? slot : more)) * kStripUnit;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int wm = wave & 1, wn = (wave >> 1) ^ ((place >> 5) & 1);              // (the other way round 32 places on: the same SIMDs)
-    // Column tiles: NT for either wave, so that no two waves store the same column (with beta both would add to it).  Beyond the last
-    // tile that holds filters the second wave has fewer, or none.
+    // The column tiles that hold filters, half of them for either wave (ENC: NT for the first, which encodes two together).  A wave
+    // computes and stores its own ones alone: no column belongs to two waves (with beta both would add to it), and a tile without
+    // filters costs as much as one with (128 x 28 x 28 x 128 with two tiles for every wave that has one -> now: 32 filters 26.7 ->
+    // 16.8 us, delivered encoded 32.7 -> 22.5, 64 filters 25.9 -> 20.3, 96 32.8 -> 27.8, encoded 36.6 -> 34.0, 128 level).
     const int tiles32 = (int)((p.N + 31) / 32), here = tiles32 - 2 * NT * tn < 2 * NT ? tiles32 - 2 * NT * tn : 2 * NT;
-    const int tile0 = 2 * NT * tn + wn * NT;
-    const bool idle = here <= wn * NT;                                           // this wave has no column to compute
+    const int split = ENC || NT == 3 ? NT : (here + 1) / 2, own = wn ? here - split : here < split ? here : split;
+    const int tile0 = 2 * NT * tn + wn * split;
+    const bool idle = own <= 0;                                                  // this wave has no column to compute
     if constexpr (NT == 2) {
-        if (mt == 4) strip_wave<KS, 4, NT, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
-        else if (mt == 3) strip_wave<KS, 3, NT, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
-        else if (mt == 2) strip_wave<KS, 2, NT, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
-        else if (mt == 1) strip_wave<KS, 1, NT, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
+        const bool narrow = own == 1;                                            // (the barriers of both kinds of wave are the same)
+        if (mt == 4) {
+            if (narrow) strip_wave<KS, 4, 1, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
+            else strip_wave<KS, 4, NT, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
+        } else if (mt == 3) {
+            if (narrow) strip_wave<KS, 3, 1, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
+            else strip_wave<KS, 3, NT, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
+        } else if (mt == 2) {
+            if (narrow) strip_wave<KS, 2, 1, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
+            else strip_wave<KS, 2, NT, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
+        } else if (mt == 1) {
+            if (narrow) strip_wave<KS, 1, 1, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
+            else strip_wave<KS, 1, NT, ENC, STREAM>(p, lds, row0, wm, tile0, idle);
+        }
     } else {
-        const bool narrow = wn == 1 && here < 2 * NT;                            // (the barriers of both kinds of wave are the same)
+        const bool narrow = own < NT;                                            // (tiles of 192 filters have five column tiles at least)
         if (mt == 3) {
             if (narrow) strip_wave<KS, 3, NT - 1, false, STREAM>(p, lds, row0, wm, tile0, idle);
             else strip_wave<KS, 3, NT, false, STREAM>(p, lds, row0, wm, tile0, idle);

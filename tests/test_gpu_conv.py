@@ -537,6 +537,8 @@ def test_conv_bfp_over_its_own_image(hb, n, h, w, c, r):
     (130, 28, 28, 72, 100, 3, 3, 1, 1, 1, 24),       # three and four units of positions, blocks of 24
     (100, 28, 28, 64, 160, 3, 3, 1, 1, 1, 32),       # two and three units on tiles of 192
     (100, 28, 28, 48, 192, 3, 3, 1, 1, 1, 24),
+    (130, 28, 28, 64, 32, 3, 3, 1, 1, 1, 32),        # one column tile in all, three and four units
+    (130, 28, 28, 48, 50, 3, 3, 1, 1, 1, 24),        # ... one of each wave
 ])
 def test_conv_strips_against_the_lowered_product(hb, n, h, w, c, f, r, s, pad, sh, sw, kb):
     """Sizes at which the product runs from strips of the image on the bf16 instruction, against the int8 product on the lowered operand.
@@ -560,8 +562,10 @@ def test_conv_strips_against_the_lowered_product(hb, n, h, w, c, f, r, s, pad, s
 
 
 @pytest.mark.parametrize("n,f,kb,per_image", [
-    (54, 40, 32, False),             # a column tile of 32 and one of 8: both the first wave's
+    (54, 24, 32, False), (54, 32, 24, True),                             # one column tile: the first wave's
+    (54, 40, 32, False),             # one of 32 and one of 8: a wave each
     (54, 64, 32, False), (54, 64, 24, True), (80, 320, 32, False),       # two whole ones alone in the last 128 columns
+    (54, 96, 32, False), (54, 80, 24, False),                            # three: two and one
     (54, 100, 24, False),            # three and a part
     (54, 160, 32, False), (54, 192, 24, True),                           # tiles of 192: a second wave of two and of three
 ])
@@ -598,6 +602,8 @@ def test_conv_strips_add_to_c_once(hb, n, f, kb, per_image):
     (4, 170, 170, 48, 144, 24, 8, 0),        # three and four units of positions, the FP32 product on tiles of 192 filters
     (130, 28, 28, 64, 128, 32, 4, 1),        # three and four units on tiles of 128 both
     (100, 20, 20, 72, 60, 24, 8, 1),         # one wave of columns only
+    (130, 28, 28, 64, 32, 32, 8, 0), (130, 28, 28, 72, 20, 24, 8, 1),    # one column tile in all
+    (130, 28, 28, 64, 96, 32, 4, 1), (100, 20, 20, 48, 75, 24, 8, 0),    # the second wave has one
 ])
 def test_conv_strips_delivered_encoded_are_the_conversion_of_the_product(hb, n, h, w, c, f, kb, bits, sr):
     """Sums that round (exponents far apart): the encoded result has the bytes of the FP32 result's conversion, so both come from strips

@@ -15,11 +15,13 @@
 // are read from a pixel of zeros.  The filters come as bf16 panels that a small kernel has laid out in the order in which they
 // are used; each wave loads its fragments straight from the caches (every one serves four matrix instructions), a tap
 // ahead.  One barrier before and one behind each strip; two workgroups per compute unit cover each other's conversions.
-// The int8 kernel -> this one, with the launch that lays out the panels: 128 x 28 x 28 x 128, 128 filters of 3 x 3 58 -> 32.2 us
-// (delivered encoded 62 -> 40), 64 x 28 x 28 x 144, 144 filters, blocks of 24 60 -> 31.8.  Its matrix instructions alone would take 13
-// and 11 us: all workgroups start together, store together (51 MB, 10 us) and wait for their first strip together.  Panels that go
-// through a ring in LDS, where two waves share a fragment, cost a barrier per tap and more than they save (38 and 40 us); a higher
-// priority for one of the two workgroups of a compute unit changes nothing.
+// The int8 kernel -> this one, each with its launch in front, on the same operands again and again: 128 x 28 x 28 x 128, 128 filters of
+// 3 x 3 52.4 -> 31.3 us (delivered encoded 55.2 -> 35.8), 64 x 28 x 28 x 144, 144 filters, blocks of 24 59.8 -> 30.7; with other inputs
+// in turn the kernels take 30.5 + 5.1 us (36.3 + 5.1) and 31.5 + 3.9.  The matrix instructions alone would take 13 and 11 us: all
+// workgroups start together, store together (51 MB, 10 us) and wait for their first strip together.  Panels that go through a ring in
+// LDS, where two waves share a fragment, cost a barrier per tap and more than they save (38 and 40 us); a higher priority for one of
+// the two workgroups of a compute unit changes nothing.  Blocks of other lengths than
+// 24 and 32 have no instance here and run on the int8 kernel.
 #include <atomic>
 
 #include "bf_pack.h"

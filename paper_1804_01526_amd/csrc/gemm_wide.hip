@@ -10,9 +10,9 @@
 // 2999 on T = 3: matrix instructions 70 % of the loop's clocks at 1.7 GHz; 2.3 us until the first stage is there, 34 us of
 // loop, 10 us in which all compute units store C at once) and go furthest on the largest tile; the smaller ones fill the chip
 // where those are too few, and long contractions of few tiles are split (wide_plan).  Operands are read as they are stored
-// (int8 [rows][kpad]): 128 bytes of k of the tile's rows per stage, whole cache lines (64 bytes: launch_gemm_wide), copied global ->
-// LDS asynchronously into a ring of as many stages as fit, rows of 128 bytes with the 16-byte chunk index XORed with
-// (row >> 1) & 7, so that copies and the fragment reads of 16 rows cover all banks.  Fragments are read one k-step (32)
+// (int8 [rows][kpad]): 128 bytes of k of the tile's rows per stage, whole cache lines, or 64 where those do not pay (launch_gemm_wide),
+// copied global -> LDS asynchronously into a ring of two to four stages, rows of 128 (64) bytes with the 16-byte chunk index XORed with
+// (row >> 1) & 7 ((row >> 2) & 3), so that copies and the fragment reads of 16 rows cover all banks.  Fragments are read one k-step (32)
 // ahead, between the matrix instructions, and the hand-over of a ring buffer (one barrier per stage) sits in the stage's last
 // k-step.
 #include "gemm_common.h"

@@ -1153,24 +1153,30 @@ def test_wide_kernel_instance_by_size(hb, M, N, K, instance):
     assert any(n.startswith(f"gemm_i8_wide_kernel<{instance},") for n in names), names
 
 
-@pytest.mark.parametrize("M,K,N,blk,beta", [
-    (1296, 20000, 144, 24, 0.0),             # fewer ranges for the last column of tiles, a last row of tiles with 16 rows
-    (300, 30000, 150, 32, 1.0),              # C +=, rows off 16 bytes
-    (432, 24000, 192, 24, 0.0), (129, 30000, 129, 32, 0.0), (640, 40000, 300, 32, 0.0), (97, 9000, 33, 24, 1.0),
-    (1000, 24000, 272, 24, 1.0),             # three columns whose whole workgroups have a compute unit each: the last behind them
-    (300, 30000, 300, 32, 0.0), (250, 20000, 416, 24, 1.0),   # ... and more of them than that: range by range
-    (700, 1500, 3000, 24, 0.0),              # unsplit, a last row of tiles with 60 rows
+@pytest.mark.parametrize("M,K,N,blk,beta,fewer", [
+    (1296, 46000, 144, 24, 0.0, True),       # fewer ranges for the last column of tiles, a last row of tiles with 16 rows
+    (1400, 46000, 150, 32, 1.0, True),
+    (1296, 20000, 144, 24, 0.0, False),      # as many: behind the others all the same
+    (300, 30000, 150, 32, 1.0, False),       # C +=, rows off 16 bytes
+    (432, 24000, 192, 24, 0.0, False), (129, 30000, 129, 32, 0.0, False), (640, 40000, 300, 32, 0.0, False), (97, 9000, 33, 24, 1.0, False),
+    (1000, 24000, 272, 24, 1.0, False),      # three columns whose whole workgroups have a compute unit each: the last behind them
+    (300, 30000, 300, 32, 0.0, False), (250, 20000, 470, 24, 1.0, False),   # ... and more of them than that, or a last one too wide
+    (700, 1500, 3000, 24, 0.0, False),       # unsplit, a last row of tiles with 60 rows
 ])
-def test_last_columns_and_rows_of_tiles(hb, M, K, N, blk, beta):
+def test_last_columns_and_rows_of_tiles(hb, M, K, N, blk, beta, fewer):
     """Last tiles of few columns, in k ranges of their own, and of few rows.  Values are small integers, so every sum is exact in FP32
-    whatever its order: equal to the bit."""
+    whatever its order: equal to the bit.  Slices that the last column does not have stay as they were in the workspace."""
     g = torch.Generator(device="cuda").manual_seed(M + N)
     print(f"[case] {M}x{K}x{N} blocks of {blk} beta {beta}", flush=True)
     A, B = (torch.randint(-7, 8, shape, device="cuda", generator=g).float() for shape in ((M, K), (K, N)))
     ta, tb = hb.encode(A, 1, hb.make_format(8, 1, blk)), hb.encode(B, 0, hb.make_format(8, blk, 1))
     C = torch.randint(-7, 8, (M, N), device="cuda", generator=g).float()
     want = A.double() @ B.double() + (C.double() if beta else 0.0)
-    assert torch.equal(hb.gemm(ta, tb, out=C, beta=beta).double(), want)
+    ws = torch.full((hb.gemm_select_workspace(ta.desc, tb.desc, 1),), 255, dtype=torch.uint8, device="cuda")     # NaN wherever it is read as FP32
+    assert torch.equal(hb.gemm(ta, tb, out=C, beta=beta, kernel=1, workspace=ws).double(), want)
+    slices = ws[:ws.numel() // (4 * M * N) * 4 * M * N].view(torch.float32).view(-1, M, N)[:, 0]
+    first, last = (torch.isnan(slices[:, col]).logical_not().cumprod(0).sum().item() for col in (0, N - 1))
+    assert (last < first) if fewer else (last == first), (first, last)
 
 
 @pytest.mark.parametrize("m,blk,kernel", [(8, 32, SCALED), (12, 64, SCALED), (8, 24, 0), (8, 32, 1)])

@@ -174,8 +174,8 @@ def test_encode_im2col_weight_gradient_orientation(hb, n, h, w, c, r, s, ph, pw,
     (3, 6, 6, 9, 2, 2, 0, 0, 3, 3),         # a stride beyond the window
 ])
 def test_encode_im2col_pieces_inside_the_tensor(hb, n, h, w, c, r, s, ph, pw, sh, sw, B, m, rounding):
-    """The weight-gradient orientation where whole pieces of positions are loaded without a check per value, and where they are not, bit
-    for bit against the oracle's encode of the lowered matrix."""
+    """The weight-gradient orientation at sizes small enough for loads with a check per value, in the geometries that decide where whole
+    pieces of positions can do without (the next test), bit for bit against the oracle's encode of the lowered matrix."""
     rng = np.random.default_rng(n * h * w + c)
     x = rng.standard_normal((n, h, w, c)).astype(np.float32)
     conv = hb.Conv2d(n, h, w, c, r, s, ph, pw, sh, sw, 0, 0)

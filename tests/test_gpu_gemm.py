@@ -1120,10 +1120,12 @@ def test_wide_kernel_large_product_sampled(hb):
 
 
 @pytest.mark.parametrize("M,N,ks", [(3900, 4090, (100, 256, 300, 520)), (3001, 2999, (100, 256, 300, 400, 520)), (1826, 3145, (60, 256, 300, 520)),
-                                    (2040, 2000, (2100, 2304, 2400, 2600)), (500, 300, (2050, 2100, 2200, 2400, 2560))])
+                                    (2040, 2000, (2100, 2304, 2400, 2600)), (500, 300, (2050, 2100, 2200, 2400, 2560)),
+                                    (3001, 2999, (1100, 1200, 1300, 1409)), (1638, 2614, (1200, 1300, 1409)), (600, 6000, (3100, 3300, 3400, 3500, 3700)),
+                                    (3543, 3523, (2500, 2600))])
 def test_wide_kernel_every_tile_and_ring(hb, M, N, ks):
-    """Tiles of 256, 192 and 128, stages of 128 bytes in rings of two, three and four and of 64 bytes: contractions of 1 to 5 stages and
-    more.  The integer sums stay below 2^24, so the product of the converted values in FP64 is the result to the bit."""
+    """Tiles of 256, 192 and 128, stages of 128 bytes in rings of two, three and four and of 64 bytes: every remainder of the stages by the
+    ring, and contractions shorter than it where those run (test_wide_kernel_instance_by_size has the lines).  The integer sums stay below 2^24, so the product of the converted values in FP64 is the result to the bit."""
     g = torch.Generator(device="cuda").manual_seed(M + N)
     for K in ks:
         print(f"[case] wide {M}x{K}x{N}", flush=True)

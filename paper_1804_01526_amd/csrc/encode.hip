@@ -1495,8 +1495,15 @@ int launch_encode_im2col(const float *x, const hbfp_conv2d &c, int64_t ho, int64
         // 5292 14.6 -> 11.5; even shares: 72 4.9 -> 5.25, 2700 6.65 -> 6.82, 2880 6.48 -> 6.85, 3600 7.3 both, 14 112 19.8 -> 18.6.  Of 24,
         // whose checked loads are slower: whole groups, 1092 5.56 -> 5.23, 1372 5.55 -> 5.60, 2100 6.57 -> 5.70; even shares, 924
         // 5.0 -> 5.05.  Blocks of other lengths have no unchecked loads, and the dealing by itself gives them nothing (16: 56.6 -> 57.7).
-        const int64_t pieces = gx * nb_cover;
-        const bool inside = forward && ((g.kblock == 32 && pieces >= (groups ? 2000 : 3500)) || (g.kblock == 24 && pieces >= (groups ? 1000 : 1500)));
+        // A window of one pixel meets none twice: blocks of 24 from 1500 pieces on (1 x 56 x 56 x 512, 1064 of them, 5.27 -> 5.65), and not
+        // where whole waves stream out of the last-level cache, from 16 to 36 Mi values (blocks of 24: 18 to 28; 10 x 112 x 112 x 256 25.4 ->
+        // 28.0, 18 x 112 x 112 x 128 23.7 -> 25.5, blocks of 24 31 x 56 x 56 x 256 21.7 -> 23.9; with fewer 12 x 112 x 112 x 64 14.0 -> 12.2,
+        // with more 22 x 112 x 112 x 256 64.8 -> 60.8, with waves that are not full 10 x 112 x 112 x 200 29.8 -> 22.3).
+        const int64_t pieces = gx * nb_cover, mi = (g.K * c.c) >> 20;
+        const bool single = (int64_t)c.r * c.s == 1;
+        const bool streams = single && c.c % 64 == 0 && (g.kblock == 32 ? mi >= 16 && mi < 36 : mi >= 18 && mi < 28);
+        const int64_t least = g.kblock == 32 ? (groups ? 2000 : 3500) : groups && !single ? 1000 : 1500;
+        const bool inside = forward && !streams && (g.kblock == 32 || g.kblock == 24) && pieces >= least;
         const dim3 grid(inside ? 8 * p.wgs8 : p.wgs);
         if (g.kbp == 32 && inside) launch_col_conv_k<32, true>(p, grid, wide, g.rounding, s);
         else if (g.kbp == 32) launch_col_conv_k<32, false>(p, grid, wide, g.rounding, s);

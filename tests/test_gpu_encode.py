@@ -199,6 +199,8 @@ def test_encode_im2col_pieces_inside_the_tensor(hb, n, h, w, c, r, s, ph, pw, sh
     (600, 4, 4, 16, 3, 3, 3, 3, 1, 1, False),        # corners move back
     (7000, 6, 6, 64, 2, 2, 0, 0, 3, 3, True),
     (3, 9, 10, 300, 3, 3, 1, 1, 1, 1, False),        # few pieces
+    (30, 100, 100, 64, 1, 1, 0, 0, 1, 1, False),     # one pixel, whole waves: 18.3 Mi values
+    (15, 100, 100, 64, 1, 1, 0, 0, 1, 1, True), (30, 100, 100, 66, 1, 1, 0, 0, 1, 1, True),
 ])
 def test_encode_im2col_weight_gradient_of_many_pieces(hb, n, h, w, c, r, s, ph, pw, sh, sw, unchecked, B, m, rounding):
     """The geometries above at sizes from which pieces inside the tensor are loaded without a check and workgroups are dealt to the XCDs
